@@ -31,6 +31,7 @@
 #include "build_dev.h"
 #include "kernels.h"
 #include "radix.h"
+#include "scan.h"
 
 namespace dbbc {
 namespace {
@@ -60,8 +61,11 @@ struct RecordIn {
   const int32_t* v;
   const int8_t* s;
   int vbits;
+  __device__ __forceinline__ uint64_t key(int32_t a, int32_t b) const {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(a)) << vbits) | static_cast<uint32_t>(b);
+  }
   __device__ __forceinline__ radix::Elt<3> load(uint32_t i) const {
-    const uint64_t key = (static_cast<uint64_t>(static_cast<uint32_t>(u[i])) << vbits) | static_cast<uint32_t>(v[i]);
+    const uint64_t key = this->key(u[i], v[i]);
     return {{static_cast<uint32_t>(key), static_cast<uint32_t>(key >> 32), (i << 1) | (s[i] < 0 ? 1u : 0u)}};
   }
 };
@@ -76,12 +80,29 @@ __global__ __launch_bounds__(kThreads) void k_record_hist(RecordIn in, uint32_t 
                                                           radix::Digits d, uint32_t* hist, unsigned long long* bad) {
   __shared__ uint32_t h[radix::kMaxPasses * radix::kDigits];
   radix::clear_counts(h, d);
-  GRID_STRIDE(i, m) {
-    const int32_t a = in.u[i], b = in.v[i];
-    if (a < 0 || a >= n_u || b < 0 || b >= n_v) atomicMin(&bad[0], static_cast<unsigned long long>(i));
-    const int8_t g = in.s[i];
-    if (g != 1 && g != -1) atomicMin(&bad[1], static_cast<unsigned long long>(i));
-    radix::count_digits(h, radix::key_of<2>(in.load(static_cast<uint32_t>(i))), d);
+  // four records' loads at a time
+  const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kThreads;
+  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kThreads + threadIdx.x; i < m; i += 4 * stride) {
+    int32_t a[4], b[4];
+    int8_t g[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t j = i + k * stride;
+      if (j < m) {
+        a[k] = in.u[j];
+        b[k] = in.v[j];
+        g[k] = in.s[j];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t j = i + k * stride;
+      if (j >= m) continue;
+      if (a[k] < 0 || a[k] >= n_u || b[k] < 0 || b[k] >= n_v)
+        atomicMin(&bad[0], static_cast<unsigned long long>(j));
+      if (g[k] != 1 && g[k] != -1) atomicMin(&bad[1], static_cast<unsigned long long>(j));
+      radix::count_digits(h, in.key(a[k], b[k]), d);
+    }
   }
   radix::add_counts(h, d, hist);
 }
@@ -136,54 +157,19 @@ constexpr uint32_t kKeepChunk = 8 * kThreads;
 
 template <int kPass>
 __global__ __launch_bounds__(kThreads) void k_keep(radix::Soa<3> a, uint32_t m, uint32_t* counts, radix::Soa<3> out) {
-  __shared__ uint32_t wsum[kThreads / 64];
-  const int tid = static_cast<int>(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+  __shared__ uint32_t sh[kThreads / 64];
   const uint32_t c0 = blockIdx.x * kKeepChunk;
   uint32_t done = 0;
   const uint32_t at = kPass ? counts[blockIdx.x] : 0u;
   for (uint32_t j = 0; j < kKeepChunk; j += kThreads) {
-    const uint32_t i = c0 + j + tid;
+    const uint32_t i = c0 + j + threadIdx.x;
     const bool keep = i < m && (i + 1 == m || key_at(a, i) != key_at(a, i + 1));
-    const uint64_t b = __ballot(keep);
-    if (lane == 0) wsum[wave] = static_cast<uint32_t>(__popcll(b));
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-    for (int w = 0; w < kThreads / 64; ++w) {
-      before += w < wave ? wsum[w] : 0u;
-      all += wsum[w];
-    }
-    if (kPass && keep)
-      out.store(at + done + before + static_cast<uint32_t>(__popcll(b & ((1ull << lane) - 1ull))), a.load(i));
+    uint32_t all;
+    const uint32_t before = block_excl<kThreads>(keep ? 1u : 0u, sh, all);
+    if (kPass && keep) out.store(at + done + before, a.load(i));
     done += all;
-    __syncthreads();
   }
-  if (!kPass && tid == 0) counts[blockIdx.x] = done;
-}
-
-// Exclusive sums of n counts in place, by one block (n is a number of
-// chunks: each thread takes a stretch of them).
-constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void k_scan_counts(uint32_t* c, uint32_t n) {
-  __shared__ uint32_t sh[kScanThreads];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t per = (n + kScanThreads - 1) / kScanThreads;
-  const uint32_t b = min(n, tid * per), e = min(n, b + per);
-  uint32_t sum = 0;
-  for (uint32_t i = b; i < e; ++i) sum += c[i];
-  sh[tid] = sum;
-  __syncthreads();
-  for (uint32_t d = 1; d < kScanThreads; d <<= 1) {
-    const uint32_t x = tid >= d ? sh[tid - d] : 0u;
-    __syncthreads();
-    sh[tid] += x;
-    __syncthreads();
-  }
-  uint32_t run = sh[tid] - sum;
-  for (uint32_t i = b; i < e; ++i) {
-    const uint32_t x = c[i];
-    c[i] = run;
-    run += x;
-  }
+  if (!kPass && threadIdx.x == 0) counts[blockIdx.x] = done;
 }
 
 // The kept records' v as a keys-only sort's input (the key's low bits).
@@ -533,18 +519,6 @@ void to_host(std::vector<T>& out, const void* src, size_t n, hipStream_t st) {
   if (n) DEV_TRY(hipMemcpyAsync(out.data(), src, n * sizeof(T), hipMemcpyDeviceToHost, st));
 }
 
-// Word arrays carved out of one allocation.
-struct Carve {
-  uint32_t* p = nullptr;
-  size_t used = 0;
-  static size_t round(size_t words) { return (words + 63) / 64 * 64; }
-  uint32_t* take(size_t words) {
-    uint32_t* q = p ? p + used : nullptr;
-    used += round(words);
-    return q;
-  }
-};
-
 #define LAUNCH(kernel, grid, threads, ...)                                             \
   do {                                                                                 \
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, __VA_ARGS__);         \
@@ -639,7 +613,7 @@ void build(int32_t n_u, int32_t n_v, int64_t m, const int32_t* u_in, const int32
     const RecordIn rin{u, v, s, vbits};
     const uint32_t m32 = static_cast<uint32_t>(m);
     clear_control(m, dig_pair);
-    LAUNCH(k_record_hist, std::min(grid_for(m), 2048), kThreads, rin, m32, n_u, n_v, dig_pair, cc.hist(0), words);
+    LAUNCH(k_record_hist, radix::hist_grid(m), kThreads, rin, m32, n_u, n_v, dig_pair, cc.hist(0), words);
     for (int p = 0; p < dig_pair.passes; ++p) {
       if (p == v_passes) LAUNCH(k_runs_v, grid_for(m), kThreads, half[cur].p[0], m32, vmask, runs[1]);
       if (p == 0)
@@ -675,7 +649,7 @@ void build(int32_t n_u, int32_t n_v, int64_t m, const int32_t* u_in, const int32
     // sort of their v (every vertex keeps a record, so every run is rewritten)
     const radix::Soa<3> from = half[cur], to = half[1 - cur];
     LAUNCH(k_keep<0>, static_cast<unsigned>(chunks_m), kThreads, from, static_cast<uint32_t>(m), chunk, to);
-    LAUNCH(k_scan_counts, 1, kScanThreads, chunk, static_cast<uint32_t>(chunks_m));
+    DEV_TRY(scan_counts(chunk, static_cast<uint32_t>(chunks_m), nullptr, st));
     LAUNCH(k_keep<1>, static_cast<unsigned>(chunks_m), kThreads, from, static_cast<uint32_t>(m), chunk, to);
     LAUNCH(k_runs_u, std::min(grid_for(me), 2048), kThreads, to, me32, vbits, runs[0], words + 2);
     const VertexIn vin{to.p[0], vmask};

@@ -163,8 +163,17 @@ template <int KW, class In>
 __global__ __launch_bounds__(kHistThreads) void k_hist(In in, uint32_t n, Digits d, uint32_t* hist) {
   __shared__ uint32_t h[kMaxPasses * kDigits];
   clear_counts(h, d);
-  for (uint64_t i = blockIdx.x * kHistThreads + threadIdx.x; i < n; i += gridDim.x * kHistThreads)
-    count_digits(h, key_of<KW>(in.load(static_cast<uint32_t>(i))), d);
+  // four independent loads at a time
+  const uint64_t stride = gridDim.x * kHistThreads;
+  for (uint64_t i = blockIdx.x * kHistThreads + threadIdx.x; i < n; i += 4 * stride) {
+    uint64_t key[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * stride < n) key[k] = key_of<KW>(in.load(static_cast<uint32_t>(i + k * stride)));
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * stride < n) count_digits(h, key[k], d);
+  }
   add_counts(h, d, hist);
 }
 
@@ -308,10 +317,15 @@ __global__ __launch_bounds__(kThreads) void k_pass(In in, Out out, uint32_t n, i
 }
 
 // Digit counts of a sort's every pass, into c (control memory, zero).
+// (At the end every block adds its counts to the same words, about 10 ns
+// each: 16 elements per thread and at most 1,024 blocks keep that short.)
+inline int hist_grid(int64_t n) {
+  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(n / (16 * kHistThreads), 1024)));
+}
 template <int KW, class In>
 hipError_t histogram(In in, int64_t n, const Digits& d, const Control& c, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  const int grid = static_cast<int>(std::min<int64_t>((n + kHistThreads - 1) / kHistThreads, 2048));
+  const int grid = hist_grid(n);
   hipLaunchKernelGGL((k_hist<KW, In>), dim3(grid), dim3(kHistThreads), 0, st, in, static_cast<uint32_t>(n), d,
                      c.hist(0));
   return hipGetLastError();
