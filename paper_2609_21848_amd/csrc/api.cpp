@@ -363,6 +363,7 @@ dbbc::DevGraphView view_of(const dbbc_graph* g) {
   v.n[0] = g->host.n_u;
   v.n[1] = g->host.n_v;
   v.m = g->host.m;
+  v.wedges = g->host.wedges_vp;
   for (int s = 0; s < 2; ++s) {
     v.off[s] = g->off[s].as<uint32_t>();
     v.adj[s] = g->adj[s].as<uint32_t>();

@@ -19,6 +19,7 @@ namespace dbbc {
 struct DevGraphView {
   int32_t n[2] = {0, 0};
   int64_t m = 0;
+  int64_t wedges = 0;  // W_VP
   int64_t max_deg[2] = {0, 0};
   const uint32_t* off[2] = {nullptr, nullptr};
   const uint32_t* adj[2] = {nullptr, nullptr};

@@ -15,12 +15,24 @@
 //   H  per-vertex plans, hub pivots (x < T) through non-hub mids (y >= T'):
 //      the part of the forward run below T (the hub pairs' sparse wedges,
 //      tallied apart and completed by the dense block).
-// Each (row, kind) is one candidate item.  Exclusive scans of the run flags
-// and lengths over the entries give every candidate's run count and work as
-// a difference of two scan values, and every run's place in its item.  The
-// candidates are classified as make_plan classifies its items (skipped,
-// small, hash, direct, reverse); one scan of the candidates' list counts
-// places every item in its list and every run in segs or small_segs.
+// Each (row, kind) is one candidate item, with its run count and work: sums
+// over the row's entries.  Nothing is kept per entry.  A block takes a chunk
+// of entries (of any rows), forms their run lengths, and leaves the chunk's
+// run counts and wedges per kind, and the sums before every row that starts
+// in it; a scan of the chunks' sums then gives every candidate's run count
+// and work as differences.  The candidates are classified as make_plan
+// classifies its items (skipped, small, hash, direct, reverse), counted per
+// chunk of rows, and placed in their lists after a scan of those counts; a
+// second pass over the entries forms the runs again and writes each at its
+// item's place.  What a run needs of its mid is one 32-byte record per mid
+// (one memory access per entry where six arrays were read).
+//
+// Measured on 50M records (5M x 2M vertices): a plan took 18.8 ms with
+// per-entry lengths and their scans (11.6) and a scan of 64-byte counts per
+// candidate (4.3), and takes 5.2: the two passes over the entries 1.5 and 1.6
+// (bound by the random 16-byte record per entry), candidates 0.85, parts 0.6.
+// On 2.2M records 1.90 -> 0.39 ms, on 20K 0.66 -> 0.15 ms (12 launches, 80
+// before).
 //
 // Per-vertex plans also record every run's mid (flagged kMidWide where its
 // credits may need two words) and first-edge position, and the owner of
@@ -36,8 +48,6 @@
 //     runs), so a part has at most part_work wedges plus its first run; the
 //     hub pivots' tally items are cut the same way at kHubTallyPartWork.
 #include <hip/hip_runtime.h>
-#include <hipcub/hipcub.hpp>
-#include <rocprim/iterator/transform_iterator.hpp>
 
 #include <algorithm>
 #include <climits>
@@ -45,6 +55,8 @@
 
 #include "kernels.h"
 #include "plan_dev.h"
+#include "radix.h"
+#include "scan.h"
 
 namespace dbbc {
 namespace {
@@ -55,7 +67,7 @@ enum : int { kF = 0, kR = 1, kM = 2, kH = 3 };  // run kinds (kH: per-vertex pla
 enum : int { kSkip = 0, kSmallC = 1, kHashC = 2, kDirectC = 3, kRevC = 4, kHubC = 5 };  // item classes
 
 constexpr uint32_t kPartMaxRuns = 65535;  // runs of a direct part (16-bit per-part counters)
-constexpr int kGroupChunk = 256;          // small items grouped per chunk
+constexpr int kGroupChunk = 256;          // small items grouped per chunk (one wavefront)
 
 struct Fail {
   int status;
@@ -78,32 +90,44 @@ int grid_for(int64_t n) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < (n); \
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
 
-// One side's arrays as the planning kernels see them.
+// What the runs through a mid y need of it: its row, the row's entries of key
+// rank below L, R and T, and those below L that rank above y itself (windows
+// are at most 32,768 keys, so the counts fit 16 bits).  16 bytes, one access
+// per entry; the largest key of its reverse runs is kept apart (rkey).
+struct alignas(16) Mid {
+  uint32_t off, end;
+  uint16_t below_L, below_R, below_T, above_L;
+};
+static_assert(kPVWindowPacked <= 65535 && kMaxReverseL <= 65535, "window counts fit 16 bits");
+
+constexpr int kPer = 4;  // entries per thread (8 take too many registers for four wavefronts a SIMD)
+constexpr uint32_t kChunk = kThreads * kPer;
+constexpr uint32_t kRowChunk = kThreads;  // rows per block where candidates are handled
+
+// A place in a chunked sequence: the sums before it.  cnt: runs; sum: wedges.
 struct PSide {
   const uint32_t* off;   // n + 1
   const uint32_t* adj;   // m
   const int32_t* rev;    // m
   const int32_t* cut;    // n
-  const uint32_t* ooff;  // the other side's offsets, entries and prefixes
-  const uint32_t* oadj;
-  const int32_t* ocut;
-  const int32_t* splitL;  // per row y of the other side: entries of rank below L, R, T
-  const int32_t* splitR;
-  const int32_t* splitT;
-  const uint32_t* row;    // row of every entry
-  uint32_t* len[4];       // run length per kind and entry (m + 1, the last 0)
-  uint32_t* cnt[4];       // exclusive scans of len > 0
-  unsigned long long* wsum[4];  // exclusive scans of len
-  uint32_t* bnd[3];       // kinds F, M (split direct items) and H: exclusive scans of part-start flags
+  const Mid* mids;       // per row of the other side
+  const uint16_t* rkey;  // ... largest key of its reverse runs
+  uint32_t* chunk_cnt[4];            // per kind: runs before each chunk of entries (chunks + 1)
+  unsigned long long* chunk_sum[4];  // ... wedges
+  uint32_t* row_cnt[4];              // per kind and row: runs of its chunk before it
+  unsigned long long* row_sum[4];    // ... wedges
   int32_t* rmax;          // per row: largest key of its reverse runs
+  uint32_t* parts;        // per candidate: parts of a split direct or a hub tally item
+  uint32_t* part_pos;     // ... and its first part's place
+  uint2* place;           // per candidate: see Place
   int32_t n, no, L, R, T, TO;
   int32_t nk;             // run kinds (candidates per row): 3, or 4 in per-vertex plans
   bool pv;                // a per-vertex plan
   bool wide_all;          // per-vertex plans: flag every run kMidWide
   unsigned long long max_deg;  // largest degree of the side (the wide-credit bound)
-  int64_t m;
+  uint32_t m;
   uint32_t side;
-  int64_t cand0;          // index of the side's first candidate (nk per row)
+  uint32_t chunks, row_chunks;
   uint32_t small_work;
   unsigned long long part_work;
 };
@@ -116,38 +140,51 @@ struct Run {
   uint32_t start, len;
 };
 
-// The run of kind k at entry e of row x.
-__device__ Run run_at(const PSide& P, int k, int32_t x, uint32_t e) {
-  const uint32_t y = P.adj[e] >> 1;
-  const uint32_t yb = P.ooff[y];
-  if (k == kF) {
-    if (e < P.off[x] + static_cast<uint32_t>(P.cut[x])) return Run{0, 0};
-    uint32_t start = yb + static_cast<uint32_t>(P.rev[e]) + 1;
-    uint32_t end;
-    if (x < P.L) {
-      end = yb + static_cast<uint32_t>(P.splitL[y]);
-      if (x < P.T && static_cast<int32_t>(y) < P.TO) start = max(start, yb + static_cast<uint32_t>(P.splitT[y]));
+// The run of kind k at entry e (its reverse position rev) of row x through
+// mid y; first_low: the row's first lower-priority entry.
+__device__ __forceinline__ Run run_at(const PSide& P, int k, int32_t x, uint32_t e, uint32_t first_low, uint32_t y,
+                                      int32_t rev, const Mid& mid) {
+  if (k == kF || k == kH) {
+    if (e < first_low) return Run{0, 0};
+    uint32_t start = mid.off + static_cast<uint32_t>(rev) + 1, end;
+    const bool hub = x < P.T && static_cast<int32_t>(y) < P.TO;
+    if (k == kH) {  // hub pivot x through a non-hub mid: the run's keys below T
+      if (x >= P.T || hub) return Run{0, 0};
+      end = mid.off + mid.below_T;
+    } else if (x < P.L) {
+      end = mid.off + mid.below_L;
+      if (hub) start = max(start, mid.off + mid.below_T);
     } else {
-      end = P.ooff[y + 1];
+      end = mid.end;
     }
     return Run{start, end > start ? end - start : 0u};
   }
-  if (k == kH) {  // hub pivot x through a non-hub mid: the run's keys below T
-    if (x >= P.T || static_cast<int32_t>(y) < P.TO || e < P.off[x] + static_cast<uint32_t>(P.cut[x]))
-      return Run{0, 0};
-    const uint32_t start = yb + static_cast<uint32_t>(P.rev[e]) + 1;
-    const uint32_t end = yb + static_cast<uint32_t>(P.splitT[y]);
-    return Run{start, end > start ? end - start : 0u};
-  }
   if (x < P.L) return Run{0, 0};
-  if (k == kR) {
-    const int32_t l = min(P.splitR[y], P.ocut[y]);
-    return Run{yb, l > 0 ? static_cast<uint32_t>(l) : 0u};
-  }
+  if (k == kR) return Run{mid.off, min(mid.below_R, mid.above_L)};
   if (P.R == P.L) return Run{0, 0};
-  const int32_t end = min(P.splitL[y], P.ocut[y]);
-  const int32_t lo = P.splitR[y];
-  return Run{yb + static_cast<uint32_t>(lo), end > lo ? static_cast<uint32_t>(end - lo) : 0u};
+  return Run{mid.off + mid.below_R, mid.above_L > mid.below_R ? mid.above_L - uint32_t{mid.below_R} : 0u};
+}
+
+__device__ __forceinline__ Mid load_mid(const Mid* mids, uint32_t y) {
+  return __builtin_bit_cast(Mid, *reinterpret_cast<const uint4*>(mids + y));
+}
+
+// Runs and wedges of candidate (x, k).
+__device__ __forceinline__ void row_totals(const PSide& P, int k, int32_t x, uint32_t& nseg, unsigned long long& work) {
+  const uint32_t b = P.off[x], e = P.off[x + 1];
+  nseg = 0;
+  work = 0;
+  if (b == e) return;
+  // rows without entries come last: the entry after a row starts the next
+  // row, or there is none
+  const bool last = e == P.m;
+  const uint32_t cb = b / kChunk, ce = last ? P.chunks : e / kChunk;
+  nseg = P.chunk_cnt[k][ce] - P.chunk_cnt[k][cb] - P.row_cnt[k][x];
+  work = P.chunk_sum[k][ce] - P.chunk_sum[k][cb] - P.row_sum[k][x];
+  if (!last) {
+    nseg += P.row_cnt[k][x + 1];
+    work += P.row_sum[k][x + 1];
+  }
 }
 
 struct Cand {
@@ -160,29 +197,25 @@ struct Cand {
   uint32_t flags;
 };
 
-// Classify candidate (x, k) as make_plan's place() does.  With parts set,
-// a split direct item's part count is read from the part-start scans.
+// Classify candidate (x, k) as make_plan's place() does.  With kParts, a
+// split direct item's (and a hub tally item's) part count is read too.
 template <bool kParts>
 __device__ Cand classify(const PSide& P, int32_t x, int k) {
   Cand c{};
   c.cls = kSkip;
   if (k == kH) {  // a hub pivot's tally item (per-vertex plans): kept with one run
     if (x >= P.T) return c;
-    const uint32_t b = P.off[x], e = P.off[x + 1];
-    c.nseg = P.cnt[kH][e] - P.cnt[kH][b];
+    row_totals(P, kH, x, c.nseg, c.work);
     if (c.nseg == 0) return c;
-    c.work = P.wsum[kH][e] - P.wsum[kH][b];
     c.cls = kHubC;
     c.key_lo = x + 1;
     c.key_hi = P.T;
     c.flags = kItemHubPairs;
-    if (kParts) c.nparts = P.bnd[2][e] - P.bnd[2][b];
+    if (kParts) c.nparts = P.parts[static_cast<int64_t>(x) * P.nk + k];
     return c;
   }
   if (k != kF && (x < P.L || (k == kM && P.R == P.L))) return c;
-  const uint32_t b = P.off[x], e = P.off[x + 1];
-  c.nseg = P.cnt[k][e] - P.cnt[k][b];
-  c.work = P.wsum[k][e] - P.wsum[k][b];
+  row_totals(P, k, x, c.nseg, c.work);
   const bool hub = k == kF && x < P.T;
   c.flags = hub ? kItemHubPairs : 0u;
   // one run: every pair of the item has at most one wedge, and adds nothing
@@ -210,131 +243,396 @@ __device__ Cand classify(const PSide& P, int32_t x, int k) {
   }
   if (c.cls == kDirectC && !P.pv && (c.work > P.part_work || c.nseg > kPartMaxRuns)) {
     c.split = true;
-    if (kParts) {
-      const uint32_t* bs = P.bnd[k == kF ? 0 : 1];
-      c.nparts = bs[e] - bs[b];
-    }
+    if (kParts) c.nparts = P.parts[static_cast<int64_t>(x) * P.nk + k];
   }
   return c;
 }
 
 // ---- kernels ------------------------------------------------------------------
 
-__global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
-  GRID_STRIDE(i, n) p[i] = v;
-}
+// The mids' records of both sides: side s's runs go through the rows y of the
+// other side.
+struct MidArgs {
+  const uint32_t* off;
+  const uint32_t* adj;
+  const int32_t* cut;
+  Mid* out;
+  uint16_t* rkey;
+  int32_t n;        // rows y
+  int32_t L, R, T;  // windows of the keys' side
+};
 
-__global__ void k_iota(uint32_t* p, int64_t n) {
-  GRID_STRIDE(i, n) p[i] = static_cast<uint32_t>(i);
-}
-
-// rows[off[x]] = x for every non-empty row (the rest is zero); an inclusive
-// max-scan then gives every entry its row.
-__global__ void k_row_marks(const uint32_t* off, int32_t n, uint32_t* rows) {
-  GRID_STRIDE(x, n) {
-    if (off[x + 1] > off[x]) rows[off[x]] = static_cast<uint32_t>(x);
-  }
-}
-
-// Per row y of the other side: entries of rank below L, R and T (rows are
-// sorted by rank; an entry is (rank << 1) | negative).
-__global__ void k_splits(const uint32_t* ooff, const uint32_t* oadj, int32_t no, int32_t L, int32_t R, int32_t T,
-                         int32_t* sL, int32_t* sR, int32_t* sT) {
-  GRID_STRIDE(y, no) {
-    const uint32_t b = ooff[y], e = ooff[y + 1];
-    auto below = [&](int32_t k) {
+__global__ __launch_bounds__(kThreads) void k_mids(MidArgs a0, MidArgs a1) {
+  GRID_STRIDE(i, static_cast<int64_t>(a0.n) + a1.n) {
+    const MidArgs& a = i < a0.n ? a0 : a1;
+    const int64_t y = i < a0.n ? i : i - a0.n;
+    const uint32_t b = a.off[y], e = a.off[y + 1];
+    // entries of rank below k (rows are sorted by rank; an entry is
+    // (rank << 1) | negative), looked for up to `to`
+    auto below = [&](int32_t k, uint32_t to) {
       const uint32_t key = static_cast<uint32_t>(k) << 1;
-      uint32_t lo = b, hi = e;
+      uint32_t lo = b, hi = to;
       while (lo < hi) {
         const uint32_t mid = lo + (hi - lo) / 2;
-        if (oadj[mid] < key)
+        if (a.adj[mid] < key)
           lo = mid + 1;
         else
           hi = mid;
       }
-      return static_cast<int32_t>(lo - b);
+      return lo;
     };
-    sL[y] = below(L);
-    sR[y] = below(R);
-    sT[y] = below(T);
+    Mid m;
+    m.off = b;
+    m.end = e;
+    const uint32_t l = below(a.L, e), r = a.R == a.L ? l : below(a.R, l);  // R <= L
+    m.below_L = static_cast<uint16_t>(l - b);
+    m.below_R = static_cast<uint16_t>(r - b);
+    m.below_T = static_cast<uint16_t>(a.T ? below(a.T, l) - b : 0u);  // T <= L
+    m.above_L = static_cast<uint16_t>(min(l - b, static_cast<uint32_t>(a.cut[y])));
+    *reinterpret_cast<uint4*>(a.out + y) = __builtin_bit_cast(uint4, m);
+    const uint32_t rl = min(m.below_R, m.above_L);
+    a.rkey[y] = static_cast<uint16_t>(rl ? a.adj[b + rl - 1] >> 1 : 0u);
   }
 }
 
-// Run lengths of every entry, and each row's largest reverse-run key.
-__global__ void k_run_lengths(PSide P) {
-  GRID_STRIDE(e64, P.m) {
-    const uint32_t e = static_cast<uint32_t>(e64);
-    const int32_t x = static_cast<int32_t>(P.row[e]);
-    for (int k = 0; k < P.nk; ++k) {
-      const Run r = run_at(P, k, x, e);
-      P.len[k][e] = r.len;
-      if (k == kR && r.len > 0) atomicMax(&P.rmax[x], static_cast<int32_t>(P.oadj[r.start + r.len - 1] >> 1));
+// The row of entry e: the last x with off[x] <= e (rows without entries come
+// last), found by one wavefront, 64 probes a step.
+__device__ __forceinline__ int32_t row_of(const uint32_t* off, int32_t n, uint32_t e) {
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  int64_t lo = 0, hi = n;  // off[lo] <= e, and off[x] > e for x >= hi (off[n] = m > e)
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t x = lo + (lane + 1) * step;
+    const uint64_t le = __ballot(x < hi && off[x < hi ? x : lo] <= e);
+    const int k = __popcll(le);  // probes at or before the row (a prefix)
+    const int64_t nlo = lo + static_cast<int64_t>(k) * step;
+    hi = min(hi, nlo + step);
+    lo = nlo;
+  }
+  return static_cast<int32_t>(lo);
+}
+
+// One block's chunk of entries of a side: each thread's kPer consecutive
+// entries and their rows.
+struct ChunkShared {
+  uint32_t head[kChunk];  // the row that starts at an entry of the chunk, or 0
+  uint32_t wmax[kThreads / 64];
+  int32_t r0;
+};
+struct ChunkRows {
+  uint32_t c0, c1;        // the chunk's entries
+  int32_t r0;             // row of the first
+  uint32_t e0;            // the thread's first entry
+  int32_t row[kPer];
+};
+
+__device__ __forceinline__ ChunkRows chunk_rows(const PSide& P, uint32_t chunk, ChunkShared& sh) {
+  const int tid = static_cast<int>(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+  ChunkRows c;
+  c.c0 = chunk * kChunk;
+  c.c1 = min(P.m, c.c0 + kChunk);
+  if (wave == 0) {
+    const int32_t r = row_of(P.off, P.n, c.c0);
+    if (lane == 0) sh.r0 = r;
+  }
+  for (uint32_t i = tid; i < kChunk; i += kThreads) sh.head[i] = 0;
+  __syncthreads();
+  c.r0 = sh.r0;
+  for (int64_t x = static_cast<int64_t>(c.r0) + 1 + tid; x < P.n; x += kThreads) {
+    const uint32_t b = P.off[x];
+    if (b >= c.c1) break;
+    sh.head[b - c.c0] = static_cast<uint32_t>(x);
+  }
+  __syncthreads();
+  c.e0 = c.c0 + tid * kPer;
+  uint32_t mx = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    mx = max(mx, sh.head[tid * kPer + j]);
+    c.row[j] = static_cast<int32_t>(mx);
+  }
+  uint32_t x = mx;  // rows grow along the entries: a running maximum
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t up = __shfl_up(x, d, 64);
+    if (lane >= d) x = max(x, up);
+  }
+  if (lane == 63) sh.wmax[wave] = x;
+  uint32_t before = __shfl_up(x, 1, 64);
+  if (lane == 0) before = 0;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) before = max(before, sh.wmax[w]);
+  before = max(before, static_cast<uint32_t>(c.r0));
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) c.row[j] = max(c.row[j], static_cast<int32_t>(before));
+  return c;
+}
+
+// Exclusive sums over the block's threads of nv 64-bit values, and totals.
+template <int kNv, int kT = kThreads>
+__device__ __forceinline__ void block_excl64(unsigned long long (&v)[kNv], unsigned long long (&total)[kNv],
+                                             unsigned long long (*sh)[kNv]) {
+  const int lane = static_cast<int>(threadIdx.x) & 63, wave = static_cast<int>(threadIdx.x) >> 6;
+  unsigned long long x[kNv];
+#pragma unroll
+  for (int k = 0; k < kNv; ++k) x[k] = v[k];
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+#pragma unroll
+    for (int k = 0; k < kNv; ++k) {
+      const unsigned long long up = __shfl_up(x[k], d, 64);
+      if (lane >= d) x[k] += up;
     }
   }
+  __syncthreads();
+  if (lane == 63)
+#pragma unroll
+    for (int k = 0; k < kNv; ++k) sh[wave][k] = x[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kNv; ++k) {
+    unsigned long long before = 0, all = 0;
+    for (int w = 0; w < kT / 64; ++w) {
+      before += w < wave ? sh[w][k] : 0ull;
+      all += sh[w][k];
+    }
+    v[k] = before + x[k] - v[k];
+    total[k] = all;
+  }
 }
 
-// Part-start flags of the runs of split direct items (kinds F and M) and of
-// the hub pivots' tally items (kind H): the first run, every kPartMaxRuns-th
-// run, and every run whose wedge range [pex, pex + len) of the item holds a
-// multiple of the part budget (part_work, or kHubTallyPartWork).
-__global__ void k_part_flags(PSide P, int k, uint32_t* flag) {
-  GRID_STRIDE(e64, P.m) {
-    const uint32_t e = static_cast<uint32_t>(e64);
-    const uint32_t len = P.len[k][e];
-    uint32_t f = 0;
-    if (len > 0) {
-      const int32_t x = static_cast<int32_t>(P.row[e]);
-      const Cand c = classify<false>(P, x, k);
-      if (c.split || c.cls == kHubC) {
-        const uint32_t b = P.off[x];
-        const uint32_t j = P.cnt[k][e] - P.cnt[k][b];
-        const unsigned long long pex = P.wsum[k][e] - P.wsum[k][b];
-        const unsigned long long pw =
-            k == kH ? static_cast<unsigned long long>(kHubTallyPartWork) : P.part_work;
-        f = (j % kPartMaxRuns == 0 || (pex + len - 1) / pw != (pex - 1) / pw) ? 1u : 0u;
+// Run counts of the four kinds of at most kChunk entries, in one word.
+__device__ __forceinline__ unsigned long long one_run(int k) { return 1ull << (16 * k); }
+__device__ __forceinline__ uint32_t runs_of(unsigned long long w, int k) {
+  return static_cast<uint32_t>(w >> (16 * k)) & 0xffffu;
+}
+
+// Pass over the entries: each chunk's runs and wedges per kind, the sums
+// before each row that starts in it, and each row's largest reverse key.
+template <int kNk>
+__global__ __launch_bounds__(kThreads, 4) void k_entries(PSides S) {
+  __shared__ ChunkShared sh;
+  __shared__ int32_t rm[kChunk + 1];  // largest reverse key + 1 of the rows from r0 on
+  __shared__ unsigned long long scan[kThreads / 64][kNk + 1];
+  const PSide& P = blockIdx.x < S.s[0].chunks ? S.s[0] : S.s[1];
+  const uint32_t chunk = blockIdx.x < S.s[0].chunks ? blockIdx.x : blockIdx.x - S.s[0].chunks;
+  const int tid = static_cast<int>(threadIdx.x);
+  for (uint32_t i = tid; i <= kChunk; i += kThreads) rm[i] = 0;
+  const ChunkRows c = chunk_rows(P, chunk, sh);
+  uint32_t w[kPer];
+  int32_t rev[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t e = c.e0 + j;
+    w[j] = e < c.c1 ? P.adj[e] : 0u;
+    rev[j] = e < c.c1 ? P.rev[e] : 0;
+  }
+  uint32_t len[kPer][kNk];
+  unsigned long long v[kNk + 1] = {};  // packed run counts, then wedges per kind
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t e = c.e0 + j;
+    const bool in = e < c.c1;
+    const uint32_t y = w[j] >> 1;
+    const Mid mid = load_mid(P.mids, y);
+    const int32_t x = c.row[j];
+    const uint32_t low = P.off[x] + static_cast<uint32_t>(P.cut[x]);
+#pragma unroll
+    for (int k = 0; k < kNk; ++k) {
+      const uint32_t l = in ? run_at(P, k, x, e, low, y, rev[j], mid).len : 0u;
+      len[j][k] = l;
+      if (l) v[0] += one_run(k);
+      v[1 + k] += l;
+    }
+    if (len[j][kR]) atomicMax(&rm[x - c.r0], P.rkey[y] + 1);
+  }
+  unsigned long long total[kNk + 1];
+  block_excl64<kNk + 1>(v, total, scan);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t e = c.e0 + j;
+    if (e < c.c1 && e == P.off[c.row[j]]) {
+#pragma unroll
+      for (int k = 0; k < kNk; ++k) {
+        P.row_cnt[k][c.row[j]] = runs_of(v[0], k);
+        P.row_sum[k][c.row[j]] = v[1 + k];
       }
     }
-    flag[e] = f;
-  }
-}
-
-// What one candidate adds to each list (scanned into list positions).
-struct PlanCount {
-  unsigned long long big_runs;    // runs in segs (hash, direct and reverse items)
-  unsigned long long small_runs;  // runs in small_segs
-  unsigned long long hub_runs;    // runs in hub_segs (per-vertex plans)
-  uint32_t small_items, hash, direct, direct_parts, direct_split, rev, rev_reduces, rev_acc, hub_parts, pad;
-};
-
-struct PlanCountSum {
-  __host__ __device__ PlanCount operator()(const PlanCount& a, const PlanCount& b) const {
-    PlanCount r;
-    r.big_runs = a.big_runs + b.big_runs;
-    r.small_runs = a.small_runs + b.small_runs;
-    r.hub_runs = a.hub_runs + b.hub_runs;
-    r.hub_parts = a.hub_parts + b.hub_parts;
-    r.pad = 0;
-    r.small_items = a.small_items + b.small_items;
-    r.hash = a.hash + b.hash;
-    r.direct = a.direct + b.direct;
-    r.direct_parts = a.direct_parts + b.direct_parts;
-    r.direct_split = a.direct_split + b.direct_split;
-    r.rev = a.rev + b.rev;
-    r.rev_reduces = a.rev_reduces + b.rev_reduces;
-    r.rev_acc = a.rev_acc + b.rev_acc;
-    return r;
-  }
-};
-
-// Plan statistics: wedges and runs per kernel (direct, small, hash,
-// reverse), then the sparse and the skipped wedges.
-enum : int { kStWedges = 0, kStRuns = 4, kStSparse = 8, kStSkipped = 9, kStWords = 10 };
-
-__device__ unsigned long long wave_sum(unsigned long long v) {
 #pragma unroll
-  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
+    for (int k = 0; k < kNk; ++k) {
+      if (len[j][k]) v[0] += one_run(k);
+      v[1 + k] += len[j][k];
+    }
+  }
+  if (tid < kNk) {
+    unsigned long long t = 0;
+#pragma unroll
+    for (int k = 0; k < kNk; ++k) t = tid == k ? total[1 + k] : t;
+    P.chunk_cnt[tid][chunk] = runs_of(total[0], tid);
+    P.chunk_sum[tid][chunk] = t;
+  }
+  __syncthreads();
+  // rows inside the chunk are stored, those that cross its ends joined
+  for (uint32_t i = tid; i <= kChunk; i += kThreads) {
+    if (rm[i] == 0) continue;
+    const int32_t x = c.r0 + static_cast<int32_t>(i);
+    if (P.off[x] >= c.c0 && P.off[x + 1] <= c.c1)
+      P.rmax[x] = rm[i] - 1;
+    else
+      atomicMax(&P.rmax[x], rm[i] - 1);
+  }
 }
+
+// scan_block, with the total after the last element.
+template <class T>
+__device__ __forceinline__ T scan_with_total(T* p, uint32_t n) {
+  const T all = scan_block(p, n);
+  if (threadIdx.x == 0) p[n] = all;
+  return all;
+}
+
+// The chunks' runs (blocks [0, 2 nk)) and wedges (the rest) per side and kind.
+__global__ __launch_bounds__(kScanThreads) void k_scan_chunks(PSides S) {
+  const int nk = S.s[0].nk;
+  const int b = static_cast<int>(blockIdx.x) % (2 * nk), side = b / nk, k = b % nk;
+  const PSide& P = S.s[side];
+  if (static_cast<int>(blockIdx.x) < 2 * nk)
+    scan_with_total(P.chunk_cnt[k], P.chunks);
+  else
+    scan_with_total(P.chunk_sum[k], P.chunks);
+}
+
+// ---- parts ---------------------------------------------------------------------
+//
+// Split direct items (kinds F and M; count plans) and the hub pivots' tally
+// items (kind H) start a part at the first run, at every kPartMaxRuns-th run
+// and at every run whose wedge range [pex, pex + len) of the item holds a
+// multiple of the part budget (part_work, or kHubTallyPartWork).  Such items
+// are few and large: they are listed (k_find_parts), and a block walks the
+// entries of one.
+
+// A listed candidate: row, kind | side << 2.
+__global__ __launch_bounds__(kThreads) void k_find_parts(PSides S, uint2* list, uint32_t max_list, uint32_t* n_list) {
+  GRID_STRIDE(i, static_cast<int64_t>(S.s[0].n) + S.s[1].n) {
+    const bool side0 = i < S.s[0].n;
+    const PSide& P = side0 ? S.s[0] : S.s[1];
+    const int32_t x = static_cast<int32_t>(side0 ? i : i - S.s[0].n);
+    if (P.pv) {
+      if (x >= P.T) continue;
+    } else {
+      // a run has at most the largest other degree of entries
+      const unsigned long long d = P.off[x + 1] - P.off[x];
+      if (d <= kPartMaxRuns && d * P.max_deg <= P.part_work) continue;
+    }
+    for (int k = 0; k < P.nk; ++k) {
+      if (k == kR || (P.pv && k != kH)) continue;
+      const Cand c = classify<false>(P, x, k);
+      if (!c.split && c.cls != kHubC) continue;
+      const uint32_t at = atomicAdd(n_list, 1u);
+      if (at < max_list) list[at] = make_uint2(static_cast<uint32_t>(x), static_cast<uint32_t>(k) | (P.side << 2));
+    }
+  }
+}
+
+// What a part's item needs: its first run (index in the item) and the item's
+// wedges before it.
+struct PartStart {
+  unsigned long long wedges;
+  uint32_t run, pad;
+};
+
+constexpr int kPartThreads = 1024;
+template <int kPass>
+__global__ __launch_bounds__(kPartThreads) void k_parts(PSides S, const uint2* list, const uint32_t* n_list,
+                                                    PartStart* direct, PartStart* hub) {
+  __shared__ unsigned long long scan[kPartThreads / 64][2];
+  __shared__ uint32_t sh[kPartThreads / 64];
+  const int tid = static_cast<int>(threadIdx.x);
+  for (uint32_t q = blockIdx.x; q < *n_list; q += gridDim.x) {
+    const int32_t x = static_cast<int32_t>(list[q].x);
+    const int k = static_cast<int>(list[q].y & 3u);
+    const PSide& P = S.s[list[q].y >> 2];
+    const uint32_t b = P.off[x], end = P.off[x + 1], low = b + static_cast<uint32_t>(P.cut[x]);
+    const int64_t cand = static_cast<int64_t>(x) * P.nk + k;
+    const unsigned long long pw = k == kH ? static_cast<unsigned long long>(kHubTallyPartWork) : P.part_work;
+    PartStart* out = kPass ? (k == kH ? hub : direct) + P.part_pos[cand] : nullptr;
+    unsigned long long runs = 0, wedges = 0;
+    uint32_t parts = 0;
+    for (uint32_t t0 = b; t0 < end; t0 += kPartThreads * kPer) {
+      uint32_t len[kPer];
+      unsigned long long v[2] = {0, 0}, total[2];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const uint32_t e = t0 + tid * kPer + j;
+        len[j] = 0;
+        if (e >= t0 && e < end) {
+          const uint32_t y = P.adj[e] >> 1;
+          len[j] = run_at(P, k, x, e, low, y, P.rev[e], load_mid(P.mids, y)).len;
+        }
+        v[0] += len[j] ? 1 : 0;
+        v[1] += len[j];
+      }
+      block_excl64<2, kPartThreads>(v, total, scan);
+      uint32_t mine = 0, flag = 0;
+      unsigned long long r = runs + v[0], w = wedges + v[1];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        if (!len[j]) continue;
+        if (r % kPartMaxRuns == 0 || (w + len[j] - 1) / pw != (w - 1) / pw) {
+          flag |= 1u << j;
+          ++mine;
+        }
+        ++r;
+        w += len[j];
+      }
+      uint32_t all;
+      uint32_t at = parts + block_excl<kPartThreads>(mine, sh, all);
+      if (kPass) {
+        r = runs + v[0];
+        w = wedges + v[1];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          if (!len[j]) continue;
+          if (flag >> j & 1u) out[at++] = PartStart{w, static_cast<uint32_t>(r), 0u};
+          ++r;
+          w += len[j];
+        }
+      }
+      parts += all;
+      runs += total[0];
+      wedges += total[1];
+    }
+    if (!kPass && tid == 0) P.parts[cand] = parts;
+    __syncthreads();
+  }
+}
+
+// ---- candidates ------------------------------------------------------------------
+
+// What the candidates add to each list (scanned into list positions), then
+// the plan's statistics: wedges and runs per kernel (direct, small, hash,
+// reverse), the sparse and the skipped wedges (summed only).
+enum : int {
+  kBigRuns = 0,    // runs in segs (hash, direct and reverse items)
+  kSmallRuns,      // runs in small_segs
+  kHubRuns,        // runs in hub_segs (per-vertex plans)
+  kSmallItems,
+  kHashItems,
+  kDirect,
+  kDirectParts,    // parts of split direct items
+  kDirectSplit,
+  kWindows,        // per-vertex plans: key windows of the direct items
+  kRev,
+  kRevReduces,
+  kRevAcc,
+  kHubParts,
+  kLists,
+  kStWedges = kLists,
+  kStRuns = kStWedges + 4,
+  kStSparse = kStRuns + 4,
+  kStSkipped,
+  kCounters
+};
 
 // Per-vertex plans: the key windows of a direct item (kPVWindowPacked keys
 // with packed counters, see pv_packed; else kPVWindow keys).
@@ -347,115 +645,174 @@ __device__ uint32_t pv_window_count(int32_t key_lo, int32_t key_hi, bool packed)
   return (static_cast<uint32_t>(key_hi - key_lo) + win - 1) / win;
 }
 
-// Each candidate's list counts; the statistics are summed per thread over
-// its candidates, then per wavefront, then once per wavefront into stats.
-__global__ void k_count(PSide P, PlanCount* counts, unsigned long long* stats) {
-  const int64_t nc = P.nk * static_cast<int64_t>(P.n);
-  unsigned long long w[4] = {0, 0, 0, 0}, r[4] = {0, 0, 0, 0}, sparse = 0, skipped = 0;
-  GRID_STRIDE(i, nc) {
-    const int32_t x = static_cast<int32_t>(i / P.nk);
-    const int k = static_cast<int>(i % P.nk);
-    const Cand c = classify<true>(P, x, k);
-    PlanCount q{};
-    int slot = -1;
-    uint32_t mult = 1;
-    switch (c.cls) {
-      case kSmallC:
-        q.small_runs = c.nseg;
-        q.small_items = 1;
-        slot = 1;
-        break;
-      case kHashC:
-        q.big_runs = c.nseg;
-        q.hash = 1;
-        slot = 2;
-        break;
-      case kDirectC:
-        q.big_runs = c.nseg;
-        q.direct = 1;
-        if (c.split) {
-          q.direct_parts = c.nparts;
-          q.direct_split = 1;
-        }
-        slot = 0;
-        if (P.pv)  // the windows share the runs
-          mult = pv_window_count(c.key_lo, c.key_hi, pv_item_packed(P, c.nseg, c.flags));
-        break;
-      case kRevC:
-        q.big_runs = c.nseg;
-        if (c.nparts) {
-          q.rev = c.nparts;
-          q.rev_reduces = 1;
-          q.rev_acc = c.nparts;
-        } else {
-          q.rev = 1;
-        }
-        slot = 3;
-        break;
-      case kHubC:  // the dense block's sparse wedges: not in the kernels' statistics
-        q.hub_runs = c.nseg;
-        q.hub_parts = c.nparts;
-        break;
-      default:
-        skipped += c.work;
-        break;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      w[j] += j == slot ? c.work * mult : 0ull;
-      r[j] += j == slot ? static_cast<unsigned long long>(c.nseg) * mult : 0ull;
-    }
-    if (slot >= 0) sparse += c.work;
-    counts[P.cand0 + i] = q;
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    w[j] = wave_sum(w[j]);
-    r[j] = wave_sum(r[j]);
-  }
-  sparse = wave_sum(sparse);
-  skipped = wave_sum(skipped);
-  if ((threadIdx.x & 63) == 0) {
-    for (int j = 0; j < 4; ++j) {
-      if (w[j]) atomicAdd(&stats[kStWedges + j], w[j]);
-      if (r[j]) atomicAdd(&stats[kStRuns + j], r[j]);
-    }
-    if (sparse) atomicAdd(&stats[kStSparse], sparse);
-    if (skipped) atomicAdd(&stats[kStSkipped], skipped);
+// Add candidate c's list counts to q.
+__device__ __forceinline__ void add_lists(const PSide& P, const Cand& c, unsigned long long* q) {
+  switch (c.cls) {
+    case kSmallC:
+      q[kSmallRuns] += c.nseg;
+      q[kSmallItems] += 1;
+      break;
+    case kHashC:
+      q[kBigRuns] += c.nseg;
+      q[kHashItems] += 1;
+      break;
+    case kDirectC:
+      q[kBigRuns] += c.nseg;
+      q[kDirect] += 1;
+      if (c.split) {
+        q[kDirectParts] += c.nparts;
+        q[kDirectSplit] += 1;
+      }
+      if (P.pv) q[kWindows] += pv_window_count(c.key_lo, c.key_hi, pv_item_packed(P, c.nseg, c.flags));
+      break;
+    case kRevC:
+      q[kBigRuns] += c.nseg;
+      q[kRev] += c.nparts ? c.nparts : 1;
+      if (c.nparts) {
+        q[kRevReduces] += 1;
+        q[kRevAcc] += c.nparts;
+      }
+      break;
+    case kHubC:  // the dense block's sparse wedges: not in the kernels' statistics
+      q[kHubRuns] += c.nseg;
+      q[kHubParts] += c.nparts;
+      break;
+    default:
+      break;
   }
 }
 
-uint32_t sat32(unsigned long long w) { return w > 0xffffffffull ? 0xffffffffu : static_cast<uint32_t>(w); }
+// A block's rows of a side (side 0's blocks first), one per thread; the
+// row's candidates.
+struct RowCands {
+  int side;
+  int32_t x;  // may be past the side's last row: no candidates
+  Cand c[4];
+};
+template <int kNk>
+__device__ __forceinline__ RowCands row_cands(const PSides& S) {
+  RowCands r;
+  r.side = blockIdx.x < S.s[0].row_chunks ? 0 : 1;
+  const PSide& P = S.s[r.side];
+  const uint32_t chunk = r.side ? blockIdx.x - S.s[0].row_chunks : blockIdx.x;
+  const int64_t x = static_cast<int64_t>(chunk) * kRowChunk + threadIdx.x;
+  r.x = static_cast<int32_t>(x);
+#pragma unroll
+  for (int k = 0; k < kNk; ++k) {
+    r.c[k] = Cand{};
+    r.c[k].cls = kSkip;
+    if (x < P.n) r.c[k] = classify<true>(P, r.x, k);
+  }
+  return r;
+}
+
+// Each block of rows: its candidates' list counts and statistics
+// (counts[q * stride + block]).
+template <int kNk>
+__global__ __launch_bounds__(kThreads) void k_count(PSides S, unsigned long long* counts, uint32_t stride) {
+  __shared__ unsigned long long sh[kThreads / 64][kCounters];
+  const RowCands r = row_cands<kNk>(S);
+  const PSide& P = S.s[r.side];
+  unsigned long long q[kCounters] = {};
+#pragma unroll
+  for (int k = 0; k < kNk; ++k) {
+    const Cand& c = r.c[k];
+    add_lists(P, c, q);
+    if (c.cls == kSkip) q[kStSkipped] += c.work;
+    if (c.cls == kSkip || c.cls == kHubC) continue;
+    const int slot = c.cls == kSmallC ? 1 : c.cls == kHashC ? 2 : c.cls == kDirectC ? 0 : 3;
+    unsigned long long mult = 1;
+    if (P.pv && slot == 0)  // the windows share the runs
+      mult = pv_window_count(c.key_lo, c.key_hi, pv_item_packed(P, c.nseg, c.flags));
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      q[kStWedges + t] += t == slot ? c.work * mult : 0ull;
+      q[kStRuns + t] += t == slot ? c.nseg * mult : 0ull;
+    }
+    q[kStSparse] += c.work;
+  }
+#pragma unroll
+  for (int t = 0; t < kCounters; ++t) {
+    unsigned long long v = q[t];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][t] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < kCounters) {
+    unsigned long long v = 0;
+    for (int w = 0; w < kThreads / 64; ++w) v += sh[w][threadIdx.x];
+    counts[static_cast<size_t>(threadIdx.x) * stride + blockIdx.x] = v;
+  }
+}
+
+// Scan of the row chunks' counts, one block per counter: the totals go to
+// out[q], the sums before side 1's first chunk to out[kCounters + q].
+__global__ __launch_bounds__(kScanThreads) void k_scan_rows(unsigned long long* counts, uint32_t stride, uint32_t n,
+                                                            uint32_t side1, unsigned long long* out) {
+  unsigned long long* c = counts + static_cast<size_t>(blockIdx.x) * stride;
+  const unsigned long long all = scan_with_total(c, n);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = all;
+    out[kCounters + blockIdx.x] = c[side1];  // (side1 <= n)
+  }
+}
+
 __device__ uint32_t dsat32(unsigned long long w) { return w > 0xffffffffull ? 0xffffffffu : static_cast<uint32_t>(w); }
 
-// A direct item before ordering: its row, kind and parts.
-struct DirectMeta {
-  int32_t x;
-  uint32_t kind_side;   // kind | side << 2
-  uint32_t nparts;      // 0: one item
-  uint32_t part_base;   // first of its part starts
-};
+// Where a candidate's runs go: run number c of its kind (over the whole side)
+// goes to x + c; y says which list: kNowhere, a list with the top bit set, or
+// the index of a small item.
+constexpr uint32_t kNowhere = 0xffffffffu, kToSegs = 0x80000000u, kToHub = 0x80000001u;
+
+// The order of hash and direct items: heaviest first, by the work's exponent
+// and its nine bits after the leading one (a 16-bit key: two sort passes);
+// per-vertex plans list side 0's first.
+__device__ __forceinline__ uint32_t work_key(unsigned long long work, uint32_t side) {
+  uint32_t f = 0;
+  if (work) {
+    const int e = 63 - __builtin_clzll(work);
+    f = (static_cast<uint32_t>(e) << 9) | (static_cast<uint32_t>(e >= 9 ? work >> (e - 9) : work << (9 - e)) & 0x1ffu);
+  }
+  return (side << 15) | (0x7fffu - f);
+}
 
 struct ItemOut {
-  Item* small;         // small items (grouped later)
-  int32_t* small_owner;  // per-vertex plans: the owner of every small item
+  // small items (grouped later): work | hub pivot << 30 | side << 31, first run, owner
+  uint32_t* small_key;
+  uint32_t* small_seg;
+  int32_t* small_owner;
   Item* hash;          // hash items, unordered
-  unsigned long long* hash_key;
-  Item* direct;        // direct items, unordered
-  unsigned long long* direct_key;
-  DirectMeta* direct_meta;
+  uint32_t* hash_key;
+  Item* direct;        // direct items that are not split (per-vertex plans: their key windows), unordered
+  uint32_t* direct_key;
+  Item* split;         // split direct items
+  uint32_t* split_part;  // ... the first part's place
   Item* rev;           // reverse items (final)
   Reduce* reduces;     // reverse reduces first
 };
 
-__global__ void k_items(PSide P, const PlanCount* pos, ItemOut o) {
-  const int64_t nc = P.nk * static_cast<int64_t>(P.n);
-  GRID_STRIDE(i, nc) {
-    const int32_t x = static_cast<int32_t>(i / P.nk);
-    const int k = static_cast<int>(i % P.nk);
-    const Cand c = classify<true>(P, x, k);
-    if (c.cls == kSkip || c.cls == kHubC) continue;  // hub tally items: k_hub_parts
-    const PlanCount q = pos[P.cand0 + i];
+// Every candidate's item into its list, and its runs' place.
+template <int kNk>
+__global__ __launch_bounds__(kThreads) void k_items(PSides S, const unsigned long long* counts, uint32_t stride,
+                                                    ItemOut o) {
+  __shared__ unsigned long long sh[kThreads / 64][kLists];
+  const RowCands rc = row_cands<kNk>(S);
+  const PSide& P = S.s[rc.side];
+  unsigned long long q[kLists] = {}, total[kLists];
+#pragma unroll
+  for (int k = 0; k < kNk; ++k) add_lists(P, rc.c[k], q);
+  block_excl64<kLists>(q, total, sh);
+#pragma unroll
+  for (int t = 0; t < kLists; ++t) q[t] += counts[static_cast<size_t>(t) * stride + blockIdx.x];
+  const int32_t x = rc.x;
+  if (x >= P.n) return;
+#pragma unroll
+  for (int k = 0; k < kNk; ++k) {
+    const Cand& c = rc.c[k];
+    const int64_t cand = static_cast<int64_t>(x) * kNk + k;
+    uint2 place = make_uint2(0u, kNowhere);
     Item it{};
     it.seg_count = c.nseg;
     it.owner = x;
@@ -467,49 +824,70 @@ __global__ void k_items(PSide P, const PlanCount* pos, ItemOut o) {
     it.work = dsat32(c.work);
     it.graph = 0;
     if (c.cls == kSmallC) {
-      it.seg_begin = static_cast<uint32_t>(q.small_runs);
-      o.small[q.small_items] = it;
-      if (P.pv) o.small_owner[q.small_items] = x;
-      continue;
-    }
-    it.seg_begin = static_cast<uint32_t>(q.big_runs);
-    if (c.cls == kHashC) {
-      o.hash[q.hash] = it;
-      o.hash_key[q.hash] = c.work;
-    } else if (c.cls == kDirectC) {
-      o.direct[q.direct] = it;
-      // per-vertex plans: side 0 first, then heaviest first (ascending keys);
-      // count plans: heaviest first (descending keys)
-      o.direct_key[q.direct] =
-          P.pv ? (static_cast<unsigned long long>(P.side) << 48) | ((1ull << 48) - 1 - min(c.work, (1ull << 48) - 1))
-               : c.work;
-      o.direct_meta[q.direct] = DirectMeta{x, static_cast<uint32_t>(k) | (P.side << 2), c.split ? c.nparts : 0u,
-                                           q.direct_parts};
-    } else if (c.nparts == 0) {
-      o.rev[q.rev] = it;
-    } else {
-      // parts of kReverseCountMaxSegs runs (their work is summed once the
-      // runs are written), reduced into one accumulator slot each
-      for (uint32_t p = 0; p < c.nparts; ++p) {
-        Item part = it;
-        part.seg_begin = it.seg_begin + p * kReverseCountMaxSegs;
-        part.seg_count = min(kReverseCountMaxSegs, c.nseg - p * kReverseCountMaxSegs);
-        part.flags |= kItemMultiPart;
-        part.acc_slot = static_cast<int32_t>(q.rev_acc + p);
-        part.work = 0;
-        o.rev[q.rev + p] = part;
+      it.seg_begin = static_cast<uint32_t>(q[kSmallRuns]);
+      place = make_uint2(it.seg_begin, static_cast<uint32_t>(q[kSmallItems]));
+      o.small_key[q[kSmallItems]] = it.work | ((c.flags & kItemHubPairs) ? 1u << 30 : 0u) | (P.side << 31);
+      o.small_seg[q[kSmallItems]] = it.seg_begin;
+      o.small_owner[q[kSmallItems]] = x;
+    } else if (c.cls == kHubC) {
+      place = make_uint2(static_cast<uint32_t>(q[kHubRuns]), kToHub);
+      P.part_pos[cand] = static_cast<uint32_t>(q[kHubParts]);
+    } else if (c.cls != kSkip) {
+      it.seg_begin = static_cast<uint32_t>(q[kBigRuns]);
+      place = make_uint2(it.seg_begin, kToSegs);
+      if (c.cls == kHashC) {
+        o.hash[q[kHashItems]] = it;
+        o.hash_key[q[kHashItems]] = work_key(c.work, 0);
+      } else if (c.cls == kDirectC) {
+        if (kNk == 4) {  // key windows that share the runs
+          const bool packed = pv_item_packed(P, c.nseg, c.flags);
+          const uint32_t nw = pv_window_count(c.key_lo, c.key_hi, packed);
+          const int32_t win = packed ? kPVWindowPacked : kPVWindow;
+          if (packed) it.flags |= kItemPacked;
+          for (uint32_t w = 0; w < nw; ++w) {
+            it.key_lo = c.key_lo + static_cast<int32_t>(w) * win;
+            it.key_hi = min(c.key_hi, it.key_lo + win);
+            o.direct[q[kWindows] + w] = it;
+            o.direct_key[q[kWindows] + w] = work_key(c.work, P.side);
+          }
+        } else if (c.split) {
+          o.split[q[kDirectSplit]] = it;
+          o.split_part[q[kDirectSplit]] = static_cast<uint32_t>(q[kDirectParts]);
+          P.part_pos[cand] = static_cast<uint32_t>(q[kDirectParts]);
+        } else {
+          o.direct[q[kDirect] - q[kDirectSplit]] = it;
+          o.direct_key[q[kDirect] - q[kDirectSplit]] = work_key(c.work, 0);
+        }
+      } else if (c.nparts == 0) {
+        o.rev[q[kRev]] = it;
+      } else {
+        // parts of kReverseCountMaxSegs runs (their work is summed once the
+        // runs are written), reduced into one accumulator slot each
+        for (uint32_t p = 0; p < c.nparts; ++p) {
+          Item part = it;
+          part.seg_begin = it.seg_begin + p * kReverseCountMaxSegs;
+          part.seg_count = min(kReverseCountMaxSegs, c.nseg - p * kReverseCountMaxSegs);
+          part.flags |= kItemMultiPart;
+          part.acc_slot = static_cast<int32_t>(q[kRevAcc] + p);
+          part.work = 0;
+          o.rev[q[kRev] + p] = part;
+        }
+        Reduce r{};
+        r.acc_slot = static_cast<int32_t>(q[kRevAcc]);
+        r.n_parts = static_cast<int32_t>(c.nparts);
+        r.owner = x;
+        r.key_lo = c.key_lo;
+        r.key_hi = c.key_hi;
+        r.flags = c.flags;
+        r.side = P.side;
+        r.graph = 0;
+        o.reduces[q[kRevReduces]] = r;
       }
-      Reduce r{};
-      r.acc_slot = static_cast<int32_t>(q.rev_acc);
-      r.n_parts = static_cast<int32_t>(c.nparts);
-      r.owner = x;
-      r.key_lo = c.key_lo;
-      r.key_hi = c.key_hi;
-      r.flags = c.flags;
-      r.side = P.side;
-      r.graph = 0;
-      o.reduces[q.rev_reduces] = r;
     }
+    // runs are numbered per kind over the side: those before the row
+    if (place.y != kNowhere) place.x -= P.chunk_cnt[k][P.off[x] / kChunk] + P.row_cnt[k][x];
+    P.place[cand] = place;
+    add_lists(P, c, q);
   }
 }
 
@@ -518,127 +896,216 @@ __global__ void k_items(PSide P, const PlanCount* pos, ItemOut o) {
 // of kGroupChunk items.  A group holds items of one side, at most
 // min(kSmallMaxItems, 2^(32 - key_bits) - 1) of them (the group's hash key is
 // (index in group << key_bits) | key), and an item whose hub-pair counts go
-// to the dense path stays alone.  Pass 0 counts each chunk's groups; pass 1
-// writes them and each item's index in its group.
+// to the dense path stays alone.  A wavefront takes a chunk: each item's
+// lanes find where a group that starts at it would end (a search over the
+// work's prefix sums, up to the next item that may not join), the chain of
+// starts from the chunk's first item is followed by lane reads (a few cycles
+// a group), and the groups are written by their first items' lanes.
+// Pass 0 counts each chunk's groups; pass 1 writes them and each item's index
+// in its group.
+struct SmallList {
+  const uint32_t* key;  // work | hub pivot << 30 | side << 31
+  const uint32_t* seg;  // first run (the next item's ends it)
+  const int32_t* owner;
+  uint32_t n, n_runs;
+  int32_t kb0, kb1;     // key bits per side
+  bool pv;
+};
+
+// v of a lane that every lane names.
+__device__ __forceinline__ uint32_t lane_word(uint32_t v, uint32_t lane) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(
+      static_cast<int>(v), __builtin_amdgcn_readfirstlane(static_cast<int>(lane))));
+}
+
 template <int kPass>
-__global__ void k_group(const Item* small, int64_t n_small, int32_t kb0, int32_t kb1, bool pv, uint32_t* chunk_groups,
-                        Item* groups, uint32_t* local_of) {
-  const int64_t n_chunks = (n_small + kGroupChunk - 1) / kGroupChunk;
-  GRID_STRIDE(ch, n_chunks) {
-    const int64_t i0 = ch * kGroupChunk, i1 = min(n_small, i0 + kGroupChunk);
-    uint32_t g = kPass ? chunk_groups[ch] : 0u;
-    Item grp{};
-    bool open = false;
-    uint32_t local = 0;
-    for (int64_t i = i0; i < i1; ++i) {
-      const Item it = small[i];
-      const int32_t kb = it.side ? kb1 : kb0;
-      const uint32_t max_items = min(kSmallMaxItems, (1u << (32 - kb)) - 1u);
-      const bool hub = (it.flags & kItemHubPairs) != 0;
-      if (open && (hub || (grp.flags & kItemHubPairs) || grp.side != it.side ||
-                   grp.work + it.work > kSmallGroupWork || local >= max_items)) {
-        if (kPass) {
-          grp.key_hi = static_cast<int32_t>(local);
-          groups[g] = grp;
-        }
-        ++g;
-        open = false;
-      }
-      if (!open) {
-        grp = Item{};
-        grp.seg_begin = it.seg_begin;
-        grp.owner = it.owner;
-        grp.acc_slot = pv ? static_cast<int32_t>(i) : -1;  // per-vertex plans: owners are listed per item
-        grp.flags = it.flags & kItemHubPairs;
-        grp.side = it.side;
-        local = 0;
-        open = true;
-      }
-      if (kPass) local_of[i] = local;
-      grp.seg_count += it.seg_count;
-      grp.work += it.work;
-      ++local;
+__global__ __launch_bounds__(kThreads) void k_group(SmallList s, uint32_t* chunk_groups, Item* groups,
+                                                    uint32_t* local_of) {
+  constexpr uint32_t kHub = 1u << 30, kSide = 1u << 31;
+  constexpr int kT = kGroupChunk / 64;
+  __shared__ uint32_t sums[kThreads / 64][kGroupChunk + 1];  // work before each item of the chunk
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t n_chunks = (s.n + kGroupChunk - 1) / kGroupChunk;
+  const uint32_t wave = threadIdx.x >> 6;
+  const uint32_t ch = blockIdx.x * (kThreads / 64) + wave;
+  if (ch >= n_chunks) return;
+  const uint32_t c0 = ch * kGroupChunk, cnt = min(s.n - c0, static_cast<uint32_t>(kGroupChunk));
+  uint32_t* P = sums[wave];
+  uint32_t key[kT];
+#pragma unroll
+  for (int t = 0; t < kT; ++t) key[t] = t * 64 + lane < cnt ? s.key[c0 + t * 64 + lane] : 0u;
+  uint32_t run = 0;
+  uint64_t stop[kT];  // items that may not join the one before
+  uint32_t last_kind = 0;
+#pragma unroll
+  for (int t = 0; t < kT; ++t) {
+    uint32_t w = key[t] & (kHub - 1), x = w;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t up = __shfl_up(x, d, 64);
+      if (lane >= static_cast<uint32_t>(d)) x += up;
     }
-    if (open) {
-      if (kPass) {
-        grp.key_hi = static_cast<int32_t>(local);
-        groups[g] = grp;
-      }
-      ++g;
-    }
-    if (!kPass) chunk_groups[ch] = g;
+    P[t * 64 + lane] = run + x - w;
+    run += lane_word(x, 63);
+    uint32_t before = __shfl_up(key[t], 1, 64);
+    if (lane == 0) before = last_kind;
+    stop[t] = __ballot((key[t] & kHub) || (before & kHub) || ((before ^ key[t]) & kSide));
+    last_kind = lane_word(key[t], 63);
   }
+  if (lane == 0) P[kGroupChunk] = run;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  uint32_t nx[kT];  // where a group that starts here ends
+#pragma unroll
+  for (int t = 0; t < kT; ++t) {
+    const uint32_t i = t * 64 + lane;
+    const uint32_t max_items = min(kSmallMaxItems, (1u << (32 - ((key[t] & kSide) ? s.kb1 : s.kb0))) - 1u);
+    uint32_t hi = min(cnt, i + max_items);  // the end is in (i, hi]
+#pragma unroll
+    for (int q = kT - 1; q >= 0; --q) {  // ... and no later than the next stop
+      const uint64_t m = q < t ? 0 : q > t ? stop[q] : lane == 63 ? 0 : stop[q] & ~((2ull << lane) - 1ull);
+      if (m) hi = min(hi, static_cast<uint32_t>(q * 64 + __builtin_ctzll(m)));
+    }
+    uint32_t lo = i + 1;
+    const uint32_t limit = P[i] + kSmallGroupWork;
+    while (lo < hi) {  // the last end whose wedges fit (an item alone always does)
+      const uint32_t mid = (lo + hi + 1) / 2;
+      if (P[mid] <= limit)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    nx[t] = lo;
+  }
+  uint64_t starts[kT] = {};
+  uint32_t pos = 0;
+#pragma unroll
+  for (int t = 0; t < kT; ++t) {
+    while (pos < min(cnt, static_cast<uint32_t>(t + 1) * 64)) {
+      starts[t] |= 1ull << (pos & 63u);
+      pos = lane_word(nx[t], pos & 63u);
+    }
+  }
+  uint32_t g = kPass ? chunk_groups[ch] : 0u;
+  uint32_t first = 0;  // the group that is open at a batch's start
+#pragma unroll
+  for (int t = 0; t < kT; ++t) {
+    if (kPass && t * 64 + lane < cnt) {
+      const uint32_t i = t * 64 + lane;
+      const uint64_t upto = starts[t] & ((2ull << lane) - 1ull);
+      const uint32_t mine = upto ? t * 64 + 63u - static_cast<uint32_t>(__clzll(static_cast<long long>(upto))) : first;
+      local_of[c0 + i] = i - mine;
+      if (mine == i) {
+        const uint32_t end = nx[t];
+        Item grp{};
+        grp.seg_begin = s.seg[c0 + i];
+        grp.seg_count = (c0 + end < s.n ? s.seg[c0 + end] : s.n_runs) - grp.seg_begin;
+        grp.owner = s.owner[c0 + i];
+        grp.key_hi = static_cast<int32_t>(end - i);
+        grp.acc_slot = s.pv ? static_cast<int32_t>(c0 + i) : -1;  // per-vertex plans: owners are listed per item
+        grp.flags = (key[t] & kHub) ? kItemHubPairs : 0u;
+        grp.side = key[t] >> 31;
+        grp.work = P[end] - P[i];
+        groups[g + __popcll(upto) - 1] = grp;
+      }
+    }
+    if (starts[t]) first = t * 64 + 63u - static_cast<uint32_t>(__clzll(static_cast<long long>(starts[t])));
+    g += static_cast<uint32_t>(__popcll(starts[t]));
+  }
+  if (!kPass && lane == 0) chunk_groups[ch] = g;
 }
 
 struct RunOut {
   Segment* segs;
   Segment* small_segs;
   const uint32_t* local_of;  // small item -> index in its group
-  uint32_t* part_start;      // split direct items: the entry of each part's first run
   // per-vertex plans
   uint32_t* seg_mid;         // each run's mid (| kMidWide), and its first edge's position
   uint32_t* seg_edge;
   uint32_t* small_seg_mid;
   uint32_t* small_seg_edge;
   Segment* hub_segs;         // the hub pivots' tally runs
-  uint32_t* hub_part_start;  // ... the entry of each tally item's first run
   uint32_t* any_wide;        // set when some run is flagged kMidWide
 };
 
-// Every run into its item's place: segs[item's first + j] for the j-th run
-// of the item, or small_segs tagged with the item's index in its group.
-__global__ void k_runs(PSide P, const PlanCount* pos, RunOut o) {
-  GRID_STRIDE(e64, P.m) {
-    const uint32_t e = static_cast<uint32_t>(e64);
-    const int32_t x = static_cast<int32_t>(P.row[e]);
-    const uint32_t b = P.off[x];
-    const uint32_t g = P.adj[e] & 1u;
-    // per-vertex plans: the run's mid, flagged when its credits may reach
-    // 2^32 (the mid's degree times the side's largest degree)
-    uint32_t mid = 0;
-    if (P.pv) {
-      const uint32_t y = P.adj[e] >> 1;
-      const unsigned long long dy = P.ooff[y + 1] - P.ooff[y];
-      const bool wide = P.wide_all || dy * P.max_deg >= (1ull << 32);
-      mid = y | (wide ? kMidWide : 0u);
+// Second pass over the entries: every run into its item's place,
+// segs[item's first + j] for the j-th run of the item, or small_segs tagged
+// with the item's index in its group.
+template <int kNk>
+__global__ __launch_bounds__(kThreads, 4) void k_runs(PSides S, RunOut o) {
+  __shared__ ChunkShared sh;
+  __shared__ unsigned long long scan[kThreads / 64][1];
+  const PSide& P = blockIdx.x < S.s[0].chunks ? S.s[0] : S.s[1];
+  const uint32_t chunk = blockIdx.x < S.s[0].chunks ? blockIdx.x : blockIdx.x - S.s[0].chunks;
+  const ChunkRows c = chunk_rows(P, chunk, sh);
+  uint32_t w[kPer];
+  int32_t rev[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t e = c.e0 + j;
+    w[j] = e < c.c1 ? P.adj[e] : 0u;
+    rev[j] = e < c.c1 ? P.rev[e] : 0;
+  }
+  Run run[kPer][kNk];
+  bool wide[kPer];
+  unsigned long long v[1] = {0}, total[1];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t e = c.e0 + j;
+    const uint32_t y = w[j] >> 1;
+    const Mid mid = load_mid(P.mids, y);
+    const int32_t x = c.row[j];
+    const uint32_t low = P.off[x] + static_cast<uint32_t>(P.cut[x]);
+    // per-vertex plans: flagged when the run's credits may reach 2^32 (the
+    // mid's degree times the side's largest degree)
+    wide[j] = kNk == 4 && (P.wide_all || static_cast<unsigned long long>(mid.end - mid.off) * P.max_deg >= (1ull << 32));
+#pragma unroll
+    for (int k = 0; k < kNk; ++k) {
+      run[j][k] = run_at(P, k, x, e, low, y, rev[j], mid);
+      if (e >= c.c1) run[j][k].len = 0;
+      if (run[j][k].len) v[0] += one_run(k);
     }
-    for (int k = 0; k < P.nk; ++k) {
-      if (P.len[k][e] == 0) continue;
-      const Cand c = classify<true>(P, x, k);
-      if (c.cls == kSkip) continue;
-      const PlanCount q = pos[P.cand0 + P.nk * static_cast<int64_t>(x) + k];
-      const Run r = run_at(P, k, x, e);
-      const uint32_t j = P.cnt[k][e] - P.cnt[k][b];
-      const uint32_t len_g = (r.len << 1) | g;
-      if (c.cls == kHubC) {
-        o.hub_segs[q.hub_runs + j] = Segment{r.start, len_g};
-        const uint32_t* bs = P.bnd[2];
-        if (bs[e + 1] != bs[e]) o.hub_part_start[q.hub_parts + (bs[e] - bs[b])] = e;
+  }
+  block_excl64<1>(v, total, scan);
+  uint32_t before[kNk];
+#pragma unroll
+  for (int k = 0; k < kNk; ++k) before[k] = P.chunk_cnt[k][chunk] + runs_of(v[0], k);
+  bool any_wide = false;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t e = c.e0 + j;
+#pragma unroll
+    for (int k = 0; k < kNk; ++k) {
+      const Run r = run[j][k];
+      if (r.len == 0) continue;
+      const uint2 place = P.place[static_cast<int64_t>(c.row[j]) * kNk + k];
+      const uint32_t at = place.x + before[k]++;
+      if (place.y == kNowhere) continue;
+      const uint32_t len_g = (r.len << 1) | (w[j] & 1u);
+      if (place.y == kToHub) {
+        o.hub_segs[at] = Segment{r.start, len_g};
         continue;
       }
-      if (P.pv && (mid & kMidWide) && *reinterpret_cast<volatile uint32_t*>(o.any_wide) == 0)
-        atomicOr(o.any_wide, 1u);
-      if (c.cls == kSmallC) {
-        const size_t at = q.small_runs + j;
-        o.small_segs[at] = Segment{r.start, (o.local_of[q.small_items] << 16) | len_g};
-        if (P.pv) {
-          o.small_seg_mid[at] = mid;
-          o.small_seg_edge[at] = e;
-        }
-      } else {
-        const size_t at = q.big_runs + j;
+      const uint32_t mid = (w[j] >> 1) | (wide[j] ? kMidWide : 0u);
+      any_wide = any_wide || wide[j];
+      if (place.y == kToSegs) {
         o.segs[at] = Segment{r.start, len_g};
-        if (P.pv) {
+        if (kNk == 4) {
           o.seg_mid[at] = mid;
           o.seg_edge[at] = e;
         }
-        if (c.split) {
-          const uint32_t* bs = P.bnd[k == kF ? 0 : 1];
-          if (bs[e + 1] != bs[e]) o.part_start[q.direct_parts + (bs[e] - bs[b])] = e;
+      } else {
+        o.small_segs[at] = Segment{r.start, (o.local_of[place.y] << 16) | len_g};
+        if (kNk == 4) {
+          o.small_seg_mid[at] = mid;
+          o.small_seg_edge[at] = e;
         }
       }
     }
   }
+  if (kNk == 4 && __ballot(any_wide) && (threadIdx.x & 63) == 0 &&
+      *reinterpret_cast<volatile uint32_t*>(o.any_wide) == 0)
+    atomicOr(o.any_wide, 1u);
 }
 
 // The work of every reverse part (at most kReverseCountMaxSegs runs).
@@ -652,142 +1119,105 @@ __global__ void k_rev_part_work(Item* rev, int64_t n, const Segment* segs) {
   }
 }
 
+// A part of an item: runs [p.run, the next part's first) of its seg_count.
+__device__ __forceinline__ Item part_of(Item it, uint32_t seg_begin, uint32_t seg_count, unsigned long long work,
+                                        const PartStart* parts, uint32_t p, uint32_t n) {
+  const PartStart s = parts[p];
+  const uint32_t run_end = p + 1 < n ? parts[p + 1].run : seg_count;
+  const unsigned long long w_end = p + 1 < n ? parts[p + 1].wedges : work;
+  it.seg_begin = seg_begin + s.run;
+  it.seg_count = run_end - s.run;
+  it.work = dsat32(w_end - s.wedges);
+  return it;
+}
+
 // The hub pivots' tally items (per-vertex plans), one per part of each
-// pivot's hub runs (parts start at the flagged runs).
-__global__ void k_hub_parts(PSide P, const PlanCount* pos, const uint32_t* part_start, Item* out) {
-  GRID_STRIDE(x64, P.T) {
-    const int32_t x = static_cast<int32_t>(x64);
+// pivot's hub runs.
+__global__ __launch_bounds__(kThreads) void k_hub_parts(PSides S, const PartStart* parts, Item* out) {
+  GRID_STRIDE(i, static_cast<int64_t>(S.s[0].T) + S.s[1].T) {
+    const PSide& P = i < S.s[0].T ? S.s[0] : S.s[1];
+    const int32_t x = static_cast<int32_t>(i < S.s[0].T ? i : i - S.s[0].T);
     const Cand c = classify<true>(P, x, kH);
     if (c.cls != kHubC) continue;
-    const PlanCount q = pos[P.cand0 + P.nk * static_cast<int64_t>(x) + kH];
-    const uint32_t b = P.off[x], end = P.off[x + 1];
-    const uint32_t* cnt = P.cnt[kH];
-    const unsigned long long* ws = P.wsum[kH];
-    for (uint32_t p = 0; p < c.nparts; ++p) {
-      const uint32_t es = part_start[q.hub_parts + p];
-      const uint32_t en = p + 1 < c.nparts ? part_start[q.hub_parts + p + 1] : end;
-      Item it{};
-      it.seg_begin = static_cast<uint32_t>(q.hub_runs) + (cnt[es] - cnt[b]);
-      it.seg_count = cnt[en] - cnt[es];
-      it.owner = x;
-      it.key_lo = c.key_lo;
-      it.key_hi = c.key_hi;
-      it.acc_slot = -1;
-      it.flags = c.flags;
-      it.side = P.side;
-      it.work = dsat32(ws[en] - ws[es]);
-      it.graph = 0;
-      out[q.hub_parts + p] = it;
-    }
+    const int64_t cand = static_cast<int64_t>(x) * P.nk + kH;
+    const uint32_t first = P.place[cand].x + P.chunk_cnt[kH][P.off[x] / kChunk] + P.row_cnt[kH][x];
+    const uint32_t at = P.part_pos[cand];
+    Item it{};
+    it.owner = x;
+    it.key_lo = c.key_lo;
+    it.key_hi = c.key_hi;
+    it.acc_slot = -1;
+    it.flags = c.flags;
+    it.side = P.side;
+    for (uint32_t p = 0; p < c.nparts; ++p) out[at + p] = part_of(it, first, c.nseg, c.work, parts + at, p, c.nparts);
   }
 }
 
-__global__ void k_gather_items(const Item* in, const uint32_t* perm, int64_t n, Item* out) {
-  GRID_STRIDE(i, n) out[i] = in[perm[i]];
-}
-
-// Direct items in order of work (heaviest first): the parts of split items,
-// then the single items.
-struct DirectCount {
-  uint32_t parts, single, split;
+// Hash and direct items in order: a sort of (key, index) whose last pass
+// moves the items themselves.
+struct OrderIn {
+  const uint32_t* key;
+  __device__ __forceinline__ radix::Elt<2> load(uint32_t i) const { return {{key[i], i}}; }
 };
-
-struct DirectCountSum {
-  __host__ __device__ DirectCount operator()(const DirectCount& a, const DirectCount& b) const {
-    return DirectCount{a.parts + b.parts, a.single + b.single, a.split + b.split};
-  }
+struct GatherOut {
+  const Item* in;
+  Item* out;
+  __device__ __forceinline__ void store(uint32_t pos, const radix::Elt<2>& e) const { out[pos] = in[e.w[1]]; }
 };
-
-__global__ void k_direct_count(PSides S, const Item* direct, const DirectMeta* meta, const uint32_t* perm, int64_t n,
-                               bool pv, DirectCount* out) {
-  GRID_STRIDE(i, n) {
-    if (pv) {  // every item as its key windows, in order
-      const Item& it = direct[perm[i]];
-      const bool packed = pv_item_packed(S.s[it.side], it.seg_count, it.flags);
-      out[i] = DirectCount{pv_window_count(it.key_lo, it.key_hi, packed), 0u, 0u};
-      continue;
-    }
-    const uint32_t np = meta[perm[i]].nparts;
-    out[i] = DirectCount{np, np ? 0u : 1u, np ? 1u : 0u};
-  }
-}
-
-struct DirectOut {
+// The parts of split direct items and their reduces.
+struct SplitOut {
   Item* items;
   Reduce* reduces;
-  uint32_t n_parts;     // parts of all split items (the singles follow)
   uint32_t acc0;        // first accumulator slot of the direct parts
-  uint32_t red0;        // first reduce of the split direct items
-  bool pv;              // per-vertex plan: key windows
 };
 
-__global__ void k_direct_write(PSides S, const Item* direct, const DirectMeta* meta, const uint32_t* perm,
-                               const DirectCount* pos, int64_t n, const uint32_t* part_start, DirectOut o) {
+__global__ void k_split_parts(PSides S, const Item* split, const uint32_t* part_at, uint32_t n, uint32_t n_parts,
+                              const PartStart* parts, SplitOut o) {
   GRID_STRIDE(i, n) {
-    const Item it = direct[perm[i]];
-    const DirectMeta md = meta[perm[i]];
-    const DirectCount q = pos[i];
-    if (o.pv) {
-      const bool packed = pv_item_packed(S.s[it.side], it.seg_count, it.flags);
-      const uint32_t nw = pv_window_count(it.key_lo, it.key_hi, packed);
-      const int32_t win = packed ? kPVWindowPacked : kPVWindow;
-      for (uint32_t w = 0; w < nw; ++w) {
-        Item iw = it;
-        iw.key_lo = it.key_lo + static_cast<int32_t>(w) * win;
-        iw.key_hi = min(it.key_hi, iw.key_lo + win);
-        if (packed) iw.flags |= kItemPacked;
-        o.items[q.parts + w] = iw;
-      }
-      continue;
-    }
-    if (md.nparts == 0) {
-      o.items[o.n_parts + q.single] = it;
-      continue;
-    }
-    const int k = static_cast<int>(md.kind_side & 3u);
-    const PSide& P = S.s[md.kind_side >> 2];
-    const uint32_t b = P.off[md.x], end = P.off[md.x + 1];
-    const uint32_t* cnt = P.cnt[k];
-    const unsigned long long* ws = P.wsum[k];
-    for (uint32_t p = 0; p < md.nparts; ++p) {
-      const uint32_t es = part_start[md.part_base + p];
-      const uint32_t en = p + 1 < md.nparts ? part_start[md.part_base + p + 1] : end;
-      Item part = it;
-      part.seg_begin = it.seg_begin + (cnt[es] - cnt[b]);
-      part.seg_count = cnt[en] - cnt[es];
-      part.work = dsat32(ws[en] - ws[es]);
+    const Item it = split[i];
+    const PSide& P = S.s[it.side];
+    const uint32_t at = part_at[i], np = (i + 1 < n ? part_at[i + 1] : n_parts) - at;
+    // the item's kind: an owner below the window is counted forward (F)
+    uint32_t nseg;
+    unsigned long long work;
+    row_totals(P, it.owner < P.L ? kF : kM, it.owner, nseg, work);
+    for (uint32_t p = 0; p < np; ++p) {
+      Item part = part_of(it, it.seg_begin, nseg, work, parts + at, p, np);
       part.flags |= kItemMultiPart;
-      part.acc_slot = static_cast<int32_t>(o.acc0 + q.parts + p);
-      o.items[q.parts + p] = part;
+      part.acc_slot = static_cast<int32_t>(o.acc0 + at + p);
+      o.items[at + p] = part;
     }
     Reduce r{};
-    r.acc_slot = static_cast<int32_t>(o.acc0 + q.parts);
-    r.n_parts = static_cast<int32_t>(md.nparts);
+    r.acc_slot = static_cast<int32_t>(o.acc0 + at);
+    r.n_parts = static_cast<int32_t>(np);
     r.owner = it.owner;
     r.key_lo = it.key_lo;
     r.key_hi = it.key_hi;
     r.flags = it.flags;
     r.side = it.side;
     r.graph = 0;
-    o.reduces[o.red0 + q.split] = r;
+    o.reduces[i] = r;
   }
 }
 
 // The dense block's signs: B[x][y] for x < T, y < T' (rows of K bytes), and
 // Bm keeps those of mids above x in the global order.
 // (pos, per-vertex plans: the CSR position of every hub edge)
-__global__ void k_hub_signs(const uint32_t* off, const uint32_t* adj, const uint32_t* rows, const int32_t* grank_s,
-                            const int32_t* grank_o, int32_t T, int32_t TO, int32_t K, int8_t* B, int8_t* Bm,
-                            int32_t* pos) {
-  const int64_t ne = off[T];
-  GRID_STRIDE(e, ne) {
-    const uint32_t x = rows[e];
+// One wavefront per row: its entries of rank below T' come first.
+__global__ __launch_bounds__(kThreads) void k_hub_signs(const uint32_t* off, const uint32_t* adj,
+                                                        const int32_t* grank_s, const int32_t* grank_o, int32_t T,
+                                                        int32_t TO, int32_t K, int8_t* B, int8_t* Bm, int32_t* pos) {
+  const int32_t x = static_cast<int32_t>((blockIdx.x * kThreads + threadIdx.x) >> 6);
+  if (x >= T) return;
+  const uint32_t end = off[x + 1];
+  const int32_t gx = grank_s[x];
+  for (uint32_t e = off[x] + (threadIdx.x & 63); e < end; e += 64) {
     const uint32_t y = adj[e] >> 1;
-    if (static_cast<int32_t>(y) >= TO) continue;
+    if (static_cast<int32_t>(y) >= TO) break;
     const int8_t sg = (adj[e] & 1u) ? int8_t(-1) : int8_t(1);
     const size_t at = static_cast<size_t>(x) * K + y;
     B[at] = sg;
-    if (grank_o[y] > grank_s[x]) Bm[at] = sg;
+    if (grank_o[y] > gx) Bm[at] = sg;
     if (pos) pos[at] = static_cast<int32_t>(e);
   }
 }
@@ -854,219 +1284,198 @@ __global__ void k_edge_positions(const uint32_t* adj_u, const int32_t* rev_u, co
 
 // ---- host side ------------------------------------------------------------------
 
-struct CubTmp {
-  DevBuf buf;
-  size_t bytes = 0;
-  void* get(size_t need) {
-    if (need > bytes) {
-      PD_TRY(buf.alloc(need));
-      bytes = need;
-    }
-    return buf.p;
-  }
-};
-
-struct NonZero {
-  __host__ __device__ uint32_t operator()(uint32_t v) const { return v ? 1u : 0u; }
-};
-struct Widen {
-  __host__ __device__ unsigned long long operator()(uint32_t v) const { return v; }
-};
-
-void fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st) {
-  if (n <= 0) return;
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(n)), dim3(kThreads), 0, st, p, n, v);
-  PD_TRY(hipGetLastError());
-}
-
-template <class In, class Out>
-void exclusive_sum(CubTmp& ct, In in, Out out, int64_t n, hipStream_t st) {
-  size_t need = 0;
-  PD_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, need, in, out, static_cast<int>(n), st));
-  void* t = ct.get(need);
-  PD_TRY(hipcub::DeviceScan::ExclusiveSum(t, need, in, out, static_cast<int>(n), st));
-}
-
-template <class T, class Op>
-void exclusive_scan(CubTmp& ct, const T* in, T* out, Op op, int64_t n, hipStream_t st) {
-  size_t need = 0;
-  PD_TRY(hipcub::DeviceScan::ExclusiveScan(nullptr, need, in, out, op, T{}, static_cast<int>(n), st));
-  void* t = ct.get(need);
-  PD_TRY(hipcub::DeviceScan::ExclusiveScan(t, need, in, out, op, T{}, static_cast<int>(n), st));
-}
-
-void sort_desc(CubTmp& ct, const unsigned long long* kin, unsigned long long* kout, const uint32_t* vin,
-               uint32_t* vout, int64_t n, hipStream_t st) {
-  size_t need = 0;
-  PD_TRY(hipcub::DeviceRadixSort::SortPairsDescending(nullptr, need, kin, kout, vin, vout, static_cast<int>(n), 0,
-                                                      64, st));
-  void* t = ct.get(need);
-  PD_TRY(hipcub::DeviceRadixSort::SortPairsDescending(t, need, kin, kout, vin, vout, static_cast<int>(n), 0, 64,
-                                                      st));
-}
-
-void sort_asc(CubTmp& ct, const unsigned long long* kin, unsigned long long* kout, const uint32_t* vin,
-              uint32_t* vout, int64_t n, hipStream_t st) {
-  size_t need = 0;
-  PD_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, need, kin, kout, vin, vout, static_cast<int>(n), 0, 64, st));
-  void* t = ct.get(need);
-  PD_TRY(hipcub::DeviceRadixSort::SortPairs(t, need, kin, kout, vin, vout, static_cast<int>(n), 0, 64, st));
-}
-
 template <class T>
 T* alloc_n(DevBuf& b, int64_t n) {
   PD_TRY(b.alloc(static_cast<size_t>(std::max<int64_t>(n, 1)) * sizeof(T)));
   return b.as<T>();
 }
 
-// One side's scratch arrays.
-struct SideBufs {
-  DevBuf rows, rows_tmp, splitL, splitR, splitT, rmax, len[4], cnt[4], wsum[4], bnd[3];
+#define LAUNCH(kernel, grid, threads, ...)                                             \
+  do {                                                                                 \
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, __VA_ARGS__);         \
+    PD_TRY(hipGetLastError());                                                         \
+  } while (0)
+
+// The planner's scratch memory, carved out of one allocation.
+struct Scratch {
+  Carve c;
+  template <class T>
+  T* take(int64_t n) {
+    return reinterpret_cast<T*>(c.take((static_cast<size_t>(std::max<int64_t>(n, 1)) * sizeof(T) + 3) / 4));
+  }
 };
 
-void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& hp, DevPlanLists& out) {
-  CubTmp ct;
-  SideBufs sb[2];
-  PSides S{};
-  for (int s = 0; s < 2; ++s) {
-    const int o = 1 - s;
-    PSide& P = S.s[s];
-    SideBufs& B = sb[s];
-    const int64_t m = g.m;
-    P.off = g.off[s];
-    P.adj = g.adj[s];
-    P.rev = g.rev[s];
-    P.cut = g.cut[s];
-    P.ooff = g.off[o];
-    P.oadj = g.adj[o];
-    P.ocut = g.cut[o];
-    P.n = g.n[s];
-    P.no = g.n[o];
-    P.L = hp.L[s];
-    P.R = hp.R[s];
-    P.T = hp.T[s];
-    P.TO = hp.T[o];
-    P.m = m;
-    P.side = static_cast<uint32_t>(s);
-    P.pv = p.per_vertex;
-    P.nk = P.pv ? 4 : 3;
-    P.wide_all = p.wide_all;
-    P.max_deg = static_cast<unsigned long long>(g.max_deg[s]);
-    P.cand0 = s == 0 ? 0 : P.nk * static_cast<int64_t>(g.n[0]);
-    P.small_work = static_cast<uint32_t>(p.small_work);
-    P.part_work = static_cast<unsigned long long>(p.part_work);
-    // the row of every entry
-    uint32_t* rows = alloc_n<uint32_t>(B.rows, m);
-    uint32_t* marks = alloc_n<uint32_t>(B.rows_tmp, m);
-    fill_u32(marks, m, 0u, st);
-    hipLaunchKernelGGL(k_row_marks, dim3(grid_for(P.n)), dim3(kThreads), 0, st, P.off, P.n, marks);
-    PD_TRY(hipGetLastError());
-    if (m > 0) {
-      size_t need = 0;
-      PD_TRY(hipcub::DeviceScan::InclusiveScan(nullptr, need, marks, rows, hipcub::Max(), static_cast<int>(m), st));
-      void* t = ct.get(need);
-      PD_TRY(hipcub::DeviceScan::InclusiveScan(t, need, marks, rows, hipcub::Max(), static_cast<int>(m), st));
-    }
-    B.rows_tmp.release();
-    P.row = rows;
-    int32_t* sL = alloc_n<int32_t>(B.splitL, P.no);
-    int32_t* sR = alloc_n<int32_t>(B.splitR, P.no);
-    int32_t* sT = alloc_n<int32_t>(B.splitT, P.no);
-    hipLaunchKernelGGL(k_splits, dim3(grid_for(P.no)), dim3(kThreads), 0, st, P.ooff, P.oadj, P.no, P.L, P.R, P.T,
-                       sL, sR, sT);
-    PD_TRY(hipGetLastError());
-    P.splitL = sL;
-    P.splitR = sR;
-    P.splitT = sT;
-    P.rmax = alloc_n<int32_t>(B.rmax, P.n);
-    fill_u32(reinterpret_cast<uint32_t*>(P.rmax), P.n, 0u, st);
-    for (int k = 0; k < P.nk; ++k) {
-      P.len[k] = alloc_n<uint32_t>(B.len[k], m + 1);
-      fill_u32(P.len[k] + m, 1, 0u, st);
-    }
-    if (m > 0) {
-      hipLaunchKernelGGL(k_run_lengths, dim3(grid_for(m)), dim3(kThreads), 0, st, P);
-      PD_TRY(hipGetLastError());
-    }
-    for (int k = 0; k < P.nk; ++k) {
-      P.cnt[k] = alloc_n<uint32_t>(B.cnt[k], m + 1);
-      P.wsum[k] = alloc_n<unsigned long long>(B.wsum[k], m + 1);
-      exclusive_sum(ct, rocprim::make_transform_iterator(P.len[k], NonZero{}), P.cnt[k], m + 1, st);
-      exclusive_sum(ct, rocprim::make_transform_iterator(P.len[k], Widen{}), P.wsum[k], m + 1, st);
-    }
-    // part starts of split direct items (kinds F and M; count plans) or of
-    // the hub pivots' tally items (kind H; per-vertex plans)
-    DevBuf flags;
-    uint32_t* fl = alloc_n<uint32_t>(flags, m + 1);
-    for (int j = 0; j < 3; ++j) {
-      if ((j == 2) != P.pv) continue;
-      const int k = j == 0 ? kF : j == 1 ? kM : kH;
-      fill_u32(fl + m, 1, 0u, st);
-      if (m > 0) {
-        hipLaunchKernelGGL(k_part_flags, dim3(grid_for(m)), dim3(kThreads), 0, st, P, k, fl);
-        PD_TRY(hipGetLastError());
-      }
-      P.bnd[j] = alloc_n<uint32_t>(B.bnd[j], m + 1);
-      exclusive_sum(ct, fl, P.bnd[j], m + 1, st);
-    }
-  }
+// Items in work order.
+void order_items(const uint32_t* key, int64_t n, uint32_t* buf, unsigned long long* ctl, const Item* in, Item* out,
+                 hipStream_t st) {
+  if (n == 0) return;
+  const radix::Digits d = radix::digits_of(0, 16);
+  const size_t w = Carve::round(static_cast<size_t>(n));
+  const radix::Soa<2> bufs[2] = {{{buf, buf + w}}, {{nullptr, nullptr}}};  // two passes: the second is not used
+  const radix::Control cc{ctl};
+  PD_TRY(launch_fill_u64(ctl, radix::control_words(n, d), 0ull, st));
+  PD_TRY((radix::histogram<1>(OrderIn{key}, n, d, cc, st)));
+  PD_TRY((radix::passes<1, 2>(OrderIn{key}, GatherOut{in, out}, bufs, n, d, cc, st)));
+}
 
-  // candidates of both sides, one scan of their list counts
-  const int nk = S.s[0].nk;
-  const int64_t nc = nk * (static_cast<int64_t>(g.n[0]) + g.n[1]);
-  DevBuf counts_b, pos_b, stats_b;
-  PlanCount* counts = alloc_n<PlanCount>(counts_b, nc + 1);
-  PlanCount* pos = alloc_n<PlanCount>(pos_b, nc + 1);
-  unsigned long long* stats = alloc_n<unsigned long long>(stats_b, kStWords);
-  PD_TRY(launch_fill_u64(stats, kStWords, 0ull, st));
-  PD_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(counts + nc), sizeof(PlanCount) / 8, 0ull, st));
-  for (int s = 0; s < 2; ++s) {
-    // a few candidates per thread: the statistics are reduced once per thread
-    const int grid = std::min(grid_for(nk * static_cast<int64_t>(g.n[s])), 2048);
-    hipLaunchKernelGGL(k_count, dim3(grid), dim3(kThreads), 0, st, S.s[s], counts, stats);
-    PD_TRY(hipGetLastError());
+void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& hp, DevPlanLists& out) {
+  PSides S{};
+  MidArgs ma[2];
+  const int nk = p.per_vertex ? 4 : 3;
+  const int64_t nn = static_cast<int64_t>(g.n[0]) + g.n[1];
+  // a direct item can be split only past these
+  const bool parts = p.per_vertex ? hp.T[0] > 0
+                                  : g.wedges > p.part_work || std::max(g.max_deg[0], g.max_deg[1]) > kPartMaxRuns;
+  DevBuf scratch_b;
+  unsigned long long *counts = nullptr, *totals_d = nullptr;
+  uint32_t* words = nullptr;  // listed candidates, any wide run; then the number of small groups (64 bits)
+  size_t clear_words = 0;
+  uint2* part_list = nullptr;
+  // candidates that can have parts: the hub pivots, or those of more than
+  // part_work wedges or kPartMaxRuns runs (a kind has at most W_VP wedges
+  // and m runs per side)
+  const int64_t max_list =
+      std::min<int64_t>(nk * nn, p.per_vertex ? int64_t{hp.T[0]} + hp.T[1]
+                                              : 4 * (g.wedges / std::max(p.part_work, 1) + g.m / kPartMaxRuns) + 8);
+  const uint32_t row_chunks[2] = {static_cast<uint32_t>((g.n[0] + int64_t{kRowChunk} - 1) / kRowChunk),
+                                  static_cast<uint32_t>((g.n[1] + int64_t{kRowChunk} - 1) / kRowChunk)};
+  const uint32_t all_row_chunks = row_chunks[0] + row_chunks[1], stride = all_row_chunks + 1;
+  Scratch sc;
+  for (int sizing = 1; sizing >= 0; --sizing) {
+    if (!sizing) {
+      PD_TRY(scratch_b.alloc(sc.c.used * 4));
+      sc.c = Carve{scratch_b.as<uint32_t>(), 0};
+    }
+    // cleared together: the words, then both sides' largest keys
+    words = sc.take<uint32_t>(4);
+    for (int s = 0; s < 2; ++s) S.s[s].rmax = sc.take<int32_t>(g.n[s]);
+    clear_words = sc.c.used;
+    for (int s = 0; s < 2; ++s) {
+      const int o = 1 - s;
+      PSide& P = S.s[s];
+      P.off = g.off[s];
+      P.adj = g.adj[s];
+      P.rev = g.rev[s];
+      P.cut = g.cut[s];
+      P.n = g.n[s];
+      P.no = g.n[o];
+      P.L = hp.L[s];
+      P.R = hp.R[s];
+      P.T = hp.T[s];
+      P.TO = hp.T[o];
+      P.m = static_cast<uint32_t>(g.m);
+      P.side = static_cast<uint32_t>(s);
+      P.pv = p.per_vertex;
+      P.nk = nk;
+      P.wide_all = p.wide_all;
+      P.max_deg = static_cast<unsigned long long>(g.max_deg[s]);
+      P.small_work = static_cast<uint32_t>(p.small_work);
+      P.part_work = static_cast<unsigned long long>(p.part_work);
+      P.chunks = static_cast<uint32_t>((g.m + kChunk - 1) / kChunk);
+      P.row_chunks = row_chunks[s];
+      Mid* mids = sc.take<Mid>(P.no);
+      P.mids = mids;
+      uint16_t* rkey = sc.take<uint16_t>(P.no);
+      P.rkey = rkey;
+      ma[s] = MidArgs{g.off[o], g.adj[o], g.cut[o], mids, rkey, P.no, P.L, P.R, P.T};
+      for (int k = 0; k < nk; ++k) {
+        P.chunk_cnt[k] = sc.take<uint32_t>(int64_t{P.chunks} + 1);
+        P.chunk_sum[k] = sc.take<unsigned long long>(int64_t{P.chunks} + 1);
+        P.row_cnt[k] = sc.take<uint32_t>(P.n);
+        P.row_sum[k] = sc.take<unsigned long long>(P.n);
+      }
+      P.parts = parts ? sc.take<uint32_t>(int64_t{nk} * P.n) : nullptr;
+      P.part_pos = parts ? sc.take<uint32_t>(int64_t{nk} * P.n) : nullptr;
+      P.place = sc.take<uint2>(int64_t{nk} * P.n);
+    }
+    part_list = parts ? sc.take<uint2>(max_list) : nullptr;
+    counts = sc.take<unsigned long long>(int64_t{kCounters} * stride);
+    totals_d = sc.take<unsigned long long>(2 * kCounters);
   }
-  exclusive_scan(ct, counts, pos, PlanCountSum{}, nc + 1, st);
-  counts_b.release();
-  PlanCount tot{}, at1{};  // the totals, and the positions of side 1's first candidate
-  unsigned long long hstats[kStWords];
-  PD_TRY(hipMemcpyAsync(&tot, pos + nc, sizeof(tot), hipMemcpyDeviceToHost, st));
-  PD_TRY(hipMemcpyAsync(&at1, pos + S.s[1].cand0, sizeof(at1), hipMemcpyDeviceToHost, st));
-  PD_TRY(hipMemcpyAsync(hstats, stats, sizeof(hstats), hipMemcpyDeviceToHost, st));
+  PD_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(words), clear_words / 2, 0ull, st));
+  LAUNCH(k_mids, grid_for(nn), kThreads, ma[0], ma[1]);
+  const uint32_t entry_blocks = S.s[0].chunks + S.s[1].chunks;
+  if (g.m > 0) {
+    if (nk == 4)
+      LAUNCH(k_entries<4>, entry_blocks, kThreads, S);
+    else
+      LAUNCH(k_entries<3>, entry_blocks, kThreads, S);
+  }
+  LAUNCH(k_scan_chunks, 4 * nk, kScanThreads, S);
+  if (parts) {
+    LAUNCH(k_find_parts, grid_for(nn), kThreads, S, part_list, static_cast<uint32_t>(max_list), words);
+    LAUNCH(k_parts<0>, 512, kPartThreads, S, part_list, words, nullptr, nullptr);
+  }
+  if (nk == 4)
+    LAUNCH(k_count<4>, all_row_chunks, kThreads, S, counts, stride);
+  else
+    LAUNCH(k_count<3>, all_row_chunks, kThreads, S, counts, stride);
+  LAUNCH(k_scan_rows, kCounters, kScanThreads, counts, stride, all_row_chunks, row_chunks[0], totals_d);
+  // the totals, and the sums before side 1's first candidate
+  unsigned long long tot[2 * kCounters];
+  PD_TRY(hipMemcpyAsync(tot, totals_d, sizeof(tot), hipMemcpyDeviceToHost, st));
   PD_TRY(hipStreamSynchronize(st));
+  const unsigned long long* at1 = tot + kCounters;
   {
     PlanSizes z{};
-    z.runs = std::max({tot.big_runs, tot.small_runs, tot.hub_runs});
-    z.items = std::max<uint64_t>({tot.small_items, tot.hash, tot.rev, tot.hub_parts,
-                                  uint64_t{tot.direct_parts} + tot.direct - tot.direct_split});
-    z.reduces = uint64_t{tot.rev_reduces} + tot.direct_split;
-    z.acc_slots = uint64_t{tot.rev_acc} + tot.direct_parts;
+    z.runs = std::max({tot[kBigRuns], tot[kSmallRuns], tot[kHubRuns]});
+    z.items = std::max<uint64_t>({tot[kSmallItems], tot[kHashItems], tot[kRev], tot[kHubParts], tot[kWindows],
+                                  tot[kDirectParts] + tot[kDirect] - tot[kDirectSplit]});
+    z.reduces = tot[kRevReduces] + tot[kDirectSplit];
+    z.acc_slots = tot[kRevAcc] + tot[kDirectParts];
     std::string err;
     const int rc = check_plan_sizes(z, err);
     if (rc != DBBC_OK) throw Fail{rc, err};
   }
-  const int64_t n_small = tot.small_items, n_hash = tot.hash, n_direct = tot.direct, n_rev = tot.rev;
-  int64_t n_dir_items = int64_t{tot.direct_parts} + tot.direct - tot.direct_split;  // per-vertex: the windows
-  const int64_t n_reduces = int64_t{tot.rev_reduces} + tot.direct_split;
-  const int64_t acc_slots = int64_t{tot.rev_acc} + tot.direct_parts;
+  const int64_t n_small = static_cast<int64_t>(tot[kSmallItems]), n_hash = static_cast<int64_t>(tot[kHashItems]);
+  const int64_t n_rev = static_cast<int64_t>(tot[kRev]), n_split = static_cast<int64_t>(tot[kDirectSplit]);
+  // direct items that are ordered, and all of them (the split items' parts)
+  const int64_t n_direct = static_cast<int64_t>(p.per_vertex ? tot[kWindows] : tot[kDirect] - tot[kDirectSplit]);
+  const int64_t n_dir_items = n_direct + static_cast<int64_t>(tot[kDirectParts]);
+  const int64_t n_reduces = static_cast<int64_t>(tot[kRevReduces] + tot[kDirectSplit]);
+  const int64_t acc_slots = static_cast<int64_t>(tot[kRevAcc] + tot[kDirectParts]);
 
   // items
-  DevBuf small_b, hash_tmp_b, hash_key_b, direct_tmp_b, direct_key_b, direct_meta_b, part_start_b;
+  DevBuf scratch2_b;
   ItemOut io{};
-  io.small = alloc_n<Item>(small_b, n_small);
-  io.hash = alloc_n<Item>(hash_tmp_b, n_hash);
-  io.hash_key = alloc_n<unsigned long long>(hash_key_b, n_hash);
-  io.direct = alloc_n<Item>(direct_tmp_b, n_direct);
-  io.direct_key = alloc_n<unsigned long long>(direct_key_b, n_direct);
-  io.direct_meta = alloc_n<DirectMeta>(direct_meta_b, n_direct);
+  Item* groups = nullptr;  // at most one per small item
+  uint32_t *group_cnt = nullptr, *local_of = nullptr, *order_buf = nullptr;
+  unsigned long long* ctl = nullptr;
+  PartStart *dir_parts = nullptr, *hub_parts = nullptr;
+  const uint32_t n_chunks = static_cast<uint32_t>((n_small + kGroupChunk - 1) / kGroupChunk);
+  const int64_t n_order = std::max(n_hash, n_direct);
+  sc = Scratch{};
+  for (int sizing = 1; sizing >= 0; --sizing) {
+    if (!sizing) {
+      PD_TRY(scratch2_b.alloc(sc.c.used * 4));
+      sc.c = Carve{scratch2_b.as<uint32_t>(), 0};
+    }
+    io.small_key = sc.take<uint32_t>(n_small);
+    io.small_seg = sc.take<uint32_t>(n_small);
+    io.small_owner = sc.take<int32_t>(p.per_vertex ? 0 : n_small);
+    groups = sc.take<Item>(n_small);
+    group_cnt = sc.take<uint32_t>(n_chunks);
+    local_of = sc.take<uint32_t>(n_small);
+    io.hash = sc.take<Item>(n_hash);
+    io.hash_key = sc.take<uint32_t>(n_hash);
+    io.direct = sc.take<Item>(n_direct);
+    io.direct_key = sc.take<uint32_t>(n_direct);
+    io.split = sc.take<Item>(n_split);
+    io.split_part = sc.take<uint32_t>(n_split);
+    order_buf = sc.take<uint32_t>(2 * static_cast<int64_t>(Carve::round(static_cast<size_t>(n_order))));
+    ctl = sc.take<unsigned long long>(static_cast<int64_t>(radix::control_bound(n_order, radix::digits_of(0, 16))));
+    dir_parts = sc.take<PartStart>(static_cast<int64_t>(tot[kDirectParts]));
+    hub_parts = sc.take<PartStart>(static_cast<int64_t>(tot[kHubParts]));
+  }
   io.rev = alloc_n<Item>(out.reverse_items, n_rev);
   io.reduces = alloc_n<Reduce>(out.reduces, n_reduces);
   if (p.per_vertex) io.small_owner = alloc_n<int32_t>(out.small_owner, n_small);
-  for (int s = 0; s < 2; ++s) {
-    hipLaunchKernelGGL(k_items, dim3(grid_for(nk * static_cast<int64_t>(g.n[s]))), dim3(kThreads), 0, st, S.s[s],
-                       pos, io);
-    PD_TRY(hipGetLastError());
-  }
+  if (nk == 4)
+    LAUNCH(k_items<4>, all_row_chunks, kThreads, S, counts, stride, io);
+  else
+    LAUNCH(k_items<3>, all_row_chunks, kThreads, S, counts, stride, io);
+  if (tot[kDirectParts] + tot[kHubParts] > 0)
+    LAUNCH(k_parts<1>, 512, kPartThreads, S, part_list, words, dir_parts, hub_parts);
 
   // small groups
   for (int s = 0; s < 2; ++s) {
@@ -1074,130 +1483,53 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     while ((int64_t{1} << kb) < g.n[s]) ++kb;
     hp.key_bits[s] = kb;
   }
-  const int64_t n_chunks = (n_small + kGroupChunk - 1) / kGroupChunk;
-  DevBuf chunk_b, chunk_pos_b, local_b;
-  uint32_t* chunk_cnt = alloc_n<uint32_t>(chunk_b, n_chunks + 1);
-  uint32_t* chunk_pos = alloc_n<uint32_t>(chunk_pos_b, n_chunks + 1);
-  uint32_t* local_of = alloc_n<uint32_t>(local_b, n_small);
-  fill_u32(chunk_cnt + n_chunks, 1, 0u, st);
+  unsigned long long* n_groups_d = reinterpret_cast<unsigned long long*>(words + 2);
   if (n_chunks > 0) {
-    hipLaunchKernelGGL(k_group<0>, dim3(grid_for(n_chunks)), dim3(kThreads), 0, st, io.small, n_small, hp.key_bits[0],
-                       hp.key_bits[1], p.per_vertex, chunk_cnt, nullptr, nullptr);
-    PD_TRY(hipGetLastError());
-  }
-  exclusive_sum(ct, chunk_cnt, chunk_pos, n_chunks + 1, st);
-  uint32_t n_groups = 0;
-  PD_TRY(hipMemcpyAsync(&n_groups, chunk_pos + n_chunks, sizeof(n_groups), hipMemcpyDeviceToHost, st));
-  PD_TRY(hipStreamSynchronize(st));
-  Item* groups = alloc_n<Item>(out.small_groups, n_groups);
-  if (n_chunks > 0) {
-    hipLaunchKernelGGL(k_group<1>, dim3(grid_for(n_chunks)), dim3(kThreads), 0, st, io.small, n_small,
-                       hp.key_bits[0], hp.key_bits[1], p.per_vertex, chunk_pos, groups, local_of);
-    PD_TRY(hipGetLastError());
+    const uint32_t blocks = (n_chunks + kThreads / 64 - 1) / (kThreads / 64);
+    const SmallList sl{io.small_key, io.small_seg, io.small_owner, static_cast<uint32_t>(n_small),
+                       static_cast<uint32_t>(tot[kSmallRuns]), hp.key_bits[0], hp.key_bits[1], p.per_vertex};
+    LAUNCH(k_group<0>, blocks, kThreads, sl, group_cnt, nullptr, nullptr);
+    PD_TRY(scan_counts(group_cnt, n_chunks, n_groups_d, st));
+    LAUNCH(k_group<1>, blocks, kThreads, sl, group_cnt, groups, local_of);
   }
 
   // runs
   RunOut ro{};
-  ro.segs = alloc_n<Segment>(out.segs, static_cast<int64_t>(tot.big_runs));
-  ro.small_segs = alloc_n<Segment>(out.small_segs, static_cast<int64_t>(tot.small_runs));
+  ro.segs = alloc_n<Segment>(out.segs, static_cast<int64_t>(tot[kBigRuns]));
+  ro.small_segs = alloc_n<Segment>(out.small_segs, static_cast<int64_t>(tot[kSmallRuns]));
   ro.local_of = local_of;
-  ro.part_start = alloc_n<uint32_t>(part_start_b, tot.direct_parts);
-  DevBuf hub_part_start_b, wide_b;
+  ro.any_wide = words + 1;
   if (p.per_vertex) {
-    ro.seg_mid = alloc_n<uint32_t>(out.seg_mid, static_cast<int64_t>(tot.big_runs));
-    ro.seg_edge = alloc_n<uint32_t>(out.seg_edge, static_cast<int64_t>(tot.big_runs));
-    ro.small_seg_mid = alloc_n<uint32_t>(out.small_seg_mid, static_cast<int64_t>(tot.small_runs));
-    ro.small_seg_edge = alloc_n<uint32_t>(out.small_seg_edge, static_cast<int64_t>(tot.small_runs));
-    ro.hub_segs = alloc_n<Segment>(out.hub_segs, static_cast<int64_t>(tot.hub_runs));
-    ro.hub_part_start = alloc_n<uint32_t>(hub_part_start_b, tot.hub_parts);
-    ro.any_wide = alloc_n<uint32_t>(wide_b, 1);
-    fill_u32(ro.any_wide, 1, 0u, st);
+    ro.seg_mid = alloc_n<uint32_t>(out.seg_mid, static_cast<int64_t>(tot[kBigRuns]));
+    ro.seg_edge = alloc_n<uint32_t>(out.seg_edge, static_cast<int64_t>(tot[kBigRuns]));
+    ro.small_seg_mid = alloc_n<uint32_t>(out.small_seg_mid, static_cast<int64_t>(tot[kSmallRuns]));
+    ro.small_seg_edge = alloc_n<uint32_t>(out.small_seg_edge, static_cast<int64_t>(tot[kSmallRuns]));
+    ro.hub_segs = alloc_n<Segment>(out.hub_segs, static_cast<int64_t>(tot[kHubRuns]));
   }
-  for (int s = 0; s < 2; ++s) {
-    if (g.m == 0) break;
-    hipLaunchKernelGGL(k_runs, dim3(grid_for(g.m)), dim3(kThreads), 0, st, S.s[s], pos, ro);
-    PD_TRY(hipGetLastError());
+  if (g.m > 0) {
+    if (nk == 4)
+      LAUNCH(k_runs<4>, entry_blocks, kThreads, S, ro);
+    else
+      LAUNCH(k_runs<3>, entry_blocks, kThreads, S, ro);
   }
-  if (n_rev > 0) {
-    hipLaunchKernelGGL(k_rev_part_work, dim3(grid_for(n_rev)), dim3(kThreads), 0, st, io.rev, n_rev, ro.segs);
-    PD_TRY(hipGetLastError());
-  }
+  if (tot[kRevReduces] > 0) LAUNCH(k_rev_part_work, grid_for(n_rev), kThreads, io.rev, n_rev, ro.segs);
   if (p.per_vertex) {  // the hub pivots' tally items, side 0 first
-    Item* hub_items = alloc_n<Item>(out.hub_items, tot.hub_parts);
-    for (int s = 0; s < 2; ++s) {
-      if (S.s[s].T == 0) continue;
-      hipLaunchKernelGGL(k_hub_parts, dim3(grid_for(S.s[s].T)), dim3(kThreads), 0, st, S.s[s], pos,
-                         ro.hub_part_start, hub_items);
-      PD_TRY(hipGetLastError());
-    }
+    Item* hub_items = alloc_n<Item>(out.hub_items, static_cast<int64_t>(tot[kHubParts]));
+    if (tot[kHubParts] > 0)
+      LAUNCH(k_hub_parts, grid_for(int64_t{hp.T[0]} + hp.T[1]), kThreads, S, hub_parts, hub_items);
   }
 
   // hash items, heaviest first
-  DevBuf kout_b, vin_b, perm_b;
-  {
-    Item* hash = alloc_n<Item>(out.hash_items, n_hash);
-    if (n_hash > 0) {
-      unsigned long long* kout = alloc_n<unsigned long long>(kout_b, n_hash);
-      uint32_t* vin = alloc_n<uint32_t>(vin_b, n_hash);
-      uint32_t* perm = alloc_n<uint32_t>(perm_b, n_hash);
-      hipLaunchKernelGGL(k_iota, dim3(grid_for(n_hash)), dim3(kThreads), 0, st, vin, n_hash);
-      PD_TRY(hipGetLastError());
-      sort_desc(ct, io.hash_key, kout, vin, perm, n_hash, st);
-      hipLaunchKernelGGL(k_gather_items, dim3(grid_for(n_hash)), dim3(kThreads), 0, st, io.hash, perm, n_hash, hash);
-      PD_TRY(hipGetLastError());
-    }
-  }
-  // direct items, heaviest first: parts of split items, then single items
-  {
-    DirectOut dout{};
-    dout.items = alloc_n<Item>(out.direct_items, n_dir_items);
-    dout.reduces = io.reduces;
-    dout.n_parts = tot.direct_parts;
-    dout.acc0 = tot.rev_acc;
-    dout.red0 = tot.rev_reduces;
-    dout.pv = p.per_vertex;
-    if (n_direct > 0) {
-      unsigned long long* kout = alloc_n<unsigned long long>(kout_b, n_direct);
-      uint32_t* vin = alloc_n<uint32_t>(vin_b, n_direct);
-      uint32_t* perm = alloc_n<uint32_t>(perm_b, n_direct);
-      hipLaunchKernelGGL(k_iota, dim3(grid_for(n_direct)), dim3(kThreads), 0, st, vin, n_direct);
-      PD_TRY(hipGetLastError());
-      if (p.per_vertex)  // side 0 first, heaviest first within a side (ascending keys)
-        sort_asc(ct, io.direct_key, kout, vin, perm, n_direct, st);
-      else
-        sort_desc(ct, io.direct_key, kout, vin, perm, n_direct, st);
-      DevBuf dc_b, dpos_b;
-      DirectCount* dc = alloc_n<DirectCount>(dc_b, n_direct + 1);
-      DirectCount* dpos = alloc_n<DirectCount>(dpos_b, n_direct + 1);
-      hipLaunchKernelGGL(k_direct_count, dim3(grid_for(n_direct)), dim3(kThreads), 0, st, S, io.direct,
-                         io.direct_meta, perm, n_direct, p.per_vertex, dc);
-      PD_TRY(hipGetLastError());
-      if (p.per_vertex) {
-        // the windows' total sizes the list; side 0's items come first (at1.direct
-        // of them), so the windows before side 1's first item are side 0's
-        fill_u32(reinterpret_cast<uint32_t*>(dc + n_direct), sizeof(DirectCount) / 4, 0u, st);
-        exclusive_scan(ct, dc, dpos, DirectCountSum{}, n_direct + 1, st);
-        DirectCount t{}, t0{};
-        PD_TRY(hipMemcpyAsync(&t, dpos + n_direct, sizeof(t), hipMemcpyDeviceToHost, st));
-        PD_TRY(hipMemcpyAsync(&t0, dpos + at1.direct, sizeof(t0), hipMemcpyDeviceToHost, st));
-        PD_TRY(hipStreamSynchronize(st));
-        n_dir_items = t.parts;
-        hp.n_direct_side0 = static_cast<int32_t>(t0.parts);
-        PlanSizes z{};
-        z.items = static_cast<uint64_t>(n_dir_items);
-        std::string err;
-        const int rc = check_plan_sizes(z, err);
-        if (rc != DBBC_OK) throw Fail{rc, err};
-        dout.items = alloc_n<Item>(out.direct_items, n_dir_items);
-      } else {
-        exclusive_scan(ct, dc, dpos, DirectCountSum{}, n_direct, st);
-      }
-      hipLaunchKernelGGL(k_direct_write, dim3(grid_for(n_direct)), dim3(kThreads), 0, st, S, io.direct,
-                         io.direct_meta, perm, dpos, n_direct, ro.part_start, dout);
-      PD_TRY(hipGetLastError());
-      PD_TRY(hipStreamSynchronize(st));  // dc_b, dpos_b leave scope
-    }
-  }
+  Item* hash = alloc_n<Item>(out.hash_items, n_hash);
+  order_items(io.hash_key, n_hash, order_buf, ctl, io.hash, hash, st);
+  // direct items: the parts of split items, then the others, heaviest first
+  // (per-vertex plans: side 0 first)
+  Item* direct = alloc_n<Item>(out.direct_items, n_dir_items);
+  if (n_split > 0)
+    LAUNCH(k_split_parts, grid_for(n_split), kThreads, S, io.split, io.split_part, static_cast<uint32_t>(n_split),
+           static_cast<uint32_t>(tot[kDirectParts]), dir_parts,
+           SplitOut{direct, io.reduces + tot[kRevReduces], static_cast<uint32_t>(tot[kRevAcc])});
+  order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + tot[kDirectParts], st);
   PD_TRY(out.acc.alloc(std::max<size_t>(static_cast<size_t>(acc_slots) * hp.acc_width * sizeof(uint32_t), 16)));
 
   // the dense block's signs
@@ -1216,11 +1548,8 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
       hpos = alloc_n<int32_t>(out.hub_pos[s], static_cast<int64_t>(TK));
       PD_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(hpos), TK / 2, ~0ull, st));
     }
-    if (g.m > 0) {
-      hipLaunchKernelGGL(k_hub_signs, dim3(grid_for(static_cast<int64_t>(g.m))), dim3(kThreads), 0, st, g.off[s],
-                         g.adj[s], S.s[s].row, g.grank[s], g.grank[1 - s], T, TO, K, Bs, Bm, hpos);
-      PD_TRY(hipGetLastError());
-    }
+    LAUNCH(k_hub_signs, (T + kThreads / 64 - 1) / (kThreads / 64), kThreads, g.off[s], g.adj[s], g.grank[s],
+           g.grank[1 - s], T, TO, K, Bs, Bm, hpos);
     if (p.per_vertex) {  // the credit products' constants
       int8_t* Bt = alloc_n<int8_t>(out.hub_Bt[s], static_cast<int64_t>(TK));
       int8_t* Bmt = alloc_n<int8_t>(out.hub_Bmt[s], static_cast<int64_t>(TK));
@@ -1242,25 +1571,33 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     }
     out.hub_K[s] = K;
   }
-  uint32_t wide_h = 0;
-  if (p.per_vertex) PD_TRY(hipMemcpyAsync(&wide_h, ro.any_wide, sizeof(wide_h), hipMemcpyDeviceToHost, st));
+  uint32_t words_h[4];
+  PD_TRY(hipMemcpyAsync(words_h, words, sizeof(words_h), hipMemcpyDeviceToHost, st));
   PD_TRY(hipStreamSynchronize(st));
-  out.any_wide = wide_h != 0;
+  out.any_wide = words_h[1] != 0;
+  const uint32_t n_groups = words_h[2];  // at most the small items
+  Item* groups_out = alloc_n<Item>(out.small_groups, n_groups);
+  if (n_groups > 0)
+    PD_TRY(hipMemcpyAsync(groups_out, groups, static_cast<size_t>(n_groups) * sizeof(Item), hipMemcpyDeviceToDevice,
+                          st));
 
   hp.acc_slots = static_cast<int32_t>(acc_slots);
-  hp.n_reverse_side0 = static_cast<int32_t>(at1.rev);
-  if (p.per_vertex) hp.n_hub_side0 = static_cast<int32_t>(at1.hub_parts);
+  hp.n_reverse_side0 = static_cast<int32_t>(at1[kRev]);
+  if (p.per_vertex) {
+    hp.n_hub_side0 = static_cast<int32_t>(at1[kHubParts]);
+    hp.n_direct_side0 = static_cast<int32_t>(at1[kWindows]);
+  }
   hp.n_items_kept[0] = static_cast<int32_t>(n_dir_items);
   hp.n_items_kept[1] = static_cast<int32_t>(n_rev);
   hp.n_items_kept[2] = static_cast<int32_t>(n_groups);
   hp.n_items_kept[3] = static_cast<int32_t>(n_hash);
   hp.n_items_kept[4] = static_cast<int32_t>(n_reduces);
   for (int j = 0; j < 4; ++j) {
-    hp.k_wedges[j] = static_cast<int64_t>(hstats[kStWedges + j]);
-    hp.k_segs[j] = static_cast<int64_t>(hstats[kStRuns + j]);
+    hp.k_wedges[j] = static_cast<int64_t>(tot[kStWedges + j]);
+    hp.k_segs[j] = static_cast<int64_t>(tot[kStRuns + j]);
   }
-  hp.w_sparse = static_cast<int64_t>(hstats[kStSparse]);
-  hp.w_skipped = static_cast<int64_t>(hstats[kStSkipped]);
+  hp.w_sparse = static_cast<int64_t>(tot[kStSparse]);
+  hp.w_skipped = static_cast<int64_t>(tot[kStSkipped]);
 }
 
 }  // namespace
@@ -1269,7 +1606,7 @@ int make_plan_device(const DevGraphView& g, const PlanParams& p, hipStream_t st,
                      std::string& err) {
   int rc = check_plan_params(p, err);
   if (rc != DBBC_OK) return rc;
-  // hipCUB takes int sizes: candidates and entries (plus one) must fit
+  // candidates and entries (plus one) are counted in 31 bits
   if ((p.per_vertex ? 4 : 3) * (static_cast<int64_t>(g.n[0]) + g.n[1]) + 1 > INT32_MAX || g.m + 1 > INT32_MAX) {
     err = "graph too large for the device planner";
     return DBBC_E_TOO_LARGE;

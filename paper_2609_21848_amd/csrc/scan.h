@@ -21,33 +21,57 @@ struct Carve {
   }
 };
 
-// Exclusive sums of n counts in place and their total (unless null), by one
-// block: n is a number of chunks, a few thousand for 100 MB of input, so each
-// thread takes a stretch of them.
+// Exclusive sums of p[0 .. n) in place, by one block of kScanThreads; returns
+// the total (in every thread).  n is a number of chunks, some ten thousands
+// at most as a rule: tiles of kScanPer elements a thread, whole lines each.
 constexpr int kScanThreads = 1024;
+constexpr uint32_t kScanPer = 8;
+
+template <class T>
+__device__ __forceinline__ T scan_block(T* p, uint32_t n) {
+  __shared__ T wsum[kScanThreads / 64];
+  const int lane = static_cast<int>(threadIdx.x) & 63, wave = static_cast<int>(threadIdx.x) >> 6;
+  T run = 0;
+  for (uint32_t t0 = 0; t0 < n; t0 += kScanThreads * kScanPer) {
+    const uint32_t i0 = t0 + threadIdx.x * kScanPer;
+    T v[kScanPer];
+    T sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kScanPer; ++j) {
+      v[j] = i0 + j < n ? p[i0 + j] : T{0};
+      sum += v[j];
+    }
+    T x = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const T up = __shfl_up(x, d, 64);
+      if (lane >= d) x += up;
+    }
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    T before = run, all = 0;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) {
+      before += w < wave ? wsum[w] : T{0};
+      all += wsum[w];
+    }
+    __syncthreads();
+    before += x - sum;
+#pragma unroll
+    for (uint32_t j = 0; j < kScanPer; ++j) {
+      if (i0 + j < n) p[i0 + j] = before;
+      before += v[j];
+    }
+    run += all;
+  }
+  return run;
+}
+
+// The same of one sequence of counts; the total to *total unless null.
 static __global__ __launch_bounds__(kScanThreads) void k_scan_counts(uint32_t* c, uint32_t n,
                                                                      unsigned long long* total) {
-  __shared__ uint32_t sh[kScanThreads];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t per = (n + kScanThreads - 1) / kScanThreads;
-  const uint32_t b = min(n, tid * per), e = min(n, b + per);
-  uint32_t sum = 0;
-  for (uint32_t i = b; i < e; ++i) sum += c[i];
-  sh[tid] = sum;
-  __syncthreads();
-  for (uint32_t d = 1; d < kScanThreads; d <<= 1) {
-    const uint32_t x = tid >= d ? sh[tid - d] : 0u;
-    __syncthreads();
-    sh[tid] += x;
-    __syncthreads();
-  }
-  uint32_t run = sh[tid] - sum;
-  for (uint32_t i = b; i < e; ++i) {
-    const uint32_t x = c[i];
-    c[i] = run;
-    run += x;
-  }
-  if (total && tid == kScanThreads - 1) *total = sh[tid];
+  const uint32_t all = scan_block(c, n);
+  if (total && threadIdx.x == 0) *total = all;
 }
 
 inline hipError_t scan_counts(uint32_t* c, uint32_t n, unsigned long long* total, hipStream_t st) {
