@@ -72,11 +72,12 @@ hipError_t upload(DevBuf& b, const std::vector<T>& v, hipStream_t st) {
 }
 
 
-// Control block of a count: [0, 4) the result slot of a lone count,
-// [4] kernel error bits, [8, 16) sixteen uint32 work-queue heads.
-constexpr size_t kCtlWords = 16;
-constexpr size_t kCtlErr = 4;
-constexpr size_t kCtlQueues = 8;
+// Control block of a count: the copies of the result slot of a lone count,
+// then a word of kernel error bits and, from kCtlQueues on, sixteen uint32
+// work-queue heads.
+constexpr size_t kCtlErr = dbbc::kResCopies * dbbc::kResCopyStride;
+constexpr size_t kCtlQueues = kCtlErr + 8;
+constexpr size_t kCtlWords = kCtlQueues + 8;
 
 struct DevPlan {
   dbbc::HostPlan host;
@@ -132,9 +133,21 @@ struct LaunchSet {
   const dbbc::Reduce* reduces = nullptr;
   int32_t n[5] = {0, 0, 0, 0, 0};  // direct, reverse, small, hash, reduces
   int64_t wedges[4] = {0, 0, 0, 0}, segs[4] = {0, 0, 0, 0};  // direct, small, hash, reverse
+  int32_t direct_max_key = 0;      // of the direct items: keys lie below it,
+  uint64_t direct_max_work = 0;    // wedges of the heaviest
+  // take in a plan's totals
+  void add(const dbbc::HostPlan& hp) {
+    for (int k = 0; k < 4; ++k) {
+      wedges[k] += hp.k_wedges[k];
+      segs[k] += hp.k_segs[k];
+    }
+    direct_max_key = std::max({direct_max_key, hp.L[0], hp.L[1]});
+    direct_max_work = std::max(direct_max_work, hp.direct_max_work);
+  }
   const dbbc::DevSideConst* sides = nullptr;
   unsigned long long* res = nullptr;
-  size_t n_res = 0;  // result words zeroed before the count
+  size_t n_res = 0;  // result words zeroed before the count (when not in the control block)
+  uint32_t res_mask = 0;  // copies of the result slots - 1
   unsigned long long* ctl = nullptr;
   std::vector<std::pair<unsigned long long*, size_t>> zero;  // hub-pair buffers
   std::vector<HubLaunch> hubs;
@@ -194,11 +207,15 @@ int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
     a.sides = L.sides;
     a.queue = queues + 0;
     a.res = L.res;
+    a.res_mask = L.res_mask;
     a.err = err;
     a.n_items = L.n[0];
     a.long_len = L.long_len;
+    a.max_key = L.direct_max_key;
+    a.wedges = static_cast<uint64_t>(L.wedges[0]);
+    a.max_work = L.direct_max_work;
     RC_TRY(tm.begin(st, "direct", L.wedges[0], L.segs[0], a.n_items, 0));
-    HIP_TRY(dbbc::launch_direct(a, std::min<int>(cus, std::max(1, a.n_items)), st));
+    HIP_TRY(dbbc::launch_direct(a, cus, st));
     RC_TRY(tm.end());
   }
   {
@@ -206,6 +223,7 @@ int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
     a.items = L.reverse;
     a.sides = L.sides;
     a.res = L.res;
+    a.res_mask = L.res_mask;
     a.err = err;
     a.n_items = L.n[1];
     a.long_len = L.long_len;
@@ -218,6 +236,7 @@ int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
     a.items = L.small;
     a.sides = L.sides;
     a.res = L.res;
+    a.res_mask = L.res_mask;
     a.err = err;
     a.n_items = L.n[2];
     a.long_len = L.long_len;
@@ -231,6 +250,7 @@ int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
     a.sides = L.sides;
     a.queue = queues + 2;
     a.res = L.res;
+    a.res_mask = L.res_mask;
     a.err = err;
     a.n_items = L.n[3];
     a.long_len = L.long_len;
@@ -243,6 +263,7 @@ int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
     a.reduces = L.reduces;
     a.sides = L.sides;
     a.res = L.res;
+    a.res_mask = L.res_mask;
     a.err = err;
     a.n_reduces = L.n[4];
     RC_TRY(tm.begin(st, "reduce", 0, 0, a.n_reduces, 0));
@@ -272,6 +293,7 @@ void add_hub_launches(DevPlan& d, unsigned long long* res, LaunchSet& L, int32_t
     a.B = d.hub_B[s].as<int8_t>();
     a.hub_xy = xy;
     a.res = res;
+    a.res_mask = L.res_mask;
     a.T = hp.T[s];
     a.K = d.hub_K[s];
     // two contractions over K for every tile of the upper triangle
@@ -438,12 +460,18 @@ int ensure_plan_into(dbbc_graph* g, const dbbc::PlanParams& p, hipStream_t st, D
   } else {
     rc = ensure_host(g, st);
     if (rc != DBBC_OK) return rc;
-    try {
-      rc = dbbc::make_plan(g->host, p, hp, err);
-    } catch (const std::bad_alloc&) {
-      return fail(DBBC_E_OOM, "host allocation failed while planning");
+    dbbc::PlanParams q = p;
+    for (;;) {
+      hp = dbbc::HostPlan();
+      try {
+        rc = dbbc::make_plan(g->host, q, hp, err);
+      } catch (const std::bad_alloc&) {
+        return fail(DBBC_E_OOM, "host allocation failed while planning");
+      }
+      if (rc != DBBC_OK) return fail(rc, err);
+      if (!dbbc::larger_parts(q, static_cast<int64_t>(hp.acc_slots) * hp.acc_width * 4)) break;
     }
-    if (rc != DBBC_OK) return fail(rc, err);
+    hp.p = p;
     HIP_TRY(upload(d.segs, hp.segs, st));
     HIP_TRY(upload(d.seg_mid, hp.seg_mid, st));
     HIP_TRY(upload(d.small_seg_mid, hp.small_seg_mid, st));
@@ -461,6 +489,8 @@ int ensure_plan_into(dbbc_graph* g, const dbbc::PlanParams& p, hipStream_t st, D
       HIP_TRY(upload(d.hub_items, hp.hub_items, st));
       HIP_TRY(upload(d.hub_segs, hp.hub_segs, st));
     }
+    for (const dbbc::Item& it : hp.direct_items)
+      hp.direct_max_work = std::max<uint64_t>(hp.direct_max_work, it.work);
     hp.n_items_kept[0] = static_cast<int32_t>(d.direct_items.bytes / sizeof(dbbc::Item));
     hp.n_items_kept[1] = static_cast<int32_t>(d.reverse_items.bytes / sizeof(dbbc::Item));
     hp.n_items_kept[2] = static_cast<int32_t>(d.small_groups.bytes / sizeof(dbbc::Item));
@@ -636,6 +666,7 @@ int params_from(const dbbc_graph* g, const dbbc_options* opt, dbbc::PlanParams& 
   if (opt->flags & ~(DBBC_OPT_TIME_KERNELS | DBBC_OPT_WIDE_EDGES | DBBC_OPT_HOST_PLAN))
     return fail(DBBC_E_INVALID_ARG, "unknown dbbc_options flag");
   p.host_planner = (opt->flags & DBBC_OPT_HOST_PLAN) != 0;
+  if (opt->part_work >= 0) p.part_room = 0;
   if (opt->hub_T >= 0) p.hub_T = opt->hub_T;
   if (opt->window_L >= 0) p.window_L = opt->window_L;
   if (opt->reverse_L >= 0) p.reverse_L = opt->reverse_L;
@@ -662,14 +693,12 @@ LaunchSet lone_launches(dbbc_graph* g, uint32_t long_len) {
   L.hash = d.hash_items.as<dbbc::Item>();
   L.reduces = d.reduces.as<dbbc::Reduce>();
   for (int k = 0; k < 5; ++k) L.n[k] = hp.n_items_kept[k];
-  for (int k = 0; k < 4; ++k) {
-    L.wedges[k] = hp.k_wedges[k];
-    L.segs[k] = hp.k_segs[k];
-  }
+  L.add(hp);
   L.sides = d.sides.as<dbbc::DevSideConst>();
   L.ctl = g->ctl.as<unsigned long long>();
   L.res = L.ctl;
   L.n_res = dbbc::kResStride;
+  L.res_mask = dbbc::kResCopies - 1;
   add_hub_launches(d, L.res, L);
   L.long_len = long_len;
   L.cus = g->dev.cus;
@@ -682,10 +711,16 @@ int check_graph(const dbbc_graph* g) {
   return DBBC_OK;
 }
 
-void read_counts(const dbbc_graph* g, const unsigned long long* slot, dbbc_counts* out) {
-  out->balanced = static_cast<int64_t>(slot[dbbc::kResBalanced]);
-  out->unbalanced = static_cast<int64_t>(slot[dbbc::kResUnbalanced]);
-  out->total = static_cast<int64_t>(slot[dbbc::kResTotal]);
+// The counts of g from its result slot, in `copies` copies.
+void read_counts(const dbbc_graph* g, const unsigned long long* slot, int copies, dbbc_counts* out) {
+  unsigned long long bal = 0, unb = 0;
+  for (int c = 0; c < copies; ++c) {
+    bal += slot[c * dbbc::kResCopyStride + dbbc::kResBalanced];
+    unb += slot[c * dbbc::kResCopyStride + dbbc::kResUnbalanced];
+  }
+  out->balanced = static_cast<int64_t>(bal);
+  out->unbalanced = static_cast<int64_t>(unb);
+  out->total = out->balanced + out->unbalanced;
   out->wedges = g->host.wedges_vp;
 }
 
@@ -721,7 +756,7 @@ int finish_lone(dbbc_graph* g, dbbc_counts* out_host, bool timed) {
     }
     g->timed_valid = true;
   }
-  read_counts(g, g->pinned, out_host);
+  read_counts(g, g->pinned, dbbc::kResCopies, out_host);
   return DBBC_OK;
 }
 
@@ -928,10 +963,7 @@ int dbbc_count_explicit(dbbc_graph* g, dbbc_counts* out_host, void* hip_stream) 
   HIP_TRY(hipMemcpyAsync(g->pinned, g->ctl.p, kCtlWords * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (g->pinned[kCtlErr]) return fail(DBBC_E_DEVICE, "explicit count: a pivot's wedges exceeded its list");
-  out_host->balanced = static_cast<int64_t>(g->pinned[dbbc::kResBalanced]);
-  out_host->unbalanced = static_cast<int64_t>(g->pinned[dbbc::kResUnbalanced]);
-  out_host->total = static_cast<int64_t>(g->pinned[dbbc::kResTotal]);
-  out_host->wedges = hg.wedges_vp;
+  read_counts(g, g->pinned, 1, out_host);
   return DBBC_OK;
 }
 
@@ -1070,6 +1102,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
       ha[s].B = d.hub_B[s].as<int8_t>();
       ha[s].hub_xy = d.hub_pairs[s].as<int32_t>();
       ha[s].res = ctl;
+      ha[s].res_mask = dbbc::kResCopies - 1;
       ha[s].T = hp.T[s];
       ha[s].K = d.hub_K[s];
       ha[s].orig = g->orig[s].as<int32_t>();
@@ -1124,6 +1157,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     a.sides = sides;
     a.queue = queues + s;
     a.res = ctl;
+    a.res_mask = dbbc::kResCopies - 1;
     a.err = err;
     a.n_items = hi - lo;
     a.long_len = long_len;
@@ -1140,6 +1174,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     a.items = d.reverse_items.as<dbbc::Item>() + lo;
     a.sides = sides;
     a.res = ctl;
+    a.res_mask = dbbc::kResCopies - 1;
     a.err = err;
     a.n_items = hi - lo;
     a.long_len = long_len;
@@ -1151,6 +1186,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     a.items = d.small_groups.as<dbbc::Item>();
     a.sides = sides;
     a.res = ctl;
+    a.res_mask = dbbc::kResCopies - 1;
     a.err = err;
     a.n_items = hp.n_items_kept[2];
     a.long_len = long_len;
@@ -1163,6 +1199,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     a.sides = sides;
     a.queue = queues + 2;
     a.res = ctl;
+    a.res_mask = dbbc::kResCopies - 1;
     a.err = err;
     a.n_items = hp.n_items_kept[3];
     a.long_len = long_len;
@@ -1309,10 +1346,12 @@ int dbbc_count_noalloc(dbbc_graph* g, const dbbc_options* opt, dbbc_counts* out_
   L.hash = d.hash_items.as<dbbc::Item>();
   L.reduces = d.reduces.as<dbbc::Reduce>();
   for (int k = 0; k < 5; ++k) L.n[k] = hp.n_items_kept[k];
+  L.add(hp);
   L.sides = sides;
   L.ctl = reinterpret_cast<unsigned long long*>(base);
   L.res = L.ctl;
   L.n_res = dbbc::kResStride;
+  L.res_mask = dbbc::kResCopies - 1;
   add_hub_launches(d, L.res, L, hub_xy);
   L.long_len = long_len;
   L.cus = g->dev.cus;
@@ -1376,10 +1415,7 @@ int assemble_batch(dbbc_batch* b, dbbc_graph* const* gs, int32_t k, const dbbc_o
     if (rc != DBBC_OK) return rc;
     const dbbc::HostPlan& hp = gs[i]->plan.host;
     for (int j = 0; j < 5; ++j) tot[j] += hp.n_items_kept[j];
-    for (int j = 0; j < 4; ++j) {
-      L.wedges[j] += hp.k_wedges[j];
-      L.segs[j] += hp.k_segs[j];
-    }
+    L.add(hp);
   }
   for (int j = 0; j < 5; ++j)
     if (tot[j] > INT32_MAX) return fail(DBBC_E_TOO_LARGE, "too many work items in one batch");
@@ -1525,7 +1561,7 @@ int dbbc_batch_read(const dbbc_batch* b, dbbc_counts* out_host) {
   if (b->pinned[k * dbbc::kResStride] != 0)
     return fail(DBBC_E_DEVICE, "a kernel reported an internal error (bits: 1 hash table full, 2 LDS layout; got " +
                                    std::to_string(b->pinned[k * dbbc::kResStride]) + ")");
-  for (size_t i = 0; i < k; ++i) read_counts(b->gs[i], b->pinned + i * dbbc::kResStride, &out_host[i]);
+  for (size_t i = 0; i < k; ++i) read_counts(b->gs[i], b->pinned + i * dbbc::kResStride, 1, &out_host[i]);
   return DBBC_OK;
 }
 

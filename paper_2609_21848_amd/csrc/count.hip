@@ -28,72 +28,91 @@ namespace dev {
 
 // ---------------------------------------------------------------------------
 // Window items: one workgroup per item (or item part), counters for keys
-// [0, L) in LDS; the sweep reads the item's whole key window.
+// [0, kKeys) in LDS; the sweep reads the item's whole key window.  An item is
+// a chain of dependent steps (ticket, descriptor, runs, entries, barrier,
+// sweep, barrier), 7 us for a few thousand wedges with one workgroup on a CU
+// at a time, so:
+//  - what the next item needs is fetched under the current one: the ticket
+//    from the first wavefront's last batch on, the descriptor (vector loads,
+//    which the sweep's LDS accesses do not wait for) under the sweep, its
+//    first runs before the barrier that ends the sweep;
+//  - where every key window of the launch is narrow, smaller workgroups with
+//    fewer counters share a CU (see direct_shape).
+// Measured: 512 graphs of up to 50,000 edges, 43,400 items of 3,550 wedges on
+// average 1,170 -> 593 us (four workgroups a CU); 50M edges, 54,600 items
+// 2.70 -> 2.55 ms (the next item's fetches alone).
 constexpr int kDirectThreads = 1024;
-constexpr int kDirectWaves = kDirectThreads / kWave;
 constexpr int kDirectKeys = 32768;
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-__global__ __launch_bounds__(kDirectThreads) void k_direct(DirectArgs a) {
-  __shared__ uint32_t cnt[kDirectKeys + kDirectThreads];  // counters, then one dummy per thread
-  __shared__ __attribute__((aligned(16))) uint32_t mtab[kDirectWaves][kGather];
-  __shared__ uint8_t mflag[kDirectWaves][kGather];
+template <int kKeys, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
+  constexpr int kWaves = kThreads / kWave;
+  static_assert(kKeys <= 32 * kThreads, "at most 32 keys per thread (32-bit sums of an item)");
+  __shared__ uint32_t cnt[kKeys + kThreads];  // counters, then one dummy per thread
+  __shared__ __attribute__((aligned(16))) uint32_t mtab[kWaves][kGather];
+  __shared__ uint8_t mflag[kWaves][kGather];
   __shared__ int32_t item_sh;
-  __shared__ unsigned long long blk[2];
+  __shared__ unsigned long long blk[2][2];  // sums of the graph that ends, by parity of its flush
   const int tid = threadIdx.x;
-  const int wave = tid / kWave;
-  for (int i = tid; i < kDirectKeys; i += kDirectThreads) cnt[i] = 0;
-  for (int i = tid; i < kDirectWaves * static_cast<int>(kGather); i += kDirectThreads) (&mflag[0][0])[i] = 0;
-  if (tid == 0) blk[0] = blk[1] = 0;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = lane_id();
+  for (int i = tid; i < kKeys; i += kThreads) cnt[i] = 0;
+  for (int i = tid; i < kWaves * static_cast<int>(kGather); i += kThreads) (&mflag[0][0])[i] = 0;
+  if (tid < 4) (&blk[0][0])[tid] = 0;
   // Per thread, for the current graph: twice the balanced count (sum of
   // p^2 + n^2 minus the wedges) and the unbalanced count.  Only the
   // workgroup's total of sq2 is even, so the halving happens there.
   int64_t sq2 = 0;
   uint64_t pnx = 0;
-  auto flush_block = [&](uint32_t g) {
-    const int64_t q = wave_sum64(sq2), x = wave_sum64(static_cast<int64_t>(pnx));
-    if ((tid & (kWave - 1)) == 0) {
-      atomicAdd(&blk[0], static_cast<unsigned long long>(q));
-      atomicAdd(&blk[1], static_cast<unsigned long long>(x));
-    }
-    __syncthreads();
-    if (tid == 0) {
-      const int64_t bal = static_cast<int64_t>(blk[0]) / 2, unb = static_cast<int64_t>(blk[1]);
-      unsigned long long* res = a.res + static_cast<size_t>(g) * kResStride;
-      if (bal) atomicAdd(res + kResBalanced, static_cast<unsigned long long>(bal));
-      if (unb) atomicAdd(res + kResUnbalanced, static_cast<unsigned long long>(unb));
-      if (bal + unb) atomicAdd(res + kResTotal, static_cast<unsigned long long>(bal + unb));
-      blk[0] = blk[1] = 0;
-    }
-    __syncthreads();
-    sq2 = 0;
-    pnx = 0;
+  uint32_t parity = 0;
+  constexpr int kItemWords = sizeof(Item) / 4;
+  // the words of item i, one per lane
+  auto fetch = [&](int32_t i) {
+    return i < a.n_items && lane < kItemWords
+               ? as_global(reinterpret_cast<const uint32_t*>(a.items))[static_cast<size_t>(i) * kItemWords + lane]
+               : 0u;
   };
-  uint32_t graph = kNoGraph;
+  auto unpack = [&](uint32_t w) {
+    Item it;
+    uint32_t* o = reinterpret_cast<uint32_t*>(&it);
+#pragma unroll
+    for (int k = 0; k < kItemWords; ++k) o[k] = readlane(w, k);
+    return it;
+  };
+  if (tid == 0) item_sh = static_cast<int32_t>(atomicAdd(a.queue, 1u));
+  __syncthreads();
+  int32_t i = __builtin_amdgcn_readfirstlane(item_sh);
+  if (i >= a.n_items) return;
+  Item it = unpack(fetch(i));
+  DevSideConst sc = load_const(a.sides, 2 * it.graph + it.side);
+  SegReg first = load_seg<false>(sc.segs, it.seg_begin + wave, it.seg_begin + it.seg_count, kWaves);
   for (;;) {
-    if (tid == 0) item_sh = static_cast<int32_t>(atomicAdd(a.queue, 1u));
-    __syncthreads();
-    const int32_t i = item_sh;
-    if (i >= a.n_items) break;
-    const Item it = load_const(a.items, i);
-    if (it.graph != graph) {
-      if (graph != kNoGraph) flush_block(graph);
-      graph = it.graph;
-    }
-    const DevSideConst sc = load_const(a.sides, 2 * it.graph + it.side);
     const uint32_t* __restrict__ adj = sc.other_adj;
     const uint32_t seg_end = it.seg_begin + it.seg_count;
     // the wavefronts take the item's segments interleaved (wavefront w the
-    // segments w, w + 16, ...), 64 per batch, so that every wavefront gets
-    // a similar mix of long and short runs
-    for (uint32_t k0 = it.seg_begin + wave; k0 < seg_end; k0 += kDirectThreads)
-      walk_batch<8, false, true>(sc.segs, k0, seg_end, adj, Marks<uint8_t>{mtab[wave], mflag[wave]}, a.long_len,
-                    DirectTallyBF<kDirectKeys>{cnt, cnt + kDirectKeys + tid}, kDirectWaves);
+    // segments w, w + kWaves, ...), 64 per batch, so that every wavefront
+    // gets a similar mix of long and short runs
+    uint32_t ticket = 0;
+    for (uint32_t k0 = it.seg_begin + wave;;) {
+      const bool last = k0 >= seg_end || seg_end - k0 <= kThreads;
+      if (last && tid == 0) ticket = atomicAdd(a.queue, 1u);
+      if (k0 < seg_end)
+        walk_regs<8, false, true>(first, adj, Marks<uint8_t>{mtab[wave], mflag[wave]}, a.long_len,
+                                  DirectTallyBF<kKeys>{cnt, cnt + kKeys + tid});
+      if (last) break;
+      k0 += kThreads;
+      first = load_seg<false>(sc.segs, k0, seg_end, kWaves);
+    }
+    if (tid == 0) item_sh = static_cast<int32_t>(ticket);
     __syncthreads();
+    const int32_t ni = __builtin_amdgcn_readfirstlane(item_sh);
+    const uint32_t next_words = fetch(ni);
     if (it.flags & kItemMultiPart) {
       // write the part's counters for the whole key window (zeros included)
       global_t<uint32_t>* __restrict__ dst = as_global(sc.acc) + static_cast<size_t>(it.acc_slot) * sc.acc_width;
-      for (uint32_t key = it.key_lo + tid; key < static_cast<uint32_t>(it.key_hi); key += kDirectThreads) {
+      for (uint32_t key = it.key_lo + tid; key < static_cast<uint32_t>(it.key_hi); key += kThreads) {
         dst[key] = cnt[key];
         cnt[key] = 0;
       }
@@ -114,7 +133,7 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct(DirectArgs a) {
       const uint32_t hi = static_cast<uint32_t>(it.key_hi);
       const uint32_t hub_hi = hub ? static_cast<uint32_t>(sc.T) : 0u;  // keys below: dense-path pairs
       uint32_t sq32 = 0, pn32 = 0;
-      for (uint32_t key = lo + 4 * tid; key < hi; key += 4 * kDirectThreads) {
+      for (uint32_t key = lo + 4 * tid; key < hi; key += 4 * kThreads) {
         const uint4 c4 = *reinterpret_cast<uint4*>(&cnt[key]);
         if ((c4.x | c4.y | c4.z | c4.w) == 0) continue;
         *reinterpret_cast<uint4*>(&cnt[key]) = make_uint4(0, 0, 0, 0);
@@ -154,9 +173,39 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct(DirectArgs a) {
       sq2 += sq32;
       pnx += pn32 >> 1;  // a sum of 2 p n terms: even
     }
+    const bool done = ni >= a.n_items;
+    const uint32_t graph = it.graph;
+    if (!done) {
+      it = unpack(next_words);
+      sc = load_const(a.sides, 2 * it.graph + it.side);
+      first = load_seg<false>(sc.segs, it.seg_begin + wave, it.seg_begin + it.seg_count, kWaves);
+    }
+    // the graph's last item of this workgroup: its sums meet in LDS, and one
+    // thread adds them to the graph's results after the barrier (the next
+    // flush uses the other words)
+    const bool flush = done || it.graph != graph;
+    if (flush) {
+      const int64_t q = wave_sum64(sq2), x = wave_sum64(static_cast<int64_t>(pnx));
+      if (lane == 0) {
+        atomicAdd(&blk[parity][0], static_cast<unsigned long long>(q));
+        atomicAdd(&blk[parity][1], static_cast<unsigned long long>(x));
+      }
+      sq2 = 0;
+      pnx = 0;
+    }
     __syncthreads();
+    if (flush) {
+      if (tid == 0) {
+        const int64_t bal = static_cast<int64_t>(blk[parity][0]) / 2, unb = static_cast<int64_t>(blk[parity][1]);
+        unsigned long long* res = a.res + static_cast<size_t>(graph) * kResStride;
+        if (bal) atomicAdd(res + kResBalanced, static_cast<unsigned long long>(bal));
+        if (unb) atomicAdd(res + kResUnbalanced, static_cast<unsigned long long>(unb));
+        blk[parity][0] = blk[parity][1] = 0;
+      }
+      parity ^= 1u;
+    }
+    if (done) break;
   }
-  if (graph != kNoGraph) flush_block(graph);
 }
 
 // ---------------------------------------------------------------------------
@@ -177,6 +226,7 @@ constexpr int kReverseWaves = kReverseThreads / kWave;
 constexpr int kReverseWords = kMaxReverseL / 2;
 
 __global__ __launch_bounds__(kReverseThreads) void k_reverse(SmallArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   // counters, each wavefront's array aligned to its size; one dummy word per lane
   __shared__ __attribute__((aligned(kReverseWords * 4))) uint32_t cnt[kReverseWaves][kReverseWords];
   __shared__ uint32_t dummies[kReverseWaves][kWave];
@@ -339,6 +389,7 @@ struct SmallInsert {
 };
 
 __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   __shared__ __attribute__((aligned(16))) uint32_t keys[kSmallWaves][kSmallSlots];
   __shared__ __attribute__((aligned(16))) uint32_t vals[kSmallWaves][kSmallSlots];
   // staging marks: bases, and 16-bit tags (item index in the group << 1 | g,
@@ -452,6 +503,7 @@ constexpr int kHashWaves = kHashThreads / kWave;
 constexpr int kHashSlots = 8192;
 
 __global__ __launch_bounds__(kHashThreads) void k_hash(HashArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   __shared__ uint32_t keys[kHashSlots];
   __shared__ unsigned long long vals[kHashSlots];
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kHashWaves][kGather];
@@ -542,15 +594,16 @@ __global__ __launch_bounds__(kHashThreads) void k_hash(HashArgs a) {
 // Multi-part pivots: add the parts' packed counters key by key, then take
 // C(., 2) of the combined counts.
 constexpr int kReduceThreads = 256;
-constexpr int kReduceSlices = 8;  // workgroups per reduce (a few dozen reduces fill no GPU)
+constexpr int kReduceMaxSlices = 64;
 
 __global__ __launch_bounds__(kReduceThreads) void k_reduce(ReduceArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   Sums sums;
   uint32_t graph = kNoGraph;
-  // work units: kReduceSlices interleaved key slices of every reduce
-  const int64_t units = static_cast<int64_t>(a.n_reduces) * kReduceSlices;
+  // work units: interleaved key slices of every reduce
+  const int64_t units = static_cast<int64_t>(a.n_reduces) * a.slices;
   for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
-    const int32_t r = static_cast<int32_t>(unit / kReduceSlices), slice = static_cast<int32_t>(unit % kReduceSlices);
+    const int32_t r = static_cast<int32_t>(unit / a.slices), slice = static_cast<int32_t>(unit % a.slices);
     const Reduce rd = load_const(a.reduces, r);
     if (rd.graph != graph) {
       if (graph != kNoGraph) flush_sums(sums, a.res + static_cast<size_t>(graph) * kResStride);
@@ -563,7 +616,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce(ReduceArgs a) {
     it.flags = rd.flags;
     const global_t<uint32_t>* acc = as_global(sc.acc) + static_cast<size_t>(rd.acc_slot) * sc.acc_width;
     for (int32_t key = rd.key_lo + slice * kReduceThreads + static_cast<int32_t>(threadIdx.x); key < rd.key_hi;
-         key += kReduceSlices * kReduceThreads) {
+         key += a.slices * kReduceThreads) {
       uint32_t p = 0, n = 0;
       // eight independent part loads per step
       int32_t j = 0;
@@ -647,9 +700,45 @@ hipError_t launch_assemble_reduces(const AssembleSrc* srcs, int k, Reduce* dst, 
   return hipGetLastError();
 }
 
-hipError_t launch_direct(const DirectArgs& a, int grid, hipStream_t st) {
+// The workgroup shape of a direct launch: counters for 32,768, 16,384 or 8,192
+// keys (as many as the launch's widest window) with 1,024, 512 or 256
+// threads, so 1, 2 or 4 workgroups on a CU.  A narrow shape overlaps the
+// fixed part of its items with other items' (about 7 us per item, the whole
+// of it on a wide workgroup's CU), but a heavy item has fewer wavefronts:
+// the shape is the one whose estimated time, the larger of the heaviest item
+// alone and all items spread over the CUs, is least.  Rates measured at 5.3
+// wedges/ns on a CU full of wavefronts.
+static int direct_shape(const DirectArgs& a, int cus) {
+  int best = 0;
+  double best_us = 0;
+  for (int shape = 0; shape < 3; ++shape) {
+    if (a.max_key > (dev::kDirectKeys >> shape)) break;
+    const double per_cu = 1 << shape, rate = 5300.0;  // workgroups on a CU, wedges/us of a CU
+    const double spread = static_cast<double>(a.n_items) * 7.0 / (cus * per_cu) +
+                          static_cast<double>(a.wedges) / (rate * cus);
+    const double heaviest = 7.0 + static_cast<double>(a.max_work) * per_cu / rate;
+    const double us = spread > heaviest ? spread : heaviest;
+    if (shape == 0 || us < best_us) {
+      best = shape;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_direct(const DirectArgs& a, int cus, hipStream_t st) {
   if (a.n_items == 0) return hipSuccess;
-  hipLaunchKernelGGL(dev::k_direct, dim3(grid), dim3(dev::kDirectThreads), 0, st, a);
+  const int shape = direct_shape(a, cus);
+  const int grid = a.n_items < (cus << shape) ? a.n_items : cus << shape;
+  if (shape == 0)
+    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys, dev::kDirectThreads>), dim3(grid), dim3(dev::kDirectThreads),
+                       0, st, a);
+  else if (shape == 1)
+    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys / 2, dev::kDirectThreads / 2>), dim3(grid),
+                       dim3(dev::kDirectThreads / 2), 0, st, a);
+  else
+    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys / 4, dev::kDirectThreads / 4>), dim3(grid),
+                       dim3(dev::kDirectThreads / 4), 0, st, a);
   return hipGetLastError();
 }
 
@@ -673,9 +762,15 @@ hipError_t launch_hash(const HashArgs& a, int grid, hipStream_t st) {
 
 hipError_t launch_reduce(const ReduceArgs& a, int max_grid, hipStream_t st) {
   if (a.n_reduces == 0) return hipSuccess;
-  const int64_t units = static_cast<int64_t>(a.n_reduces) * dev::kReduceSlices;
+  // a reduce in as many slices as fill the grid (a chain of part loads per
+  // key: 42 reduces of 32,768 keys took 34 us in 8 slices, 16 keys a thread)
+  ReduceArgs b = a;
+  b.slices = max_grid / a.n_reduces;
+  if (b.slices < 8) b.slices = 8;
+  if (b.slices > dev::kReduceMaxSlices) b.slices = dev::kReduceMaxSlices;
+  const int64_t units = static_cast<int64_t>(a.n_reduces) * b.slices;
   const int grid = static_cast<int>(units < max_grid ? units : max_grid);
-  hipLaunchKernelGGL(dev::k_reduce, dim3(grid), dim3(dev::kReduceThreads), 0, st, a);
+  hipLaunchKernelGGL(dev::k_reduce, dim3(grid), dim3(dev::kReduceThreads), 0, st, b);
   return hipGetLastError();
 }
 

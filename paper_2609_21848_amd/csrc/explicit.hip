@@ -124,7 +124,6 @@ __global__ __launch_bounds__(kExThreads) void k_explicit(ExplicitArgs a) {
   if (lane == 0) {
     if (bal) atomicAdd(a.res + kResBalanced, bal);
     if (unb) atomicAdd(a.res + kResUnbalanced, unb);
-    if (bal + unb) atomicAdd(a.res + kResTotal, bal + unb);
   }
 }
 

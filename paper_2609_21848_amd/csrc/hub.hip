@@ -245,30 +245,26 @@ __global__ __launch_bounds__(kHubThreads, 2) void k_hub(HubPair hp) {
     }
   }
   int64_t bal = (sxx + syy - 2 * sx) / 4, unb = (sxx - syy) / 4;
-  int64_t tot = bal + unb, wd = sx - x0;
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) {
     bal += __shfl_xor(bal, d, 64);
     unb += __shfl_xor(unb, d, 64);
-    tot += __shfl_xor(tot, d, 64);
-    wd += __shfl_xor(wd, d, 64);
   }
-  // one set of atomics per workgroup: every workgroup adds to the same four
-  // words, and atomics to one address are serialized (per wavefront they
-  // took half the kernel's time)
-  __shared__ int64_t wsum[kHubThreads / 64][4];
+  // one set of atomics per workgroup: atomics to one address are serialized
+  // (per wavefront they took half the kernel's time)
+  __shared__ int64_t wsum[kHubThreads / 64][2];
   if (lane == 0) {
     wsum[wave][0] = bal;
     wsum[wave][1] = unb;
-    wsum[wave][2] = tot;
-    wsum[wave][3] = wd;
   }
   __syncthreads();
-  if (tid < 4) {
+  if (tid < 2) {
     int64_t v = 0;
 #pragma unroll
     for (int w = 0; w < kHubThreads / 64; ++w) v += wsum[w][tid];
-    if (v) atomicAdd(a.res + tid, static_cast<unsigned long long>(v));
+    static_assert(kResBalanced == 0 && kResUnbalanced == 1, "the sums' order");
+    if (v) atomicAdd(a.res + static_cast<size_t>(blockIdx.x & a.res_mask) * kResCopyStride + tid,
+                     static_cast<unsigned long long>(v));
   }
 }
 

@@ -118,10 +118,13 @@ struct PlanParams {
   bool per_vertex = false;  // plan for the per-vertex pass (no multi-part items)
   bool wide_all = false;    // per-vertex plans: flag every run kMidWide
   bool host_planner = false;  // count plans: make the plan on the host
+  // bytes the parts' counters may take before part_work is raised (0: as
+  // part_work says, which the caller chose)
+  int64_t part_room = 0;
   bool operator==(const PlanParams& o) const {
     return hub_T == o.hub_T && window_L == o.window_L && reverse_L == o.reverse_L &&
            small_work == o.small_work && part_work == o.part_work && per_vertex == o.per_vertex &&
-           wide_all == o.wide_all && host_planner == o.host_planner;
+           wide_all == o.wide_all && host_planner == o.host_planner && part_room == o.part_room;
   }
 };
 
@@ -185,6 +188,7 @@ struct HostPlan {
   // list lengths (direct, reverse, small groups, hash, reduces) once the
   // lists live on the device only
   int32_t n_items_kept[5] = {0, 0, 0, 0, 0};
+  uint64_t direct_max_work = 0;  // wedges of the heaviest direct item (or part)
   int32_t n_reverse_side0 = 0;  // reverse items are listed side 0 first
   int32_t n_direct_side0 = 0;   // per-vertex plans: direct items side 0 first
   int32_t acc_slots = 0;
@@ -225,6 +229,15 @@ int check_plan_sizes(const PlanSizes& z, std::string& err);
 // once; the default block is trimmed so that its upper triangle of tiles
 // fits in one round.
 PlanParams default_params(const HostGraph& g, int32_t hub_slots = 512);
+// Largest default part budget.
+constexpr int32_t kMaxPartWork = 1 << 24;
+// Whether parts that take `bytes` of counters are too many for p: raises
+// p.part_work for another plan.
+inline bool larger_parts(PlanParams& p, int64_t bytes) {
+  if (p.part_room == 0 || bytes <= p.part_room || p.part_work >= kMaxPartWork) return false;
+  p.part_work = p.part_work > kMaxPartWork / 4 ? kMaxPartWork : 4 * p.part_work;
+  return true;
+}
 // Checks of the plan knobs (a DBBC status; err filled on failure).
 int check_plan_params(const PlanParams& p, std::string& err);
 // The windows L, R, the dense block T per side and the accumulator width of

@@ -14,14 +14,22 @@ namespace dbbc {
 // the last entry of a run.
 constexpr size_t kAdjPad = 64;
 
-// Layout of a graph's int64 result slot (res + graph * kResStride).
+// Layout of a graph's int64 result slot (res + graph * kResStride); the total
+// is the sum of the two.
 enum : int {
   kResBalanced = 0,
   kResUnbalanced = 1,
-  kResTotal = 2,
-  kResDenseWedges = 3,
   kResStride = 4,
 };
+// Every workgroup of a launch ends by adding to its graph's slot, and atomics
+// to one address are served one after the other, about 10 ns each: 1,024
+// workgroups of a short launch would wait 10 us per word.  A lone count keeps
+// its slot in kResCopies copies, each on a cache line of its own, and
+// workgroup b adds to copy b mod kResCopies (res_mask = kResCopies - 1 in the
+// kernels' arguments); the host adds them up.  In a batch each graph has a
+// slot (res_mask = 0).
+constexpr int kResCopies = 16;
+constexpr int kResCopyStride = 16;
 enum : unsigned long long {
   kErrHashFull = 1ull,
   kErrLdsLayout = 2ull,  // an LDS array lacks the alignment its addressing assumes
@@ -76,9 +84,14 @@ struct DirectArgs {
   const DevSideConst* sides;
   uint32_t* queue;
   unsigned long long* res;   // per-graph result slots
+  uint32_t res_mask;         // copies of the slots (see kResCopies) - 1
   unsigned long long* err;   // kErr* bits
   int32_t n_items;
   uint32_t long_len;  // runs at least this long are streamed by the whole wavefront
+  // count pass: what the workgroup shape is picked by
+  int32_t max_key;    // keys lie below this
+  uint64_t wedges;    // of all items
+  uint64_t max_work;  // of the heaviest item
 };
 
 // Reverse items (items) or small-item groups (items = groups, segs tagged).
@@ -86,6 +99,7 @@ struct SmallArgs {
   const Item* items;
   const DevSideConst* sides;
   unsigned long long* res;   // per-graph result slots
+  uint32_t res_mask;
   unsigned long long* err;   // kErr* bits
   int32_t n_items;
   uint32_t long_len;
@@ -96,6 +110,7 @@ struct HashArgs {
   const DevSideConst* sides;
   uint32_t* queue;
   unsigned long long* res;   // per-graph result slots
+  uint32_t res_mask;         // copies of the slots (see kResCopies) - 1
   unsigned long long* err;   // kErr* bits
   int32_t n_items;
   uint32_t long_len;
@@ -105,8 +120,10 @@ struct ReduceArgs {
   const Reduce* reduces;
   const DevSideConst* sides;
   unsigned long long* res;   // per-graph result slots
+  uint32_t res_mask;
   unsigned long long* err;   // kErr* bits
   int32_t n_reduces;
+  int32_t slices;     // workgroups per reduce (set by the launcher)
 };
 
 // Source of one graph's item (or reduce) list for the batch assembly copy.
@@ -125,7 +142,8 @@ struct HubArgs {
   const int8_t* Bm = nullptr;    // [T x K] row-major, K = padded mid count
   const int8_t* B = nullptr;     // [T x K]
   int32_t* hub_xy = nullptr;     // [2 x T x T] sparse partials: p + n, then p - n
-  unsigned long long* res = nullptr;  // res[0..2] sums, res[3] dense wedges
+  unsigned long long* res = nullptr;  // the graph's result slot
+  uint32_t res_mask = 0;
   int32_t T = 0;                 // rows (pairs side)
   int32_t K = 0;                 // padded contraction length (multiple of kHubKPad)
   // per-vertex pass only (bal != null): the completed counts X = P + N and
@@ -141,7 +159,8 @@ hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v
 // Write the two side-table entries src2[0..2) (host values) to device
 // memory dst by a kernel (no copy from host memory).
 hipError_t launch_store_sides(const DevSideConst* src2, DevSideConst* dst, hipStream_t st);
-hipError_t launch_direct(const DirectArgs& a, int grid, hipStream_t st);
+// (cus: the device's; the grid follows from the workgroup shape)
+hipError_t launch_direct(const DirectArgs& a, int cus, hipStream_t st);
 hipError_t launch_small(const SmallArgs& a, int grid, hipStream_t st);
 hipError_t launch_reverse(const SmallArgs& a, int grid, hipStream_t st);
 hipError_t launch_hash(const HashArgs& a, int grid, hipStream_t st);

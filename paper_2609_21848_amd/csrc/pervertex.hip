@@ -282,6 +282,7 @@ constexpr int kPVDirectWaves = kPVDirectThreads / kWave;
 
 template <bool kEdge>
 __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   __shared__ uint32_t C[kPVWindowPacked];  // P | N, or packed words
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVDirectWaves][2 * kWave];
   __shared__ uint8_t mflag[kPVDirectWaves][kGather];
@@ -309,7 +310,6 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
       const int64_t bal = (q - ww) / 2;
       if (bal) atomicAdd(res + kResBalanced, static_cast<unsigned long long>(bal));
       if (x) atomicAdd(res + kResUnbalanced, static_cast<unsigned long long>(x));
-      if (bal + x) atomicAdd(res + kResTotal, static_cast<unsigned long long>(bal + x));
     }
     sums = Sums{};
     sq64 = pn64 = w64 = 0;
@@ -469,6 +469,7 @@ constexpr int kPVReverseWords = kMaxReverseL / 2;
 
 template <bool kEdge>
 __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   // counters, each wavefront's array aligned to its size (the tally's
   // AND-OR addresses); one dummy word per lane
   __shared__ __attribute__((aligned(kPVReverseWords * 4))) uint32_t cnt[kPVReverseWaves][kPVReverseWords];
@@ -590,6 +591,7 @@ constexpr int kPVSmallSlots = 2 * kSmallGroupWork;
 
 template <bool kEdge>
 __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   __shared__ uint32_t keys[kPVSmallWaves][kPVSmallSlots];
   __shared__ uint32_t vals[kPVSmallWaves][kPVSmallSlots];
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVSmallWaves][kGather];
@@ -742,6 +744,7 @@ constexpr int kPVHashSlots = 8192;
 
 template <bool kEdge>
 __global__ __launch_bounds__(kPVHashThreads) void k_pv_hash(HashArgs a) {
+  a.res = own_copy(a.res, a.res_mask);
   __shared__ uint32_t keys[kPVHashSlots];
   __shared__ unsigned long long vals[kPVHashSlots];
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVHashWaves][kGather];

@@ -66,7 +66,20 @@ PlanParams default_params(const HostGraph& g, int32_t hub_slots) {
   while (nt > 1 && nt * (nt + 1) / 2 > hub_slots) --nt;
   if (p.hub_T > 0) p.hub_T = nt * 128;
   p.small_work = static_cast<int32_t>(kSmallGroupWork);
-  p.part_work = 1 << 24;
+  // A direct item runs on one CU: an item of more than a CU's share of the
+  // wedges would outlast the rest of its launch, so half of that is the budget
+  // of a part (2M edges, 73M wedges: the launch 179 us with the heaviest item
+  // whole, 86 in parts of 2^18; 8M edges: 454 -> 267 us at 2^20; 334K edges:
+  // parts below 2^18 cost more than they save, 82 -> 86 us at 2^17).  A part's
+  // counters take a window of words, written once and read once; where all
+  // parts' take more than 24 bytes per edge, or with the dense block's planes
+  // more than the scratch of counts without allocation, the budget is raised
+  // (larger_parts).
+  p.part_work = static_cast<int32_t>(
+      std::min<int64_t>(kMaxPartWork, std::max<int64_t>(1 << 18, g.wedges_vp / std::max(1, hub_slots))));
+  const int64_t scratch = static_cast<int64_t>(DBBC_NOALLOC_SCRATCH_BYTES) - (1 << 20) -
+                          16 * static_cast<int64_t>(p.hub_T) * p.hub_T;  // two int32 planes on each side
+  p.part_room = std::max<int64_t>(1, scratch > 0 ? std::min(24 * g.m, scratch) : 24 * g.m);
   return p;
 }
 

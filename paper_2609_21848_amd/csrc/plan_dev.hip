@@ -709,15 +709,18 @@ __device__ __forceinline__ RowCands row_cands(const PSides& S) {
 // Each block of rows: its candidates' list counts and statistics
 // (counts[q * stride + block]).
 template <int kNk>
-__global__ __launch_bounds__(kThreads) void k_count(PSides S, unsigned long long* counts, uint32_t stride) {
+__global__ __launch_bounds__(kThreads) void k_count(PSides S, unsigned long long* counts, uint32_t stride,
+                                                    unsigned long long* max_direct) {
   __shared__ unsigned long long sh[kThreads / 64][kCounters];
   const RowCands r = row_cands<kNk>(S);
   const PSide& P = S.s[r.side];
   unsigned long long q[kCounters] = {};
+  unsigned long long heaviest = 0;  // direct item (a split one: about its parts' budget)
 #pragma unroll
   for (int k = 0; k < kNk; ++k) {
     const Cand& c = r.c[k];
     add_lists(P, c, q);
+    if (c.cls == kDirectC) heaviest = max(heaviest, c.split ? min(c.work, P.part_work) : c.work);
     if (c.cls == kSkip) q[kStSkipped] += c.work;
     if (c.cls == kSkip || c.cls == kHubC) continue;
     const int slot = c.cls == kSmallC ? 1 : c.cls == kHashC ? 2 : c.cls == kDirectC ? 0 : 3;
@@ -737,6 +740,11 @@ __global__ __launch_bounds__(kThreads) void k_count(PSides S, unsigned long long
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][t] = v;
+  }
+  if (__ballot(heaviest != 0)) {  // (few wavefronts have direct items)
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) heaviest = max(heaviest, __shfl_xor(heaviest, d, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(max_direct, heaviest);
   }
   __syncthreads();
   if (threadIdx.x < kCounters) {
@@ -1328,7 +1336,9 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
                                   : g.wedges > p.part_work || std::max(g.max_deg[0], g.max_deg[1]) > kPartMaxRuns;
   DevBuf scratch_b;
   unsigned long long *counts = nullptr, *totals_d = nullptr;
-  uint32_t* words = nullptr;  // listed candidates, any wide run; then the number of small groups (64 bits)
+  // listed candidates, any wide run; then (64 bits each) the number of small
+  // groups and the heaviest direct item
+  uint32_t* words = nullptr;
   size_t clear_words = 0;
   uint2* part_list = nullptr;
   // candidates that can have parts: the hub pivots, or those of more than
@@ -1347,7 +1357,7 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
       sc.c = Carve{scratch_b.as<uint32_t>(), 0};
     }
     // cleared together: the words, then both sides' largest keys
-    words = sc.take<uint32_t>(4);
+    words = sc.take<uint32_t>(6);
     for (int s = 0; s < 2; ++s) S.s[s].rmax = sc.take<int32_t>(g.n[s]);
     clear_words = sc.c.used;
     for (int s = 0; s < 2; ++s) {
@@ -1393,6 +1403,8 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     totals_d = sc.take<unsigned long long>(2 * kCounters);
   }
   PD_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(words), clear_words / 2, 0ull, st));
+  unsigned long long* n_groups_d = reinterpret_cast<unsigned long long*>(words + 2);
+  unsigned long long* max_direct_d = reinterpret_cast<unsigned long long*>(words + 4);
   LAUNCH(k_mids, grid_for(nn), kThreads, ma[0], ma[1]);
   const uint32_t entry_blocks = S.s[0].chunks + S.s[1].chunks;
   if (g.m > 0) {
@@ -1402,19 +1414,23 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
       LAUNCH(k_entries<3>, entry_blocks, kThreads, S);
   }
   LAUNCH(k_scan_chunks, 4 * nk, kScanThreads, S);
-  if (parts) {
-    LAUNCH(k_find_parts, grid_for(nn), kThreads, S, part_list, static_cast<uint32_t>(max_list), words);
-    LAUNCH(k_parts<0>, 512, kPartThreads, S, part_list, words, nullptr, nullptr);
+  unsigned long long tot[2 * kCounters];  // the totals, and the sums before side 1's first candidate
+  for (PlanParams q = p;;) {
+    if (parts) {
+      LAUNCH(k_find_parts, grid_for(nn), kThreads, S, part_list, static_cast<uint32_t>(max_list), words);
+      LAUNCH(k_parts<0>, 512, kPartThreads, S, part_list, words, nullptr, nullptr);
+    }
+    if (nk == 4)
+      LAUNCH(k_count<4>, all_row_chunks, kThreads, S, counts, stride, max_direct_d);
+    else
+      LAUNCH(k_count<3>, all_row_chunks, kThreads, S, counts, stride, max_direct_d);
+    LAUNCH(k_scan_rows, kCounters, kScanThreads, counts, stride, all_row_chunks, row_chunks[0], totals_d);
+    PD_TRY(hipMemcpyAsync(tot, totals_d, sizeof(tot), hipMemcpyDeviceToHost, st));
+    PD_TRY(hipStreamSynchronize(st));
+    if (!larger_parts(q, static_cast<int64_t>(tot[kRevAcc] + tot[kDirectParts]) * hp.acc_width * 4)) break;
+    for (PSide& P : S.s) P.part_work = static_cast<unsigned long long>(q.part_work);
+    PD_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(words), 3, 0ull, st));
   }
-  if (nk == 4)
-    LAUNCH(k_count<4>, all_row_chunks, kThreads, S, counts, stride);
-  else
-    LAUNCH(k_count<3>, all_row_chunks, kThreads, S, counts, stride);
-  LAUNCH(k_scan_rows, kCounters, kScanThreads, counts, stride, all_row_chunks, row_chunks[0], totals_d);
-  // the totals, and the sums before side 1's first candidate
-  unsigned long long tot[2 * kCounters];
-  PD_TRY(hipMemcpyAsync(tot, totals_d, sizeof(tot), hipMemcpyDeviceToHost, st));
-  PD_TRY(hipStreamSynchronize(st));
   const unsigned long long* at1 = tot + kCounters;
   {
     PlanSizes z{};
@@ -1483,7 +1499,6 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     while ((int64_t{1} << kb) < g.n[s]) ++kb;
     hp.key_bits[s] = kb;
   }
-  unsigned long long* n_groups_d = reinterpret_cast<unsigned long long*>(words + 2);
   if (n_chunks > 0) {
     const uint32_t blocks = (n_chunks + kThreads / 64 - 1) / (kThreads / 64);
     const SmallList sl{io.small_key, io.small_seg, io.small_owner, static_cast<uint32_t>(n_small),
@@ -1571,7 +1586,7 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     }
     out.hub_K[s] = K;
   }
-  uint32_t words_h[4];
+  uint32_t words_h[6];
   PD_TRY(hipMemcpyAsync(words_h, words, sizeof(words_h), hipMemcpyDeviceToHost, st));
   PD_TRY(hipStreamSynchronize(st));
   out.any_wide = words_h[1] != 0;
@@ -1581,6 +1596,7 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     PD_TRY(hipMemcpyAsync(groups_out, groups, static_cast<size_t>(n_groups) * sizeof(Item), hipMemcpyDeviceToDevice,
                           st));
 
+  hp.direct_max_work = words_h[4] | (static_cast<uint64_t>(words_h[5]) << 32);
   hp.acc_slots = static_cast<int32_t>(acc_slots);
   hp.n_reverse_side0 = static_cast<int32_t>(at1[kRev]);
   if (p.per_vertex) {

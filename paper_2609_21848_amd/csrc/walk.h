@@ -498,14 +498,18 @@ __device__ __forceinline__ HashTally<G> hash_tally(G g) {
 }
 
 struct Sums {
-  int64_t bal = 0, unb = 0, tot = 0;
+  int64_t bal = 0, unb = 0;
   __device__ __forceinline__ void add(uint32_t p, uint32_t n) {
     const int64_t P = p, N = n;
     bal += P * (P - 1) / 2 + N * (N - 1) / 2;
     unb += P * N;
-    tot += (P + N) * (P + N - 1) / 2;
   }
 };
+
+// This workgroup's copy of the result slots.
+__device__ __forceinline__ unsigned long long* own_copy(unsigned long long* res, uint32_t res_mask) {
+  return res + static_cast<size_t>(blockIdx.x & res_mask) * kResCopyStride;
+}
 
 // The sums of a wavefront (or workgroup) belong to one graph at a time:
 // items of a graph are contiguous in every list, and the running sums are
@@ -521,11 +525,10 @@ __device__ __forceinline__ int64_t wave_sum64(int64_t x) {
 // Add the wavefront's sums to a graph's results (one atomic per wavefront
 // and value).
 __device__ __forceinline__ void flush_sums(const Sums& s, unsigned long long* res) {
-  const int64_t b = wave_sum64(s.bal), u = wave_sum64(s.unb), t = wave_sum64(s.tot);
+  const int64_t b = wave_sum64(s.bal), u = wave_sum64(s.unb);
   if (lane_id() == 0) {
     if (b) atomicAdd(res + kResBalanced, static_cast<unsigned long long>(b));
     if (u) atomicAdd(res + kResUnbalanced, static_cast<unsigned long long>(u));
-    if (t) atomicAdd(res + kResTotal, static_cast<unsigned long long>(t));
   }
 }
 
@@ -580,7 +583,6 @@ struct SqTotals {
       const int64_t bal = (q - ww) / 2;
       if (bal) atomicAdd(res + kResBalanced, static_cast<unsigned long long>(bal));
       if (x) atomicAdd(res + kResUnbalanced, static_cast<unsigned long long>(x));
-      if (bal + x) atomicAdd(res + kResTotal, static_cast<unsigned long long>(bal + x));
     }
   }
 };
@@ -626,7 +628,6 @@ __device__ __forceinline__ void flush_block_end(int64_t bal, int64_t unb, uint32
       unsigned long long* r = res + static_cast<size_t>(g) * kResStride;
       if (b) atomicAdd(r + kResBalanced, static_cast<unsigned long long>(b));
       if (u) atomicAdd(r + kResUnbalanced, static_cast<unsigned long long>(u));
-      if (b + u) atomicAdd(r + kResTotal, static_cast<unsigned long long>(b + u));
     };
     for (int w = 0; w < nwaves; ++w) {
       const WaveSums v = sh[w];
@@ -649,7 +650,6 @@ __device__ __forceinline__ void flush_block_end(const SqTotals& t, uint32_t grap
   const int64_t ww = wave_sum64(static_cast<int64_t>(t.w));
   flush_block_end((q - ww) / 2, x, graph, sh, nwaves, res);
 }
-// (Sums: its total is bal + unb, C(p + n, 2) = C(p, 2) + C(n, 2) + p n)
 __device__ __forceinline__ void flush_block_end(const Sums& s, uint32_t graph, WaveSums* sh, int nwaves,
                                                 unsigned long long* res) {
   flush_block_end(wave_sum64(s.bal), wave_sum64(s.unb), graph, sh, nwaves, res);
