@@ -125,6 +125,7 @@ struct PSide {
   bool pv;                // a per-vertex plan
   bool wide_all;          // per-vertex plans: flag every run kMidWide
   unsigned long long max_deg;  // largest degree of the side (the wide-credit bound)
+  unsigned long long max_mid;  // largest degree of the other side (a run's most entries)
   uint32_t m;
   uint32_t side;
   uint32_t chunks, row_chunks;
@@ -520,9 +521,8 @@ __global__ __launch_bounds__(kThreads) void k_find_parts(PSides S, uint2* list, 
     if (P.pv) {
       if (x >= P.T) continue;
     } else {
-      // a run has at most the largest other degree of entries
       const unsigned long long d = P.off[x + 1] - P.off[x];
-      if (d <= kPartMaxRuns && d * P.max_deg <= P.part_work) continue;
+      if (d <= kPartMaxRuns && d * P.max_mid <= P.part_work) continue;
     }
     for (int k = 0; k < P.nk; ++k) {
       if (k == kR || (P.pv && k != kH)) continue;
@@ -1379,6 +1379,7 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
       P.nk = nk;
       P.wide_all = p.wide_all;
       P.max_deg = static_cast<unsigned long long>(g.max_deg[s]);
+      P.max_mid = static_cast<unsigned long long>(g.max_deg[o]);
       P.small_work = static_cast<uint32_t>(p.small_work);
       P.part_work = static_cast<unsigned long long>(p.part_work);
       P.chunks = static_cast<uint32_t>((g.m + kChunk - 1) / kChunk);

@@ -75,3 +75,17 @@ def test_small_items_of_all_sizes_and_sparse_sides(dbbc, opts):
         u.append(rng.choice(700 if y % 3 else 60, min(d, 60), replace=False))
         v.append(np.full(len(u[-1]), y * 4))
     _check(dbbc, n_u, n_v, np.concatenate(u), np.concatenate(v), opts)
+
+
+@pytest.mark.parametrize("swap", [False, True])
+@pytest.mark.parametrize("part_work", [4096, 20000])
+def test_parts_of_rows_whose_mids_are_far_larger(dbbc, swap, part_work):
+    # 900 rows of degree 12 to 20 through 40 mids of some hundred entries: heavy
+    # items whose own side has small degrees only
+    rng = np.random.default_rng(5)
+    u = np.repeat(np.arange(900), 12 + np.arange(900) % 9)
+    v = np.concatenate([rng.choice(40, 12 + x % 9, replace=False) for x in range(900)])
+    n = (900, 40)
+    if swap:
+        u, v, n = v, u, n[::-1]
+    _check(dbbc, *n, u, v, dict(part_work=part_work, small_work=2, hub_T=0, window_L=1024, reverse_L=64))
