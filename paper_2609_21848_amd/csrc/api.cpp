@@ -1149,6 +1149,17 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   for (int s = 0; s < 2; ++s)
     HIP_TRY(dbbc::launch_fill_u64(g->pv_keys[s].as<unsigned long long>(), 2 * static_cast<size_t>(dbbc::kPVKeyRanks),
                                   0ull, st));
+  if (hp.n_heavy[0] + hp.n_heavy[1] > 0)
+    HIP_TRY(dbbc::launch_fill_u64(d.acc.as<unsigned long long>(),
+                                  static_cast<size_t>(hp.acc_slots) * hp.acc_width / 2, 0ull, st));
+  for (int s = 0; s < 2; ++s) {  // the parts of heavy items (each side's first)
+    dbbc::DirectArgs a{};
+    a.items = d.direct_items.as<dbbc::Item>() + (s == 0 ? 0 : hp.n_direct_side0);
+    a.sides = sides;
+    a.n_items = hp.n_heavy[s];
+    a.long_len = long_len;
+    HIP_TRY(dbbc::launch_pv_heavy_tally(a, std::min<int>(cus, std::max(1, a.n_items)), st));
+  }
   for (int s = 0; s < 2; ++s) {
     const int32_t lo = s == 0 ? 0 : hp.n_direct_side0;
     const int32_t hi = s == 0 ? hp.n_direct_side0 : hp.n_items_kept[0];

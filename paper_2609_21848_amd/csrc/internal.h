@@ -81,7 +81,8 @@ constexpr uint32_t kReverseCountMaxSegs = 127;
 
 // Flags of an item.
 enum : uint32_t {
-  kItemMultiPart = 1u,  // partial counts go to a global accumulator
+  kItemMultiPart = 1u,  // partial counts go to a global accumulator (per-vertex direct items: the parts
+                        // of an item share the accumulator acc_slot; work = part << 16 | parts)
   kItemHubPairs = 2u,   // keys below hub_T are flushed to the hub-pair buffer
   kItemPacked = 4u,     // per-vertex direct item: p and n share one 32-bit word
 };
@@ -121,10 +122,13 @@ struct PlanParams {
   // bytes the parts' counters may take before part_work is raised (0: as
   // part_work says, which the caller chose)
   int64_t part_room = 0;
+  // per-vertex plans: wedge budget of a part of a direct item
+  int64_t pv_part_work = int64_t{1} << 62;
   bool operator==(const PlanParams& o) const {
     return hub_T == o.hub_T && window_L == o.window_L && reverse_L == o.reverse_L &&
            small_work == o.small_work && part_work == o.part_work && per_vertex == o.per_vertex &&
-           wide_all == o.wide_all && host_planner == o.host_planner && part_room == o.part_room;
+           wide_all == o.wide_all && host_planner == o.host_planner && part_room == o.part_room &&
+           pv_part_work == o.pv_part_work;
   }
 };
 
@@ -191,6 +195,7 @@ struct HostPlan {
   uint64_t direct_max_work = 0;  // wedges of the heaviest direct item (or part)
   int32_t n_reverse_side0 = 0;  // reverse items are listed side 0 first
   int32_t n_direct_side0 = 0;   // per-vertex plans: direct items side 0 first
+  int32_t n_heavy[2] = {0, 0};  // ... each side's first n_heavy items are parts
   int32_t acc_slots = 0;
   int32_t acc_width = 0;           // max window over the sides
   // per sparse kernel (0 = direct, 1 = small, 2 = hash, 3 = reverse):

@@ -227,6 +227,9 @@ hipError_t launch_hub_credit(const HubCreditArgs& a, hipStream_t st);
 
 // Per-vertex pass (plans made with per_vertex): direct items, reverse items,
 // small-item groups and hash items.
+// (launch_pv_heavy_tally: the parts among the direct items, before either
+// side's direct launch; their accumulators start at zero)
+hipError_t launch_pv_heavy_tally(const DirectArgs& a, int grid, hipStream_t st);
 hipError_t launch_pv_direct(const DirectArgs& a, int grid, hipStream_t st);
 // Largest rank a per-vertex direct item's key may have (the widest window),
 // and the adding of the rank-indexed key credits of side s (ranks below n)

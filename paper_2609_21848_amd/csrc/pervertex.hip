@@ -280,6 +280,69 @@ struct PairCredit {
 constexpr int kPVDirectThreads = 1024;
 constexpr int kPVDirectWaves = kPVDirectThreads / kWave;
 
+// An item's wedges into C: packed 16|16-bit words by key, or P | N halves.
+__device__ __forceinline__ void pv_direct_tally(const Item& it, const DevSideConst& sc, uint32_t long_len,
+                                                const Marks<uint8_t>& mk, uint32_t* C, bool packed) {
+  const uint32_t lo = static_cast<uint32_t>(it.key_lo), hi = static_cast<uint32_t>(it.key_hi);
+  const uint32_t seg_end = it.seg_begin + it.seg_count;
+  uint32_t* const P = C;
+  uint32_t* const N = C + kPVWindow;
+  for (uint32_t k0 = it.seg_begin + threadIdx.x / kWave; k0 < seg_end; k0 += kPVDirectThreads) {
+    const SegReg sr = load_seg<false>(sc.segs, k0, seg_end, kPVDirectWaves);
+    if (packed)
+      walk_regs<4, false, true>(sr, sc.other_adj, mk, long_len, hash_tally([&](uint32_t e, uint32_t tag) {
+                                  const uint32_t key = e >> 1;
+                                  if (key >= lo && key < hi) atomicAdd(&C[key - lo], wedge_inc(e, tag));
+                                }));
+    else
+      walk_regs<4, false, true>(sr, sc.other_adj, mk, long_len, hash_tally([&](uint32_t e, uint32_t tag) {
+                                  const uint32_t key = e >> 1;
+                                  if (key >= lo && key < hi) atomicAdd(((e ^ tag) & 1u) ? &N[key - lo] : &P[key - lo], 1u);
+                                }));
+  }
+}
+
+// Heavy items.  An item runs on one CU, so a pivot with more than a CU's
+// share of the wedges would outlast its launch (2M edges, per-edge pass:
+// 1.14 ms for one item of 0.95M wedges, the others' work 0.3 ms).  Such items
+// are cut into parts: this launch tallies the parts and adds their counters
+// into the accumulator of the item's key window (consecutive keys, a few cache
+// lines per instruction; unpacked: p, then n from the next 16-byte piece); the
+// main launch's parts load the whole counters, credit their own runs' wedges,
+// and sweep a slice of the keys.
+__device__ __forceinline__ uint32_t pv_acc_half(uint32_t keys) { return (keys + 3u) & ~3u; }
+
+__global__ __launch_bounds__(kPVDirectThreads) void k_pv_heavy_tally(DirectArgs a) {
+  __shared__ uint32_t C[kPVWindowPacked];
+  __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVDirectWaves][2 * kWave];
+  __shared__ uint8_t mflag[kPVDirectWaves][kGather];
+  const int tid = threadIdx.x;
+  const int wave = tid / kWave;
+  for (int i = tid; i < kPVWindowPacked; i += kPVDirectThreads) C[i] = 0;
+  for (int i = tid; i < kPVDirectWaves * static_cast<int>(kGather); i += kPVDirectThreads) (&mflag[0][0])[i] = 0;
+  __syncthreads();
+  for (int32_t i = blockIdx.x; i < a.n_items; i += gridDim.x) {
+    const Item it = load_const(a.items, i);
+    const DevSideConst sc = load_const(a.sides, 2 * it.graph + it.side);
+    const bool packed = (it.flags & kItemPacked) != 0;
+    pv_direct_tally(it, sc, a.long_len, Marks<uint8_t>{mtab[wave], mflag[wave]}, C, packed);
+    __syncthreads();
+    global_t<uint32_t>* to = as_global(sc.acc) + static_cast<size_t>(it.acc_slot) * sc.acc_width;
+    const uint32_t keys = static_cast<uint32_t>(it.key_hi - it.key_lo);
+    for (int h = 0; h < (packed ? 1 : 2); ++h) {
+      uint32_t* const from = C + h * kPVWindow;
+      for (uint32_t k = tid; k < keys; k += kPVDirectThreads) {
+        const uint32_t v = from[k];
+        if (v) {
+          from[k] = 0;
+          __hip_atomic_fetch_add(to + h * pv_acc_half(keys) + k, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
 template <bool kEdge>
 __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
   a.res = own_copy(a.res, a.res_mask);
@@ -332,22 +395,19 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
     // a hub pivot's keys below T are hub pairs: their completed counts come
     // from the dense block and their key credits were given there
     const uint32_t hubT = (it.flags & kItemHubPairs) ? static_cast<uint32_t>(sc.T) : 0u;
-    // tally (the wavefronts take the item's segments interleaved, so that
-    // every wavefront gets a similar mix of long and short runs)
-    for (uint32_t k0 = it.seg_begin + wave; k0 < seg_end; k0 += kPVDirectThreads) {
-      RunEnds re;
-      const SegReg sr = load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, k0, seg_end, re, kPVDirectWaves);
-      if (packed)
-        walk_regs<4, false, true>(sr, sc.other_adj, mk, a.long_len, hash_tally([&](uint32_t e, uint32_t tag) {
-                                    const uint32_t key = e >> 1;
-                                    if (key >= lo && key < hi) atomicAdd(&C[key - lo], wedge_inc(e, tag));
-                                  }));
-      else
-        walk_regs<4, false, true>(sr, sc.other_adj, mk, a.long_len, hash_tally([&](uint32_t e, uint32_t tag) {
-                                    const uint32_t key = e >> 1;
-                                    if (key >= lo && key < hi)
-                                      atomicAdd(((e ^ tag) & 1u) ? &N[key - lo] : &P[key - lo], 1u);
-                                  }));
+    const bool part = (it.flags & kItemMultiPart) != 0;
+    if (part) {
+      // a part of a heavy item: the tally launch before this one left the
+      // item's whole counts in its accumulator
+      const u32x4* from = reinterpret_cast<const u32x4*>(sc.acc + static_cast<size_t>(it.acc_slot) * sc.acc_width);
+      for (uint32_t k = 4 * tid; k < hi - lo; k += 4 * kPVDirectThreads) {
+        *reinterpret_cast<u32x4*>(&C[k]) = *as_global(from + k / 4);
+        if (!packed) *reinterpret_cast<u32x4*>(&N[k]) = *as_global(from + (pv_acc_half(hi - lo) + k) / 4);
+      }
+    } else {
+      // tally (the wavefronts take the item's segments interleaved, so that
+      // every wavefront gets a similar mix of long and short runs)
+      pv_direct_tally(it, sc, a.long_len, mk, C, packed);
     }
     __syncthreads();
     // credit the mids
@@ -400,13 +460,21 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
     // key's credits fit 32 bits).  Key credits go to the rank-indexed sums
     // (the threads' keys are consecutive: one instruction's atomics touch a
     // few cache lines, where input-id order would scatter them over 64).
+    // A part sweeps its slice of the keys, and clears them all.
     PairCredit pc;
+    uint32_t k_lo = 0, k_hi = hi - lo;
+    if (part) {
+      const uint32_t idx = it.work >> 16, n = it.work & 0xffffu, step = (hi - lo + n - 1) / n;
+      k_lo = min(hi - lo, idx * step);
+      k_hi = min(hi - lo, k_lo + step);
+    }
     for (uint32_t k = tid; k < hi - lo; k += kPVDirectThreads) {
       const uint32_t v = C[k];
       const uint32_t p = packed ? v & 0xffffu : v, n = packed ? v >> 16 : N[k];
       if (p | n) {
         C[k] = 0;
         if (!packed) N[k] = 0;
+        if (k < k_lo || k >= k_hi) continue;
         const uint32_t key = lo + k;
         if (key < hubT) continue;  // a hub pair: credited by the dense block
         if (packed) {
@@ -937,6 +1005,11 @@ hipError_t hash_(const HashArgs& a, int grid, hipStream_t st) {
 
 }  // namespace
 
+hipError_t launch_pv_heavy_tally(const DirectArgs& a, int grid, hipStream_t st) {
+  if (a.n_items == 0) return hipSuccess;
+  hipLaunchKernelGGL(dev::k_pv_heavy_tally, dim3(grid), dim3(dev::kPVDirectThreads), 0, st, a);
+  return hipGetLastError();
+}
 hipError_t launch_pv_direct(const DirectArgs& a, int grid, hipStream_t st) { return direct_<false>(a, grid, st); }
 hipError_t launch_pv_reverse(const SmallArgs& a, int grid, hipStream_t st) { return reverse_<false>(a, grid, st); }
 hipError_t launch_pv_small(const SmallArgs& a, int grid, hipStream_t st) { return small_<false>(a, grid, st); }

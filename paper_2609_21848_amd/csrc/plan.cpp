@@ -77,6 +77,20 @@ PlanParams default_params(const HostGraph& g, int32_t hub_slots) {
   // (larger_parts).
   p.part_work = static_cast<int32_t>(
       std::min<int64_t>(kMaxPartWork, std::max<int64_t>(1 << 18, g.wedges_vp / std::max(1, hub_slots))));
+  // The per-vertex and per-edge passes walk an item's wedges twice and credit
+  // them, 100 us and more per 2^17 wedges on one CU, so their parts are
+  // smaller; each costs about 10 us more than its wedges (a key window added
+  // into the item's counters and read back).  Measured, ms per pass unsplit,
+  // at the best budget and at this rule's: per-vertex 334K edges (W 8.8M) 0.44
+  // / 0.27 at 2^15 / 0.27, 2M (73M) 1.77 / 1.09 at 2^17 / 1.11, 8M (458M) 12.9 /
+  // 5.5 at 2^18 / 5.5, 20M (2.2G) 18.4 / 14.8 at 2^18 / 14.8; per-edge 2M 2.33 /
+  // 1.65, 8M 18.4 / 9.5, 20M 30.9 / 26.4.  At 50M (11.4G) the launches hold
+  // enough items beside their heaviest, and parts below 2^22 only cost (44.1 ->
+  // 44.6 ms): past 2^21 the budget is the count's largest.
+  const int64_t pv_budget =
+      std::max<int64_t>(1 << 15, std::min(g.wedges_vp / std::max(1, hub_slots),
+                                          (1 << 16) + g.wedges_vp / (8 * std::max(1, hub_slots))));
+  p.pv_part_work = pv_budget > (1 << 21) ? kMaxPartWork : pv_budget;
   const int64_t scratch = static_cast<int64_t>(DBBC_NOALLOC_SCRATCH_BYTES) - (1 << 20) -
                           16 * static_cast<int64_t>(p.hub_T) * p.hub_T;  // two int32 planes on each side
   p.part_room = std::max<int64_t>(1, scratch > 0 ? std::min(24 * g.m, scratch) : 24 * g.m);
@@ -412,7 +426,9 @@ void plan_windows(const int32_t n[2], const PlanParams& p, HostPlan& plan) {
   }
   // The dense path needs a block on both sides of the pair.
   if (plan.T[0] == 0 || plan.T[1] == 0) plan.T[0] = plan.T[1] = 0;
-  plan.acc_width = std::max(plan.L[0], plan.L[1]);
+  plan.acc_width = (std::max(plan.L[0], plan.L[1]) + 3) / 4 * 4;  // whole 16-byte pieces
+  if (p.per_vertex)  // p and n apart (32 bits each) fit as well
+    plan.acc_width = std::min(2 * plan.acc_width, kPVWindowPacked);
 }
 
 int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::string& err) {

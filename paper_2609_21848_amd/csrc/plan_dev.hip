@@ -36,8 +36,8 @@
 //
 // Per-vertex plans also record every run's mid (flagged kMidWide where its
 // credits may need two words) and first-edge position, and the owner of
-// every small item; they have no multi-part items (a direct item is cut into
-// key windows that share its runs) and reverse endpoints with more than
+// every small item; a direct item is cut into key windows that share its runs,
+// or, past pv_part_work wedges, into parts that share its counters, and reverse endpoints with more than
 // kReverseMaxSegs runs become direct items.
 // Where the result differs from make_plan's, both are valid plans of the
 // same wedges (the counts are the same):
@@ -198,6 +198,20 @@ struct Cand {
   uint32_t flags;
 };
 
+// Per-vertex plans: the key windows of a direct item (kPVWindowPacked keys
+// with packed counters, see pv_packed; else kPVWindow keys).
+__device__ bool pv_item_packed(const PSide& P, uint32_t nseg, uint32_t flags) {
+  const int64_t deg_T = P.T < P.n ? static_cast<int64_t>(P.off[P.T + 1] - P.off[P.T]) : 0;
+  return pv_packed(nseg, (flags & kItemHubPairs) != 0, deg_T);
+}
+__device__ uint32_t pv_window_count(int32_t key_lo, int32_t key_hi, bool packed) {
+  const uint32_t win = static_cast<uint32_t>(packed ? kPVWindowPacked : kPVWindow);
+  return (static_cast<uint32_t>(key_hi - key_lo) + win - 1) / win;
+}
+__device__ uint32_t pv_item_windows(const PSide& P, const Cand& c) {
+  return pv_window_count(c.key_lo, c.key_hi, pv_item_packed(P, c.nseg, c.flags));
+}
+
 // Classify candidate (x, k) as make_plan's place() does.  With kParts, a
 // split direct item's (and a hub tally item's) part count is read too.
 template <bool kParts>
@@ -242,7 +256,7 @@ __device__ Cand classify(const PSide& P, int32_t x, int k) {
     c.key_hi = P.L;
     c.cls = small ? kSmallC : kDirectC;
   }
-  if (c.cls == kDirectC && !P.pv && (c.work > P.part_work || c.nseg > kPartMaxRuns)) {
+  if (c.cls == kDirectC && (c.work > P.part_work || (!P.pv && c.nseg > kPartMaxRuns))) {
     c.split = true;
     if (kParts) c.nparts = P.parts[static_cast<int64_t>(x) * P.nk + k];
   }
@@ -505,8 +519,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_chunks(PSides S) {
 
 // ---- parts ---------------------------------------------------------------------
 //
-// Split direct items (kinds F and M; count plans) and the hub pivots' tally
-// items (kind H) start a part at the first run, at every kPartMaxRuns-th run
+// Split direct items (kinds F and M) and the hub pivots' tally items (kind H)
+// start a part at the first run, at every kPartMaxRuns-th run
 // and at every run whose wedge range [pex, pex + len) of the item holds a
 // multiple of the part budget (part_work, or kHubTallyPartWork).  Such items
 // are few and large: they are listed (k_find_parts), and a block walks the
@@ -518,14 +532,10 @@ __global__ __launch_bounds__(kThreads) void k_find_parts(PSides S, uint2* list, 
     const bool side0 = i < S.s[0].n;
     const PSide& P = side0 ? S.s[0] : S.s[1];
     const int32_t x = static_cast<int32_t>(side0 ? i : i - S.s[0].n);
-    if (P.pv) {
-      if (x >= P.T) continue;
-    } else {
-      const unsigned long long d = P.off[x + 1] - P.off[x];
-      if (d <= kPartMaxRuns && d * P.max_mid <= P.part_work) continue;
-    }
+    const unsigned long long d = P.off[x + 1] - P.off[x];
+    if (!(P.pv && x < P.T) && d <= kPartMaxRuns && d * P.max_mid <= P.part_work) continue;
     for (int k = 0; k < P.nk; ++k) {
-      if (k == kR || (P.pv && k != kH)) continue;
+      if (k == kR) continue;
       const Cand c = classify<false>(P, x, k);
       if (!c.split && c.cls != kHubC) continue;
       const uint32_t at = atomicAdd(n_list, 1u);
@@ -634,17 +644,6 @@ enum : int {
   kCounters
 };
 
-// Per-vertex plans: the key windows of a direct item (kPVWindowPacked keys
-// with packed counters, see pv_packed; else kPVWindow keys).
-__device__ bool pv_item_packed(const PSide& P, uint32_t nseg, uint32_t flags) {
-  const int64_t deg_T = P.T < P.n ? static_cast<int64_t>(P.off[P.T + 1] - P.off[P.T]) : 0;
-  return pv_packed(nseg, (flags & kItemHubPairs) != 0, deg_T);
-}
-__device__ uint32_t pv_window_count(int32_t key_lo, int32_t key_hi, bool packed) {
-  const uint32_t win = static_cast<uint32_t>(packed ? kPVWindowPacked : kPVWindow);
-  return (static_cast<uint32_t>(key_hi - key_lo) + win - 1) / win;
-}
-
 // Add candidate c's list counts to q.
 __device__ __forceinline__ void add_lists(const PSide& P, const Cand& c, unsigned long long* q) {
   switch (c.cls) {
@@ -656,15 +655,18 @@ __device__ __forceinline__ void add_lists(const PSide& P, const Cand& c, unsigne
       q[kBigRuns] += c.nseg;
       q[kHashItems] += 1;
       break;
-    case kDirectC:
+    case kDirectC: {
+      const uint32_t nw = P.pv ? pv_item_windows(P, c) : 1u;
       q[kBigRuns] += c.nseg;
       q[kDirect] += 1;
-      if (c.split) {
-        q[kDirectParts] += c.nparts;
-        q[kDirectSplit] += 1;
+      if (c.split) {  // every window in the same parts
+        q[kDirectParts] += nw * c.nparts;
+        q[kDirectSplit] += nw;
+      } else if (P.pv) {
+        q[kWindows] += nw;
       }
-      if (P.pv) q[kWindows] += pv_window_count(c.key_lo, c.key_hi, pv_item_packed(P, c.nseg, c.flags));
       break;
+    }
     case kRevC:
       q[kBigRuns] += c.nseg;
       q[kRev] += c.nparts ? c.nparts : 1;
@@ -726,7 +728,7 @@ __global__ __launch_bounds__(kThreads) void k_count(PSides S, unsigned long long
     const int slot = c.cls == kSmallC ? 1 : c.cls == kHashC ? 2 : c.cls == kDirectC ? 0 : 3;
     unsigned long long mult = 1;
     if (P.pv && slot == 0)  // the windows share the runs
-      mult = pv_window_count(c.key_lo, c.key_hi, pv_item_packed(P, c.nseg, c.flags));
+      mult = pv_item_windows(P, c);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       q[kStWedges + t] += t == slot ? c.work * mult : 0ull;
@@ -847,6 +849,7 @@ __global__ __launch_bounds__(kThreads) void k_items(PSides S, const unsigned lon
         o.hash[q[kHashItems]] = it;
         o.hash_key[q[kHashItems]] = work_key(c.work, 0);
       } else if (c.cls == kDirectC) {
+        if (c.split) P.part_pos[cand] = static_cast<uint32_t>(q[kDirectParts]);
         if (kNk == 4) {  // key windows that share the runs
           const bool packed = pv_item_packed(P, c.nseg, c.flags);
           const uint32_t nw = pv_window_count(c.key_lo, c.key_hi, packed);
@@ -855,13 +858,18 @@ __global__ __launch_bounds__(kThreads) void k_items(PSides S, const unsigned lon
           for (uint32_t w = 0; w < nw; ++w) {
             it.key_lo = c.key_lo + static_cast<int32_t>(w) * win;
             it.key_hi = min(c.key_hi, it.key_lo + win);
-            o.direct[q[kWindows] + w] = it;
-            o.direct_key[q[kWindows] + w] = work_key(c.work, P.side);
+            if (c.split) {
+              it.work = w;
+              o.split[q[kDirectSplit] + w] = it;
+              o.split_part[q[kDirectSplit] + w] = static_cast<uint32_t>(q[kDirectParts]) + w * c.nparts;
+            } else {
+              o.direct[q[kWindows] + w] = it;
+              o.direct_key[q[kWindows] + w] = work_key(c.work, P.side);
+            }
           }
         } else if (c.split) {
           o.split[q[kDirectSplit]] = it;
           o.split_part[q[kDirectSplit]] = static_cast<uint32_t>(q[kDirectParts]);
-          P.part_pos[cand] = static_cast<uint32_t>(q[kDirectParts]);
         } else {
           o.direct[q[kDirect] - q[kDirectSplit]] = it;
           o.direct_key[q[kDirect] - q[kDirectSplit]] = work_key(c.work, 0);
@@ -1170,13 +1178,19 @@ struct OrderIn {
 struct GatherOut {
   const Item* in;
   Item* out;
-  __device__ __forceinline__ void store(uint32_t pos, const radix::Elt<2>& e) const { out[pos] = in[e.w[1]]; }
+  uint32_t skip1;  // places left out before side 1's items
+  __device__ __forceinline__ void store(uint32_t pos, const radix::Elt<2>& e) const {
+    const Item it = in[e.w[1]];
+    out[pos + (it.side ? skip1 : 0u)] = it;
+  }
 };
-// The parts of split direct items and their reduces.
+// The parts of split direct items, and (count plans) their reduces.
 struct SplitOut {
   Item* items;
   Reduce* reduces;
-  uint32_t acc0;        // first accumulator slot of the direct parts
+  uint32_t acc0;        // count plans: first accumulator slot of the direct parts (one each)
+  uint32_t skip1;       // per-vertex plans: places of side 0's other items, before side 1's parts
+  bool pv;              // per-vertex plans: an item's parts share an accumulator
 };
 
 __global__ void k_split_parts(PSides S, const Item* split, const uint32_t* part_at, uint32_t n, uint32_t n_parts,
@@ -1189,12 +1203,15 @@ __global__ void k_split_parts(PSides S, const Item* split, const uint32_t* part_
     uint32_t nseg;
     unsigned long long work;
     row_totals(P, it.owner < P.L ? kF : kM, it.owner, nseg, work);
+    const PartStart* first = parts + at - (o.pv ? it.work * np : 0u);  // (pv: work is the item's window)
     for (uint32_t p = 0; p < np; ++p) {
-      Item part = part_of(it, it.seg_begin, nseg, work, parts + at, p, np);
+      Item part = part_of(it, it.seg_begin, nseg, work, first, p, np);
       part.flags |= kItemMultiPart;
-      part.acc_slot = static_cast<int32_t>(o.acc0 + at + p);
-      o.items[at + p] = part;
+      part.acc_slot = static_cast<int32_t>(o.pv ? i : o.acc0 + at + p);
+      if (o.pv) part.work = (p << 16) | np;
+      o.items[at + p + (it.side ? o.skip1 : 0u)] = part;
     }
+    if (o.pv) continue;
     Reduce r{};
     r.acc_slot = static_cast<int32_t>(o.acc0 + at);
     r.n_parts = static_cast<int32_t>(np);
@@ -1315,7 +1332,7 @@ struct Scratch {
 
 // Items in work order.
 void order_items(const uint32_t* key, int64_t n, uint32_t* buf, unsigned long long* ctl, const Item* in, Item* out,
-                 hipStream_t st) {
+                 uint32_t skip1, hipStream_t st) {
   if (n == 0) return;
   const radix::Digits d = radix::digits_of(0, 16);
   const size_t w = Carve::round(static_cast<size_t>(n));
@@ -1323,7 +1340,7 @@ void order_items(const uint32_t* key, int64_t n, uint32_t* buf, unsigned long lo
   const radix::Control cc{ctl};
   PD_TRY(launch_fill_u64(ctl, radix::control_words(n, d), 0ull, st));
   PD_TRY((radix::histogram<1>(OrderIn{key}, n, d, cc, st)));
-  PD_TRY((radix::passes<1, 2>(OrderIn{key}, GatherOut{in, out}, bufs, n, d, cc, st)));
+  PD_TRY((radix::passes<1, 2>(OrderIn{key}, GatherOut{in, out, skip1}, bufs, n, d, cc, st)));
 }
 
 void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& hp, DevPlanLists& out) {
@@ -1332,8 +1349,9 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   const int nk = p.per_vertex ? 4 : 3;
   const int64_t nn = static_cast<int64_t>(g.n[0]) + g.n[1];
   // a direct item can be split only past these
-  const bool parts = p.per_vertex ? hp.T[0] > 0
-                                  : g.wedges > p.part_work || std::max(g.max_deg[0], g.max_deg[1]) > kPartMaxRuns;
+  const int64_t part_work = p.per_vertex ? p.pv_part_work : p.part_work;
+  const bool parts = g.wedges > part_work || (p.per_vertex ? hp.T[0] > 0
+                                                           : std::max(g.max_deg[0], g.max_deg[1]) > kPartMaxRuns);
   DevBuf scratch_b;
   unsigned long long *counts = nullptr, *totals_d = nullptr;
   // listed candidates, any wide run; then (64 bits each) the number of small
@@ -1345,8 +1363,8 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   // part_work wedges or kPartMaxRuns runs (a kind has at most W_VP wedges
   // and m runs per side)
   const int64_t max_list =
-      std::min<int64_t>(nk * nn, p.per_vertex ? int64_t{hp.T[0]} + hp.T[1]
-                                              : 4 * (g.wedges / std::max(p.part_work, 1) + g.m / kPartMaxRuns) + 8);
+      std::min<int64_t>(nk * nn, int64_t{hp.T[0]} + hp.T[1] +
+                                     4 * (g.wedges / std::max<int64_t>(part_work, 1) + g.m / kPartMaxRuns) + 8);
   const uint32_t row_chunks[2] = {static_cast<uint32_t>((g.n[0] + int64_t{kRowChunk} - 1) / kRowChunk),
                                   static_cast<uint32_t>((g.n[1] + int64_t{kRowChunk} - 1) / kRowChunk)};
   const uint32_t all_row_chunks = row_chunks[0] + row_chunks[1], stride = all_row_chunks + 1;
@@ -1381,7 +1399,7 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
       P.max_deg = static_cast<unsigned long long>(g.max_deg[s]);
       P.max_mid = static_cast<unsigned long long>(g.max_deg[o]);
       P.small_work = static_cast<uint32_t>(p.small_work);
-      P.part_work = static_cast<unsigned long long>(p.part_work);
+      P.part_work = static_cast<unsigned long long>(part_work);
       P.chunks = static_cast<uint32_t>((g.m + kChunk - 1) / kChunk);
       P.row_chunks = row_chunks[s];
       Mid* mids = sc.take<Mid>(P.no);
@@ -1428,7 +1446,7 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     LAUNCH(k_scan_rows, kCounters, kScanThreads, counts, stride, all_row_chunks, row_chunks[0], totals_d);
     PD_TRY(hipMemcpyAsync(tot, totals_d, sizeof(tot), hipMemcpyDeviceToHost, st));
     PD_TRY(hipStreamSynchronize(st));
-    if (!larger_parts(q, static_cast<int64_t>(tot[kRevAcc] + tot[kDirectParts]) * hp.acc_width * 4)) break;
+    if (p.per_vertex || !larger_parts(q, static_cast<int64_t>(tot[kRevAcc] + tot[kDirectParts]) * hp.acc_width * 4)) break;
     for (PSide& P : S.s) P.part_work = static_cast<unsigned long long>(q.part_work);
     PD_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(words), 3, 0ull, st));
   }
@@ -1436,8 +1454,9 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   {
     PlanSizes z{};
     z.runs = std::max({tot[kBigRuns], tot[kSmallRuns], tot[kHubRuns]});
-    z.items = std::max<uint64_t>({tot[kSmallItems], tot[kHashItems], tot[kRev], tot[kHubParts], tot[kWindows],
-                                  tot[kDirectParts] + tot[kDirect] - tot[kDirectSplit]});
+    z.items = std::max<uint64_t>({tot[kSmallItems], tot[kHashItems], tot[kRev], tot[kHubParts],
+                                  tot[kDirectParts] +
+                                      (p.per_vertex ? tot[kWindows] : tot[kDirect] - tot[kDirectSplit])});
     z.reduces = tot[kRevReduces] + tot[kDirectSplit];
     z.acc_slots = tot[kRevAcc] + tot[kDirectParts];
     std::string err;
@@ -1449,8 +1468,8 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   // direct items that are ordered, and all of them (the split items' parts)
   const int64_t n_direct = static_cast<int64_t>(p.per_vertex ? tot[kWindows] : tot[kDirect] - tot[kDirectSplit]);
   const int64_t n_dir_items = n_direct + static_cast<int64_t>(tot[kDirectParts]);
-  const int64_t n_reduces = static_cast<int64_t>(tot[kRevReduces] + tot[kDirectSplit]);
-  const int64_t acc_slots = static_cast<int64_t>(tot[kRevAcc] + tot[kDirectParts]);
+  const int64_t n_reduces = static_cast<int64_t>(tot[kRevReduces]) + (p.per_vertex ? 0 : n_split);
+  const int64_t acc_slots = static_cast<int64_t>(tot[kRevAcc] + (p.per_vertex ? tot[kDirectSplit] : tot[kDirectParts]));
 
   // items
   DevBuf scratch2_b;
@@ -1537,15 +1556,20 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
 
   // hash items, heaviest first
   Item* hash = alloc_n<Item>(out.hash_items, n_hash);
-  order_items(io.hash_key, n_hash, order_buf, ctl, io.hash, hash, st);
+  order_items(io.hash_key, n_hash, order_buf, ctl, io.hash, hash, 0, st);
   // direct items: the parts of split items, then the others, heaviest first
-  // (per-vertex plans: side 0 first)
+  // (per-vertex plans: side 0's of both, then side 1's)
   Item* direct = alloc_n<Item>(out.direct_items, n_dir_items);
   if (n_split > 0)
     LAUNCH(k_split_parts, grid_for(n_split), kThreads, S, io.split, io.split_part, static_cast<uint32_t>(n_split),
            static_cast<uint32_t>(tot[kDirectParts]), dir_parts,
-           SplitOut{direct, io.reduces + tot[kRevReduces], static_cast<uint32_t>(tot[kRevAcc])});
-  order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + tot[kDirectParts], st);
+           SplitOut{direct, io.reduces + tot[kRevReduces], static_cast<uint32_t>(tot[kRevAcc]),
+                    p.per_vertex ? static_cast<uint32_t>(at1[kWindows]) : 0u, p.per_vertex});
+  if (p.per_vertex)
+    order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + at1[kDirectParts],
+                static_cast<uint32_t>(tot[kDirectParts] - at1[kDirectParts]), st);
+  else
+    order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + tot[kDirectParts], 0, st);
   PD_TRY(out.acc.alloc(std::max<size_t>(static_cast<size_t>(acc_slots) * hp.acc_width * sizeof(uint32_t), 16)));
 
   // the dense block's signs
@@ -1602,7 +1626,9 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   hp.n_reverse_side0 = static_cast<int32_t>(at1[kRev]);
   if (p.per_vertex) {
     hp.n_hub_side0 = static_cast<int32_t>(at1[kHubParts]);
-    hp.n_direct_side0 = static_cast<int32_t>(at1[kWindows]);
+    hp.n_direct_side0 = static_cast<int32_t>(at1[kWindows] + at1[kDirectParts]);
+    hp.n_heavy[0] = static_cast<int32_t>(at1[kDirectParts]);
+    hp.n_heavy[1] = static_cast<int32_t>(tot[kDirectParts] - at1[kDirectParts]);
   }
   hp.n_items_kept[0] = static_cast<int32_t>(n_dir_items);
   hp.n_items_kept[1] = static_cast<int32_t>(n_rev);
