@@ -82,11 +82,8 @@ __device__ __forceinline__ void add_global(global_t<unsigned long long>* p, unsi
   __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <class Look, bool kEdge, class Acc, bool kHoist = false, bool kPack = false>
+template <class Look, bool kEdge, class Acc, bool kPack = false>
 struct Credit {
-  // kHoist: a staging round's four slots read their counters before any is
-  // used (add_staged); Look must then be branch-free and safe for any entry
-  static constexpr bool kStaged = kHoist;
   Look look;
   Acc* cb;  // per-wavefront LDS: balanced credit per run lane (kPack: both,
             // balanced in the low and unbalanced in the high 32 bits)
@@ -140,23 +137,6 @@ struct Credit {
     slot_add(j, b, u);
     edge(j, pos, b, u);
   }
-  // a staging round's slots (their runs' LDS slots take the shares)
-  __device__ __forceinline__ void add_staged(const Staged& s) {
-    uint32_t p[kStageU], n[kStageU];
-    bool ok[kStageU];
-#pragma unroll
-    for (int q = 0; q < kStageU; ++q) ok[q] = look(s.valid[q] ? s.e[q] : 0u, s.tag[q], p[q], n[q]) && s.valid[q];
-#pragma unroll
-    for (int q = 0; q < kStageU; ++q) {
-      if (!ok[q]) continue;
-      const bool sym = ((s.e[q] ^ s.tag[q]) & 1u) == 0;
-      const uint32_t b = sym ? p[q] - 1u : n[q] - 1u;
-      const uint32_t u = sym ? n[q] : p[q];
-      const uint32_t j = (s.tag[q] >> 1) & 63u;
-      slot_add(j, b, u);
-      edge(j, s.pos[q], b, u);
-    }
-  }
   // a chunk slot (every lane in the chunk's run): summed in registers until
   // the run changes (a wave-uniform test)
   __device__ __forceinline__ void add_chunk(uint32_t e, uint32_t tag, bool valid, uint32_t pos) {
@@ -177,21 +157,19 @@ struct Credit {
   }
 };
 
-template <bool kEdge, bool kHoist = false, bool kPack = false, class Look, class Acc>
-__device__ __forceinline__ Credit<Look, kEdge, Acc, kHoist, kPack> credit(Look l, Acc* cb, Acc* cu,
-                                                                          const DevSideConst& sc, const RunEnds& re) {
+template <bool kEdge, bool kPack = false, class Look, class Acc>
+__device__ __forceinline__ Credit<Look, kEdge, Acc, kPack> credit(Look l, Acc* cb, Acc* cu, const DevSideConst& sc,
+                                                                  const RunEnds& re) {
   static_assert(!kPack || sizeof(Acc) == 8, "packed slots are 64-bit");
-  Credit<Look, kEdge, Acc, kHoist, kPack> c{l, cb, cu, as_global(sc.epack_o), as_global(sc.ewb_o),
-                                            as_global(sc.ewu_o)};
+  Credit<Look, kEdge, Acc, kPack> c{l, cb, cu, as_global(sc.epack_o), as_global(sc.ewb_o), as_global(sc.ewu_o)};
   if (kEdge) c.wide = __ballot(re.wide != 0);
   return c;
 }
 
 // A run's credits b and u to its mid (and, with kEdge, to its first edge).
 template <bool kEdge>
-__device__ __forceinline__ void mid_credits_out(unsigned long long b, unsigned long long u, RunEnds re,
+__device__ __forceinline__ void mid_credits_out(unsigned long long b, unsigned long long u, RunEnds re, int32_t id,
                                                 const DevSideConst& sc) {
-  const int32_t id = sc.orig_mid[re.mid];
   if (b) atomicAdd(&sc.bal_mid[id], b);
   if (u) atomicAdd(&sc.unb_mid[id], u);
   if (kEdge) {
@@ -214,7 +192,7 @@ __device__ __forceinline__ void flush_mid_credits(Acc* cb, Acc* cu, RunEnds re, 
   if (b | u) {
     cb[lane] = 0;
     cu[lane] = 0;
-    mid_credits_out<kEdge>(b, u, re, sc);
+    mid_credits_out<kEdge>(b, u, re, sc.orig_mid[re.mid], sc);
   }
   wave_sync_lds();
 }
@@ -228,7 +206,7 @@ __device__ __forceinline__ void flush_mid_credits_packed(unsigned long long* cbu
   const unsigned long long v = cbu[lane];
   if (v) {
     cbu[lane] = 0;
-    mid_credits_out<kEdge>(v & 0xffffffffull, v >> 32, re, sc);
+    mid_credits_out<kEdge>(v & 0xffffffffull, v >> 32, re, sc.orig_mid[re.mid], sc);
   }
   wave_sync_lds();
 }
@@ -417,7 +395,7 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
       if (packed && hubT == 0) {
         // p, n < 2^16 and at most kPVWindowPacked keys per window: a run's
         // credits per window stay below 2^31, so one packed LDS word per run
-        auto c = credit<kEdge, false, true>(
+        auto c = credit<kEdge, true>(
             [&](uint32_t e, uint32_t, uint32_t& p, uint32_t& n) {
               const uint32_t key = e >> 1;
               if (key < lo || key >= hi) return false;
@@ -531,9 +509,100 @@ __global__ void k_pv_key_flush(const DevSideConst* sides, int32_t s, int32_t n) 
 // workgroup at the end (a launch holds the items of one side).  A pair's
 // credit is below 2^15 (p + n <= 255), so the workgroup's 32-bit key sums
 // hold up to 2^16 items (the launch sizes its grid for that).
+// Bound by instruction issue at the 12 wavefronts per CU that the LDS holds
+// (VALU busy half of the time) and by an item's chain of dependent loads.  So the
+// next item's descriptor, first runs and mids are loaded under the current item
+// and serve both walks; the tally's first staging rounds stay in registers for
+// the credit walk; that walk takes a wedge's shares out of a counter word with
+// one byte permutation; and the item's totals are half its runs' credits.
+// 50M edges, both sides: 22.4 -> 15.6 ms (the loads 18.6, the credit walk 16.5,
+// the sweep's test of whole words 15.6); 2M edges, per-edge: 0.53 -> 0.41 ms.
 constexpr int kPVReverseWaves = 12;
 constexpr int kPVReverseThreads = kPVReverseWaves * kWave;
 constexpr int kPVReverseWords = kMaxReverseL / 2;
+// staging rounds whose entries stay in registers from the tally to the credits
+// (50M edges, per-vertex, side U: 10.9 ms with none, 10.5 with 1 or 2, 10.6 with 3,
+// 11.0 with 4, which spill; per-edge 20M: 6.69, 6.62, 7.02 ms with 0, 1, 2)
+constexpr int pv_reverse_kept(bool edge) { return edge ? 1 : 2; }
+
+// Credit walk of a reverse batch.  A wedge's shares are one byte permutation of
+// its key's counter word: byte p | n << 8 of the key's half, as own sign's count
+// | other's << 16; less 1 (its own wedge), that is its balanced | unbalanced << 16.
+// A chunk's four counter words are read before any is used, and its run's sum
+// stays in one register per lane (at most 16 chunks of 4 shares of at most 255)
+// until the run ends; then the run's lane takes the wavefront's sum.  Staged
+// shares that are not zero go to their run's LDS slot.
+template <bool kEdge>
+struct ReverseCredit {
+  static constexpr bool kStaged = true, kChunk4 = true;
+  uint32_t base;             // LDS address of the counter words, aligned to their size
+  unsigned long long* cbu;   // per run lane: balanced | unbalanced << 32
+  global_t<unsigned long long>* ep;  // per-edge credits, as in Credit
+  global_t<unsigned long long>* wb;
+  global_t<unsigned long long>* wu;
+  uint64_t wide = 0;
+  uint32_t cur = kNoRun, sum = 0;  // the chunks' run (wavefront-uniform), and its shares so far
+  uint32_t mb = 0, mu = 0;         // this lane's run: the chunks' credits
+  static constexpr uint32_t kNoRun = 0xffffffffu;
+  static_assert(kMaxReverseL / kChunk * 4 * 255 < 65536, "a run's chunk shares fit 16 bits per lane");
+  __device__ __forceinline__ uint32_t word(uint32_t e) const {
+    return *(const lds_u32*)static_cast<uintptr_t>(base | (e & (4 * kPVReverseWords - 4)));
+  }
+  // own sign's count | other sign's << 16
+  static __device__ __forceinline__ uint32_t counts(uint32_t w, uint32_t e, uint32_t g) {
+    const uint32_t t = (e ^ g) & 3u;  // g is 0 or 1: key parity, asymmetric
+    return __builtin_amdgcn_perm(w, w, 0x0c010c00u ^ (t | (t << 16)));
+  }
+  __device__ __forceinline__ void edge(uint32_t j, uint32_t pos, uint32_t s) const {
+    if (!kEdge || s == 0) return;
+    const uint32_t b = s & 0xffffu, u = s >> 16;
+    if ((wide >> j) & 1u) {
+      if (b) add_global(wb + pos, b);
+      if (u) add_global(wu + pos, u);
+    } else {
+      add_global(ep + pos, (static_cast<unsigned long long>(u) << 32) | b);
+    }
+  }
+  __device__ __forceinline__ void put() {
+    if (cur == kNoRun) return;
+    const uint32_t b = wave_sum32(sum & 0xffffu), u = wave_sum32(sum >> 16);
+    sum = 0;
+    const bool own = static_cast<uint32_t>(lane_id()) == cur;
+    mb += own ? b : 0u;
+    mu += own ? u : 0u;
+  }
+  __device__ __forceinline__ void add_chunk4(const uint32_t (&e)[4], uint32_t tag, uint32_t rem,
+                                             const uint32_t (&off)[4], uint32_t pos) {
+    const uint32_t j = (tag >> 1) & 63u, g = tag & 1u;
+    if (j != cur) {
+      put();
+      cur = j;
+    }
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = word(e[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t c = off[q] < rem ? counts(w[q], e[q], g) : 1u;
+      sum += c - 1u;
+      edge(j, pos + off[q], c - 1u);
+    }
+  }
+  __device__ __forceinline__ void add_staged(const Staged& s) {
+    uint32_t w[kStageU];
+#pragma unroll
+    for (int q = 0; q < kStageU; ++q) w[q] = word(s.valid[q] ? s.e[q] : 0u);
+#pragma unroll
+    for (int q = 0; q < kStageU; ++q) {
+      const uint32_t c = counts(w[q], s.e[q], s.tag[q] & 1u) - 1u;
+      if (s.valid[q] && c != 0) {
+        const uint32_t j = (s.tag[q] >> 1) & 63u;
+        atomicAdd(&cbu[j], (static_cast<unsigned long long>(c >> 16) << 32) | (c & 0xffffu));
+        edge(j, s.pos[q], c);
+      }
+    }
+  }
+};
 
 template <bool kEdge>
 __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
@@ -544,15 +613,15 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
   __shared__ uint32_t dummies[kPVReverseWaves][kWave];
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVReverseWaves][kGather];
   __shared__ uint8_t mflag[kPVReverseWaves][kGather];
-  // a run's mid credits, balanced | unbalanced << 32: each at most the
-  // run's length (< 4096) times 255
+  // a run's mid credits of staged wedges, balanced | unbalanced << 32: each at
+  // most the run's length (at most 4096) times 255
   __shared__ unsigned long long cbu[kPVReverseWaves][kWave];
   // the workgroup's key credits, balanced | unbalanced << 32 (each half
   // below 2^31, see above)
   __shared__ unsigned long long ksum[kMaxReverseL];
-  // chunk slots in flight per walk: 8 where the registers allow (the
-  // per-edge walks keep 4)
-  constexpr int kU = kEdge ? 4 : 8;
+  // chunk slots in flight per walk: as many as the registers allow (the
+  // per-edge walks keep positions too)
+  constexpr int kU = kEdge ? 4 : 6;
   // wave index, known to the compiler as wavefront-uniform
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = lane_id();
@@ -564,78 +633,129 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
   cbu[wave][lane] = 0;
   wave_sync_lds();
   const Marks<uint8_t> mk{mtab[wave], mflag[wave]};
-  SqTotals tot;  // the pass's global counts, from 32-bit per-item sums
+  int64_t tot_b = 0, tot_u = 0;  // the pass's global counts (wavefront-uniform)
   uint32_t graph = kNoGraph;
-  const int32_t stride = static_cast<int32_t>(gridDim.x) * kPVReverseWaves;
-  for (int32_t i = static_cast<int32_t>(blockIdx.x) * kPVReverseWaves + wave; i < a.n_items; i += stride) {
-    const Item it = load_const(a.items, i);
+  const int32_t n = a.n_items, stride = static_cast<int32_t>(gridDim.x) * kPVReverseWaves;
+  int32_t i = static_cast<int32_t>(blockIdx.x) * kPVReverseWaves + wave;
+  // The next item's descriptor and first 64 runs are loaded under the current
+  // item; both walks of an item's first runs share one load.
+  const auto first_runs = [&](const Item& t, const DevSideConst& sc, RunEnds& re) {
+    const uint32_t e = t.seg_begin + t.seg_count;
+    return load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, t.seg_begin,
+                                     t.seg_begin + kWave < e ? t.seg_begin + kWave : e, re);
+  };
+  Item nxt{};
+  SegReg nseg{0, 0, 0};
+  RunEnds nre;
+  Item cur{};
+  if (i < n) {
+    cur = load_const(a.items, i);
+    nseg = first_runs(cur, load_const(a.sides, 2 * cur.graph + cur.side), nre);
+  }
+  if (i + stride < n) nxt = load_const(a.items, i + stride);
+  for (; i < n; i += stride) {
+    const Item it = cur;
     if (it.graph != graph) {
-      if (graph != kNoGraph) tot.flush(a.res + static_cast<size_t>(graph) * kResStride);
-      tot = SqTotals{};
+      if (graph != kNoGraph && lane == 0) {
+        unsigned long long* res = a.res + static_cast<size_t>(graph) * kResStride;
+        if (tot_b) atomicAdd(res + kResBalanced, static_cast<unsigned long long>(tot_b));
+        if (tot_u) atomicAdd(res + kResUnbalanced, static_cast<unsigned long long>(tot_u));
+      }
+      tot_b = tot_u = 0;
       graph = it.graph;
     }
     const DevSideConst sc = load_const(a.sides, 2 * it.graph + it.side);
+    SegReg sr = nseg;
+    RunEnds re = nre;
+    // where the item's credits go, known before they are
+    const int32_t owner_id = *(const const_t<int32_t>*)(sc.orig + it.owner);
+    int32_t mid_id = as_global(sc.orig_mid)[re.mid];
+    if (i + stride < n) nseg = first_runs(nxt, load_const(a.sides, 2 * nxt.graph + nxt.side), nre);
+    cur = nxt;
+    if (i + 2 * stride < n) nxt = load_const(a.items, i + 2 * stride);
     const uint32_t seg_end = it.seg_begin + it.seg_count;
-    for (uint32_t k0 = it.seg_begin; k0 < seg_end; k0 += kWave) {
-      const uint32_t k1 = k0 + kWave < seg_end ? k0 + kWave : seg_end;
-      RunEnds re;
-      walk_regs<kU, false, true>(load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, k0, k1, re), sc.other_adj,
-                                mk, a.long_len, PairTallyBF<kPVReverseWords>{lds_addr(C), lds_addr(&dummies[wave][lane])});
+    const auto load_runs = [&](uint32_t k) {
+      sr = load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, k, k + kWave < seg_end ? k + kWave : seg_end, re);
+      mid_id = as_global(sc.orig_mid)[re.mid];
+    };
+    // tally
+    KeptRounds<pv_reverse_kept(kEdge), kEdge> kept;
+    uint32_t k0 = it.seg_begin;
+    for (;;) {
+      walk_regs<kU, false, true>(sr, sc.other_adj, mk, a.long_len,
+                                 PairTallyBF<kPVReverseWords>{lds_addr(C), lds_addr(&dummies[wave][lane])}, kept);
+      if (k0 + kWave >= seg_end) break;
+      k0 += kWave;
+      load_runs(k0);
     }
     wave_sync_lds();
-    for (uint32_t k0 = it.seg_begin; k0 < seg_end; k0 += kWave) {
-      const uint32_t k1 = k0 + kWave < seg_end ? k0 + kWave : seg_end;
-      RunEnds re;
-      const SegReg sr = load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, k0, k1, re);
-      auto c = credit<kEdge, true, true>(
-          [&](uint32_t e, uint32_t, uint32_t& p, uint32_t& n) {
-            const uint32_t key = e >> 1;  // (masked: the hoisted reads also take masked slots)
-            const uint32_t h = C[(key >> 1) & (kPVReverseWords - 1)] >> ((key & 1u) << 4);
-            p = h & 0xffu;
-            n = (h >> 8) & 0xffu;
-            return true;
-          },
-          cbu[wave], static_cast<unsigned long long*>(nullptr), sc, re);
-      walk_regs<kU, kEdge>(sr, sc.other_adj, mk, a.long_len, c);
-      c.flush();
-      flush_mid_credits_packed<kEdge>(cbu[wave], re, sc);
+    // credits, the last batch first: its runs are at hand, and its first
+    // staging rounds are kept
+    uint32_t cb = 0, cu = 0;  // the credits of this lane's runs
+    for (bool replay = true;; replay = false) {
+      ReverseCredit<kEdge> c{lds_addr(C), cbu[wave], as_global(sc.epack_o), as_global(sc.ewb_o), as_global(sc.ewu_o)};
+      if (kEdge) c.wide = __ballot(re.wide != 0);
+      walk_regs<kU, kEdge, false, true>(sr, sc.other_adj, mk, a.long_len, c, kept, replay);
+      c.put();
+      wave_sync_lds();
+      const unsigned long long v = cbu[wave][lane];
+      cbu[wave][lane] = 0;
+      const uint32_t b = c.mb + static_cast<uint32_t>(v), u = c.mu + static_cast<uint32_t>(v >> 32);
+      if (b | u) mid_credits_out<kEdge>(b, u, re, mid_id, sc);
+      cb += b;
+      cu += u;
+      wave_sync_lds();
+      if (k0 == it.seg_begin) break;
+      k0 -= kWave;
+      load_runs(k0);
     }
-    // the key credits: 16-byte reads of the counter words, quads of zero
-    // words skipped; a pair with one wedge adds nothing.  p, n <= 255, so a
-    // lane's sums over its keys of one item stay in 32 bits.
-    SqSums ss;
-    uint32_t oc = 0, ox = 0;  // owner sums
-    auto local = [&](uint32_t key, uint32_t p, uint32_t n) {
-      ss.add(p, n);
-      const uint32_t cb2 = (__umul24(p, p - 1u) + __umul24(n, n - 1u)) >> 1, cx = __umul24(p, n);
-      if (cb2 | cx) atomicAdd(&ksum[key], (static_cast<unsigned long long>(cx) << 32) | cb2);
-      oc += cb2;
-      ox += cx;
+    // The keys' credits, two 16-byte pieces of counter words per lane and step
+    // (words past the item's keys are zero).  A pair with one wedge adds nothing
+    // to its key: a word is looked at if one of its bytes is 2 or more, or both
+    // of a key's are 1.
+    auto local = [&](uint32_t key, uint32_t c) {  // c = p | n << 8
+      const uint32_t p = c & 0xffu, n = c >> 8;
+      const uint32_t cb2 = (__builtin_amdgcn_udot4(c, c, 0u, false) - p - n) >> 1, cx = __umul24(p, n);
+      atomicAdd(&ksum[key], (static_cast<unsigned long long>(cx) << 32) | cb2);
     };
-    const int32_t w_hi = (it.key_hi + 1) >> 1;
-    for (int32_t w0 = 4 * lane; w0 < w_hi; w0 += 4 * kWave) {
-      const uint4 c4 = *reinterpret_cast<const uint4*>(&C[w0]);
-      if ((c4.x | c4.y | c4.z | c4.w) == 0) continue;
-      *reinterpret_cast<uint4*>(&C[w0]) = make_uint4(0, 0, 0, 0);
-      const uint32_t cw[4] = {c4.x, c4.y, c4.z, c4.w};
+    const uint32_t w_hi = static_cast<uint32_t>(it.key_hi + 1) >> 1;
+    for (uint32_t w0 = 0; w0 < w_hi; w0 += 8 * kWave) {
+      uint32_t cw[8], hit[8];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t c2 = cw[q];
-        const uint32_t wd = static_cast<uint32_t>(w0 + q);
-        if (c2 & 0xffffu) local(2 * wd, c2 & 0xffu, (c2 >> 8) & 0xffu);
-        if (c2 >> 16) local(2 * wd + 1, (c2 >> 16) & 0xffu, c2 >> 24);
+      for (int h = 0; h < 2; ++h) {
+        uint4* at = reinterpret_cast<uint4*>(&C[w0 + static_cast<uint32_t>(4 * (h * kWave + lane))]);
+        const uint4 c4 = *at;
+        *at = make_uint4(0, 0, 0, 0);
+        cw[4 * h] = c4.x, cw[4 * h + 1] = c4.y, cw[4 * h + 2] = c4.z, cw[4 * h + 3] = c4.w;
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) hit[q] = (cw[q] & 0xfefefefeu) | (cw[q] & (cw[q] >> 8) & 0x00010001u);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if ((hit[4 * h] | hit[4 * h + 1] | hit[4 * h + 2] | hit[4 * h + 3]) == 0) continue;
+#pragma unroll
+        for (int q = 4 * h; q < 4 * h + 4; ++q) {
+          if (hit[q] == 0) continue;
+          const uint32_t key = 2 * (w0 + static_cast<uint32_t>(4 * (h * kWave + lane) + q - 4 * h));
+          local(key, cw[q] & 0xffffu);
+          local(key + 1, cw[q] >> 16);
+        }
       }
     }
-    tot.add(ss);
-    const int64_t oc2 = wave_sum64(oc), ox2 = wave_sum64(ox);
+    // The owner's credits, and the pass's totals: a butterfly of the item
+    // credits its two mids (p, n <= 255 and at most 255 runs of at most 4,096
+    // wedges: sums below 2^28).
+    const uint32_t item_b = wave_sum32(cb) / 2, item_u = wave_sum32(cu) / 2;
+    tot_b += item_b;
+    tot_u += item_u;
     if (lane == 0) {
-      if (oc2) atomicAdd(&sc.bal[sc.orig[it.owner]], static_cast<unsigned long long>(oc2));
-      if (ox2) atomicAdd(&sc.unb[sc.orig[it.owner]], static_cast<unsigned long long>(ox2));
+      if (item_b) add_global(as_global(sc.bal) + owner_id, item_b);
+      if (item_u) add_global(as_global(sc.unb) + owner_id, item_u);
     }
     wave_sync_lds();
   }
   __shared__ WaveSums wsum[kPVReverseWaves];
-  flush_block_end(tot, graph, wsum, kPVReverseWaves, a.res);
+  flush_block_end(tot_b, tot_u, graph, wsum, kPVReverseWaves, a.res);
   // the workgroup's key credits (all items of a launch are of one side)
   __syncthreads();
   if (a.n_items > 0) {
@@ -730,7 +850,7 @@ __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
       if (hubT == 0) {
         // a plain group has at most kSmallGroupWork wedges: a run's credits
         // stay below 2^18, so one packed LDS word per run
-        auto c = credit<kEdge, false, true>(
+        auto c = credit<kEdge, true>(
             [&](uint32_t e, uint32_t tag, uint32_t& p, uint32_t& n) {
               const uint32_t key = hkey(e, tag);
               uint32_t h = mix32(key) & mask;

@@ -197,6 +197,40 @@ __device__ __forceinline__ void stage_round(Staged& s, M mk, uint32_t excl, uint
   }
 }
 
+// The first kRounds staging rounds of a batch that is walked twice, kept in
+// registers between the walks: the second walk takes their entries from here
+// (no staging, no loads).  An entry and its run's tag share a word: entries
+// below 2^16 (keys below 2^15) and plain tags (run lane << 1 | g).  With kPos
+// the entries' positions are kept too.
+template <int kRounds_, bool kPos>
+struct KeptRounds {
+  static constexpr int kRounds = kRounds_;
+  uint32_t et[kRounds_ * kStageU];
+  uint32_t pos[kPos ? kRounds_ * kStageU : 1];
+  __device__ __forceinline__ void put(int r, const Staged& s) {
+#pragma unroll
+    for (int u = 0; u < kStageU; ++u) {
+      et[r * kStageU + u] = s.e[u] | (s.tag[u] << 16);
+      if (kPos) pos[r * kStageU + u] = s.pos[u];
+    }
+  }
+  __device__ __forceinline__ Staged get(int r, uint32_t total) const {
+    Staged s;
+#pragma unroll
+    for (int u = 0; u < kStageU; ++u) {
+      const int k = r * kStageU + u;
+      s.e[u] = et[k] & 0xffffu;
+      s.tag[u] = et[k] >> 16;
+      s.pos[u] = kPos ? pos[k] : 0u;
+      s.valid[u] = static_cast<uint32_t>(k * kWave + lane_id()) < total;
+    }
+    return s;
+  }
+};
+struct NoKept {
+  static constexpr int kRounds = 0;
+};
+
 // Count of set bits of m in the lanes below this one.
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
@@ -273,6 +307,13 @@ template <class F, class = void>
 struct HasStaged : std::false_type {};
 template <class F>
 struct HasStaged<F, std::enable_if_t<F::kStaged>> : std::true_type {};
+// ... and one that takes a chunk's four words per lane at once
+// (add_chunk4(entries, tag, entries left in the run, offsets in the chunk,
+// position of the chunk)), flagged by kChunk4.
+template <class F, class = void>
+struct HasChunk4 : std::false_type {};
+template <class F>
+struct HasChunk4<F, std::enable_if_t<F::kChunk4>> : std::true_type {};
 
 // Walk a batch of up to 64 runs (one per lane, in registers) with one
 // wavefront, calling f.add(entry, tag, valid[, pos]) once per wedge slot.
@@ -295,9 +336,16 @@ struct HasStaged<F, std::enable_if_t<F::kStaged>> : std::true_type {};
 // counting kernels with direct LDS counters use it; the hash-table and
 // per-vertex walks (bound by latency, or with functors whose code is large)
 // measured faster in the plain form.
-template <int U, bool kLaneMajor = false, bool kCompact = false, class M, class F>
+// A walk with kept rounds (Kept) fills them (kReplay false) or, where replay
+// holds (wavefront-uniform), takes its first staging rounds from them (kReplay,
+// plain form).
+template <int U, bool kLaneMajor = false, bool kCompact = false, bool kReplay = false, class M, class F,
+          class Kept = NoKept>
 __device__ __forceinline__ void walk_regs(SegReg sr, const uint32_t* __restrict__ adj, M marks,
-                                          uint32_t long_len, F&& f) {
+                                          uint32_t long_len, F&& f, Kept&& kept = Kept{}, bool replay = false) {
+  constexpr uint32_t kKept = std::remove_reference_t<Kept>::kRounds;
+  const uint32_t kept_end = kReplay && replay ? kKept * kGather : 0u;  // positions taken from the kept rounds
+  static_assert(!kReplay || !kCompact, "later rounds are staged from the middle of the batch");
   const int lane = lane_id();
   const uint32_t start = sr.start, tag = sr.tag, len = sr.len;
   // long_len >= 16, so a long run keeps at least 13 entries after its head
@@ -317,12 +365,12 @@ __device__ __forceinline__ void walk_regs(SegReg sr, const uint32_t* __restrict_
   bool staged = false;
   auto first_round = [&]() {
     staged = true;
-    if (!total) return;
+    if (total <= kept_end) return;
     if (kCompact) {
       fill_table(marks, slen, base, tag);
       stage_round_table(cur, marks, excl, slen, total, 0, carry, adj);
     } else {
-      stage_round(cur, marks, excl, slen, base, tag, total, 0, adj);
+      stage_round(cur, marks, excl, slen, base, tag, total, kept_end, adj);
     }
   };
   if (!kCompact) first_round();
@@ -374,7 +422,9 @@ __device__ __forceinline__ void walk_regs(SegReg sr, const uint32_t* __restrict_
     for (int u = 0; u < U; ++u) {
       if (u < nv) {
         const uint32_t e4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-        if (kCompact && vrem[u] >= kChunk) {  // the whole chunk lies in the run (uniform)
+        if constexpr (HasChunk4<std::remove_reference_t<F>>::value) {
+          f.add_chunk4(e4, vg[u], vrem[u], koff, vpos[u]);
+        } else if (kCompact && vrem[u] >= kChunk) {  // the whole chunk lies in the run (uniform)
 #pragma unroll
           for (int q = 0; q < 4; ++q) walk_add_chunk(f, e4[q], vg[u], true, vpos[u] + koff[q], 0);
         } else {
@@ -385,23 +435,46 @@ __device__ __forceinline__ void walk_regs(SegReg sr, const uint32_t* __restrict_
     }
   }
   if (!staged) first_round();
-  for (uint32_t done = 0; done < total; done += kGather) {
-    const bool more = done + kGather < total;
-    Staged nxt;
-    if (more) {
-      if (kCompact)
-        stage_round_table(nxt, marks, excl, slen, total, done + kGather, carry, adj);
-      else
-        stage_round(nxt, marks, excl, slen, base, tag, total, done + kGather, adj);
-    }
+  auto put_round = [&](const Staged& r, uint32_t done) {
     if constexpr (HasStaged<std::remove_reference_t<F>>::value) {
-      f.add_staged(cur);
+      f.add_staged(r);
     } else {
 #pragma unroll
       for (int u = 0; u < kStageU; ++u)
         if (!kCompact || done + static_cast<uint32_t>(u * kWave) < total)
-          walk_add(f, cur.e[u], cur.tag[u], cur.valid[u], cur.pos[u], 0);
+          walk_add(f, r.e[u], r.tag[u], r.valid[u], r.pos[u], 0);
     }
+  };
+  auto next_round = [&](Staged& r, uint32_t done) {
+    if (kCompact)
+      stage_round_table(r, marks, excl, slen, total, done, carry, adj);
+    else
+      stage_round(r, marks, excl, slen, base, tag, total, done, adj);
+  };
+  uint32_t done = kept_end;
+  if constexpr (kKept > 0) {
+#pragma unroll
+    for (uint32_t r = 0; r < kKept; ++r) {
+      if (r * kGather < (kReplay && !replay ? 0u : total)) {
+        if constexpr (kReplay) {
+          put_round(kept.get(r, total), r * kGather);
+        } else {
+          Staged nxt;
+          const bool more = (r + 1) * kGather < total;
+          if (more) next_round(nxt, (r + 1) * kGather);
+          kept.put(r, cur);
+          put_round(cur, r * kGather);
+          if (more) cur = nxt;
+        }
+      }
+    }
+    if (!kReplay) done = kKept * kGather;
+  }
+  for (; done < total; done += kGather) {
+    const bool more = done + kGather < total;
+    Staged nxt;
+    if (more) next_round(nxt, done + kGather);
+    put_round(cur, done);
     if (!more) break;
     cur = nxt;
   }
@@ -515,6 +588,13 @@ __device__ __forceinline__ unsigned long long* own_copy(unsigned long long* res,
 // items of a graph are contiguous in every list, and the running sums are
 // flushed to the graph's result slot when an item of another graph comes.
 constexpr uint32_t kNoGraph = 0xffffffffu;
+
+// Sum over the wavefront (below 2^32), known to the compiler as uniform.
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t x) {
+  uint32_t total;
+  wave_excl_scan(x, &total);
+  return total;
+}
 
 __device__ __forceinline__ int64_t wave_sum64(int64_t x) {
 #pragma unroll
