@@ -255,30 +255,119 @@ struct PairCredit {
 // form (a 64-entry table per wavefront), which leaves the LDS to the
 // counters.  Key credits are global atomics (the keys that many items
 // share, a side's top vertices, are the dense block's when it is on).
+// An item is two walks with dependent loads before each, and its wedges' credits
+// were 20 instructions and an LDS round trip each.  So the next item's
+// descriptor and first runs are loaded under the sweep and serve both walks; a
+// packed item's counters are indexed by key and its credits take four words at a
+// time (PackedCredit); and a hub pivot's completed pair counts are copied into
+// its counter words, where they fit 16 bits (a plane read per wedge before).
+// 50M edges, both sides: 15.6 -> 9.3 ms (without the key credits 7.8, without
+// the mids' 8.0, without the credit walk 5.2).
 constexpr int kPVDirectThreads = 1024;
 constexpr int kPVDirectWaves = kPVDirectThreads / kWave;
 
-// An item's wedges into C: packed 16|16-bit words by key, or P | N halves.
+// An item's wedges into C: packed 16|16-bit words by key (one window, every key
+// of the item below kPVWindowPacked; masked slots go to the lane's dummy word),
+// or P | N halves by the key's place in the window.  The wavefronts take the
+// item's runs interleaved, so that each gets a similar mix of long and short
+// ones; `first` is the wavefront's first batch.
 __device__ __forceinline__ void pv_direct_tally(const Item& it, const DevSideConst& sc, uint32_t long_len,
-                                                const Marks<uint8_t>& mk, uint32_t* C, bool packed) {
+                                                const Marks<uint8_t>& mk, SegReg first, uint32_t* C,
+                                                uint32_t* dummy, bool packed) {
   const uint32_t lo = static_cast<uint32_t>(it.key_lo), hi = static_cast<uint32_t>(it.key_hi);
   const uint32_t seg_end = it.seg_begin + it.seg_count;
   uint32_t* const P = C;
   uint32_t* const N = C + kPVWindow;
-  for (uint32_t k0 = it.seg_begin + threadIdx.x / kWave; k0 < seg_end; k0 += kPVDirectThreads) {
-    const SegReg sr = load_seg<false>(sc.segs, k0, seg_end, kPVDirectWaves);
+  for (uint32_t k0 = it.seg_begin + threadIdx.x / kWave; k0 < seg_end;) {
     if (packed)
-      walk_regs<4, false, true>(sr, sc.other_adj, mk, long_len, hash_tally([&](uint32_t e, uint32_t tag) {
-                                  const uint32_t key = e >> 1;
-                                  if (key >= lo && key < hi) atomicAdd(&C[key - lo], wedge_inc(e, tag));
-                                }));
+      walk_regs<8, false, true>(first, sc.other_adj, mk, long_len, DirectTallyBF<kPVWindowPacked>{C, dummy});
     else
-      walk_regs<4, false, true>(sr, sc.other_adj, mk, long_len, hash_tally([&](uint32_t e, uint32_t tag) {
+      walk_regs<4, false, true>(first, sc.other_adj, mk, long_len, hash_tally([&](uint32_t e, uint32_t tag) {
                                   const uint32_t key = e >> 1;
                                   if (key >= lo && key < hi) atomicAdd(((e ^ tag) & 1u) ? &N[key - lo] : &P[key - lo], 1u);
                                 }));
+    k0 += kPVDirectThreads;
+    if (k0 < seg_end) first = load_seg<false>(sc.segs, k0, seg_end, kPVDirectWaves);
   }
 }
+
+// Credit walk of a packed item's batch.  A wedge's shares are its key's counter
+// word, turned so that its own sign's count is the low half, less 1 (its own
+// wedge): balanced | unbalanced << 16.  A chunk's four words are read before any
+// is used, and its run's sums stay in registers until the run ends; then the
+// run's lane takes the wavefront's sums.  Staged shares that are not zero go to
+// their run's LDS slot.  (p, n < 2^16 and at most kPVWindowPacked keys: a run's
+// credits stay below 2^31.)
+template <bool kEdge>
+struct PackedCredit {
+  static constexpr bool kStaged = true, kChunk4 = true;
+  const uint32_t* C;
+  unsigned long long* cbu;           // per run lane: balanced | unbalanced << 32
+  global_t<unsigned long long>* ep;  // per-edge credits, as in Credit
+  global_t<unsigned long long>* wb;
+  global_t<unsigned long long>* wu;
+  uint64_t wide = 0;
+  uint32_t cur = kNoRun, sb = 0, su = 0, slots = 0;  // the chunks' run (wavefront-uniform), its sums and slots per lane
+  uint32_t mb = 0, mu = 0;                           // this lane's run: the chunks' credits
+  static constexpr uint32_t kNoRun = 0xffffffffu;
+  __device__ __forceinline__ uint32_t word(uint32_t e) const { return C[(e >> 1) & (kPVWindowPacked - 1)]; }
+  // own sign's count | other sign's << 16
+  static __device__ __forceinline__ uint32_t counts(uint32_t w, uint32_t e, uint32_t g) {
+    return __builtin_amdgcn_alignbit(w, w, ((e << 4) + (g << 4)) & 31u);
+  }
+  __device__ __forceinline__ void edge(uint32_t j, uint32_t pos, uint32_t s) const {
+    if (!kEdge || s == 0) return;
+    const uint32_t b = s & 0xffffu, u = s >> 16;
+    if ((wide >> j) & 1u) {
+      if (b) add_global(wb + pos, b);
+      if (u) add_global(wu + pos, u);
+    } else {
+      add_global(ep + pos, (static_cast<unsigned long long>(u) << 32) | b);
+    }
+  }
+  __device__ __forceinline__ void put() {
+    if (cur == kNoRun) return;
+    const uint32_t b = wave_sum32(sb - slots), u = wave_sum32(su);
+    sb = su = slots = 0;
+    const bool own = static_cast<uint32_t>(lane_id()) == cur;
+    mb += own ? b : 0u;
+    mu += own ? u : 0u;
+  }
+  __device__ __forceinline__ void add_chunk4(const uint32_t (&e)[4], uint32_t tag, uint32_t rem,
+                                             const uint32_t (&off)[4], uint32_t pos) {
+    const uint32_t j = (tag >> 1) & 63u, g = tag & 1u;
+    if (j != cur) {
+      put();
+      cur = j;
+    }
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = word(e[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t c = off[q] < rem ? counts(w[q], e[q], g) : 1u;
+      sb += c & 0xffffu;
+      su += c >> 16;
+      edge(j, pos + off[q], c - 1u);
+    }
+    slots += 4;
+  }
+  __device__ __forceinline__ void add_staged(const Staged& s) {
+    uint32_t w[kStageU];
+#pragma unroll
+    for (int q = 0; q < kStageU; ++q) w[q] = word(s.valid[q] ? s.e[q] : 0u);
+#pragma unroll
+    for (int q = 0; q < kStageU; ++q) {
+      if (!s.valid[q]) continue;
+      const uint32_t c = counts(w[q], s.e[q], s.tag[q] & 1u) - 1u;
+      if (c != 0) {
+        const uint32_t j = (s.tag[q] >> 1) & 63u;
+        atomicAdd(&cbu[j], (static_cast<unsigned long long>(c >> 16) << 32) | (c & 0xffffu));
+        edge(j, s.pos[q], c);
+      }
+    }
+  }
+};
 
 // Heavy items.  An item runs on one CU, so a pivot with more than a CU's
 // share of the wedges would outlast its launch (2M edges, per-edge pass:
@@ -294,8 +383,9 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_heavy_tally(DirectArgs 
   __shared__ uint32_t C[kPVWindowPacked];
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVDirectWaves][2 * kWave];
   __shared__ uint8_t mflag[kPVDirectWaves][kGather];
+  __shared__ uint32_t dummies[kPVDirectThreads];
   const int tid = threadIdx.x;
-  const int wave = tid / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   for (int i = tid; i < kPVWindowPacked; i += kPVDirectThreads) C[i] = 0;
   for (int i = tid; i < kPVDirectWaves * static_cast<int>(kGather); i += kPVDirectThreads) (&mflag[0][0])[i] = 0;
   __syncthreads();
@@ -303,13 +393,17 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_heavy_tally(DirectArgs 
     const Item it = load_const(a.items, i);
     const DevSideConst sc = load_const(a.sides, 2 * it.graph + it.side);
     const bool packed = (it.flags & kItemPacked) != 0;
-    pv_direct_tally(it, sc, a.long_len, Marks<uint8_t>{mtab[wave], mflag[wave]}, C, packed);
+    pv_direct_tally(it, sc, a.long_len, Marks<uint8_t>{mtab[wave], mflag[wave]},
+                    load_seg<false>(sc.segs, it.seg_begin + wave, it.seg_begin + it.seg_count, kPVDirectWaves), C,
+                    &dummies[tid], packed);
     __syncthreads();
     global_t<uint32_t>* to = as_global(sc.acc) + static_cast<size_t>(it.acc_slot) * sc.acc_width;
-    const uint32_t keys = static_cast<uint32_t>(it.key_hi - it.key_lo);
+    // packed: words by key; unpacked: by the key's place in the window
+    const uint32_t lo = packed ? static_cast<uint32_t>(it.key_lo) : 0u;
+    const uint32_t keys = static_cast<uint32_t>(packed ? it.key_hi : it.key_hi - it.key_lo);
     for (int h = 0; h < (packed ? 1 : 2); ++h) {
       uint32_t* const from = C + h * kPVWindow;
-      for (uint32_t k = tid; k < keys; k += kPVDirectThreads) {
+      for (uint32_t k = lo + tid; k < keys; k += kPVDirectThreads) {
         const uint32_t v = from[k];
         if (v) {
           from[k] = 0;
@@ -327,46 +421,59 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
   __shared__ uint32_t C[kPVWindowPacked];  // P | N, or packed words
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVDirectWaves][2 * kWave];
   __shared__ uint8_t mflag[kPVDirectWaves][kGather];
+  // cu: unpacked items' unbalanced slots; a packed item's tally takes them for
+  // dummy words
   __shared__ unsigned long long cb[kPVDirectWaves][kWave], cu[kPVDirectWaves][kWave];
   __shared__ int32_t item_sh;
   static_assert(2 * kPVWindow == kPVWindowPacked, "P | N halves fill the packed window");
   const int tid = threadIdx.x;
-  const int wave = tid / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = lane_id();
   for (int i = tid; i < kPVWindowPacked; i += kPVDirectThreads) C[i] = 0;
   uint32_t* const P = C;
   uint32_t* const N = C + kPVWindow;
   for (int i = tid; i < kPVDirectWaves * static_cast<int>(kGather); i += kPVDirectThreads) (&mflag[0][0])[i] = 0;
   cb[wave][lane] = 0;
-  cu[wave][lane] = 0;
   const Marks<uint8_t> mk{mtab[wave], mflag[wave]};
-  Sums sums;                              // unpacked items' pairs
-  uint64_t sq64 = 0, pn64 = 0, w64 = 0;   // packed items' pairs: sums of p^2 + n^2, p n, p + n
-  auto flush_all = [&](uint32_t g) {
-    unsigned long long* res = a.res + static_cast<size_t>(g) * kResStride;
-    flush_sums(sums, res);
-    const int64_t q = wave_sum64(static_cast<int64_t>(sq64)), x = wave_sum64(static_cast<int64_t>(pn64));
-    const int64_t ww = wave_sum64(static_cast<int64_t>(w64));
-    if (lane == 0) {
-      const int64_t bal = (q - ww) / 2;
-      if (bal) atomicAdd(res + kResBalanced, static_cast<unsigned long long>(bal));
-      if (x) atomicAdd(res + kResUnbalanced, static_cast<unsigned long long>(x));
-    }
-    sums = Sums{};
-    sq64 = pn64 = w64 = 0;
-  };
+  int64_t tot_b = 0, tot_u = 0;  // this lane's pairs of the current graph
   uint32_t graph = kNoGraph;
-  for (;;) {
-    if (tid == 0) item_sh = static_cast<int32_t>(atomicAdd(a.queue, 1u));
-    __syncthreads();
-    const int32_t i = item_sh;
-    if (i >= a.n_items) break;
-    const Item it = load_const(a.items, i);
+  constexpr int kItemWords = sizeof(Item) / 4;
+  // the words of item i, one per lane
+  auto fetch = [&](int32_t i) {
+    return i < a.n_items && lane < kItemWords
+               ? as_global(reinterpret_cast<const uint32_t*>(a.items))[static_cast<size_t>(i) * kItemWords + lane]
+               : 0u;
+  };
+  auto unpack = [&](uint32_t w) {
+    Item it;
+    uint32_t* o = reinterpret_cast<uint32_t*>(&it);
+#pragma unroll
+    for (int k = 0; k < kItemWords; ++k) o[k] = readlane(w, k);
+    return it;
+  };
+  auto load_runs = [&](const Item& it, const DevSideConst& sc, uint32_t k0, RunEnds& re) {
+    return load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, k0, it.seg_begin + it.seg_count, re,
+                                     kPVDirectWaves);
+  };
+  if (tid == 0) item_sh = static_cast<int32_t>(atomicAdd(a.queue, 1u));
+  __syncthreads();
+  int32_t i = __builtin_amdgcn_readfirstlane(item_sh);
+  Item it{};
+  DevSideConst sc{};
+  RunEnds fre;
+  SegReg first{0, 0, 0};
+  if (i < a.n_items) {
+    it = unpack(fetch(i));
+    sc = load_const(a.sides, 2 * it.graph + it.side);
+    first = load_runs(it, sc, it.seg_begin + wave, fre);
+    graph = it.graph;
+  }
+  while (i < a.n_items) {
     if (it.graph != graph) {
-      if (graph != kNoGraph) flush_all(graph);
+      flush_sums(Sums{tot_b, tot_u}, a.res + static_cast<size_t>(graph) * kResStride);
+      tot_b = tot_u = 0;
       graph = it.graph;
     }
-    const DevSideConst sc = load_const(a.sides, 2 * it.graph + it.side);
     const uint32_t lo = static_cast<uint32_t>(it.key_lo), hi = static_cast<uint32_t>(it.key_hi);
     const uint32_t seg_end = it.seg_begin + it.seg_count;
     const bool packed = (it.flags & kItemPacked) != 0;
@@ -376,115 +483,136 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
     const bool part = (it.flags & kItemMultiPart) != 0;
     if (part) {
       // a part of a heavy item: the tally launch before this one left the
-      // item's whole counts in its accumulator
+      // item's whole counts in its accumulator (packed: by key, zeros below lo)
       const u32x4* from = reinterpret_cast<const u32x4*>(sc.acc + static_cast<size_t>(it.acc_slot) * sc.acc_width);
-      for (uint32_t k = 4 * tid; k < hi - lo; k += 4 * kPVDirectThreads) {
+      const uint32_t k_begin = packed ? lo & ~3u : 0u, k_end = packed ? hi : hi - lo;
+      for (uint32_t k = k_begin + 4 * tid; k < k_end; k += 4 * kPVDirectThreads) {
         *reinterpret_cast<u32x4*>(&C[k]) = *as_global(from + k / 4);
         if (!packed) *reinterpret_cast<u32x4*>(&N[k]) = *as_global(from + (pv_acc_half(hi - lo) + k) / 4);
       }
     } else {
-      // tally (the wavefronts take the item's segments interleaved, so that
-      // every wavefront gets a similar mix of long and short runs)
-      pv_direct_tally(it, sc, a.long_len, mk, C, packed);
+      pv_direct_tally(it, sc, a.long_len, mk, first, C, reinterpret_cast<uint32_t*>(&cu[wave][lane]), packed);
     }
     __syncthreads();
-    // credit the mids
-    for (uint32_t k0 = it.seg_begin + wave; k0 < seg_end; k0 += kPVDirectThreads) {
-      RunEnds re;
-      const SegReg sr = load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, k0, seg_end, re, kPVDirectWaves);
-      if (packed && hubT == 0) {
-        // p, n < 2^16 and at most kPVWindowPacked keys per window: a run's
-        // credits per window stay below 2^31, so one packed LDS word per run
-        auto c = credit<kEdge, true>(
-            [&](uint32_t e, uint32_t, uint32_t& p, uint32_t& n) {
-              const uint32_t key = e >> 1;
-              if (key < lo || key >= hi) return false;
-              const uint32_t v = C[key - lo];
-              p = v & 0xffffu;
-              n = v >> 16;
-              return true;
-            },
-            cb[wave], static_cast<unsigned long long*>(nullptr), sc, re);
-        walk_regs<4, kEdge, true>(sr, sc.other_adj, mk, a.long_len, c);
-        c.flush();
-        flush_mid_credits_packed<kEdge>(cb[wave], re, sc);
-        continue;
+    // the hub pairs' counts take their words, unless one has 2^16 wedges or more
+    bool fast = packed;
+    if (packed && hubT > lo) {
+      const size_t TT = static_cast<size_t>(sc.T) * sc.T;
+      const global_t<int32_t>* xy = as_global(sc.hub_xy) + static_cast<size_t>(it.owner) * sc.T;
+      int32_t big = 0;
+      for (uint32_t k = lo + tid; k < hubT; k += kPVDirectThreads) {
+        const int32_t X = xy[k], Y = xy[TT + k];
+        big |= X >> 16;
+        C[k] = static_cast<uint32_t>((X + Y) / 2) | (static_cast<uint32_t>((X - Y) / 2) << 16);
       }
-      auto c = credit<kEdge>(
-          [&](uint32_t e, uint32_t, uint32_t& p, uint32_t& n) {
-            const uint32_t key = e >> 1;
-            if (key < lo || key >= hi) return false;
-            if (key < hubT) {
-              hub_counts(sc, static_cast<uint32_t>(it.owner), key, p, n);
-              return true;
-            }
-            if (packed) {
-              const uint32_t v = C[key - lo];
-              p = v & 0xffffu;
-              n = v >> 16;
-            } else {
-              p = P[key - lo];
-              n = N[key - lo];
-            }
-            return true;
-          },
-          cb[wave], cu[wave], sc, re);
-      walk_regs<4, kEdge, true>(sr, sc.other_adj, mk, a.long_len, c);
-      c.flush();
-      flush_mid_credits<kEdge>(cb[wave], cu[wave], re, sc);
+      fast = __syncthreads_or(big) == 0;
     }
+    // credit the mids
+    uint32_t ticket = 0;
+    SegReg sr = first;
+    RunEnds re = fre;
+    if (!fast) cu[wave][lane] = 0;
+    for (uint32_t k0 = it.seg_begin + wave;;) {
+      const bool last = k0 >= seg_end || seg_end - k0 <= kPVDirectThreads;
+      if (last && tid == 0) ticket = atomicAdd(a.queue, 1u);
+      if (k0 < seg_end) {
+        if (fast) {
+          PackedCredit<kEdge> c{C, cb[wave], as_global(sc.epack_o), as_global(sc.ewb_o), as_global(sc.ewu_o)};
+          if (kEdge) c.wide = __ballot(re.wide != 0);
+          walk_regs<kEdge ? 4 : 8, kEdge, true>(sr, sc.other_adj, mk, a.long_len, c);
+          c.put();
+          wave_sync_lds();
+          const unsigned long long v = cb[wave][lane];
+          const uint32_t b = c.mb + static_cast<uint32_t>(v), u = c.mu + static_cast<uint32_t>(v >> 32);
+          if (b | u) {
+            cb[wave][lane] = 0;
+            mid_credits_out<kEdge>(b, u, re, sc.orig_mid[re.mid], sc);
+          }
+          wave_sync_lds();
+        } else {
+          auto c = credit<kEdge>(
+              [&](uint32_t e, uint32_t, uint32_t& p, uint32_t& n) {
+                const uint32_t key = e >> 1;
+                if (key < lo || key >= hi) return false;
+                if (key < hubT) {
+                  hub_counts(sc, static_cast<uint32_t>(it.owner), key, p, n);
+                  return true;
+                }
+                if (packed) {
+                  const uint32_t v = C[key];
+                  p = v & 0xffffu;
+                  n = v >> 16;
+                } else {
+                  p = P[key - lo];
+                  n = N[key - lo];
+                }
+                return true;
+              },
+              cb[wave], cu[wave], sc, re);
+          walk_regs<4, kEdge, true>(sr, sc.other_adj, mk, a.long_len, c);
+          c.flush();
+          flush_mid_credits<kEdge>(cb[wave], cu[wave], re, sc);
+        }
+      }
+      if (last) break;
+      k0 += kPVDirectThreads;
+      sr = load_runs(it, sc, k0, re);
+    }
+    if (tid == 0) item_sh = static_cast<int32_t>(ticket);
     __syncthreads();
+    i = __builtin_amdgcn_readfirstlane(item_sh);
+    const uint32_t next_words = fetch(i);
     // credit the keys and the owner (packed counts: p + n < 2^16, so a
     // key's credits fit 32 bits).  Key credits go to the rank-indexed sums
     // (the threads' keys are consecutive: one instruction's atomics touch a
     // few cache lines, where input-id order would scatter them over 64).
     // A part sweeps its slice of the keys, and clears them all.
     PairCredit pc;
-    uint32_t k_lo = 0, k_hi = hi - lo;
+    uint32_t k_lo = lo, k_hi = hi;
     if (part) {
       const uint32_t idx = it.work >> 16, n = it.work & 0xffffu, step = (hi - lo + n - 1) / n;
-      k_lo = min(hi - lo, idx * step);
-      k_hi = min(hi - lo, k_lo + step);
+      k_lo = min(hi, lo + idx * step);
+      k_hi = min(hi, k_lo + step);
     }
-    for (uint32_t k = tid; k < hi - lo; k += kPVDirectThreads) {
-      const uint32_t v = C[k];
-      const uint32_t p = packed ? v & 0xffffu : v, n = packed ? v >> 16 : N[k];
-      if (p | n) {
+    k_lo = max(k_lo, hubT);  // hub pairs are credited by the dense block
+    if (packed) {
+      for (uint32_t k = lo + tid; k < hi; k += kPVDirectThreads) {
+        const uint32_t v = C[k];
+        if (v == 0) continue;
         C[k] = 0;
-        if (!packed) N[k] = 0;
         if (k < k_lo || k >= k_hi) continue;
-        const uint32_t key = lo + k;
-        if (key < hubT) continue;  // a hub pair: credited by the dense block
-        if (packed) {
-          const uint32_t cb2 = (__umul24(p, p - 1u) + __umul24(n, n - 1u)) >> 1, cx = __umul24(p, n);
-          sq64 += static_cast<uint64_t>(__umul24(p, p)) + __umul24(n, n);
-          pn64 += cx;
-          w64 += p + n;
-          if (cb2) atomicAdd(&sc.key_bal[key], static_cast<unsigned long long>(cb2));
-          if (cx) atomicAdd(&sc.key_unb[key], static_cast<unsigned long long>(cx));
-          pc.c += cb2;
-          pc.x += cx;
-        } else {
-          sums.add(p, n);
-          const int64_t P64 = p, N64 = n;
-          const int64_t cb64 = P64 * (P64 - 1) / 2 + N64 * (N64 - 1) / 2, cx64 = P64 * N64;
-          if (cb64) atomicAdd(&sc.key_bal[key], static_cast<unsigned long long>(cb64));
-          if (cx64) atomicAdd(&sc.key_unb[key], static_cast<unsigned long long>(cx64));
-          pc.c += cb64;
-          pc.x += cx64;
-        }
+        const uint32_t p = v & 0xffffu, n = v >> 16;
+        const uint32_t cb2 = (mul24(p, p - 1u) + mul24(n, n - 1u)) >> 1, cx = mul24(p, n);
+        if (cb2) atomicAdd(&sc.key_bal[k], static_cast<unsigned long long>(cb2));
+        if (cx) atomicAdd(&sc.key_unb[k], static_cast<unsigned long long>(cx));
+        pc.c += cb2;
+        pc.x += cx;
+      }
+    } else {
+      for (uint32_t k = lo + tid; k < hi; k += kPVDirectThreads) {
+        const int64_t p = P[k - lo], n = N[k - lo];
+        if ((p | n) == 0) continue;
+        P[k - lo] = N[k - lo] = 0;
+        if (k < k_lo || k >= k_hi) continue;
+        const int64_t cb2 = p * (p - 1) / 2 + n * (n - 1) / 2, cx = p * n;
+        if (cb2) atomicAdd(&sc.key_bal[k], static_cast<unsigned long long>(cb2));
+        if (cx) atomicAdd(&sc.key_unb[k], static_cast<unsigned long long>(cx));
+        pc.c += cb2;
+        pc.x += cx;
       }
     }
+    tot_b += pc.c;
+    tot_u += pc.x;
     pc.to_owner(sc, it.owner);
+    if (i < a.n_items) {
+      it = unpack(next_words);
+      sc = load_const(a.sides, 2 * it.graph + it.side);
+      first = load_runs(it, sc, it.seg_begin + wave, fre);
+    }
     __syncthreads();
   }
-  {
-    const int64_t q = wave_sum64(static_cast<int64_t>(sq64)), x = wave_sum64(static_cast<int64_t>(pn64));
-    const int64_t ww = wave_sum64(static_cast<int64_t>(w64));
-    __shared__ WaveSums wsum[kPVDirectWaves];
-    flush_block_end(wave_sum64(sums.bal) + (q - ww) / 2, wave_sum64(sums.unb) + x, graph, wsum, kPVDirectWaves,
-                    a.res);
-  }
+  __shared__ WaveSums wsum[kPVDirectWaves];
+  flush_block_end(wave_sum64(tot_b), wave_sum64(tot_u), graph, wsum, kPVDirectWaves, a.res);
 }
 
 // The direct items' key credits of side s (by rank, ranks below n) into the
@@ -715,7 +843,7 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
     // of a key's are 1.
     auto local = [&](uint32_t key, uint32_t c) {  // c = p | n << 8
       const uint32_t p = c & 0xffu, n = c >> 8;
-      const uint32_t cb2 = (__builtin_amdgcn_udot4(c, c, 0u, false) - p - n) >> 1, cx = __umul24(p, n);
+      const uint32_t cb2 = (__builtin_amdgcn_udot4(c, c, 0u, false) - p - n) >> 1, cx = mul24(p, n);
       atomicAdd(&ksum[key], (static_cast<unsigned long long>(cx) << 32) | cb2);
     };
     const uint32_t w_hi = static_cast<uint32_t>(it.key_hi + 1) >> 1;

@@ -589,6 +589,10 @@ __device__ __forceinline__ unsigned long long* own_copy(unsigned long long* res,
 // flushed to the graph's result slot when an item of another graph comes.
 constexpr uint32_t kNoGraph = 0xffffffffu;
 
+// The low 32 bits of a 24-bit product (__umul24 is typed int: a product of 2^31
+// or more would widen, or shift, as a negative number).
+__device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return static_cast<uint32_t>(__umul24(a, b)); }
+
 // Sum over the wavefront (below 2^32), known to the compiler as uniform.
 __device__ __forceinline__ uint32_t wave_sum32(uint32_t x) {
   uint32_t total;
