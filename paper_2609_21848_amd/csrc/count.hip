@@ -148,8 +148,8 @@ __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a) {
                 sq2 += p + n;
               }
             } else {
-              sq2 += static_cast<int64_t>(__umul24(p, p)) + static_cast<int64_t>(__umul24(n, n));
-              pnx += __umul24(p, n);
+              sq2 += static_cast<int64_t>(mul24(p, p)) + static_cast<int64_t>(mul24(n, n));
+              pnx += mul24(p, n);
             }
           }
         } else if (acc32) {

@@ -16,6 +16,10 @@ namespace dev {
 
 constexpr int kWave = 64;
 
+// The low 32 bits of a 24-bit product (__umul24 is typed int: a product of 2^31
+// or more would widen, or shift, as a negative number).
+__device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return static_cast<uint32_t>(__umul24(a, b)); }
+
 // Address-space views.  Pointers read from device tables (the per-graph side
 // constants) are generic to the compiler, which would then emit flat
 // accesses; CSR runs, entries and accumulators are global memory, so they
@@ -589,10 +593,6 @@ __device__ __forceinline__ unsigned long long* own_copy(unsigned long long* res,
 // flushed to the graph's result slot when an item of another graph comes.
 constexpr uint32_t kNoGraph = 0xffffffffu;
 
-// The low 32 bits of a 24-bit product (__umul24 is typed int: a product of 2^31
-// or more would widen, or shift, as a negative number).
-__device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return static_cast<uint32_t>(__umul24(a, b)); }
-
 // Sum over the wavefront (below 2^32), known to the compiler as uniform.
 __device__ __forceinline__ uint32_t wave_sum32(uint32_t x) {
   uint32_t total;
@@ -643,9 +643,9 @@ __device__ __forceinline__ void emit(const Item& it, uint32_t key, uint32_t p, u
 struct SqSums {
   uint32_t sq = 0, pn = 0, w = 0;
   __device__ __forceinline__ void add(uint32_t p, uint32_t n) {
-    sq += __umul24(p, p);
-    sq += __umul24(n, n);
-    pn += __umul24(p, n);
+    sq += mul24(p, p);
+    sq += mul24(n, n);
+    pn += mul24(p, n);
     w += p + n;
   }
 };
