@@ -1065,10 +1065,13 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   }
   unsigned long long* ctl = g->ctl.as<unsigned long long>();
   HIP_TRY(dbbc::launch_fill_u64(ctl, kCtlWords, 0ull, st));
+  // The per-edge pass credits edges alone; its two-word credits are used where
+  // runs are flagged wide, or by the dense block.
+  const bool wide = d.any_wide || hp.T[0] > 0 || hp.T[1] > 0;
   for (int s = 0; s < 2; ++s) {
-    for (int k = 0; k < 2; ++k)
+    for (int k = 0; k < 2 && !edge; ++k)
       HIP_TRY(dbbc::launch_fill_u64(g->pv_out[s][k].as<unsigned long long>(), static_cast<size_t>(n[s]), 0ull, st));
-    for (int k = 0; k < 3 && edge; ++k)
+    for (int k = 0; k < (wide ? 3 : 1) && edge; ++k)
       HIP_TRY(dbbc::launch_fill_u64(g->pe_out[s][k].as<unsigned long long>(), m, 0ull, st));
   }
   unsigned long long* err = ctl + kCtlErr;
@@ -1105,9 +1108,10 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
       ha[s].res_mask = dbbc::kResCopies - 1;
       ha[s].T = hp.T[s];
       ha[s].K = d.hub_K[s];
+      ha[s].store = true;
       ha[s].orig = g->orig[s].as<int32_t>();
-      ha[s].bal = g->pv_out[s][0].as<unsigned long long>();
-      ha[s].unb = g->pv_out[s][1].as<unsigned long long>();
+      ha[s].bal = edge ? nullptr : g->pv_out[s][0].as<unsigned long long>();
+      ha[s].unb = edge ? nullptr : g->pv_out[s][1].as<unsigned long long>();
     }
     HIP_TRY(dbbc::launch_hub(ha, 2, st));
     for (int s = 0; s < 2; ++s) {
@@ -1126,7 +1130,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
         ca.E = pm ? d.hub_Bm[s].as<int8_t>() : d.hub_B[s].as<int8_t>();
         ca.Zc = pm ? d.hub_Zc[s].as<int32_t>() : d.hub_Zcp[s].as<int32_t>();
         ca.pos = edge ? d.hub_pos[s].as<int32_t>() : nullptr;
-        ca.orig_mid = pm ? g->orig[1 - s].as<int32_t>() : nullptr;
+        ca.orig_mid = pm && !edge ? g->orig[1 - s].as<int32_t>() : nullptr;
         ca.bal_mid = g->pv_out[1 - s][0].as<unsigned long long>();
         ca.unb_mid = g->pv_out[1 - s][1].as<unsigned long long>();
         ca.ewb = g->pe_out[s][1].as<unsigned long long>();
@@ -1146,7 +1150,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   }
   // direct items: one launch per side; their key credits are summed by rank
   // and added to the outputs after both launches
-  for (int s = 0; s < 2; ++s)
+  for (int s = 0; s < 2 && !edge; ++s)
     HIP_TRY(dbbc::launch_fill_u64(g->pv_keys[s].as<unsigned long long>(), 2 * static_cast<size_t>(dbbc::kPVKeyRanks),
                                   0ull, st));
   if (hp.n_heavy[0] + hp.n_heavy[1] > 0)
@@ -1175,7 +1179,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     const int grid = std::min<int>(cus, std::max(1, a.n_items));
     HIP_TRY(edge ? dbbc::launch_pe_direct(a, grid, st) : dbbc::launch_pv_direct(a, grid, st));
   }
-  for (int s = 0; s < 2; ++s) HIP_TRY(dbbc::launch_pv_key_flush(sides, s, hp.L[s], st));
+  for (int s = 0; s < 2 && !edge; ++s) HIP_TRY(dbbc::launch_pv_key_flush(sides, s, hp.L[s], st));
   // reverse items: one launch per side (their key credits are summed per
   // workgroup for one side's reverse window)
   for (int s = 0; s < 2; ++s) {
@@ -1230,8 +1234,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     a.rec = g->edge_rec.as<uint32_t>();
     a.pos_v = g->edge_pos_v.as<uint32_t>();
     a.m = g->host.m;
-    // runs flagged wide, or the dense block's credits (kept in the two-word form)
-    a.wide = d.any_wide || hp.T[0] > 0 || hp.T[1] > 0 ? 1 : 0;
+    a.wide = wide ? 1 : 0;
     a.off_u = g->off[0].as<uint32_t>();
     a.off_v = g->off[1].as<uint32_t>();
     a.adj_u = g->adj[0].as<uint32_t>();

@@ -196,10 +196,10 @@ __global__ __launch_bounds__(kHubThreads, 2) void k_hub(HubPair hp) {
         syy += static_cast<int64_t>(yv) * yv;
         sx += xv;
       }
-  if (a.bal) {
-    // per-vertex pass: store the completed counts (zeros where w is not
-    // below x) and credit each pair's C(P,2) + C(N,2) and P N to x (row
-    // sums) and w (column sums)
+  if (a.store) {
+    // per-vertex and per-edge passes: store the completed counts (zeros where
+    // w is not below x) and, per-vertex, credit each pair's C(P,2) + C(N,2) and
+    // P N to x (row sums) and w (column sums)
     int32_t* hx = a.hub_xy;
     int64_t cb[2] = {0, 0}, cu[2] = {0, 0};  // column sums per j
 #pragma unroll
@@ -215,12 +215,14 @@ __global__ __launch_bounds__(kHubThreads, 2) void k_hub(HubPair hp) {
           const int64_t xv = keep ? X[i][j][q] : 0, yv = keep ? Y[i][j][q] : 0;
           hx[static_cast<size_t>(x) * a.T + w] = static_cast<int32_t>(xv);
           hx[TT + static_cast<size_t>(x) * a.T + w] = static_cast<int32_t>(yv);
+          if (!a.bal) continue;
           const int64_t fb = (xv * xv + yv * yv - 2 * xv) / 4, fu = (xv * xv - yv * yv) / 4;
           rb += fb;
           ru += fu;
           cb[j] += fb;
           cu[j] += fu;
         }
+        if (!a.bal) continue;
 #pragma unroll
         for (int d = 16; d > 0; d >>= 1) {
           rb += __shfl_xor(rb, d, 64);
@@ -233,7 +235,7 @@ __global__ __launch_bounds__(kHubThreads, 2) void k_hub(HubPair hp) {
         }
       }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < 2 && a.bal; ++j) {
       int64_t b = cb[j], u = cu[j];
       b += __shfl_xor(b, 32, 64);
       u += __shfl_xor(u, 32, 64);

@@ -146,10 +146,11 @@ struct HubArgs {
   uint32_t res_mask = 0;
   int32_t T = 0;                 // rows (pairs side)
   int32_t K = 0;                 // padded contraction length (multiple of kHubKPad)
-  // per-vertex pass only (bal != null): the completed counts X = P + N and
-  // Y = P - N of every hub pair (x, w), w below x, are stored back into
-  // hub_xy (zeros at w not below x), and each pair's C(P,2) + C(N,2) and
-  // P N are credited to both its vertices; null in the count pass
+  // per-vertex and per-edge passes only (store): the completed counts
+  // X = P + N and Y = P - N of every hub pair (x, w), w below x, are stored
+  // back into hub_xy (zeros at w not below x); with bal (per-vertex) each
+  // pair's C(P,2) + C(N,2) and P N are credited to both its vertices
+  bool store = false;
   const int32_t* orig = nullptr;      // side rank -> input id
   unsigned long long* bal = nullptr;  // per-vertex outputs of the side (input id order)
   unsigned long long* unb = nullptr;

@@ -29,7 +29,9 @@
 // share (p - 1 and n, or n - 1 and p) is also the number of butterflies of
 // the pair that contain each of its two edges, since such a butterfly is the
 // union of this wedge and one other wedge of the pair.  The run's first edge
-// takes the run's summed share with the mid; the walked entry's edge takes
+// takes the run's summed share in the mid's place (the pass has no per-vertex
+// output: 2M edges 1.63 -> 1.16 ms, 20M 24.3 -> 19.6 ms without the vertices'
+// credits, their sums and the fills); the walked entry's edge takes
 // its wedge's share at its position in the other side's CSR, one 64-bit
 // atomic per wedge with both values packed (two for runs flagged kMidWide).
 // The credit walk then reads long runs lane-major, so that the atomics of a
@@ -166,24 +168,24 @@ __device__ __forceinline__ Credit<Look, kEdge, Acc, kPack> credit(Look l, Acc* c
   return c;
 }
 
-// A run's credits b and u to its mid (and, with kEdge, to its first edge).
-template <bool kEdge>
-__device__ __forceinline__ void mid_credits_out(unsigned long long b, unsigned long long u, RunEnds re, int32_t id,
+// A run's credits b and u: to its mid (id: its input id), or with kEdge to its
+// first edge (the per-edge pass has no per-vertex output).
+template <bool kEdge, class Id>
+__device__ __forceinline__ void run_credits_out(unsigned long long b, unsigned long long u, RunEnds re, Id id,
                                                 const DevSideConst& sc) {
-  if (b) atomicAdd(&sc.bal_mid[id], b);
-  if (u) atomicAdd(&sc.unb_mid[id], u);
-  if (kEdge) {
-    if (re.wide) {
-      if (b) add_global(as_global(sc.ewb) + re.edge, b);
-      if (u) add_global(as_global(sc.ewu) + re.edge, u);
-    } else {  // the run's credits are below 2^32 (no wide flag)
-      add_global(as_global(sc.epack) + re.edge, (u << 32) | b);
-    }
+  if constexpr (!kEdge) {
+    const int32_t mid = id();
+    if (b) atomicAdd(&sc.bal_mid[mid], b);
+    if (u) atomicAdd(&sc.unb_mid[mid], u);
+  } else if (re.wide) {
+    if (b) add_global(as_global(sc.ewb) + re.edge, b);
+    if (u) add_global(as_global(sc.ewu) + re.edge, u);
+  } else {  // the run's credits are below 2^32 (no wide flag)
+    add_global(as_global(sc.epack) + re.edge, (u << 32) | b);
   }
 }
 
-// After a batch's credit walk: each lane adds its run's credits to the mid
-// (and, with kEdge, to the run's first edge).
+// After a batch's credit walk: each lane puts its run's credits out.
 template <bool kEdge, class Acc>
 __device__ __forceinline__ void flush_mid_credits(Acc* cb, Acc* cu, RunEnds re, const DevSideConst& sc) {
   wave_sync_lds();
@@ -192,7 +194,7 @@ __device__ __forceinline__ void flush_mid_credits(Acc* cb, Acc* cu, RunEnds re, 
   if (b | u) {
     cb[lane] = 0;
     cu[lane] = 0;
-    mid_credits_out<kEdge>(b, u, re, sc.orig_mid[re.mid], sc);
+    run_credits_out<kEdge>(b, u, re, [&] { return sc.orig_mid[re.mid]; }, sc);
   }
   wave_sync_lds();
 }
@@ -206,7 +208,7 @@ __device__ __forceinline__ void flush_mid_credits_packed(unsigned long long* cbu
   const unsigned long long v = cbu[lane];
   if (v) {
     cbu[lane] = 0;
-    mid_credits_out<kEdge>(v & 0xffffffffull, v >> 32, re, sc.orig_mid[re.mid], sc);
+    run_credits_out<kEdge>(v & 0xffffffffull, v >> 32, re, [&] { return sc.orig_mid[re.mid]; }, sc);
   }
   wave_sync_lds();
 }
@@ -222,11 +224,14 @@ __device__ __forceinline__ void hub_counts(const DevSideConst& sc, uint32_t x, u
   n = static_cast<uint32_t>((X - Y) / 2);
 }
 
-// Key credits of one pair (p, n) at key vertex `key` of side s.
+// Key credits of one pair (p, n) at key vertex `key` of side s (with kEdge, the
+// global sums alone).
+template <bool kEdge>
 struct PairCredit {
   int64_t c = 0, x = 0;  // owner sums
   __device__ __forceinline__ void add(const DevSideConst& sc, uint32_t key, uint32_t p, uint32_t n, Sums& s) {
     s.add(p, n);
+    if (kEdge) return;
     const int64_t P = p, N = n;
     const int64_t cb = P * (P - 1) / 2 + N * (N - 1) / 2, cx = P * N;
     if (cb) atomicAdd(&sc.bal[sc.orig[key]], static_cast<unsigned long long>(cb));
@@ -236,6 +241,7 @@ struct PairCredit {
   }
   // The wavefront's owner sums to `owner` (one atomic per wavefront).
   __device__ __forceinline__ void to_owner(const DevSideConst& sc, int32_t owner) {
+    if (kEdge) return;
     const int64_t c2 = wave_sum64(c), x2 = wave_sum64(x);
     if (lane_id() == 0) {
       if (c2) atomicAdd(&sc.bal[sc.orig[owner]], static_cast<unsigned long long>(c2));
@@ -526,7 +532,7 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
           const uint32_t b = c.mb + static_cast<uint32_t>(v), u = c.mu + static_cast<uint32_t>(v >> 32);
           if (b | u) {
             cb[wave][lane] = 0;
-            mid_credits_out<kEdge>(b, u, re, sc.orig_mid[re.mid], sc);
+            run_credits_out<kEdge>(b, u, re, [&] { return sc.orig_mid[re.mid]; }, sc);
           }
           wave_sync_lds();
         } else {
@@ -567,7 +573,7 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
     // (the threads' keys are consecutive: one instruction's atomics touch a
     // few cache lines, where input-id order would scatter them over 64).
     // A part sweeps its slice of the keys, and clears them all.
-    PairCredit pc;
+    PairCredit<kEdge> pc;
     uint32_t k_lo = lo, k_hi = hi;
     if (part) {
       const uint32_t idx = it.work >> 16, n = it.work & 0xffffu, step = (hi - lo + n - 1) / n;
@@ -583,8 +589,8 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
         if (k < k_lo || k >= k_hi) continue;
         const uint32_t p = v & 0xffffu, n = v >> 16;
         const uint32_t cb2 = (mul24(p, p - 1u) + mul24(n, n - 1u)) >> 1, cx = mul24(p, n);
-        if (cb2) atomicAdd(&sc.key_bal[k], static_cast<unsigned long long>(cb2));
-        if (cx) atomicAdd(&sc.key_unb[k], static_cast<unsigned long long>(cx));
+        if (!kEdge && cb2) atomicAdd(&sc.key_bal[k], static_cast<unsigned long long>(cb2));
+        if (!kEdge && cx) atomicAdd(&sc.key_unb[k], static_cast<unsigned long long>(cx));
         pc.c += cb2;
         pc.x += cx;
       }
@@ -595,8 +601,8 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
         P[k - lo] = N[k - lo] = 0;
         if (k < k_lo || k >= k_hi) continue;
         const int64_t cb2 = p * (p - 1) / 2 + n * (n - 1) / 2, cx = p * n;
-        if (cb2) atomicAdd(&sc.key_bal[k], static_cast<unsigned long long>(cb2));
-        if (cx) atomicAdd(&sc.key_unb[k], static_cast<unsigned long long>(cx));
+        if (!kEdge && cb2) atomicAdd(&sc.key_bal[k], static_cast<unsigned long long>(cb2));
+        if (!kEdge && cx) atomicAdd(&sc.key_unb[k], static_cast<unsigned long long>(cx));
         pc.c += cb2;
         pc.x += cx;
       }
@@ -746,7 +752,7 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
   __shared__ unsigned long long cbu[kPVReverseWaves][kWave];
   // the workgroup's key credits, balanced | unbalanced << 32 (each half
   // below 2^31, see above)
-  __shared__ unsigned long long ksum[kMaxReverseL];
+  __shared__ unsigned long long ksum[kEdge ? 1 : kMaxReverseL];
   // chunk slots in flight per walk: as many as the registers allow (the
   // per-edge walks keep positions too)
   constexpr int kU = kEdge ? 4 : 6;
@@ -755,7 +761,7 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
   const int lane = lane_id();
   uint32_t* C = cnt[wave];
   if (lane == 0 && (lds_addr(C) & (kPVReverseWords * 4 - 1)) != 0) atomicOr(a.err, kErrLdsLayout);
-  for (int i = threadIdx.x; i < kMaxReverseL; i += kPVReverseThreads) ksum[i] = 0;
+  for (int i = threadIdx.x; i < (kEdge ? 1 : kMaxReverseL); i += kPVReverseThreads) ksum[i] = 0;
   for (int i = lane; i < kPVReverseWords; i += kWave) C[i] = 0;
   for (int i = lane; i < static_cast<int>(kGather); i += kWave) mflag[wave][i] = 0;
   cbu[wave][lane] = 0;
@@ -796,15 +802,15 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
     SegReg sr = nseg;
     RunEnds re = nre;
     // where the item's credits go, known before they are
-    const int32_t owner_id = *(const const_t<int32_t>*)(sc.orig + it.owner);
-    int32_t mid_id = as_global(sc.orig_mid)[re.mid];
+    const int32_t owner_id = kEdge ? 0 : *(const const_t<int32_t>*)(sc.orig + it.owner);
+    int32_t mid_id = kEdge ? 0 : as_global(sc.orig_mid)[re.mid];
     if (i + stride < n) nseg = first_runs(nxt, load_const(a.sides, 2 * nxt.graph + nxt.side), nre);
     cur = nxt;
     if (i + 2 * stride < n) nxt = load_const(a.items, i + 2 * stride);
     const uint32_t seg_end = it.seg_begin + it.seg_count;
     const auto load_runs = [&](uint32_t k) {
       sr = load_seg_pv<false, kEdge>(sc.segs, sc.seg_mid, sc.seg_edge, k, k + kWave < seg_end ? k + kWave : seg_end, re);
-      mid_id = as_global(sc.orig_mid)[re.mid];
+      if (!kEdge) mid_id = as_global(sc.orig_mid)[re.mid];
     };
     // tally
     KeptRounds<pv_reverse_kept(kEdge), kEdge> kept;
@@ -829,7 +835,7 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
       const unsigned long long v = cbu[wave][lane];
       cbu[wave][lane] = 0;
       const uint32_t b = c.mb + static_cast<uint32_t>(v), u = c.mu + static_cast<uint32_t>(v >> 32);
-      if (b | u) mid_credits_out<kEdge>(b, u, re, mid_id, sc);
+      if (b | u) run_credits_out<kEdge>(b, u, re, [&] { return mid_id; }, sc);
       cb += b;
       cu += u;
       wave_sync_lds();
@@ -854,8 +860,10 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
         uint4* at = reinterpret_cast<uint4*>(&C[w0 + static_cast<uint32_t>(4 * (h * kWave + lane))]);
         const uint4 c4 = *at;
         *at = make_uint4(0, 0, 0, 0);
+        if (kEdge) continue;  // no per-vertex output
         cw[4 * h] = c4.x, cw[4 * h + 1] = c4.y, cw[4 * h + 2] = c4.z, cw[4 * h + 3] = c4.w;
       }
+      if (kEdge) continue;
 #pragma unroll
       for (int q = 0; q < 8; ++q) hit[q] = (cw[q] & 0xfefefefeu) | (cw[q] & (cw[q] >> 8) & 0x00010001u);
 #pragma unroll
@@ -876,7 +884,7 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
     const uint32_t item_b = wave_sum32(cb) / 2, item_u = wave_sum32(cu) / 2;
     tot_b += item_b;
     tot_u += item_u;
-    if (lane == 0) {
+    if (!kEdge && lane == 0) {
       if (item_b) add_global(as_global(sc.bal) + owner_id, item_b);
       if (item_u) add_global(as_global(sc.unb) + owner_id, item_u);
     }
@@ -884,6 +892,7 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
   }
   __shared__ WaveSums wsum[kPVReverseWaves];
   flush_block_end(tot_b, tot_u, graph, wsum, kPVReverseWaves, a.res);
+  if (kEdge) return;
   // the workgroup's key credits (all items of a launch are of one side)
   __syncthreads();
   if (a.n_items > 0) {
@@ -1035,7 +1044,7 @@ __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
       K[h] = kEmpty;
       V[h] = 0;
       if ((key & kmask) < hubT) continue;  // a hub pair: credited by the dense block
-      PairCredit pc;
+      PairCredit<kEdge> pc;
       pc.add(sc, key & kmask, v & 0xffffu, v >> 16, sums);
       if (pc.c | pc.x) {  // a pair with one wedge credits nothing
         const int32_t id = sc.orig[sc.small_owner[it.acc_slot + static_cast<int32_t>(key >> kb)]];
@@ -1102,7 +1111,7 @@ __global__ __launch_bounds__(kPVHashThreads) void k_pv_hash(HashArgs a) {
     atomicAdd(&work_sh, w);
     __syncthreads();
     const uint32_t passes = (work_sh + kPVHashSlots / 4 - 1) / (kPVHashSlots / 4);
-    PairCredit pc;
+    PairCredit<kEdge> pc;
     for (uint32_t pass = 0; pass < passes; ++pass) {
       auto mine = [&](uint32_t key, uint32_t& hk) {
         hk = mix32(key);
