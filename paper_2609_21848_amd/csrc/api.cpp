@@ -195,9 +195,13 @@ struct Timing {
 // CU's LDS, so they cannot share CUs, and running them side by side on
 // several streams was measured slower than in sequence.
 int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
-  HIP_TRY(dbbc::launch_fill_u64(L.ctl, kCtlWords, 0ull, st));
-  if (L.res != L.ctl) HIP_TRY(dbbc::launch_fill_u64(L.res, L.n_res, 0ull, st));
-  for (const auto& z : L.zero) HIP_TRY(dbbc::launch_fill_u64(z.first, z.second, 0ull, st));
+  {
+    dbbc::Ranges z;
+    z.zero(L.ctl, kCtlWords);
+    if (L.res != L.ctl) z.zero(L.res, L.n_res);
+    for (const auto& h : L.zero) z.zero(h.first, h.second);
+    HIP_TRY(dbbc::launch_zero(z, st));
+  }
   unsigned long long* err = L.ctl + kCtlErr;
   uint32_t* queues = reinterpret_cast<uint32_t*>(L.ctl + kCtlQueues);
   const int cus = L.cus;
@@ -740,8 +744,9 @@ int enqueue_lone(dbbc_graph* g, const dbbc_options* opt, hipStream_t st) {
   rc = enqueue(L, st, tm);
   g->timers_used = tm.used;
   if (rc != DBBC_OK) return rc;
-  HIP_TRY(hipMemcpyAsync(g->pinned, g->ctl.p, kCtlWords * sizeof(unsigned long long),
-                         hipMemcpyDeviceToHost, st));
+  dbbc::Ranges out;
+  out.copy(g->pinned, g->ctl.p, kCtlWords);
+  HIP_TRY(dbbc::launch_copy(out, st));
   return DBBC_OK;
 }
 
@@ -1011,6 +1016,16 @@ namespace {
 static_assert(dbbc::kPVKeyRanks >= dbbc::kPVWindowPacked && dbbc::kPVWindowPacked == 32768,
               "key sums cover the widest window");
 
+// Whether p is memory of device dev at a whole word.
+bool kernel_writable(const void* p, int dev) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();  // memory HIP does not know
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == dev && (reinterpret_cast<uintptr_t>(p) & 7u) == 0;
+}
+
 // The per-vertex pass, with per-edge credits when edge is set: tally and
 // credit walks over every item of the per-vertex plan, then (per-edge) the
 // combination of the two CSRs' credits into input-record order.
@@ -1064,16 +1079,19 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     HIP_TRY(hipStreamSynchronize(st));
   }
   unsigned long long* ctl = g->ctl.as<unsigned long long>();
-  HIP_TRY(dbbc::launch_fill_u64(ctl, kCtlWords, 0ull, st));
+  dbbc::Ranges zero;
+  zero.zero(ctl, kCtlWords);
   // The per-edge pass credits edges alone; its two-word credits are used where
   // runs are flagged wide, or by the dense block.
   const bool wide = d.any_wide || hp.T[0] > 0 || hp.T[1] > 0;
   for (int s = 0; s < 2; ++s) {
-    for (int k = 0; k < 2 && !edge; ++k)
-      HIP_TRY(dbbc::launch_fill_u64(g->pv_out[s][k].as<unsigned long long>(), static_cast<size_t>(n[s]), 0ull, st));
-    for (int k = 0; k < (wide ? 3 : 1) && edge; ++k)
-      HIP_TRY(dbbc::launch_fill_u64(g->pe_out[s][k].as<unsigned long long>(), m, 0ull, st));
+    for (int k = 0; k < 2 && !edge; ++k) zero.zero(g->pv_out[s][k].p, static_cast<size_t>(n[s]));
+    if (!edge) zero.zero(g->pv_keys[s].p, 2 * static_cast<size_t>(dbbc::kPVKeyRanks));
+    for (int k = 0; k < (wide ? 3 : 1) && edge; ++k) zero.zero(g->pe_out[s][k].p, m);
+    if (hp.T[0] > 0) zero.zero(d.hub_pairs[s].p, static_cast<size_t>(hp.T[s]) * hp.T[s]);
   }
+  if (hp.n_heavy[0] + hp.n_heavy[1] > 0) zero.zero(d.acc.p, static_cast<size_t>(hp.acc_slots) * hp.acc_width / 2);
+  HIP_TRY(dbbc::launch_zero(zero, st));
   unsigned long long* err = ctl + kCtlErr;
   uint32_t* queues = reinterpret_cast<uint32_t*>(ctl + kCtlQueues);
   const dbbc::DevSideConst* sides = d.sides.as<dbbc::DevSideConst>();
@@ -1084,8 +1102,6 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     // wedges; the sparse kernels below read the completed counts.
     dbbc::HubTallyArgs ta[2];
     for (int s = 0; s < 2; ++s) {
-      HIP_TRY(dbbc::launch_fill_u64(d.hub_pairs[s].as<unsigned long long>(),
-                                    static_cast<size_t>(hp.T[s]) * hp.T[s], 0ull, st));
       const int32_t lo = s == 0 ? 0 : hp.n_hub_side0;
       const int32_t hi = s == 0 ? hp.n_hub_side0 : static_cast<int32_t>(d.hub_items.bytes / sizeof(dbbc::Item));
       ta[s] = dbbc::HubTallyArgs{};
@@ -1150,12 +1166,6 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   }
   // direct items: one launch per side; their key credits are summed by rank
   // and added to the outputs after both launches
-  for (int s = 0; s < 2 && !edge; ++s)
-    HIP_TRY(dbbc::launch_fill_u64(g->pv_keys[s].as<unsigned long long>(), 2 * static_cast<size_t>(dbbc::kPVKeyRanks),
-                                  0ull, st));
-  if (hp.n_heavy[0] + hp.n_heavy[1] > 0)
-    HIP_TRY(dbbc::launch_fill_u64(d.acc.as<unsigned long long>(),
-                                  static_cast<size_t>(hp.acc_slots) * hp.acc_width / 2, 0ull, st));
   for (int s = 0; s < 2; ++s) {  // the parts of heavy items (each side's first)
     dbbc::DirectArgs a{};
     a.items = d.direct_items.as<dbbc::Item>() + (s == 0 ? 0 : hp.n_direct_side0);
@@ -1256,12 +1266,20 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     const int grid = static_cast<int>(std::min<int64_t>(8 * cus, std::max<int64_t>(1, (a.m + 255) / 256)));
     HIP_TRY(dbbc::launch_edge_combine(a, grid, st));
   }
+  // the outputs in one launch with the results, where a kernel on this device
+  // can write them; elsewhere (another device's memory, host memory) by copies
+  dbbc::Ranges out;
   for (int s = 0; s < 2; ++s)
-    for (int k = 0; k < 2; ++k)
-      if (vout[s][k])
+    for (int k = 0; k < 2; ++k) {
+      if (!vout[s][k]) continue;
+      if (kernel_writable(vout[s][k], g->dev.id))
+        out.copy(vout[s][k], g->pv_out[s][k].p, static_cast<size_t>(n[s]));
+      else
         HIP_TRY(hipMemcpyAsync(vout[s][k], g->pv_out[s][k].p, static_cast<size_t>(n[s]) * sizeof(int64_t),
                                hipMemcpyDeviceToDevice, st));
-  HIP_TRY(hipMemcpyAsync(g->pinned, g->ctl.p, kCtlWords * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+    }
+  out.copy(g->pinned, ctl, kCtlWords);
+  HIP_TRY(dbbc::launch_copy(out, st));
   HIP_TRY(hipStreamSynchronize(st));
   dbbc_counts c{};
   rc = finish_lone(g, &c, false);
@@ -1372,7 +1390,9 @@ int dbbc_count_noalloc(dbbc_graph* g, const dbbc_options* opt, dbbc_counts* out_
   Timing tm{nullptr, 0, st};
   rc = enqueue(L, st, tm);
   if (rc != DBBC_OK) return rc;
-  HIP_TRY(hipMemcpyAsync(g->pinned, L.ctl, kCtlWords * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+  dbbc::Ranges out;
+  out.copy(g->pinned, L.ctl, kCtlWords);
+  HIP_TRY(dbbc::launch_copy(out, st));
   HIP_TRY(hipStreamSynchronize(st));
   return finish_lone(g, out_host, false);
 }
@@ -1560,10 +1580,10 @@ int dbbc_batch_launch(dbbc_batch* b, void* hip_stream) {
     int rc = enqueue(b->L, st, tm);
     if (rc != DBBC_OK) return rc;
   }
-  HIP_TRY(hipMemcpyAsync(b->pinned, b->res.p, k * dbbc::kResStride * sizeof(unsigned long long),
-                         hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(b->pinned + k * dbbc::kResStride, b->ctl.as<unsigned long long>() + kCtlErr,
-                         sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+  dbbc::Ranges out;
+  out.copy(b->pinned, b->res.p, k * dbbc::kResStride);
+  out.copy(b->pinned + k * dbbc::kResStride, b->ctl.as<unsigned long long>() + kCtlErr, 1);
+  HIP_TRY(dbbc::launch_copy(out, st));
   return DBBC_OK;
 }
 

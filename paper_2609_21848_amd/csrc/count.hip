@@ -660,6 +660,20 @@ __global__ void k_fill_u64(unsigned long long* p, size_t n, unsigned long long v
     p[i] = v;
 }
 
+struct RangeArgs {
+  Ranges::Range r[Ranges::kMax];
+  int n;
+};
+template <bool kCopy>
+__global__ void k_ranges(RangeArgs a) {
+  const size_t first = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
+  const size_t step = static_cast<size_t>(gridDim.x) * blockDim.x;
+  for (int k = 0; k < a.n; ++k) {
+    const Ranges::Range r = a.r[k];
+    for (size_t i = first; i < r.words; i += step) r.dst[i] = kCopy ? r.src[i] : 0ull;
+  }
+}
+
 // Store a graph's two side-table entries (passed by value) at dst.
 struct SidePair {
   DevSideConst s[2];
@@ -687,6 +701,29 @@ hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v
   hipLaunchKernelGGL(dev::k_fill_u64, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p, n, v);
   return hipGetLastError();
 }
+
+namespace {
+template <bool kCopy>
+hipError_t ranges_(const Ranges& ranges, hipStream_t st) {
+  for (size_t at = 0; at < ranges.r.size(); at += Ranges::kMax) {
+    dev::RangeArgs a{};
+    a.n = static_cast<int>(std::min<size_t>(Ranges::kMax, ranges.r.size() - at));
+    size_t longest = 0;
+    for (int k = 0; k < a.n; ++k) {
+      a.r[k] = ranges.r[at + k];
+      longest = std::max(longest, a.r[k].words);
+    }
+    const size_t blocks = std::min<size_t>((longest + 255) / 256, 4096);
+    hipLaunchKernelGGL(dev::k_ranges<kCopy>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+}  // namespace
+
+hipError_t launch_zero(const Ranges& r, hipStream_t st) { return ranges_<false>(r, st); }
+hipError_t launch_copy(const Ranges& r, hipStream_t st) { return ranges_<true>(r, st); }
 
 hipError_t launch_assemble_items(const AssembleSrc* srcs, int k, Item* dst, hipStream_t st) {
   if (k == 0) return hipSuccess;
