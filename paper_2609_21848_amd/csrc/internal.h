@@ -194,8 +194,7 @@ struct HostPlan {
   int32_t n_items_kept[5] = {0, 0, 0, 0, 0};
   uint64_t direct_max_work = 0;  // wedges of the heaviest direct item (or part)
   int32_t n_reverse_side0 = 0;  // reverse items are listed side 0 first
-  int32_t n_direct_side0 = 0;   // per-vertex plans: direct items side 0 first
-  int32_t n_heavy[2] = {0, 0};  // ... each side's first n_heavy items are parts
+  int32_t n_heavy = 0;          // per-vertex plans: the first n_heavy direct items are parts
   int32_t acc_slots = 0;
   int32_t acc_width = 0;           // max window over the sides
   // per sparse kernel (0 = direct, 1 = small, 2 = hash, 3 = reverse):

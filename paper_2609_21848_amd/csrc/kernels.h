@@ -255,10 +255,10 @@ hipError_t launch_hub_credit(const HubCreditArgs& a, hipStream_t st);
 hipError_t launch_pv_heavy_tally(const DirectArgs& a, int grid, hipStream_t st);
 hipError_t launch_pv_direct(const DirectArgs& a, int grid, hipStream_t st);
 // Largest rank a per-vertex direct item's key may have (the widest window),
-// and the adding of the rank-indexed key credits of side s (ranks below n)
-// into its per-vertex outputs.
+// and the adding of the rank-indexed key credits of both sides (ranks below n)
+// into their per-vertex outputs.
 constexpr int32_t kPVKeyRanks = 32768;
-hipError_t launch_pv_key_flush(const DevSideConst* sides, int32_t s, int32_t n, hipStream_t st);
+hipError_t launch_pv_key_flush(const DevSideConst* sides, int32_t n, hipStream_t st);
 hipError_t launch_pv_reverse(const SmallArgs& a, int grid, hipStream_t st);
 hipError_t launch_pv_small(const SmallArgs& a, int grid, hipStream_t st);
 hipError_t launch_pv_hash(const HashArgs& a, int grid, hipStream_t st);

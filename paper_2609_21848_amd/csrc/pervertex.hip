@@ -621,10 +621,10 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
   flush_block_end(wave_sum64(tot_b), wave_sum64(tot_u), graph, wsum, kPVDirectWaves, a.res);
 }
 
-// The direct items' key credits of side s (by rank, ranks below n) into the
-// per-vertex outputs (input-id order).
-__global__ void k_pv_key_flush(const DevSideConst* sides, int32_t s, int32_t n) {
-  const DevSideConst sc = load_const(sides, s);
+// The direct items' key credits of both sides (blockIdx.y; by rank, ranks below
+// n, zero past a side's window) into the per-vertex outputs (input-id order).
+__global__ void k_pv_key_flush(const DevSideConst* sides, int32_t n) {
+  const DevSideConst sc = load_const(sides, blockIdx.y);
   for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
     const unsigned long long b = sc.key_bal[k], u = sc.key_unb[k];
     if (b | u) {
@@ -1276,9 +1276,9 @@ hipError_t launch_pe_reverse(const SmallArgs& a, int grid, hipStream_t st) { ret
 hipError_t launch_pe_small(const SmallArgs& a, int grid, hipStream_t st) { return small_<true>(a, grid, st); }
 hipError_t launch_pe_hash(const HashArgs& a, int grid, hipStream_t st) { return hash_<true>(a, grid, st); }
 
-hipError_t launch_pv_key_flush(const DevSideConst* sides, int32_t s, int32_t n, hipStream_t st) {
+hipError_t launch_pv_key_flush(const DevSideConst* sides, int32_t n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(dev::k_pv_key_flush, dim3((n + 255) / 256), dim3(256), 0, st, sides, s, n);
+  hipLaunchKernelGGL(dev::k_pv_key_flush, dim3((n + 255) / 256, 2), dim3(256), 0, st, sides, n);
   return hipGetLastError();
 }
 

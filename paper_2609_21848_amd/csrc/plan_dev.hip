@@ -777,15 +777,14 @@ __device__ uint32_t dsat32(unsigned long long w) { return w > 0xffffffffull ? 0x
 constexpr uint32_t kNowhere = 0xffffffffu, kToSegs = 0x80000000u, kToHub = 0x80000001u;
 
 // The order of hash and direct items: heaviest first, by the work's exponent
-// and its nine bits after the leading one (a 16-bit key: two sort passes);
-// per-vertex plans list side 0's first.
-__device__ __forceinline__ uint32_t work_key(unsigned long long work, uint32_t side) {
+// and its nine bits after the leading one (a 16-bit key: two sort passes).
+__device__ __forceinline__ uint32_t work_key(unsigned long long work) {
   uint32_t f = 0;
   if (work) {
     const int e = 63 - __builtin_clzll(work);
     f = (static_cast<uint32_t>(e) << 9) | (static_cast<uint32_t>(e >= 9 ? work >> (e - 9) : work << (9 - e)) & 0x1ffu);
   }
-  return (side << 15) | (0x7fffu - f);
+  return 0x7fffu - f;
 }
 
 struct ItemOut {
@@ -847,7 +846,7 @@ __global__ __launch_bounds__(kThreads) void k_items(PSides S, const unsigned lon
       place = make_uint2(it.seg_begin, kToSegs);
       if (c.cls == kHashC) {
         o.hash[q[kHashItems]] = it;
-        o.hash_key[q[kHashItems]] = work_key(c.work, 0);
+        o.hash_key[q[kHashItems]] = work_key(c.work);
       } else if (c.cls == kDirectC) {
         if (c.split) P.part_pos[cand] = static_cast<uint32_t>(q[kDirectParts]);
         if (kNk == 4) {  // key windows that share the runs
@@ -864,7 +863,7 @@ __global__ __launch_bounds__(kThreads) void k_items(PSides S, const unsigned lon
               o.split_part[q[kDirectSplit] + w] = static_cast<uint32_t>(q[kDirectParts]) + w * c.nparts;
             } else {
               o.direct[q[kWindows] + w] = it;
-              o.direct_key[q[kWindows] + w] = work_key(c.work, P.side);
+              o.direct_key[q[kWindows] + w] = work_key(c.work);
             }
           }
         } else if (c.split) {
@@ -872,7 +871,7 @@ __global__ __launch_bounds__(kThreads) void k_items(PSides S, const unsigned lon
           o.split_part[q[kDirectSplit]] = static_cast<uint32_t>(q[kDirectParts]);
         } else {
           o.direct[q[kDirect] - q[kDirectSplit]] = it;
-          o.direct_key[q[kDirect] - q[kDirectSplit]] = work_key(c.work, 0);
+          o.direct_key[q[kDirect] - q[kDirectSplit]] = work_key(c.work);
         }
       } else if (c.nparts == 0) {
         o.rev[q[kRev]] = it;
@@ -1178,18 +1177,13 @@ struct OrderIn {
 struct GatherOut {
   const Item* in;
   Item* out;
-  uint32_t skip1;  // places left out before side 1's items
-  __device__ __forceinline__ void store(uint32_t pos, const radix::Elt<2>& e) const {
-    const Item it = in[e.w[1]];
-    out[pos + (it.side ? skip1 : 0u)] = it;
-  }
+  __device__ __forceinline__ void store(uint32_t pos, const radix::Elt<2>& e) const { out[pos] = in[e.w[1]]; }
 };
 // The parts of split direct items, and (count plans) their reduces.
 struct SplitOut {
   Item* items;
   Reduce* reduces;
   uint32_t acc0;        // count plans: first accumulator slot of the direct parts (one each)
-  uint32_t skip1;       // per-vertex plans: places of side 0's other items, before side 1's parts
   bool pv;              // per-vertex plans: an item's parts share an accumulator
 };
 
@@ -1209,7 +1203,7 @@ __global__ void k_split_parts(PSides S, const Item* split, const uint32_t* part_
       part.flags |= kItemMultiPart;
       part.acc_slot = static_cast<int32_t>(o.pv ? i : o.acc0 + at + p);
       if (o.pv) part.work = (p << 16) | np;
-      o.items[at + p + (it.side ? o.skip1 : 0u)] = part;
+      o.items[at + p] = part;
     }
     if (o.pv) continue;
     Reduce r{};
@@ -1332,7 +1326,7 @@ struct Scratch {
 
 // Items in work order.
 void order_items(const uint32_t* key, int64_t n, uint32_t* buf, unsigned long long* ctl, const Item* in, Item* out,
-                 uint32_t skip1, hipStream_t st) {
+                 hipStream_t st) {
   if (n == 0) return;
   const radix::Digits d = radix::digits_of(0, 16);
   const size_t w = Carve::round(static_cast<size_t>(n));
@@ -1340,7 +1334,7 @@ void order_items(const uint32_t* key, int64_t n, uint32_t* buf, unsigned long lo
   const radix::Control cc{ctl};
   PD_TRY(launch_fill_u64(ctl, radix::control_words(n, d), 0ull, st));
   PD_TRY((radix::histogram<1>(OrderIn{key}, n, d, cc, st)));
-  PD_TRY((radix::passes<1, 2>(OrderIn{key}, GatherOut{in, out, skip1}, bufs, n, d, cc, st)));
+  PD_TRY((radix::passes<1, 2>(OrderIn{key}, GatherOut{in, out}, bufs, n, d, cc, st)));
 }
 
 void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& hp, DevPlanLists& out) {
@@ -1556,20 +1550,14 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
 
   // hash items, heaviest first
   Item* hash = alloc_n<Item>(out.hash_items, n_hash);
-  order_items(io.hash_key, n_hash, order_buf, ctl, io.hash, hash, 0, st);
+  order_items(io.hash_key, n_hash, order_buf, ctl, io.hash, hash, st);
   // direct items: the parts of split items, then the others, heaviest first
-  // (per-vertex plans: side 0's of both, then side 1's)
   Item* direct = alloc_n<Item>(out.direct_items, n_dir_items);
   if (n_split > 0)
     LAUNCH(k_split_parts, grid_for(n_split), kThreads, S, io.split, io.split_part, static_cast<uint32_t>(n_split),
            static_cast<uint32_t>(tot[kDirectParts]), dir_parts,
-           SplitOut{direct, io.reduces + tot[kRevReduces], static_cast<uint32_t>(tot[kRevAcc]),
-                    p.per_vertex ? static_cast<uint32_t>(at1[kWindows]) : 0u, p.per_vertex});
-  if (p.per_vertex)
-    order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + at1[kDirectParts],
-                static_cast<uint32_t>(tot[kDirectParts] - at1[kDirectParts]), st);
-  else
-    order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + tot[kDirectParts], 0, st);
+           SplitOut{direct, io.reduces + tot[kRevReduces], static_cast<uint32_t>(tot[kRevAcc]), p.per_vertex});
+  order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + tot[kDirectParts], st);
   PD_TRY(out.acc.alloc(std::max<size_t>(static_cast<size_t>(acc_slots) * hp.acc_width * sizeof(uint32_t), 16)));
 
   // the dense block's signs
@@ -1626,9 +1614,7 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   hp.n_reverse_side0 = static_cast<int32_t>(at1[kRev]);
   if (p.per_vertex) {
     hp.n_hub_side0 = static_cast<int32_t>(at1[kHubParts]);
-    hp.n_direct_side0 = static_cast<int32_t>(at1[kWindows] + at1[kDirectParts]);
-    hp.n_heavy[0] = static_cast<int32_t>(at1[kDirectParts]);
-    hp.n_heavy[1] = static_cast<int32_t>(tot[kDirectParts] - at1[kDirectParts]);
+    hp.n_heavy = static_cast<int32_t>(tot[kDirectParts]);
   }
   hp.n_items_kept[0] = static_cast<int32_t>(n_dir_items);
   hp.n_items_kept[1] = static_cast<int32_t>(n_rev);
