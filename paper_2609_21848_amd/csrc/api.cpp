@@ -245,7 +245,7 @@ int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
     a.n_items = L.n[2];
     a.long_len = L.long_len;
     RC_TRY(tm.begin(st, "small", L.wedges[1], L.segs[1], a.n_items, 0));
-    HIP_TRY(dbbc::launch_small(a, std::min<int>(4 * cus, std::max(1, (a.n_items + 3) / 4)), st));
+    HIP_TRY(dbbc::launch_small(a, cus, st));
     RC_TRY(tm.end());
   }
   {
@@ -1215,8 +1215,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     a.err = err;
     a.n_items = hp.n_items_kept[2];
     a.long_len = long_len;
-    const int grid = std::min<int>(3 * cus, std::max(1, (a.n_items + 3) / 4));
-    HIP_TRY(edge ? dbbc::launch_pe_small(a, grid, st) : dbbc::launch_pv_small(a, grid, st));
+    HIP_TRY(edge ? dbbc::launch_pe_small(a, cus, st) : dbbc::launch_pv_small(a, cus, st));
   }
   {
     dbbc::HashArgs a{};

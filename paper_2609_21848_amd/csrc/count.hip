@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kReverseThreads) void k_reverse(SmallArgs a) {
     Item nxt2{};
     if (j2 < n) nxt2 = load_const(a.items, j2);
     const DevSideConst sc = load_const(a.sides, 2 * it.graph + it.side);
-    walk_item<8, false, true>(it, first, sc.segs, sc.other_adj, Marks<uint8_t>{mtab[wave], mflag[wave]}, a.long_len,
+    walk_item<8, false, true>(it, first, 0, sc.segs, sc.other_adj, Marks<uint8_t>{mtab[wave], mflag[wave]}, a.long_len,
                  PairTallyBF<kReverseWords>{lds_addr(C), lds_addr(&dummies[wave][lane])});
     wave_sync_lds();
     const int32_t w_hi = (it.key_hi + 1) >> 1;  // counter words of the item's keys
@@ -388,10 +388,13 @@ struct SmallInsert {
   }
 };
 
+// kTeam wavefronts take a group together (small_team): its runs interleaved, one
+// table, a slice of the table's sweep each.
+template <int kTeam>
 __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs a) {
   a.res = own_copy(a.res, a.res_mask);
-  __shared__ __attribute__((aligned(16))) uint32_t keys[kSmallWaves][kSmallSlots];
-  __shared__ __attribute__((aligned(16))) uint32_t vals[kSmallWaves][kSmallSlots];
+  __shared__ __attribute__((aligned(16))) uint32_t keys[kSmallWaves / kTeam][kSmallSlots];
+  __shared__ __attribute__((aligned(16))) uint32_t vals[kSmallWaves / kTeam][kSmallSlots];
   // staging marks: bases, and 16-bit tags (item index in the group << 1 | g,
   // with the presence bit; a group holds at most kSmallMaxItems items)
   __shared__ __attribute__((aligned(16))) uint32_t mbase[kSmallWaves][kGather];
@@ -401,22 +404,31 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs a) {
   // wave index, known to the compiler as wavefront-uniform
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = lane_id();
-  uint32_t* K = keys[wave];
-  uint32_t* Vv = vals[wave];
-  for (int i = lane; i < kSmallSlots; i += kWave) {
+  const int member = wave % kTeam;
+  uint32_t* K = keys[wave / kTeam];
+  uint32_t* Vv = vals[wave / kTeam];
+  const auto team_sync = [] {
+    if (kTeam == 1)
+      wave_sync_lds();
+    else
+      __syncthreads();
+  };
+  static_assert(kTeam == 1 || kTeam == kSmallWaves, "a team's barrier is the workgroup's");
+  for (int i = member * kWave + lane; i < kSmallSlots; i += kTeam * kWave) {
     K[i] = kEmpty;
     Vv[i] = 0;
   }
   for (int i = lane; i < static_cast<int>(kGather); i += kWave) mtag[wave][i] = 0;
-  wave_sync_lds();
+  team_sync();
   SqTotals tot;
-  const int32_t stride = static_cast<int32_t>(gridDim.x) * kSmallWaves;
-  int32_t i = static_cast<int32_t>(blockIdx.x) * kSmallWaves + wave;
+  constexpr int kTeams = kSmallWaves / kTeam;
+  const int32_t stride = static_cast<int32_t>(gridDim.x) * kTeams;
+  int32_t i = static_cast<int32_t>(blockIdx.x) * kTeams + wave / kTeam;
   Item nxt{};
   SegReg nfirst{0, 0, 0};
   if (i < a.n_items) {
     nxt = load_const(a.items, i);
-    nfirst = first_batch<true>(nxt, load_const(a.sides, 2 * nxt.graph + nxt.side).small_segs);
+    nfirst = first_batch<true, kTeam>(nxt, load_const(a.sides, 2 * nxt.graph + nxt.side).small_segs, member);
   }
   uint32_t graph = kNoGraph;
   for (; i < a.n_items; i += stride) {
@@ -438,10 +450,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs a) {
     const uint32_t size = w2 <= 64 ? 64u : 1u << (32 - __builtin_clz(w2 - 1));
     const uint32_t mask = size - 1;
     const uint32_t hshift = 32u - static_cast<uint32_t>(__builtin_ctz(size));
-    walk_item<4, true>(it, first, sc.small_segs, sc.other_adj, Marks<uint16_t>{mbase[wave], mtag[wave]}, a.long_len,
+    walk_item<4, true, false, kTeam>(it, first, member, sc.small_segs, sc.other_adj, Marks<uint16_t>{mbase[wave], mtag[wave]}, a.long_len,
                        SmallInsert{K, Vv, &sinks[wave][lane], kb, hshift, mask, a.err});
-    if (j < a.n_items) nfirst = first_batch<true>(nxt, load_const(a.sides, 2 * nxt.graph + nxt.side).small_segs);
-    wave_sync_lds();
+    if (j < a.n_items) nfirst = first_batch<true, kTeam>(nxt, load_const(a.sides, 2 * nxt.graph + nxt.side).small_segs, member);
+    team_sync();
     // p, n <= kSmallGroupWork per key and sum p + n <= kSmallGroupWork
     // per group, so the group's sums of squares stay below 2^19.  16-byte
     // LDS accesses, 4 slots per lane; an empty slot's count is 0, which adds
@@ -451,8 +463,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs a) {
       // the keys are only reset; a slot's p^2 + n^2 and 2 p n are 16-bit dot
       // products of its count word with itself and with its halves swapped,
       // and the sum of p + n over the group is its work
-      uint32_t sq32 = 0, pn32 = 0;
-      for (uint32_t h = 4 * lane; h < size; h += 4 * kWave) {
+      // (a team's wavefronts sum their own slots' p + n: each halves its own sums)
+      uint32_t sq32 = 0, pn32 = 0, w32 = 0;
+      for (uint32_t h = 4 * (member * kWave + lane); h < size; h += 4 * kTeam * kWave) {
         const uint4 c4 = *reinterpret_cast<const uint4*>(&Vv[h]);
         *reinterpret_cast<uint4*>(&K[h]) = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
         *reinterpret_cast<uint4*>(&Vv[h]) = make_uint4(0, 0, 0, 0);
@@ -463,15 +476,19 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs a) {
           const u16x2 rr = __builtin_bit_cast(u16x2, __builtin_amdgcn_alignbit(cv[q4], cv[q4], 16));
           sq32 = __builtin_amdgcn_udot2(hh, hh, sq32, false);
           pn32 = __builtin_amdgcn_udot2(hh, rr, pn32, false);
+          if (kTeam > 1) w32 = __builtin_amdgcn_udot2(hh, u16x2{1, 1}, w32, false);
         }
       }
       tot.sq += sq32;
       tot.pn2 += pn32;
-      if (lane == 0) tot.w += it.work;
+      if (kTeam > 1)
+        tot.w += w32;
+      else if (lane == 0)
+        tot.w += it.work;
     } else {
       // a hub pivot's item (alone in its group): keys below T are hub pairs
       const uint32_t kmask = (1u << kb) - 1u;
-      for (uint32_t h = 4 * lane; h < size; h += 4 * kWave) {
+      for (uint32_t h = 4 * (member * kWave + lane); h < size; h += 4 * kTeam * kWave) {
         const uint4 k4 = *reinterpret_cast<const uint4*>(&K[h]);
         const uint4 c4 = *reinterpret_cast<const uint4*>(&Vv[h]);
         *reinterpret_cast<uint4*>(&K[h]) = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
@@ -488,7 +505,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs a) {
       }
     }
     tot.add(ss);
-    wave_sync_lds();
+    team_sync();
   }
   __shared__ WaveSums wsum[kSmallWaves];
   flush_block_end(tot, graph, wsum, kSmallWaves, a.res);
@@ -785,9 +802,12 @@ hipError_t launch_reverse(const SmallArgs& a, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_small(const SmallArgs& a, int grid, hipStream_t st) {
+hipError_t launch_small(const SmallArgs& a, int cus, hipStream_t st) {
   if (a.n_items == 0) return hipSuccess;
-  hipLaunchKernelGGL(dev::k_small, dim3(grid), dim3(dev::kSmallThreads), 0, st, a);
+  if (small_team(a.n_items, cus) > 1)
+    hipLaunchKernelGGL(dev::k_small<dev::kSmallWaves>, dim3(a.n_items), dim3(dev::kSmallThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL(dev::k_small<1>, dim3(std::min(4 * cus, (a.n_items + 3) / 4)), dim3(dev::kSmallThreads), 0, st, a);
   return hipGetLastError();
 }
 

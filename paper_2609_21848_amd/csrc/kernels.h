@@ -184,7 +184,14 @@ hipError_t launch_copy(const Ranges& r, hipStream_t st);
 hipError_t launch_store_sides(const DevSideConst* src2, DevSideConst* dst, hipStream_t st);
 // (cus: the device's; the grid follows from the workgroup shape)
 hipError_t launch_direct(const DirectArgs& a, int cus, hipStream_t st);
-hipError_t launch_small(const SmallArgs& a, int grid, hipStream_t st);
+// Wavefronts that take a small-item group together.  A group is a chain of
+// dependent loads and probes, 12 us for 512 wedges; where all groups fit on the
+// device at once with a workgroup each (5 a CU), the four wavefronts of one
+// share a group: 20K edges, 264 groups, per count 37.5 -> 30.8 us; 334K edges
+// per-vertex, 1,240 groups 183 -> 168 us.  With more groups than that the chip is
+// full, and a team's barriers only cost.
+inline int small_team(int32_t n_groups, int cus) { return n_groups <= 5 * cus ? 4 : 1; }
+hipError_t launch_small(const SmallArgs& a, int cus, hipStream_t st);
 hipError_t launch_reverse(const SmallArgs& a, int grid, hipStream_t st);
 hipError_t launch_hash(const HashArgs& a, int grid, hipStream_t st);
 hipError_t launch_reduce(const ReduceArgs& a, int max_grid, hipStream_t st);
@@ -260,7 +267,7 @@ hipError_t launch_pv_direct(const DirectArgs& a, int grid, hipStream_t st);
 constexpr int32_t kPVKeyRanks = 32768;
 hipError_t launch_pv_key_flush(const DevSideConst* sides, int32_t n, hipStream_t st);
 hipError_t launch_pv_reverse(const SmallArgs& a, int grid, hipStream_t st);
-hipError_t launch_pv_small(const SmallArgs& a, int grid, hipStream_t st);
+hipError_t launch_pv_small(const SmallArgs& a, int cus, hipStream_t st);
 hipError_t launch_pv_hash(const HashArgs& a, int grid, hipStream_t st);
 // Per-edge outputs by input record: out[rec[k]] = e[0][k] + e[1][pos_v[k]]
 // over the U-CSR positions k (e[s] holds the credits by position in side s's
@@ -292,7 +299,7 @@ struct EdgeCombineArgs {
 // The per-vertex pass with per-edge credits as well (the same plans).
 hipError_t launch_pe_direct(const DirectArgs& a, int grid, hipStream_t st);
 hipError_t launch_pe_reverse(const SmallArgs& a, int grid, hipStream_t st);
-hipError_t launch_pe_small(const SmallArgs& a, int grid, hipStream_t st);
+hipError_t launch_pe_small(const SmallArgs& a, int cus, hipStream_t st);
 hipError_t launch_pe_hash(const HashArgs& a, int grid, hipStream_t st);
 hipError_t launch_edge_combine(const EdgeCombineArgs& a, int grid, hipStream_t st);
 

@@ -914,32 +914,42 @@ constexpr int kPVSmallThreads = 256;
 constexpr int kPVSmallWaves = kPVSmallThreads / kWave;
 constexpr int kPVSmallSlots = 2 * kSmallGroupWork;
 
-template <bool kEdge>
+// kTeam wavefronts take a group together, as in the count pass (small_team).
+template <bool kEdge, int kTeam>
 __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
   a.res = own_copy(a.res, a.res_mask);
-  __shared__ uint32_t keys[kPVSmallWaves][kPVSmallSlots];
-  __shared__ uint32_t vals[kPVSmallWaves][kPVSmallSlots];
+  __shared__ uint32_t keys[kPVSmallWaves / kTeam][kPVSmallSlots];
+  __shared__ uint32_t vals[kPVSmallWaves / kTeam][kPVSmallSlots];
   __shared__ __attribute__((aligned(16))) uint32_t mtab[kPVSmallWaves][kGather];
   __shared__ uint32_t mflag[kPVSmallWaves][kGather];
   __shared__ unsigned long long cb[kPVSmallWaves][kWave], cu[kPVSmallWaves][kWave];
   // wave index, known to the compiler as wavefront-uniform
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = lane_id();
-  uint32_t* K = keys[wave];
-  uint32_t* V = vals[wave];
-  for (int i = lane; i < kPVSmallSlots; i += kWave) {
+  const int member = wave % kTeam;
+  uint32_t* K = keys[wave / kTeam];
+  uint32_t* V = vals[wave / kTeam];
+  const auto team_sync = [] {
+    if (kTeam == 1)
+      wave_sync_lds();
+    else
+      __syncthreads();
+  };
+  static_assert(kTeam == 1 || kTeam == kPVSmallWaves, "a team's barrier is the workgroup's");
+  for (int i = member * kWave + lane; i < kPVSmallSlots; i += kTeam * kWave) {
     K[i] = kEmpty;
     V[i] = 0;
   }
   for (int i = lane; i < static_cast<int>(kGather); i += kWave) mflag[wave][i] = 0;
   cb[wave][lane] = 0;
   cu[wave][lane] = 0;
-  wave_sync_lds();
+  team_sync();
   const Marks<uint32_t> mk{mtab[wave], mflag[wave]};
   Sums sums;
   uint32_t graph = kNoGraph;
-  const int32_t stride = static_cast<int32_t>(gridDim.x) * kPVSmallWaves;
-  for (int32_t i = static_cast<int32_t>(blockIdx.x) * kPVSmallWaves + wave; i < a.n_items; i += stride) {
+  constexpr int kTeams = kPVSmallWaves / kTeam;
+  const int32_t stride = static_cast<int32_t>(gridDim.x) * kTeams;
+  for (int32_t i = static_cast<int32_t>(blockIdx.x) * kTeams + wave / kTeam; i < a.n_items; i += stride) {
     const Item it = load_const(a.items, i);
     if (it.graph != graph) {
       if (graph != kNoGraph) flush_sums(sums, a.res + static_cast<size_t>(graph) * kResStride);
@@ -955,10 +965,10 @@ __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
     auto hkey = [&](uint32_t e, uint32_t tag) { return (((tag & ~kMidWide) >> 7) << kb) | (e >> 1); };
     // a hub pivot's group (alone in it): keys below T as in k_pv_direct
     const uint32_t hubT = (it.flags & kItemHubPairs) ? static_cast<uint32_t>(sc.T) : 0u;
-    for (uint32_t k0 = it.seg_begin; k0 < seg_end; k0 += kWave) {
-      const uint32_t k1 = k0 + kWave < seg_end ? k0 + kWave : seg_end;
+    for (uint32_t k0 = it.seg_begin + member; k0 < seg_end; k0 += kTeam * kWave) {
+      const uint32_t k1 = k0 + kTeam * kWave < seg_end ? k0 + kTeam * kWave : seg_end;
       RunEnds re;
-      walk_regs<4>(load_seg_pv<true, kEdge>(sc.small_segs, sc.small_seg_mid, sc.small_seg_edge, k0, k1, re), sc.other_adj, mk,
+      walk_regs<4>(load_seg_pv<true, kEdge>(sc.small_segs, sc.small_seg_mid, sc.small_seg_edge, k0, k1, re, kTeam), sc.other_adj, mk,
                    a.long_len, hash_tally([&](uint32_t e, uint32_t tag) {
                      const uint32_t key = hkey(e, tag);
                      const uint32_t inc = ((e ^ tag) & 1u) ? 0x10000u : 1u;
@@ -979,11 +989,11 @@ __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
                      }
                    }));
     }
-    wave_sync_lds();
-    for (uint32_t k0 = it.seg_begin; k0 < seg_end; k0 += kWave) {
-      const uint32_t k1 = k0 + kWave < seg_end ? k0 + kWave : seg_end;
+    team_sync();
+    for (uint32_t k0 = it.seg_begin + member; k0 < seg_end; k0 += kTeam * kWave) {
+      const uint32_t k1 = k0 + kTeam * kWave < seg_end ? k0 + kTeam * kWave : seg_end;
       RunEnds re;
-      const SegReg sr = load_seg_pv<true, kEdge>(sc.small_segs, sc.small_seg_mid, sc.small_seg_edge, k0, k1, re);
+      const SegReg sr = load_seg_pv<true, kEdge>(sc.small_segs, sc.small_seg_mid, sc.small_seg_edge, k0, k1, re, kTeam);
       if (hubT == 0) {
         // a plain group has at most kSmallGroupWork wedges: a run's credits
         // stay below 2^18, so one packed LDS word per run
@@ -1036,8 +1046,9 @@ __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
       c.flush();
       flush_mid_credits<kEdge>(cb[wave], cu[wave], re, sc);
     }
+    if (kTeam > 1) __syncthreads();
     const uint32_t kmask = (1u << kb) - 1u;
-    for (uint32_t h = lane; h < size; h += kWave) {
+    for (uint32_t h = member * kWave + lane; h < size; h += kTeam * kWave) {
       const uint32_t key = K[h];
       if (key == kEmpty) continue;
       const uint32_t v = V[h];
@@ -1052,7 +1063,7 @@ __global__ __launch_bounds__(kPVSmallThreads) void k_pv_small(SmallArgs a) {
         if (pc.x) atomicAdd(&sc.unb[id], static_cast<unsigned long long>(pc.x));
       }
     }
-    wave_sync_lds();
+    team_sync();
   }
   __shared__ WaveSums wsum[kPVSmallWaves];
   flush_block_end(sums, graph, wsum, kPVSmallWaves, a.res);
@@ -1247,9 +1258,14 @@ hipError_t reverse_(const SmallArgs& a, int grid, hipStream_t st) {
 }
 
 template <bool kEdge>
-hipError_t small_(const SmallArgs& a, int grid, hipStream_t st) {
+hipError_t small_(const SmallArgs& a, int cus, hipStream_t st) {
   if (a.n_items == 0) return hipSuccess;
-  hipLaunchKernelGGL(dev::k_pv_small<kEdge>, dim3(grid), dim3(dev::kPVSmallThreads), 0, st, a);
+  if (small_team(a.n_items, cus) > 1)
+    hipLaunchKernelGGL((dev::k_pv_small<kEdge, dev::kPVSmallWaves>), dim3(a.n_items), dim3(dev::kPVSmallThreads), 0, st,
+                       a);
+  else
+    hipLaunchKernelGGL((dev::k_pv_small<kEdge, 1>), dim3(std::min(3 * cus, (a.n_items + 3) / 4)),
+                       dim3(dev::kPVSmallThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1269,11 +1285,11 @@ hipError_t launch_pv_heavy_tally(const DirectArgs& a, int grid, hipStream_t st) 
 }
 hipError_t launch_pv_direct(const DirectArgs& a, int grid, hipStream_t st) { return direct_<false>(a, grid, st); }
 hipError_t launch_pv_reverse(const SmallArgs& a, int grid, hipStream_t st) { return reverse_<false>(a, grid, st); }
-hipError_t launch_pv_small(const SmallArgs& a, int grid, hipStream_t st) { return small_<false>(a, grid, st); }
+hipError_t launch_pv_small(const SmallArgs& a, int cus, hipStream_t st) { return small_<false>(a, cus, st); }
 hipError_t launch_pv_hash(const HashArgs& a, int grid, hipStream_t st) { return hash_<false>(a, grid, st); }
 hipError_t launch_pe_direct(const DirectArgs& a, int grid, hipStream_t st) { return direct_<true>(a, grid, st); }
 hipError_t launch_pe_reverse(const SmallArgs& a, int grid, hipStream_t st) { return reverse_<true>(a, grid, st); }
-hipError_t launch_pe_small(const SmallArgs& a, int grid, hipStream_t st) { return small_<true>(a, grid, st); }
+hipError_t launch_pe_small(const SmallArgs& a, int cus, hipStream_t st) { return small_<true>(a, cus, st); }
 hipError_t launch_pe_hash(const HashArgs& a, int grid, hipStream_t st) { return hash_<true>(a, grid, st); }
 
 hipError_t launch_pv_key_flush(const DevSideConst* sides, int32_t n, hipStream_t st) {

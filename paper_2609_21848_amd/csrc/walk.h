@@ -493,23 +493,29 @@ __device__ __forceinline__ void walk_batch(const Segment* __restrict__ segs, uin
 
 // Walk every run of an item with one wavefront; the first batch of 64 runs
 // was loaded beforehand (first).
-template <int U, bool kTagged = false, bool kCompact = false, class M, class F>
-__device__ __forceinline__ void walk_item(const Item& it, SegReg first, const Segment* __restrict__ segs,
+// kTeam wavefronts share an item (kTeam > 1): wavefront `member` takes its runs
+// member, member + kTeam, ...
+template <int U, bool kTagged = false, bool kCompact = false, int kTeam = 1, class M, class F>
+__device__ __forceinline__ void walk_item(const Item& it, SegReg first, uint32_t member,
+                                          const Segment* __restrict__ segs,
                                           const uint32_t* __restrict__ adj, M marks,
                                           uint32_t long_len, F&& f) {
   const uint32_t seg_end = it.seg_begin + it.seg_count;
-  walk_regs<U, false, kCompact>(first, adj, marks, long_len, f);
-  for (uint32_t k0 = it.seg_begin + kWave; k0 < seg_end; k0 += kWave) {
-    const uint32_t k1 = k0 + kWave < seg_end ? k0 + kWave : seg_end;
-    walk_regs<U, false, kCompact>(load_seg<kTagged>(segs, k0, k1), adj, marks, long_len, f);
+  for (uint32_t k0 = it.seg_begin + kTeam * kWave + member;; k0 += kTeam * kWave) {
+    SegReg next{0, 0, 0};  // the next batch, loaded under this one
+    if (k0 < seg_end)
+      next = load_seg<kTagged>(segs, k0, k0 + kTeam * kWave < seg_end ? k0 + kTeam * kWave : seg_end, kTeam);
+    walk_regs<U, false, kCompact>(first, adj, marks, long_len, f);
+    if (k0 >= seg_end) break;
+    first = next;
   }
 }
 
-template <bool kTagged = false>
-__device__ __forceinline__ SegReg first_batch(const Item& it, const Segment* __restrict__ segs) {
+template <bool kTagged = false, int kTeam = 1>
+__device__ __forceinline__ SegReg first_batch(const Item& it, const Segment* __restrict__ segs, uint32_t member = 0) {
   const uint32_t seg_end = it.seg_begin + it.seg_count;
-  return load_seg<kTagged>(segs, it.seg_begin,
-                           it.seg_begin + kWave < seg_end ? it.seg_begin + kWave : seg_end);
+  return load_seg<kTagged>(segs, it.seg_begin + member,
+                           it.seg_begin + kTeam * kWave < seg_end ? it.seg_begin + kTeam * kWave : seg_end, kTeam);
 }
 
 // Packed counter increment of one wedge: +1 symmetric or +2^16 asymmetric,
