@@ -369,12 +369,12 @@ __device__ __forceinline__ void walk_regs(SegReg sr, const uint32_t* __restrict_
   bool staged = false;
   auto first_round = [&]() {
     staged = true;
-    if (total <= kept_end) return;
+    if (kReplay ? total <= kept_end : total == 0) return;
     if (kCompact) {
       fill_table(marks, slen, base, tag);
       stage_round_table(cur, marks, excl, slen, total, 0, carry, adj);
     } else {
-      stage_round(cur, marks, excl, slen, base, tag, total, kept_end, adj);
+      stage_round(cur, marks, excl, slen, base, tag, total, kReplay ? kept_end : 0u, adj);
     }
   };
   if (!kCompact) first_round();
@@ -439,6 +439,31 @@ __device__ __forceinline__ void walk_regs(SegReg sr, const uint32_t* __restrict_
     }
   }
   if (!staged) first_round();
+  // (this loop through the helpers below made the compiler hold more in
+  // registers: the count's reverse kernel 4.77 against 4.52 ms at 50M edges)
+  if constexpr (kKept == 0) {
+    for (uint32_t done = 0; done < total; done += kGather) {
+      const bool more = done + kGather < total;
+      Staged nxt;
+      if (more) {
+        if (kCompact)
+          stage_round_table(nxt, marks, excl, slen, total, done + kGather, carry, adj);
+        else
+          stage_round(nxt, marks, excl, slen, base, tag, total, done + kGather, adj);
+      }
+      if constexpr (HasStaged<std::remove_reference_t<F>>::value) {
+        f.add_staged(cur);
+      } else {
+#pragma unroll
+        for (int u = 0; u < kStageU; ++u)
+          if (!kCompact || done + static_cast<uint32_t>(u * kWave) < total)
+            walk_add(f, cur.e[u], cur.tag[u], cur.valid[u], cur.pos[u], 0);
+      }
+      if (!more) break;
+      cur = nxt;
+    }
+    return;
+  }
   auto put_round = [&](const Staged& r, uint32_t done) {
     if constexpr (HasStaged<std::remove_reference_t<F>>::value) {
       f.add_staged(r);
@@ -502,12 +527,9 @@ __device__ __forceinline__ void walk_item(const Item& it, SegReg first, uint32_t
                                           uint32_t long_len, F&& f) {
   const uint32_t seg_end = it.seg_begin + it.seg_count;
   for (uint32_t k0 = it.seg_begin + kTeam * kWave + member;; k0 += kTeam * kWave) {
-    SegReg next{0, 0, 0};  // the next batch, loaded under this one
-    if (k0 < seg_end)
-      next = load_seg<kTagged>(segs, k0, k0 + kTeam * kWave < seg_end ? k0 + kTeam * kWave : seg_end, kTeam);
     walk_regs<U, false, kCompact>(first, adj, marks, long_len, f);
     if (k0 >= seg_end) break;
-    first = next;
+    first = load_seg<kTagged>(segs, k0, k0 + kTeam * kWave < seg_end ? k0 + kTeam * kWave : seg_end, kTeam);
   }
 }
 
