@@ -72,6 +72,19 @@ constexpr uint32_t kSmallGroupWork = 512;
 // runs, item index << 1 | g with a presence bit, fit 16 bits).
 constexpr uint32_t kSmallMaxItems = 16383;
 
+// Reverse items of at most this many wedges are small items instead: a reverse
+// item clears and sweeps a window of up to 4,096 keys whatever its wedges, a
+// small one pays a hash probe (per-vertex and per-edge: two) per wedge.  Measured
+// at 0 / 32 / 64 / 96 / 128 / 192 / 256: count of 2M edges 254 / 244 / 225 / 215 /
+// 214 / 205 / 211 us, of 50M 8.65 / 8.57 / 8.50 / 8.48 / 8.46 / 8.48 / 8.57 ms;
+// per-edge 2M 974 / 950 / 926 / 922 / 934 / 923 / 930 us, 20M 19.5 / 19.1 / 18.9 /
+// 18.9 / 19.0 / 19.3 / 19.5 ms; per-vertex 50M 31.0 / 30.9 / 30.8 / 30.9 / 31.0 /
+// 31.8 / 33.0 ms.
+constexpr int64_t reverse_small_work(bool per_vertex, int64_t small_work) {
+  const int64_t most = per_vertex ? 64 : 192;
+  return small_work < most ? small_work : most;
+}
+
 // Reverse items keep two 8-bit counters per key (symmetric, asymmetric), so
 // a reverse item (or item part) has at most this many segments.
 constexpr uint32_t kReverseMaxSegs = 255;

@@ -528,7 +528,9 @@ int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::stri
       it.flags = flags;
       it.side = static_cast<uint32_t>(s);
       it.work = static_cast<uint32_t>(std::min<int64_t>(work, 0xffffffffll));
-      if (kind == kReverseTail && pv && nseg > kReverseMaxSegs) {
+      if (kind == kReverseTail && work <= reverse_small_work(pv, p.small_work)) {
+        P.small_items.push_back(it);
+      } else if (kind == kReverseTail && pv && nseg > kReverseMaxSegs) {
         P.big_direct.push_back(it);  // per-vertex counts: one direct item
       } else if (kind == kReverseTail) {
         // parts of at most kReverseMaxSegs segments (8-bit counters; signed

@@ -245,6 +245,10 @@ __device__ Cand classify(const PSide& P, int32_t x, int k) {
     // rows are sorted by rank: the keys stop at the largest run end
     c.key_lo = 0;
     c.key_hi = min(P.R, max(P.rmax[x], 0) + 1);
+    if (c.work <= static_cast<unsigned long long>(reverse_small_work(P.pv, P.small_work))) {
+      c.cls = kSmallC;
+      return c;
+    }
     if (P.pv) {  // no parts: one reverse item, or a direct item past kReverseMaxSegs runs
       c.cls = c.nseg > kReverseMaxSegs ? kDirectC : kRevC;
       return c;
