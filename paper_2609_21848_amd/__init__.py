@@ -10,7 +10,9 @@ computes counts itself.  PyTorch is used only for device tensors and streams.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+import struct
 from typing import NamedTuple
 
 import numpy as np
@@ -67,6 +69,15 @@ class Counts(NamedTuple):
 
 class _Counts(ctypes.Structure):
     _fields_ = [(k, ctypes.c_int64) for k in ("balanced", "unbalanced", "total", "wedges")]
+
+
+# Counts of the int64s of a _Counts array: unpacked and built in C (512 results
+# 0.30 -> 0.06 ms against reading each structure's fields).
+_new_counts = functools.partial(tuple.__new__, Counts)
+
+
+def _counts_list(out, k: int) -> list:
+    return list(map(_new_counts, struct.iter_unpack("=4q", out)))[:k]
 
 
 class _Stats(ctypes.Structure):
@@ -407,14 +418,14 @@ def dbbc_batch_read(b: int) -> list:
     k = load().dbbc_batch_size(b)
     out = (_Counts * max(k, 1))()
     _check(load().dbbc_batch_read(b, out), "dbbc_batch_read")
-    return [Counts(c.balanced, c.unbalanced, c.total, c.wedges) for c in out[:k]]
+    return _counts_list(out, k)
 
 
 def dbbc_batch_count(b: int, stream=None) -> list:
     k = load().dbbc_batch_size(b)
     out = (_Counts * max(k, 1))()
     _check(load().dbbc_batch_count(b, out, _stream_ptr(stream)), "dbbc_batch_count")
-    return [Counts(c.balanced, c.unbalanced, c.total, c.wedges) for c in out[:k]]
+    return _counts_list(out, k)
 
 
 def dbbc_batch_destroy(b: int) -> None:
@@ -427,7 +438,7 @@ def dbbc_count_batch(gs, options: Options | None = None, stream=None) -> list:
     out = (_Counts * max(k, 1))()
     opt = ctypes.byref(options) if options is not None else None
     _check(load().dbbc_count_batch(arr, k, opt, out, _stream_ptr(stream)), "dbbc_count_batch")
-    return [Counts(c.balanced, c.unbalanced, c.total, c.wedges) for c in out[:k]]
+    return _counts_list(out, k)
 
 
 def dbbc_autotune(gs, start: Options | None = None, reps: int = 3, stream=None):
