@@ -326,6 +326,7 @@ struct dbbc_graph {
                                     // prefix; per row: global rank (the planners' input)
   DevBuf pv_out[2][2];    // per-vertex outputs [side][balanced, unbalanced]
   DevBuf pv_keys[2];      // per side: the direct items' key credits by rank (balanced, then unbalanced)
+  DevBuf pv_mid[2];       // credits to the mids, a pair of words per vertex of the side
   DevBuf pe_out[2][3];    // per-edge credits by CSR position [side][packed, wide bal, wide unb]
   DevBuf edge_rec, edge_pos_v;  // U-CSR position -> input record, -> V-CSR position
   DevBuf pe_tmp;          // stands in for a NULL per-edge output
@@ -600,6 +601,7 @@ int ensure_plan_into(dbbc_graph* g, const dbbc::PlanParams& p, hipStream_t st, D
       c.unb = g->pv_out[s][1].as<unsigned long long>();
       c.bal_mid = g->pv_out[1 - s][0].as<unsigned long long>();
       c.unb_mid = g->pv_out[1 - s][1].as<unsigned long long>();
+      c.mid_pairs = g->pv_mid[1 - s].as<unsigned long long>();
       c.key_bal = g->pv_keys[s].as<unsigned long long>();
       c.key_unb = c.key_bal + dbbc::kPVKeyRanks;
       c.seg_edge = d.seg_edge.as<uint32_t>();
@@ -887,7 +889,7 @@ int dbbc_graph_stats(const dbbc_graph* g, dbbc_stats* out) {
     b += g->adj[k].bytes + g->off[k].bytes + g->orig[k].bytes + g->raw_ids[k].bytes + g->rev[k].bytes +
          g->cut[k].bytes + g->grank[k].bytes;
     for (int j = 0; j < 2; ++j) b += g->pv_out[k][j].bytes;
-    b += g->pv_keys[k].bytes;
+    b += g->pv_keys[k].bytes + g->pv_mid[k].bytes;
     for (int j = 0; j < 3; ++j) b += g->pe_out[k][j].bytes;
   }
   s.device_bytes = static_cast<int64_t>(b);
@@ -1049,6 +1051,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   for (int s = 0; s < 2; ++s) {
     for (int k = 0; k < 2; ++k)
       HIP_TRY(g->pv_out[s][k].reserve(static_cast<size_t>(n[s]) * sizeof(unsigned long long)));
+    HIP_TRY(g->pv_mid[s].reserve(2 * static_cast<size_t>(n[s]) * sizeof(unsigned long long)));
     HIP_TRY(g->pv_keys[s].reserve(2 * static_cast<size_t>(dbbc::kPVKeyRanks) * sizeof(unsigned long long)));
   }
   if (edge) {
@@ -1086,6 +1089,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   const bool wide = d.any_wide || hp.T[0] > 0 || hp.T[1] > 0;
   for (int s = 0; s < 2; ++s) {
     for (int k = 0; k < 2 && !edge; ++k) zero.zero(g->pv_out[s][k].p, static_cast<size_t>(n[s]));
+    if (!edge) zero.zero(g->pv_mid[s].p, 2 * static_cast<size_t>(n[s]));
     if (!edge) zero.zero(g->pv_keys[s].p, 2 * static_cast<size_t>(dbbc::kPVKeyRanks));
     for (int k = 0; k < (wide ? 3 : 1) && edge; ++k) zero.zero(g->pe_out[s][k].p, m);
     if (hp.T[0] > 0) zero.zero(d.hub_pairs[s].p, static_cast<size_t>(hp.T[s]) * hp.T[s]);
@@ -1265,20 +1269,36 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     const int grid = static_cast<int>(std::min<int64_t>(8 * cus, std::max<int64_t>(1, (a.m + 255) / 256)));
     HIP_TRY(dbbc::launch_edge_combine(a, grid, st));
   }
-  // the outputs in one launch with the results, where a kernel on this device
-  // can write them; elsewhere (another device's memory, host memory) by copies
-  dbbc::Ranges out;
-  for (int s = 0; s < 2; ++s)
-    for (int k = 0; k < 2; ++k) {
-      if (!vout[s][k]) continue;
-      if (kernel_writable(vout[s][k], g->dev.id))
-        out.copy(vout[s][k], g->pv_out[s][k].p, static_cast<size_t>(n[s]));
-      else
-        HIP_TRY(hipMemcpyAsync(vout[s][k], g->pv_out[s][k].p, static_cast<size_t>(n[s]) * sizeof(int64_t),
-                               hipMemcpyDeviceToDevice, st));
+  if (edge) {
+    dbbc::Ranges out;
+    out.copy(g->pinned, ctl, kCtlWords);
+    HIP_TRY(dbbc::launch_copy(out, st));
+  } else {
+    // the outputs in one launch with the results, where a kernel on this device
+    // can write them; elsewhere (another device's memory, host memory) by copies
+    dbbc::VertexOutArgs a{};
+    bool copy[2][2] = {};
+    for (int s = 0; s < 2; ++s) {
+      a.n[s] = n[s];
+      a.mid[s] = g->pv_mid[s].as<unsigned long long>();
+      for (int k = 0; k < 2; ++k) {
+        a.acc[s][k] = g->pv_out[s][k].as<unsigned long long>();
+        if (!vout[s][k]) continue;
+        copy[s][k] = !kernel_writable(vout[s][k], g->dev.id);
+        a.out[s][k] = copy[s][k] ? g->pv_out[s][k].as<unsigned long long>()
+                                 : reinterpret_cast<unsigned long long*>(vout[s][k]);
+      }
     }
-  out.copy(g->pinned, ctl, kCtlWords);
-  HIP_TRY(dbbc::launch_copy(out, st));
+    a.from = ctl;
+    a.to = g->pinned;
+    a.words = static_cast<int32_t>(kCtlWords);
+    HIP_TRY(dbbc::launch_vertex_out(a, st));
+    for (int s = 0; s < 2; ++s)
+      for (int k = 0; k < 2; ++k)
+        if (copy[s][k])
+          HIP_TRY(hipMemcpyAsync(vout[s][k], g->pv_out[s][k].p, static_cast<size_t>(n[s]) * sizeof(int64_t),
+                                 hipMemcpyDeviceToDevice, st));
+  }
   HIP_TRY(hipStreamSynchronize(st));
   dbbc_counts c{};
   rc = finish_lone(g, &c, false);

@@ -60,6 +60,7 @@ struct DevSideConst {
   unsigned long long* unb;
   unsigned long long* bal_mid;    // ... of the other side
   unsigned long long* unb_mid;
+  unsigned long long* mid_pairs;  // credits to the other side's vertices, balanced and unbalanced side by side
   // key credits of the direct items by side-s rank (their keys are below
   // the window, kPVKeyRanks), added to bal / unb after the direct launches
   unsigned long long* key_bal;
@@ -158,6 +159,20 @@ struct HubArgs {
 };
 
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t st);
+
+// The per-vertex pass's outputs: out[s][k][id] = acc[s][k][id] + mid[s][2 id + k]
+// for both sides s and both values k (a null out: not wanted), and the words
+// `from` to `to` (results to pinned host memory).
+struct VertexOutArgs {
+  const unsigned long long* acc[2][2];
+  const unsigned long long* mid[2];
+  unsigned long long* out[2][2];
+  int32_t n[2];
+  const unsigned long long* from;
+  unsigned long long* to;
+  int32_t words;
+};
+hipError_t launch_vertex_out(const VertexOutArgs& a, hipStream_t st);
 
 // Ranges of 8-byte words that are cleared, or copied, together: a launch for
 // every kMax of them.  A launch costs 2 - 4 us beside the work of a range of

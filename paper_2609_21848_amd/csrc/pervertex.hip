@@ -185,6 +185,24 @@ __device__ __forceinline__ void run_credits_out(unsigned long long b, unsigned l
   }
 }
 
+// A batch's run credits to their mids (per-vertex; lane: its run's b, u and its
+// mid's input id; every lane takes part).  The adds of a pair sit side by side and
+// go out from two lanes of one instruction: an add costs its 64-byte line, 23 - 27 G
+// of them a second whatever they hold, so two arrays would cost two lines a run
+// (50M edges: direct 9.40 -> 8.74, reverse 15.13 -> 14.67 ms).
+__device__ __forceinline__ void mid_pairs_out(uint32_t b, uint32_t u, uint32_t id, const DevSideConst& sc) {
+  const uint64_t any = __ballot((b | u) != 0);
+  const uint32_t lane = static_cast<uint32_t>(lane_id());
+#pragma unroll
+  for (uint32_t h = 0; h < 2; ++h) {
+    if (static_cast<uint32_t>(any >> (32 * h)) == 0) continue;
+    const uint32_t src = 32 * h + (lane >> 1);
+    const uint32_t vb = bpermute(b, src), vu = bpermute(u, src), vi = bpermute(id, src);
+    const uint32_t v = lane & 1u ? vu : vb;
+    if (v) add_global(as_global(sc.mid_pairs) + 2 * static_cast<size_t>(vi) + (lane & 1u), v);
+  }
+}
+
 // After a batch's credit walk: each lane puts its run's credits out.
 template <bool kEdge, class Acc>
 __device__ __forceinline__ void flush_mid_credits(Acc* cb, Acc* cu, RunEnds re, const DevSideConst& sc) {
@@ -530,9 +548,11 @@ __global__ __launch_bounds__(kPVDirectThreads) void k_pv_direct(DirectArgs a) {
           wave_sync_lds();
           const unsigned long long v = cb[wave][lane];
           const uint32_t b = c.mb + static_cast<uint32_t>(v), u = c.mu + static_cast<uint32_t>(v >> 32);
-          if (b | u) {
-            cb[wave][lane] = 0;
-            run_credits_out<kEdge>(b, u, re, [&] { return sc.orig_mid[re.mid]; }, sc);
+          if (v) cb[wave][lane] = 0;
+          if constexpr (kEdge) {
+            if (b | u) run_credits_out<kEdge>(b, u, re, [] { return 0; }, sc);
+          } else {
+            mid_pairs_out(b, u, b | u ? static_cast<uint32_t>(as_global(sc.orig_mid)[re.mid]) : 0u, sc);
           }
           wave_sync_lds();
         } else {
@@ -633,6 +653,18 @@ __global__ void k_pv_key_flush(const DevSideConst* sides, int32_t n) {
       if (u) atomicAdd(&sc.unb[id], u);
     }
   }
+}
+
+__global__ void k_vertex_out(VertexOutArgs a) {
+  const int32_t first = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
+  const int32_t step = static_cast<int32_t>(gridDim.x * blockDim.x);
+  for (int s = 0; s < 2; ++s)
+    for (int32_t i = first; i < a.n[s]; i += step) {
+      const ulonglong2 mid = reinterpret_cast<const ulonglong2*>(a.mid[s])[i];
+      if (a.out[s][0]) a.out[s][0][i] = a.acc[s][0][i] + mid.x;
+      if (a.out[s][1]) a.out[s][1][i] = a.acc[s][1][i] + mid.y;
+    }
+  for (int32_t i = first; i < a.words; i += step) a.to[i] = a.from[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -835,7 +867,11 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
       const unsigned long long v = cbu[wave][lane];
       cbu[wave][lane] = 0;
       const uint32_t b = c.mb + static_cast<uint32_t>(v), u = c.mu + static_cast<uint32_t>(v >> 32);
-      if (b | u) run_credits_out<kEdge>(b, u, re, [&] { return mid_id; }, sc);
+      if constexpr (kEdge) {
+        if (b | u) run_credits_out<kEdge>(b, u, re, [] { return 0; }, sc);
+      } else {
+        mid_pairs_out(b, u, static_cast<uint32_t>(mid_id), sc);
+      }
       cb += b;
       cu += u;
       wave_sync_lds();
@@ -1295,6 +1331,13 @@ hipError_t launch_pe_hash(const HashArgs& a, int grid, hipStream_t st) { return 
 hipError_t launch_pv_key_flush(const DevSideConst* sides, int32_t n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(dev::k_pv_key_flush, dim3((n + 255) / 256, 2), dim3(256), 0, st, sides, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_vertex_out(const VertexOutArgs& a, hipStream_t st) {
+  const int32_t n = std::max({a.n[0], a.n[1], a.words});
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(dev::k_vertex_out, dim3(std::min((n + 255) / 256, 4096)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
