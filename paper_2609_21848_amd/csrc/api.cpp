@@ -29,9 +29,11 @@ int fail(int status, const std::string& msg) {
 #define HIP_TRY(expr)                                                                \
   do {                                                                               \
     hipError_t e_ = (expr);                                                          \
-    if (e_ != hipSuccess)                                                            \
+    if (e_ != hipSuccess) {                                                          \
+      (void)hipGetLastError(); /* reported here, not by the next launch */           \
       return fail(e_ == hipErrorOutOfMemory ? DBBC_E_OOM : DBBC_E_DEVICE,            \
                   std::string(#expr) + ": " + hipGetErrorString(e_));                \
+    }                                                                                \
   } while (0)
 
 struct DeviceInfo {
@@ -1018,14 +1020,20 @@ namespace {
 static_assert(dbbc::kPVKeyRanks >= dbbc::kPVWindowPacked && dbbc::kPVWindowPacked == 32768,
               "key sums cover the widest window");
 
-// Whether p is memory of device dev at a whole word.
-bool kernel_writable(const void* p, int dev) {
+// Whether the words p[0 .. n) are memory of device dev that a kernel can write:
+// whole words inside one allocation.  (A copy to memory that ends earlier is
+// refused by the runtime; a kernel would write past it.)
+bool kernel_writable(void* p, size_t n, int dev) {
   hipPointerAttribute_t a{};
-  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+  hipDeviceptr_t base{};
+  size_t bytes = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != dev ||
+      hipMemGetAddressRange(&base, &bytes, reinterpret_cast<hipDeviceptr_t>(p)) != hipSuccess) {
     (void)hipGetLastError();  // memory HIP does not know
     return false;
   }
-  return a.type == hipMemoryTypeDevice && a.device == dev && (reinterpret_cast<uintptr_t>(p) & 7u) == 0;
+  const uintptr_t at = reinterpret_cast<uintptr_t>(p), from = reinterpret_cast<uintptr_t>(base);
+  return (at & 7u) == 0 && at >= from && at - from <= bytes && n * sizeof(int64_t) <= bytes - (at - from);
 }
 
 // The per-vertex pass, with per-edge credits when edge is set: tally and
@@ -1275,7 +1283,8 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     HIP_TRY(dbbc::launch_copy(out, st));
   } else {
     // the outputs in one launch with the results, where a kernel on this device
-    // can write them; elsewhere (another device's memory, host memory) by copies
+    // can write them; elsewhere (another device's memory, host memory, an
+    // allocation too small) by copies
     dbbc::VertexOutArgs a{};
     bool copy[2][2] = {};
     for (int s = 0; s < 2; ++s) {
@@ -1284,7 +1293,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
       for (int k = 0; k < 2; ++k) {
         a.acc[s][k] = g->pv_out[s][k].as<unsigned long long>();
         if (!vout[s][k]) continue;
-        copy[s][k] = !kernel_writable(vout[s][k], g->dev.id);
+        copy[s][k] = !kernel_writable(vout[s][k], static_cast<size_t>(n[s]), g->dev.id);
         a.out[s][k] = copy[s][k] ? g->pv_out[s][k].as<unsigned long long>()
                                  : reinterpret_cast<unsigned long long*>(vout[s][k]);
       }
