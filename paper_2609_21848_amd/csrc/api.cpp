@@ -36,6 +36,12 @@ int fail(int status, const std::string& msg) {
     }                                                                                \
   } while (0)
 
+#define RC_TRY(expr)                \
+  do {                              \
+    int rc_ = (expr);               \
+    if (rc_ != DBBC_OK) return rc_; \
+  } while (0)
+
 struct DeviceInfo {
   int id = -1;
   int cus = 0;
@@ -151,8 +157,16 @@ struct LaunchSet {
   size_t n_res = 0;  // result words zeroed before the count (when not in the control block)
   uint32_t res_mask = 0;  // copies of the result slots - 1
   unsigned long long* ctl = nullptr;
-  std::vector<std::pair<unsigned long long*, size_t>> zero;  // hub-pair buffers
-  std::vector<HubLaunch> hubs;
+  HubLaunch hub;                                // a lone count's dense launch (n = 0: none)
+  const std::vector<HubLaunch>* hubs = nullptr;  // a batch's
+  // f(launch) for every dense launch, f returning a status
+  template <class F>
+  int each_hub(F f) const {
+    if (hub.n > 0) RC_TRY(f(hub));
+    if (hubs)
+      for (const HubLaunch& h : *hubs) RC_TRY(f(h));
+    return DBBC_OK;
+  }
   uint32_t long_len = 0;
   int cus = 0;
 };
@@ -184,12 +198,6 @@ struct Timing {
   }
 };
 
-#define RC_TRY(expr)                \
-  do {                              \
-    int rc_ = (expr);               \
-    if (rc_ != DBBC_OK) return rc_; \
-  } while (0)
-
 // Enqueue a whole count on stream st.  Every buffer the kernels accumulate
 // into is cleared by a fill kernel first (never a memset node, so that the
 // sequence can be captured into a HIP graph and replayed).  The kernels run
@@ -198,11 +206,15 @@ struct Timing {
 // several streams was measured slower than in sequence.
 int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
   {
-    dbbc::Ranges z;
+    dbbc::Ranges z(st);
     z.zero(L.ctl, kCtlWords);
     if (L.res != L.ctl) z.zero(L.res, L.n_res);
-    for (const auto& h : L.zero) z.zero(h.first, h.second);
-    HIP_TRY(dbbc::launch_zero(z, st));
+    RC_TRY(L.each_hub([&](const HubLaunch& h) {
+      // the hub pairs: two int32 T x T planes, cleared as T x T 64-bit words
+      for (int k = 0; k < h.n; ++k) z.zero(h.a[k].hub_xy, static_cast<size_t>(h.a[k].T) * h.a[k].T);
+      return DBBC_OK;
+    }));
+    HIP_TRY(z.launch());
   }
   unsigned long long* err = L.ctl + kCtlErr;
   uint32_t* queues = reinterpret_cast<uint32_t*>(L.ctl + kCtlQueues);
@@ -276,30 +288,28 @@ int enqueue(const LaunchSet& L, hipStream_t st, Timing& tm) {
     HIP_TRY(dbbc::launch_reduce(a, 4 * cus, st));
     RC_TRY(tm.end());
   }
-  for (const HubLaunch& h : L.hubs) {
+  return L.each_hub([&](const HubLaunch& h) {
     RC_TRY(tm.begin(st, h.name, 0, 0, h.tiles, h.macs));
     HIP_TRY(dbbc::launch_hub(h.a, h.n, st));
-    RC_TRY(tm.end());
-  }
-  return DBBC_OK;
+    return tm.end();
+  });
 }
 
-// Dense hub launches of a graph's plan, results into res (its slot); the
-// hub-pair partials in hub_xy[s] (default: the plan's own buffers).
-void add_hub_launches(DevPlan& d, unsigned long long* res, LaunchSet& L, int32_t* const* hub_xy = nullptr) {
+// The dense hub launch of a graph's plan (n = 0: none), results into res (its
+// slot, in res_mask + 1 copies); the hub-pair partials in hub_xy[s] (default:
+// the plan's own buffers).
+HubLaunch hub_launch(const DevPlan& d, unsigned long long* res, uint32_t res_mask, int32_t* const* hub_xy = nullptr) {
   const dbbc::HostPlan& hp = d.host;
   HubLaunch h{};
   for (int s = 0; s < 2; ++s) {
     if (hp.T[s] == 0) continue;
     int32_t* xy = hub_xy ? hub_xy[s] : d.hub_pairs[s].as<int32_t>();
-    // two int32 T x T planes, cleared as T x T 64-bit words
-    L.zero.push_back({reinterpret_cast<unsigned long long*>(xy), static_cast<size_t>(hp.T[s]) * hp.T[s]});
     dbbc::HubArgs& a = h.a[h.n++];
     a.Bm = d.hub_Bm[s].as<int8_t>();
     a.B = d.hub_B[s].as<int8_t>();
     a.hub_xy = xy;
     a.res = res;
-    a.res_mask = L.res_mask;
+    a.res_mask = res_mask;
     a.T = hp.T[s];
     a.K = d.hub_K[s];
     // two contractions over K for every tile of the upper triangle
@@ -308,7 +318,7 @@ void add_hub_launches(DevPlan& d, unsigned long long* res, LaunchSet& L, int32_t
     h.tiles += tiles;
     h.macs += 2 * tiles * 128 * 128 * static_cast<int64_t>(a.K);
   }
-  if (h.n > 0) L.hubs.push_back(h);
+  return h;
 }
 
 }  // namespace
@@ -354,6 +364,7 @@ struct dbbc_batch {
   DeviceInfo dev;
   DevBuf direct, reverse, small, hash, reduces, sides, srcs, res, ctl;
   LaunchSet L;
+  std::vector<HubLaunch> hubs;
   unsigned long long* pinned = nullptr;  // k result slots, then the error word
   size_t pinned_words = 0;
   hipStream_t cap = nullptr;
@@ -707,7 +718,7 @@ LaunchSet lone_launches(dbbc_graph* g, uint32_t long_len) {
   L.res = L.ctl;
   L.n_res = dbbc::kResStride;
   L.res_mask = dbbc::kResCopies - 1;
-  add_hub_launches(d, L.res, L);
+  L.hub = hub_launch(d, L.res, L.res_mask);
   L.long_len = long_len;
   L.cus = g->dev.cus;
   return L;
@@ -748,9 +759,9 @@ int enqueue_lone(dbbc_graph* g, const dbbc_options* opt, hipStream_t st) {
   rc = enqueue(L, st, tm);
   g->timers_used = tm.used;
   if (rc != DBBC_OK) return rc;
-  dbbc::Ranges out;
+  dbbc::Ranges out(st);
   out.copy(g->pinned, g->ctl.p, kCtlWords);
-  HIP_TRY(dbbc::launch_copy(out, st));
+  HIP_TRY(out.launch());
   return DBBC_OK;
 }
 
@@ -1090,7 +1101,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     HIP_TRY(hipStreamSynchronize(st));
   }
   unsigned long long* ctl = g->ctl.as<unsigned long long>();
-  dbbc::Ranges zero;
+  dbbc::Ranges zero(st);
   zero.zero(ctl, kCtlWords);
   // The per-edge pass credits edges alone; its two-word credits are used where
   // runs are flagged wide, or by the dense block.
@@ -1103,7 +1114,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     if (hp.T[0] > 0) zero.zero(d.hub_pairs[s].p, static_cast<size_t>(hp.T[s]) * hp.T[s]);
   }
   if (hp.n_heavy > 0) zero.zero(d.acc.p, static_cast<size_t>(hp.acc_slots) * hp.acc_width / 2);
-  HIP_TRY(dbbc::launch_zero(zero, st));
+  HIP_TRY(zero.launch());
   unsigned long long* err = ctl + kCtlErr;
   uint32_t* queues = reinterpret_cast<uint32_t*>(ctl + kCtlQueues);
   const dbbc::DevSideConst* sides = d.sides.as<dbbc::DevSideConst>();
@@ -1278,9 +1289,9 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
     HIP_TRY(dbbc::launch_edge_combine(a, grid, st));
   }
   if (edge) {
-    dbbc::Ranges out;
+    dbbc::Ranges out(st);
     out.copy(g->pinned, ctl, kCtlWords);
-    HIP_TRY(dbbc::launch_copy(out, st));
+    HIP_TRY(out.launch());
   } else {
     // the outputs in one launch with the results, where a kernel on this device
     // can write them; elsewhere (another device's memory, host memory, an
@@ -1412,15 +1423,15 @@ int dbbc_count_noalloc(dbbc_graph* g, const dbbc_options* opt, dbbc_counts* out_
   L.res = L.ctl;
   L.n_res = dbbc::kResStride;
   L.res_mask = dbbc::kResCopies - 1;
-  add_hub_launches(d, L.res, L, hub_xy);
+  L.hub = hub_launch(d, L.res, L.res_mask, hub_xy);
   L.long_len = long_len;
   L.cus = g->dev.cus;
   Timing tm{nullptr, 0, st};
   rc = enqueue(L, st, tm);
   if (rc != DBBC_OK) return rc;
-  dbbc::Ranges out;
+  dbbc::Ranges out(st);
   out.copy(g->pinned, L.ctl, kCtlWords);
-  HIP_TRY(dbbc::launch_copy(out, st));
+  HIP_TRY(out.launch());
   HIP_TRY(hipStreamSynchronize(st));
   return finish_lone(g, out_host, false);
 }
@@ -1462,6 +1473,7 @@ int assemble_batch(dbbc_batch* b, dbbc_graph* const* gs, int32_t k, const dbbc_o
   b->gs.clear();
   b->gens.clear();
   b->L = LaunchSet{};
+  b->hubs.clear();
   int rc;
   uint32_t long_len = kDefaultLongLen;
   int64_t tot[5] = {0, 0, 0, 0, 0};
@@ -1536,8 +1548,11 @@ int assemble_batch(dbbc_batch* b, dbbc_graph* const* gs, int32_t k, const dbbc_o
   L.ctl = b->ctl.as<unsigned long long>();
   L.res = b->res.as<unsigned long long>();
   L.n_res = static_cast<size_t>(k) * dbbc::kResStride;
-  for (int32_t i = 0; i < k; ++i)
-    add_hub_launches(gs[i]->plan, L.res + static_cast<size_t>(i) * dbbc::kResStride, L);
+  for (int32_t i = 0; i < k; ++i) {
+    const HubLaunch h = hub_launch(gs[i]->plan, L.res + static_cast<size_t>(i) * dbbc::kResStride, L.res_mask);
+    if (h.n > 0) b->hubs.push_back(h);
+  }
+  L.hubs = &b->hubs;
   L.long_len = long_len;
   L.cus = b->dev.cus;
   if (flags & DBBC_BATCH_CAPTURE) {
@@ -1608,10 +1623,10 @@ int dbbc_batch_launch(dbbc_batch* b, void* hip_stream) {
     int rc = enqueue(b->L, st, tm);
     if (rc != DBBC_OK) return rc;
   }
-  dbbc::Ranges out;
+  dbbc::Ranges out(st);
   out.copy(b->pinned, b->res.p, k * dbbc::kResStride);
   out.copy(b->pinned + k * dbbc::kResStride, b->ctl.as<unsigned long long>() + kCtlErr, 1);
-  HIP_TRY(dbbc::launch_copy(out, st));
+  HIP_TRY(out.launch());
   return DBBC_OK;
 }
 

@@ -719,28 +719,25 @@ hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v
   return hipGetLastError();
 }
 
-namespace {
-template <bool kCopy>
-hipError_t ranges_(const Ranges& ranges, hipStream_t st) {
-  for (size_t at = 0; at < ranges.r.size(); at += Ranges::kMax) {
-    dev::RangeArgs a{};
-    a.n = static_cast<int>(std::min<size_t>(Ranges::kMax, ranges.r.size() - at));
-    size_t longest = 0;
-    for (int k = 0; k < a.n; ++k) {
-      a.r[k] = ranges.r[at + k];
-      longest = std::max(longest, a.r[k].words);
-    }
-    const size_t blocks = std::min<size_t>((longest + 255) / 256, 4096);
-    hipLaunchKernelGGL(dev::k_ranges<kCopy>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+hipError_t Ranges::launch() {
+  if (n_ == 0) return err_;
+  dev::RangeArgs a{};
+  size_t longest = 0;
+  a.n = n_;
+  for (int k = 0; k < n_; ++k) {
+    a.r[k] = r_[k];
+    longest = std::max(longest, r_[k].words);
   }
-  return hipSuccess;
+  n_ = 0;
+  const dim3 grid(static_cast<unsigned>(std::min<size_t>((longest + 255) / 256, 4096)));
+  if (copies_)
+    hipLaunchKernelGGL(dev::k_ranges<true>, grid, dim3(256), 0, st_, a);
+  else
+    hipLaunchKernelGGL(dev::k_ranges<false>, grid, dim3(256), 0, st_, a);
+  const hipError_t e = hipGetLastError();
+  if (err_ == hipSuccess) err_ = e;
+  return err_;
 }
-}  // namespace
-
-hipError_t launch_zero(const Ranges& r, hipStream_t st) { return ranges_<false>(r, st); }
-hipError_t launch_copy(const Ranges& r, hipStream_t st) { return ranges_<true>(r, st); }
 
 hipError_t launch_assemble_items(const AssembleSrc* srcs, int k, Item* dst, hipStream_t st) {
   if (k == 0) return hipSuccess;

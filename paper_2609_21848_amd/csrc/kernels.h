@@ -5,7 +5,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <vector>
 
 #include "internal.h"
 
@@ -177,23 +176,36 @@ hipError_t launch_vertex_out(const VertexOutArgs& a, hipStream_t st);
 // Ranges of 8-byte words that are cleared, or copied, together: a launch for
 // every kMax of them.  A launch costs 2 - 4 us beside the work of a range of
 // this library's smaller graphs, and a pass clears and copies up to a dozen:
-// per-vertex pass of 334K edges 262 -> 230 us.
-struct Ranges {
+// per-vertex pass of 334K edges 262 -> 230 us.  (No heap memory: counts that may
+// not allocate use them too.)
+class Ranges {
+ public:
   static constexpr int kMax = 12;
   struct Range {
     unsigned long long* dst;
     const unsigned long long* src;  // copies only
     size_t words;
   };
-  std::vector<Range> r;
-  void zero(void* dst, size_t words) { copy(dst, nullptr, words); }
-  void copy(void* dst, const void* src, size_t words) {
-    if (words) r.push_back({static_cast<unsigned long long*>(dst), static_cast<const unsigned long long*>(src), words});
+  explicit Ranges(hipStream_t st) : st_(st) {}
+  void zero(void* dst, size_t words) { add(dst, nullptr, words, false); }
+  // dst may be pinned host memory.
+  void copy(void* dst, const void* src, size_t words) { add(dst, src, words, true); }
+  // Enqueue what is not enqueued yet; the first error of any launch.
+  hipError_t launch();
+
+ private:
+  void add(void* dst, const void* src, size_t words, bool copies) {
+    if (!words) return;
+    if (n_ == kMax || (n_ && copies != copies_)) (void)launch();
+    copies_ = copies;
+    r_[n_++] = {static_cast<unsigned long long*>(dst), static_cast<const unsigned long long*>(src), words};
   }
+  Range r_[kMax];
+  int n_ = 0;
+  bool copies_ = false;
+  hipStream_t st_;
+  hipError_t err_ = hipSuccess;
 };
-hipError_t launch_zero(const Ranges& r, hipStream_t st);
-// dst may be pinned host memory.
-hipError_t launch_copy(const Ranges& r, hipStream_t st);
 // Write the two side-table entries src2[0..2) (host values) to device
 // memory dst by a kernel (no copy from host memory).
 hipError_t launch_store_sides(const DevSideConst* src2, DevSideConst* dst, hipStream_t st);
