@@ -685,7 +685,6 @@ int params_from(const dbbc_graph* g, const dbbc_options* opt, dbbc::PlanParams& 
   if (opt->flags & ~(DBBC_OPT_TIME_KERNELS | DBBC_OPT_WIDE_EDGES | DBBC_OPT_HOST_PLAN))
     return fail(DBBC_E_INVALID_ARG, "unknown dbbc_options flag");
   p.host_planner = (opt->flags & DBBC_OPT_HOST_PLAN) != 0;
-  if (opt->part_work >= 0) p.part_room = 0;
   if (opt->hub_T >= 0) p.hub_T = opt->hub_T;
   if (opt->window_L >= 0) p.window_L = opt->window_L;
   if (opt->reverse_L >= 0) p.reverse_L = opt->reverse_L;
@@ -698,6 +697,11 @@ int params_from(const dbbc_graph* g, const dbbc_options* opt, dbbc::PlanParams& 
     long_len = static_cast<uint32_t>(opt->long_len);
   }
   if (p.hub_T > p.window_L) p.hub_T = std::min(p.hub_T, p.window_L);
+  // after the options: a block of another size leaves the parts another room
+  if (opt->part_work >= 0)
+    p.part_room = 0;
+  else
+    dbbc::set_part_room(g->host, p);
   return DBBC_OK;
 }
 

@@ -246,6 +246,9 @@ int check_plan_sizes(const PlanSizes& z, std::string& err);
 // once; the default block is trimmed so that its upper triangle of tiles
 // fits in one round.
 PlanParams default_params(const HostGraph& g, int32_t hub_slots = 512);
+// The room of p's parts (p.part_room), for the block that p plans: set once
+// every knob has its value.
+void set_part_room(const HostGraph& g, PlanParams& p);
 // Largest default part budget.
 constexpr int32_t kMaxPartWork = 1 << 24;
 // Whether parts that take `bytes` of counters are too many for p: raises

@@ -44,6 +44,18 @@ double hub_density(const HostGraph& g, int32_t T) {
   return static_cast<double>(nnz) / (static_cast<double>(T) * T);
 }
 
+namespace {
+
+// The dense block's rows per side: tiled by 128 (at most kMaxPVHubT in the
+// per-vertex pass), none unless both sides have some.
+void hub_rows(const int32_t n[2], const PlanParams& p, int32_t T[2]) {
+  for (int s = 0; s < 2; ++s)
+    T[s] = std::min<int32_t>(p.per_vertex ? std::min(p.hub_T, kMaxPVHubT) : p.hub_T, n[s] / 128 * 128);
+  if (T[0] == 0 || T[1] == 0) T[0] = T[1] = 0;
+}
+
+}  // namespace
+
 PlanParams default_params(const HostGraph& g, int32_t hub_slots) {
   PlanParams p;
   p.window_L = 32768;
@@ -91,10 +103,17 @@ PlanParams default_params(const HostGraph& g, int32_t hub_slots) {
       std::max<int64_t>(1 << 15, std::min(g.wedges_vp / std::max(1, hub_slots),
                                           (1 << 16) + g.wedges_vp / (8 * std::max(1, hub_slots))));
   p.pv_part_work = pv_budget > (1 << 21) ? kMaxPartWork : pv_budget;
-  const int64_t scratch = static_cast<int64_t>(DBBC_NOALLOC_SCRATCH_BYTES) - (1 << 20) -
-                          16 * static_cast<int64_t>(p.hub_T) * p.hub_T;  // two int32 planes on each side
-  p.part_room = std::max<int64_t>(1, scratch > 0 ? std::min(24 * g.m, scratch) : 24 * g.m);
+  set_part_room(g, p);
   return p;
+}
+
+void set_part_room(const HostGraph& g, PlanParams& p) {
+  const int32_t n[2] = {g.n_u, g.n_v};
+  int32_t T[2];
+  hub_rows(n, p, T);
+  int64_t scratch = static_cast<int64_t>(DBBC_NOALLOC_SCRATCH_BYTES) - (1 << 20);
+  for (int64_t t : T) scratch -= 8 * t * t;  // two int32 planes
+  p.part_room = std::max<int64_t>(1, scratch > 0 ? std::min(24 * g.m, scratch) : 24 * g.m);
 }
 
 namespace {
@@ -416,16 +435,11 @@ int check_plan_params(const PlanParams& p, std::string& err) {
 }
 
 void plan_windows(const int32_t n[2], const PlanParams& p, HostPlan& plan) {
-  const bool pv = p.per_vertex;
   for (int s = 0; s < 2; ++s) {
     plan.L[s] = std::min<int32_t>(p.window_L, n[s]);
     plan.R[s] = std::min<int32_t>(p.reverse_L, plan.L[s]);
-    // the dense block is tiled by 128 rows (at most kMaxPVHubT in the
-    // per-vertex pass)
-    plan.T[s] = std::min<int32_t>(pv ? std::min(p.hub_T, kMaxPVHubT) : p.hub_T, n[s] / 128 * 128);
   }
-  // The dense path needs a block on both sides of the pair.
-  if (plan.T[0] == 0 || plan.T[1] == 0) plan.T[0] = plan.T[1] = 0;
+  hub_rows(n, p, plan.T);
   plan.acc_width = (std::max(plan.L[0], plan.L[1]) + 3) / 4 * 4;  // whole 16-byte pieces
   if (p.per_vertex)  // p and n apart (32 bits each) fit as well
     plan.acc_width = std::min(2 * plan.acc_width, kPVWindowPacked);
