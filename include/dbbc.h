@@ -226,8 +226,9 @@ int dbbc_count(dbbc_graph *g, const dbbc_options *opt, dbbc_counts *out_host, vo
  *              id order, caller-owned device memory; any may be NULL; they
  *              are overwritten
  *   out_host : the global counts of the same pass (host memory, may be NULL)
- * The pass keeps a plan and four n-sized int64 arrays of its own on the
- * handle, beside those of dbbc_count. */
+ * The pass keeps on the handle, beside the plan of dbbc_count, a plan of its
+ * own (with counters of heavy pivots' items, at most 64 MiB or 24 bytes per
+ * edge, whichever is more), four int64 words per vertex and 1 MiB. */
 int dbbc_count_per_vertex(dbbc_graph *g, const dbbc_options *opt, int64_t *bal_u, int64_t *bal_v,
                           int64_t *unb_u, int64_t *unb_v, dbbc_counts *out_host, void *hip_stream);
 

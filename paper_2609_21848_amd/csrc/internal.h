@@ -129,19 +129,21 @@ struct PlanParams {
   int32_t reverse_L = 0;
   int32_t small_work = 0;
   int32_t part_work = 0;
-  bool per_vertex = false;  // plan for the per-vertex pass (no multi-part items)
+  bool per_vertex = false;  // plan for the per-vertex pass
   bool wide_all = false;    // per-vertex plans: flag every run kMidWide
   bool host_planner = false;  // count plans: make the plan on the host
   // bytes the parts' counters may take before part_work is raised (0: as
   // part_work says, which the caller chose)
   int64_t part_room = 0;
-  // per-vertex plans: wedge budget of a part of a direct item
+  // per-vertex plans: wedge budget of a part of a direct item, and the bytes
+  // that the split items' counters may take before it is raised
   int64_t pv_part_work = int64_t{1} << 62;
+  int64_t pv_part_room = 0;
   bool operator==(const PlanParams& o) const {
     return hub_T == o.hub_T && window_L == o.window_L && reverse_L == o.reverse_L &&
            small_work == o.small_work && part_work == o.part_work && per_vertex == o.per_vertex &&
            wide_all == o.wide_all && host_planner == o.host_planner && part_room == o.part_room &&
-           pv_part_work == o.pv_part_work;
+           pv_part_work == o.pv_part_work && pv_part_room == o.pv_part_room;
   }
 };
 
@@ -252,8 +254,14 @@ void set_part_room(const HostGraph& g, PlanParams& p);
 // Largest default part budget.
 constexpr int32_t kMaxPartWork = 1 << 24;
 // Whether parts that take `bytes` of counters are too many for p: raises
-// p.part_work for another plan.
+// p.part_work (per-vertex plans: p.pv_part_work, until they fit) for another
+// plan.
 inline bool larger_parts(PlanParams& p, int64_t bytes) {
+  if (p.per_vertex) {
+    if (bytes <= p.pv_part_room || p.pv_part_work >= int64_t{1} << 61) return false;
+    p.pv_part_work *= 2;
+    return true;
+  }
   if (p.part_room == 0 || bytes <= p.part_room || p.part_work >= kMaxPartWork) return false;
   p.part_work = p.part_work > kMaxPartWork / 4 ? kMaxPartWork : 4 * p.part_work;
   return true;

@@ -103,6 +103,13 @@ PlanParams default_params(const HostGraph& g, int32_t hub_slots) {
       std::max<int64_t>(1 << 15, std::min(g.wedges_vp / std::max(1, hub_slots),
                                           (1 << 16) + g.wedges_vp / (8 * std::max(1, hub_slots))));
   p.pv_part_work = pv_budget > (1 << 21) ? kMaxPartWork : pv_budget;
+  // Each split item's key windows take up to 128 KiB of counters each, which
+  // every pass clears, so a graph of thousands of pivots just above the budget
+  // (2,000 of 200K wedges each over 4M edges) would hold 153 MB of them, more
+  // than its plan's runs.  Past 24 bytes an edge, as in the count, and 64 MiB
+  // (334K edges take 9.3 MB, 28 bytes an edge) the budget is raised: that graph
+  // 51 MB, per-vertex 1.27 -> 1.24 ms, per-edge 3.36 -> 3.26.
+  p.pv_part_room = std::max<int64_t>(int64_t{64} << 20, 24 * g.m);
   set_part_room(g, p);
   return p;
 }

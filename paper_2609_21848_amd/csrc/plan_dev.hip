@@ -1444,8 +1444,10 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     LAUNCH(k_scan_rows, kCounters, kScanThreads, counts, stride, all_row_chunks, row_chunks[0], totals_d);
     PD_TRY(hipMemcpyAsync(tot, totals_d, sizeof(tot), hipMemcpyDeviceToHost, st));
     PD_TRY(hipStreamSynchronize(st));
-    if (p.per_vertex || !larger_parts(q, static_cast<int64_t>(tot[kRevAcc] + tot[kDirectParts]) * hp.acc_width * 4)) break;
-    for (PSide& P : S.s) P.part_work = static_cast<unsigned long long>(q.part_work);
+    // per-vertex plans: a split item's parts share its windows' counters
+    const unsigned long long slots = tot[kRevAcc] + (p.per_vertex ? tot[kDirectSplit] : tot[kDirectParts]);
+    if (!larger_parts(q, static_cast<int64_t>(slots) * hp.acc_width * 4)) break;
+    for (PSide& P : S.s) P.part_work = static_cast<unsigned long long>(p.per_vertex ? q.pv_part_work : q.part_work);
     PD_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(words), 3, 0ull, st));
   }
   const unsigned long long* at1 = tot + kCounters;
