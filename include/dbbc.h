@@ -247,8 +247,8 @@ int dbbc_count_per_vertex(dbbc_graph *g, const dbbc_options *opt, int64_t *bal_u
  *              are overwritten.  A record dropped as a duplicate reads 0
  *              (the last record of the pair carries the edge's counts).
  *   out_host : the global counts of the same pass (host memory, may be NULL)
- * Besides the per-vertex pass's state, the handle keeps four int64 arrays
- * and two int32 maps of the edge count on the device. */
+ * The handle keeps the per-vertex pass's plan (both passes share it), and six
+ * int64 arrays and two int32 maps of the edge count. */
 int dbbc_count_per_edge(dbbc_graph *g, const dbbc_options *opt, int64_t *bal_e, int64_t *unb_e,
                         dbbc_counts *out_host, void *hip_stream);
 

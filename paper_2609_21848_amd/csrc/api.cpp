@@ -434,6 +434,35 @@ bool plans_on_device(const dbbc_graph* g, const dbbc::PlanParams& p) {
   return kinds * (static_cast<int64_t>(g->host.n_u) + g->host.n_v) + 1 <= INT32_MAX && g->host.m + 1 <= INT32_MAX;
 }
 
+// The buffers that the per-vertex and per-edge passes sum their credits in, as
+// far as they are there (each pass reserves its own), into a per-vertex plan's
+// side table; returns whether the table changed.
+bool set_local_buffers(dbbc_graph* g, dbbc::DevSideConst side[2]) {
+  bool changed = false;
+  auto set = [&](unsigned long long*& to, const DevBuf& b, size_t at = 0) {
+    unsigned long long* p = b.p ? b.as<unsigned long long>() + at : nullptr;
+    changed = changed || to != p;
+    to = p;
+  };
+  for (int s = 0; s < 2; ++s) {
+    dbbc::DevSideConst& c = side[s];
+    set(c.bal, g->pv_out[s][0]);
+    set(c.unb, g->pv_out[s][1]);
+    set(c.bal_mid, g->pv_out[1 - s][0]);
+    set(c.unb_mid, g->pv_out[1 - s][1]);
+    set(c.mid_pairs, g->pv_mid[1 - s]);
+    set(c.key_bal, g->pv_keys[s]);
+    set(c.key_unb, g->pv_keys[s], dbbc::kPVKeyRanks);
+    set(c.epack, g->pe_out[s][0]);
+    set(c.ewb, g->pe_out[s][1]);
+    set(c.ewu, g->pe_out[s][2]);
+    set(c.epack_o, g->pe_out[1 - s][0]);
+    set(c.ewb_o, g->pe_out[1 - s][1]);
+    set(c.ewu_o, g->pe_out[1 - s][2]);
+  }
+  return changed;
+}
+
 int ensure_plan_into(dbbc_graph* g, const dbbc::PlanParams& p, hipStream_t st, DevPlan& d) {
   if (d.valid && d.host.p == p) return DBBC_OK;
   d.valid = false;
@@ -610,23 +639,11 @@ int ensure_plan_into(dbbc_graph* g, const dbbc::PlanParams& p, hipStream_t st, D
       c.small_owner = d.small_owner.as<int32_t>();
       c.orig = g->orig[s].as<int32_t>();
       c.orig_mid = g->orig[1 - s].as<int32_t>();
-      c.bal = g->pv_out[s][0].as<unsigned long long>();
-      c.unb = g->pv_out[s][1].as<unsigned long long>();
-      c.bal_mid = g->pv_out[1 - s][0].as<unsigned long long>();
-      c.unb_mid = g->pv_out[1 - s][1].as<unsigned long long>();
-      c.mid_pairs = g->pv_mid[1 - s].as<unsigned long long>();
-      c.key_bal = g->pv_keys[s].as<unsigned long long>();
-      c.key_unb = c.key_bal + dbbc::kPVKeyRanks;
       c.seg_edge = d.seg_edge.as<uint32_t>();
       c.small_seg_edge = d.small_seg_edge.as<uint32_t>();
-      c.epack = g->pe_out[s][0].as<unsigned long long>();
-      c.ewb = g->pe_out[s][1].as<unsigned long long>();
-      c.ewu = g->pe_out[s][2].as<unsigned long long>();
-      c.epack_o = g->pe_out[1 - s][0].as<unsigned long long>();
-      c.ewb_o = g->pe_out[1 - s][1].as<unsigned long long>();
-      c.ewu_o = g->pe_out[1 - s][2].as<unsigned long long>();
     }
   }
+  if (p.per_vertex) set_local_buffers(g, d.side);
   HIP_TRY(d.sides.alloc(sizeof(d.side)));
   HIP_TRY(hipMemcpyAsync(d.sides.p, d.side, sizeof(d.side), hipMemcpyHostToDevice, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -1071,7 +1088,7 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   p.wide_all = edge && opt && (opt->flags & DBBC_OPT_WIDE_EDGES);
   const int32_t n[2] = {g->host.n_u, g->host.n_v};
   const size_t m = static_cast<size_t>(g->host.m);
-  for (int s = 0; s < 2; ++s) {
+  for (int s = 0; s < 2 && !edge; ++s) {
     for (int k = 0; k < 2; ++k)
       HIP_TRY(g->pv_out[s][k].reserve(static_cast<size_t>(n[s]) * sizeof(unsigned long long)));
     HIP_TRY(g->pv_mid[s].reserve(2 * static_cast<size_t>(n[s]) * sizeof(unsigned long long)));
@@ -1091,18 +1108,12 @@ int local_counts(dbbc_graph* g, const dbbc_options* opt, int64_t* const vout[2][
   if (rc != DBBC_OK) return rc;
   DevPlan& d = g->pv_plan;
   const dbbc::HostPlan& hp = d.host;
-  // the per-edge buffers may have been allocated after the plan's side table
-  if (edge && d.side[0].epack != g->pe_out[0][0].as<unsigned long long>()) {
-    for (int s = 0; s < 2; ++s) {
-      d.side[s].epack = g->pe_out[s][0].as<unsigned long long>();
-      d.side[s].ewb = g->pe_out[s][1].as<unsigned long long>();
-      d.side[s].ewu = g->pe_out[s][2].as<unsigned long long>();
-      d.side[s].epack_o = g->pe_out[1 - s][0].as<unsigned long long>();
-      d.side[s].ewb_o = g->pe_out[1 - s][1].as<unsigned long long>();
-      d.side[s].ewu_o = g->pe_out[1 - s][2].as<unsigned long long>();
-    }
+  // a pass's buffers may have been allocated after the plan's side table
+  if (set_local_buffers(g, d.side)) {
+    d.valid = false;
     HIP_TRY(hipMemcpyAsync(d.sides.p, d.side, sizeof(d.side), hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
+    d.valid = true;
   }
   unsigned long long* ctl = g->ctl.as<unsigned long long>();
   dbbc::Ranges zero(st);
