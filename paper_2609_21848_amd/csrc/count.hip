@@ -43,7 +43,6 @@ namespace dev {
 // 2.70 -> 2.55 ms (the next item's fetches alone).
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectKeys = 32768;
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 template <int kKeys, int kThreads>
 __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a) {

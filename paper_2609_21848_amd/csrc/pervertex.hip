@@ -320,11 +320,12 @@ __device__ __forceinline__ void pv_direct_tally(const Item& it, const DevSideCon
 // wedge): balanced | unbalanced << 16.  A chunk's four words are read before any
 // is used, and its run's sums stay in registers until the run ends; then the
 // run's lane takes the wavefront's sums.  Staged shares that are not zero go to
-// their run's LDS slot.  (p, n < 2^16 and at most kPVWindowPacked keys: a run's
-// credits stay below 2^31.)
+// their run's LDS slot.
 template <bool kEdge>
 struct PackedCredit {
   static constexpr bool kStaged = true, kChunk4 = true;
+  // a run has at most one entry per key of the window, p and n are below 2^16
+  static_assert(uint64_t{kPVWindowPacked} * 65535 < (uint64_t{1} << 32), "a run's credits fit 32 bits");
   const uint32_t* C;
   unsigned long long* cbu;           // per run lane: balanced | unbalanced << 32
   global_t<unsigned long long>* ep;  // per-edge credits, as in Credit
@@ -674,7 +675,7 @@ __global__ void k_vertex_out(VertexOutArgs a) {
 // their credits are summed per workgroup in LDS and reach HBM once per
 // workgroup at the end (a launch holds the items of one side).  A pair's
 // credit is below 2^15 (p + n <= 255), so the workgroup's 32-bit key sums
-// hold up to 2^16 items (the launch sizes its grid for that).
+// hold up to kPVReverseBlockItems items (the launch sizes its grid for that).
 // Bound by instruction issue at the 12 wavefronts per CU that the LDS holds
 // (VALU busy half of the time) and by an item's chain of dependent loads.  So the
 // next item's descriptor, first runs and mids are loaded under the current item
@@ -686,6 +687,11 @@ __global__ void k_vertex_out(VertexOutArgs a) {
 constexpr int kPVReverseWaves = 12;
 constexpr int kPVReverseThreads = kPVReverseWaves * kWave;
 constexpr int kPVReverseWords = kMaxReverseL / 2;
+constexpr int64_t kPVReverseBlockItems = int64_t{1} << 16;
+// (wavefronts take items in turn: one more each at most)
+static_assert((kPVReverseBlockItems + kPVReverseWaves) * (kReverseMaxSegs * (kReverseMaxSegs - 1) / 2) <
+                  (int64_t{1} << 32),
+              "a workgroup's key credits fit 32 bits");
 // staging rounds whose entries stay in registers from the tally to the credits
 // (50M edges, per-vertex, side U: 10.9 ms with none, 10.5 with 1 or 2, 10.6 with 3,
 // 11.0 with 4, which spill; per-edge 20M: 6.69, 6.62, 7.02 ms with 0, 1, 2)
@@ -694,23 +700,23 @@ constexpr int pv_reverse_kept(bool edge) { return edge ? 1 : 2; }
 // Credit walk of a reverse batch.  A wedge's shares are one byte permutation of
 // its key's counter word: byte p | n << 8 of the key's half, as own sign's count
 // | other's << 16; less 1 (its own wedge), that is its balanced | unbalanced << 16.
-// A chunk's four counter words are read before any is used, and its run's sum
-// stays in one register per lane (at most 16 chunks of 4 shares of at most 255)
-// until the run ends; then the run's lane takes the wavefront's sum.  Staged
-// shares that are not zero go to their run's LDS slot.
+// A chunk's four counter words are read before any is used, and its run's sums
+// stay in registers until the run ends; then the run's lane takes the wavefront's
+// sums.  Staged shares that are not zero go to their run's LDS slot.
 template <bool kEdge>
 struct ReverseCredit {
   static constexpr bool kStaged = true, kChunk4 = true;
+  // ... the keys of the reverse window, and p, n are at most the item's runs
+  static_assert(uint64_t{kMaxReverseL} * kReverseMaxSegs < (uint64_t{1} << 32), "a run's credits fit 32 bits");
   uint32_t base;             // LDS address of the counter words, aligned to their size
   unsigned long long* cbu;   // per run lane: balanced | unbalanced << 32
   global_t<unsigned long long>* ep;  // per-edge credits, as in Credit
   global_t<unsigned long long>* wb;
   global_t<unsigned long long>* wu;
   uint64_t wide = 0;
-  uint32_t cur = kNoRun, sum = 0;  // the chunks' run (wavefront-uniform), and its shares so far
+  uint32_t cur = kNoRun, sb = 0, su = 0, slots = 0;  // the chunks' run (wavefront-uniform), its sums and slots per lane
   uint32_t mb = 0, mu = 0;         // this lane's run: the chunks' credits
   static constexpr uint32_t kNoRun = 0xffffffffu;
-  static_assert(kMaxReverseL / kChunk * 4 * 255 < 65536, "a run's chunk shares fit 16 bits per lane");
   __device__ __forceinline__ uint32_t word(uint32_t e) const {
     return *(const lds_u32*)static_cast<uintptr_t>(base | (e & (4 * kPVReverseWords - 4)));
   }
@@ -731,8 +737,8 @@ struct ReverseCredit {
   }
   __device__ __forceinline__ void put() {
     if (cur == kNoRun) return;
-    const uint32_t b = wave_sum32(sum & 0xffffu), u = wave_sum32(sum >> 16);
-    sum = 0;
+    const uint32_t b = wave_sum32(sb - slots), u = wave_sum32(su);
+    sb = su = slots = 0;
     const bool own = static_cast<uint32_t>(lane_id()) == cur;
     mb += own ? b : 0u;
     mu += own ? u : 0u;
@@ -750,9 +756,12 @@ struct ReverseCredit {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const uint32_t c = off[q] < rem ? counts(w[q], e[q], g) : 1u;
-      sum += c - 1u;
+      const u16x2 h = __builtin_bit_cast(u16x2, c);
+      sb = __builtin_amdgcn_udot2(h, u16x2{1, 0}, sb, false);
+      su = __builtin_amdgcn_udot2(h, u16x2{0, 1}, su, false);
       edge(j, pos + off[q], c - 1u);
     }
+    slots += 4;
   }
   __device__ __forceinline__ void add_staged(const Staged& s) {
     uint32_t w[kStageU];
@@ -782,8 +791,7 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
   // a run's mid credits of staged wedges, balanced | unbalanced << 32: each at
   // most the run's length (at most 4096) times 255
   __shared__ unsigned long long cbu[kPVReverseWaves][kWave];
-  // the workgroup's key credits, balanced | unbalanced << 32 (each half
-  // below 2^31, see above)
+  // the workgroup's key credits, balanced | unbalanced << 32
   __shared__ unsigned long long ksum[kEdge ? 1 : kMaxReverseL];
   // chunk slots in flight per walk: as many as the registers allow (the
   // per-edge walks keep positions too)
@@ -915,8 +923,9 @@ __global__ __launch_bounds__(kPVReverseThreads) void k_pv_reverse(SmallArgs a) {
       }
     }
     // The owner's credits, and the pass's totals: a butterfly of the item
-    // credits its two mids (p, n <= 255 and at most 255 runs of at most 4,096
-    // wedges: sums below 2^28).
+    // credits its two mids.
+    static_assert(uint64_t{kReverseMaxSegs} * kMaxReverseL * kReverseMaxSegs < (uint64_t{1} << 32),
+                  "an item's credits fit 32 bits");
     const uint32_t item_b = wave_sum32(cb) / 2, item_u = wave_sum32(cu) / 2;
     tot_b += item_b;
     tot_u += item_u;
@@ -1285,8 +1294,7 @@ hipError_t direct_(const DirectArgs& a, int grid, hipStream_t st) {
 template <bool kEdge>
 hipError_t reverse_(const SmallArgs& a, int grid, hipStream_t st) {
   if (a.n_items == 0) return hipSuccess;
-  // at most 2^16 items per workgroup (its 32-bit key sums)
-  const int64_t per = int64_t{1} << 16;
+  const int64_t per = dev::kPVReverseBlockItems;
   const int64_t need = (static_cast<int64_t>(a.n_items) + per - 1) / per;
   if (grid < need) grid = static_cast<int>(need);
   hipLaunchKernelGGL(dev::k_pv_reverse<kEdge>, dim3(grid), dim3(dev::kPVReverseThreads), 0, st, a);

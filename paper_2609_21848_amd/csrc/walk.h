@@ -31,6 +31,7 @@ template <class T>
 using global_t = __attribute__((address_space(1))) T;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 template <class T>
 using const_t = __attribute__((address_space(4))) T;
 
