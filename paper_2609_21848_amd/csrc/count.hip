@@ -33,9 +33,9 @@ namespace dev {
 // sweep, barrier), 7 us for a few thousand wedges with one workgroup on a CU
 // at a time, so:
 //  - what the next item needs is fetched under the current one: the ticket
-//    from the first wavefront's last batch on, the descriptor (vector loads,
-//    which the sweep's LDS accesses do not wait for) under the sweep, its
-//    first runs before the barrier that ends the sweep;
+//    (after the walk, or before it: see early_work), the descriptor (vector
+//    loads, which the sweep's LDS accesses do not wait for) under the sweep,
+//    its first runs before the barrier that ends the sweep;
 //  - where every key window of the launch is narrow, smaller workgroups with
 //    fewer counters share a CU (see direct_shape).
 // Measured: 512 graphs of up to 50,000 edges, 43,400 items of 3,550 wedges on
@@ -80,6 +80,14 @@ __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a) {
     for (int k = 0; k < kItemWords; ++k) o[k] = readlane(w, k);
     return it;
   };
+  // An item takes the next ticket before its own walk only where it ends long before
+  // the launch does (a quarter of the mean workgroup's remaining work at most): the
+  // next item waits for it, and one that a heavy item of a short launch held back
+  // ended the launch.  Ticket always before / always after / by this rule, us:
+  // complete 400 x 400 (398 items) 34.9 / 28.2 / 28.5, 1,000 pivots of 4,000 keys 82
+  // / 74 / 75, a batch of 100 graphs (110K items) 1942 / 2222 / 1977.
+  const float early_work =
+      0.25f * static_cast<float>(a.wedges) / (static_cast<float>(a.n_items) * static_cast<float>(gridDim.x));
   if (tid == 0) item_sh = static_cast<int32_t>(atomicAdd(a.queue, 1u));
   __syncthreads();
   int32_t i = __builtin_amdgcn_readfirstlane(item_sh);
@@ -93,10 +101,11 @@ __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a) {
     // the wavefronts take the item's segments interleaved (wavefront w the
     // segments w, w + kWaves, ...), 64 per batch, so that every wavefront
     // gets a similar mix of long and short runs
+    const bool early = static_cast<float>(it.work) <= static_cast<float>(a.n_items - i) * early_work;
     uint32_t ticket = 0;
     for (uint32_t k0 = it.seg_begin + wave;;) {
       const bool last = k0 >= seg_end || seg_end - k0 <= kThreads;
-      if (last && tid == 0) ticket = atomicAdd(a.queue, 1u);
+      if (last && early && tid == 0) ticket = atomicAdd(a.queue, 1u);
       if (k0 < seg_end)
         walk_regs<8, false, true>(first, adj, Marks<uint8_t>{mtab[wave], mflag[wave]}, a.long_len,
                                   DirectTallyBF<kKeys>{cnt, cnt + kKeys + tid});
@@ -104,10 +113,10 @@ __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a) {
       k0 += kThreads;
       first = load_seg<false>(sc.segs, k0, seg_end, kWaves);
     }
-    if (tid == 0) item_sh = static_cast<int32_t>(ticket);
+    if (tid == 0) item_sh = static_cast<int32_t>(early ? ticket : atomicAdd(a.queue, 1u));
     __syncthreads();
-    const int32_t ni = __builtin_amdgcn_readfirstlane(item_sh);
-    const uint32_t next_words = fetch(ni);
+    i = __builtin_amdgcn_readfirstlane(item_sh);
+    const uint32_t next_words = fetch(i);
     if (it.flags & kItemMultiPart) {
       // write the part's counters for the whole key window (zeros included)
       global_t<uint32_t>* __restrict__ dst = as_global(sc.acc) + static_cast<size_t>(it.acc_slot) * sc.acc_width;
@@ -172,7 +181,7 @@ __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a) {
       sq2 += sq32;
       pnx += pn32 >> 1;  // a sum of 2 p n terms: even
     }
-    const bool done = ni >= a.n_items;
+    const bool done = i >= a.n_items;
     const uint32_t graph = it.graph;
     if (!done) {
       it = unpack(next_words);
