@@ -36,10 +36,10 @@ namespace dev {
 //    (after the walk, or before it: see early_work), the descriptor (vector
 //    loads, which the sweep's LDS accesses do not wait for) under the sweep,
 //    its first runs before the barrier that ends the sweep;
-//  - where every key window of the launch is narrow, smaller workgroups with
-//    fewer counters share a CU (see direct_shape).
+//  - where every key window of the launch is narrow, two smaller workgroups with
+//    half the counters can share a CU (see narrow_direct).
 // Measured: 512 graphs of up to 50,000 edges, 43,400 items of 3,550 wedges on
-// average 1,170 -> 593 us (four workgroups a CU); 50M edges, 54,600 items
+// average 1,170 -> 580 us (two workgroups a CU); 50M edges, 54,600 items
 // 2.70 -> 2.55 ms (the next item's fetches alone).
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectKeys = 32768;
@@ -759,45 +759,15 @@ hipError_t launch_assemble_reduces(const AssembleSrc* srcs, int k, Reduce* dst, 
   return hipGetLastError();
 }
 
-// The workgroup shape of a direct launch: counters for 32,768, 16,384 or 8,192
-// keys (as many as the launch's widest window) with 1,024, 512 or 256
-// threads, so 1, 2 or 4 workgroups on a CU.  A narrow shape overlaps the
-// fixed part of its items with other items' (about 7 us per item, the whole
-// of it on a wide workgroup's CU), but a heavy item has fewer wavefronts:
-// the shape is the one whose estimated time, the larger of the heaviest item
-// alone and all items spread over the CUs, is least.  Rates measured at 5.3
-// wedges/ns on a CU full of wavefronts.
-static int direct_shape(const DirectArgs& a, int cus) {
-  int best = 0;
-  double best_us = 0;
-  for (int shape = 0; shape < 3; ++shape) {
-    if (a.max_key > (dev::kDirectKeys >> shape)) break;
-    const double per_cu = 1 << shape, rate = 5300.0;  // workgroups on a CU, wedges/us of a CU
-    const double spread = static_cast<double>(a.n_items) * 7.0 / (cus * per_cu) +
-                          static_cast<double>(a.wedges) / (rate * cus);
-    const double heaviest = 7.0 + static_cast<double>(a.max_work) * per_cu / rate;
-    const double us = spread > heaviest ? spread : heaviest;
-    if (shape == 0 || us < best_us) {
-      best = shape;
-      best_us = us;
-    }
-  }
-  return best;
-}
-
 hipError_t launch_direct(const DirectArgs& a, int cus, hipStream_t st) {
   if (a.n_items == 0) return hipSuccess;
-  const int shape = direct_shape(a, cus);
-  const int grid = a.n_items < (cus << shape) ? a.n_items : cus << shape;
-  if (shape == 0)
-    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys, dev::kDirectThreads>), dim3(grid), dim3(dev::kDirectThreads),
-                       0, st, a);
-  else if (shape == 1)
-    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys / 2, dev::kDirectThreads / 2>), dim3(grid),
-                       dim3(dev::kDirectThreads / 2), 0, st, a);
+  static_assert(dev::kDirectKeys == 2 * kNarrowDirectKeys, "a narrow workgroup has half the counters");
+  if (narrow_direct(a.n_items, a.wedges, a.max_work, a.max_key, cus))
+    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys / 2, dev::kDirectThreads / 2>),
+                       dim3(std::min(a.n_items, 2 * cus)), dim3(dev::kDirectThreads / 2), 0, st, a);
   else
-    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys / 4, dev::kDirectThreads / 4>), dim3(grid),
-                       dim3(dev::kDirectThreads / 4), 0, st, a);
+    hipLaunchKernelGGL((dev::k_direct<dev::kDirectKeys, dev::kDirectThreads>), dim3(std::min(a.n_items, cus)),
+                       dim3(dev::kDirectThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -85,6 +85,31 @@ constexpr int64_t reverse_small_work(bool per_vertex, int64_t small_work) {
   return small_work < most ? small_work : most;
 }
 
+// Whether a count's direct launch takes narrow workgroups, two on a CU with 512
+// threads and counters for kNarrowDirectKeys keys each, or wide ones, one on a CU
+// with 1,024 threads and counters for the widest window (max_key: the launch's).
+// An item costs a wide workgroup about 7 us beside its wedges and a narrow one
+// 1.9 times that (two at once gain little on it: chains of loads), a CU walks 6.5
+// wedges/ns with one wide and 1.2 times that with two narrow ones (the barriers
+// of one are filled by the other), and a launch ends with some of its heaviest
+// items alone on their CUs, where a narrow workgroup has half the wavefronts.
+// The shape is the one with the shorter estimate: over 169 launches timed with
+// both (500 to 5M wedges an item, alone and in batches) 0.3 % behind the better
+// one on average, 5 % at most.  Wide / narrow, us: a batch of 512 small graphs
+// 583 / 498, 2,000 pivots of 8,000 keys 120 / 108, complete 3000 x 3000 3492 /
+// 3237, 5000 x 300 149 / 187, two graphs of 300K edges 94 / 116.  (Four
+// workgroups of 256 threads lost to two: 5000 x 300 279, 3000 x 3000 alone 2 %
+// better.)
+constexpr int32_t kNarrowDirectKeys = 16384;
+inline bool narrow_direct(int32_t n_items, uint64_t wedges, uint64_t max_work, int32_t max_key, int cus) {
+  if (max_key > kNarrowDirectKeys) return false;
+  const auto estimate = [&](double per_cu, double item_us, double rate) {  // rate: wedges/us of a CU
+    return n_items * item_us / (cus * per_cu) + static_cast<double>(wedges) / (rate * cus) +
+           0.75 * (item_us + static_cast<double>(max_work) * per_cu / rate);
+  };
+  return estimate(2, 7 * 1.9, 6500 * 1.2) < estimate(1, 7, 6500);
+}
+
 // Reverse items keep two 8-bit counters per key (symmetric, asymmetric), so
 // a reverse item (or item part) has at most this many segments.
 constexpr uint32_t kReverseMaxSegs = 255;
