@@ -810,9 +810,12 @@ int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::stri
     const int rc = check_plan_sizes(z, err);
     if (rc != DBBC_OK) return rc;
   }
-  // parts first (they are the heaviest), then the single-part items
   plan.direct_items = std::move(parts);
   plan.direct_items.insert(plan.direct_items.end(), singles.begin(), singles.end());
+  if (!pv)  // heaviest first, the parts among the others
+    std::stable_sort(plan.direct_items.begin(), plan.direct_items.end(), [](const Item& a, const Item& b) {
+      return direct_order_work(a.work, a.seg_count) > direct_order_work(b.work, b.seg_count);
+    });
   // heavy tail pivots first as well
   std::stable_sort(plan.hash_items.begin(), plan.hash_items.end(),
                    [&](const Item& a, const Item& b) { return item_work(plan, a) > item_work(plan, b); });

@@ -791,6 +791,11 @@ __device__ __forceinline__ uint32_t work_key(unsigned long long work) {
   return 0x7fffu - f;
 }
 
+// A count's direct items and parts (see direct_order_work).
+__device__ __forceinline__ uint32_t direct_key(unsigned long long work, uint32_t runs) {
+  return work_key(direct_order_work(work, runs));
+}
+
 struct ItemOut {
   // small items (grouped later): work | hub pivot << 30 | side << 31, first run, owner
   uint32_t* small_key;
@@ -875,7 +880,7 @@ __global__ __launch_bounds__(kThreads) void k_items(PSides S, const unsigned lon
           o.split_part[q[kDirectSplit]] = static_cast<uint32_t>(q[kDirectParts]);
         } else {
           o.direct[q[kDirect] - q[kDirectSplit]] = it;
-          o.direct_key[q[kDirect] - q[kDirectSplit]] = work_key(c.work);
+          o.direct_key[q[kDirect] - q[kDirectSplit]] = direct_key(c.work, c.nseg);
         }
       } else if (c.nparts == 0) {
         o.rev[q[kRev]] = it;
@@ -1186,6 +1191,7 @@ struct GatherOut {
 // The parts of split direct items, and (count plans) their reduces.
 struct SplitOut {
   Item* items;
+  uint32_t* key;        // count plans: the parts' place in the order of all direct items
   Reduce* reduces;
   uint32_t acc0;        // count plans: first accumulator slot of the direct parts (one each)
   bool pv;              // per-vertex plans: an item's parts share an accumulator
@@ -1206,7 +1212,10 @@ __global__ void k_split_parts(PSides S, const Item* split, const uint32_t* part_
       Item part = part_of(it, it.seg_begin, nseg, work, first, p, np);
       part.flags |= kItemMultiPart;
       part.acc_slot = static_cast<int32_t>(o.pv ? i : o.acc0 + at + p);
-      if (o.pv) part.work = (p << 16) | np;
+      if (o.pv)
+        part.work = (p << 16) | np;
+      else
+        o.key[at + p] = direct_key(part.work, part.seg_count);
       o.items[at + p] = part;
     }
     if (o.pv) continue;
@@ -1479,7 +1488,8 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   unsigned long long* ctl = nullptr;
   PartStart *dir_parts = nullptr, *hub_parts = nullptr;
   const uint32_t n_chunks = static_cast<uint32_t>((n_small + kGroupChunk - 1) / kGroupChunk);
-  const int64_t n_order = std::max(n_hash, n_direct);
+  const int64_t n_direct_key = p.per_vertex ? n_direct : n_dir_items;  // direct items that are ordered
+  const int64_t n_order = std::max(n_hash, n_direct_key);
   sc = Scratch{};
   for (int sizing = 1; sizing >= 0; --sizing) {
     if (!sizing) {
@@ -1494,8 +1504,8 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
     local_of = sc.take<uint32_t>(n_small);
     io.hash = sc.take<Item>(n_hash);
     io.hash_key = sc.take<uint32_t>(n_hash);
-    io.direct = sc.take<Item>(n_direct);
-    io.direct_key = sc.take<uint32_t>(n_direct);
+    io.direct = sc.take<Item>(n_direct_key);
+    io.direct_key = sc.take<uint32_t>(n_direct_key);
     io.split = sc.take<Item>(n_split);
     io.split_part = sc.take<uint32_t>(n_split);
     order_buf = sc.take<uint32_t>(2 * static_cast<int64_t>(Carve::round(static_cast<size_t>(n_order))));
@@ -1557,13 +1567,14 @@ void plan(const DevGraphView& g, const PlanParams& p, hipStream_t st, HostPlan& 
   // hash items, heaviest first
   Item* hash = alloc_n<Item>(out.hash_items, n_hash);
   order_items(io.hash_key, n_hash, order_buf, ctl, io.hash, hash, st);
-  // direct items: the parts of split items, then the others, heaviest first
+  // direct items, heaviest first (per-vertex plans: the parts of split items, then
+  // the others: parts are tallied by a launch of their own)
   Item* direct = alloc_n<Item>(out.direct_items, n_dir_items);
   if (n_split > 0)
     LAUNCH(k_split_parts, grid_for(n_split), kThreads, S, io.split, io.split_part, static_cast<uint32_t>(n_split),
            static_cast<uint32_t>(tot[kDirectParts]), dir_parts,
-           SplitOut{direct, io.reduces + tot[kRevReduces], static_cast<uint32_t>(tot[kRevAcc]), p.per_vertex});
-  order_items(io.direct_key, n_direct, order_buf, ctl, io.direct, direct + tot[kDirectParts], st);
+           SplitOut{p.per_vertex ? direct : io.direct + n_direct, io.direct_key + n_direct, io.reduces + tot[kRevReduces], static_cast<uint32_t>(tot[kRevAcc]), p.per_vertex});
+  order_items(io.direct_key, n_direct_key, order_buf, ctl, io.direct, direct + (p.per_vertex ? tot[kDirectParts] : 0), st);
   PD_TRY(out.acc.alloc(std::max<size_t>(static_cast<size_t>(acc_slots) * hp.acc_width * sizeof(uint32_t), 16)));
 
   // the dense block's signs
