@@ -507,18 +507,12 @@ int ensure_plan_into(dbbc_graph* g, const dbbc::PlanParams& p, hipStream_t st, D
   } else {
     rc = ensure_host(g, st);
     if (rc != DBBC_OK) return rc;
-    dbbc::PlanParams q = p;
-    for (;;) {
-      hp = dbbc::HostPlan();
-      try {
-        rc = dbbc::make_plan(g->host, q, hp, err);
-      } catch (const std::bad_alloc&) {
-        return fail(DBBC_E_OOM, "host allocation failed while planning");
-      }
-      if (rc != DBBC_OK) return fail(rc, err);
-      if (!dbbc::larger_parts(q, static_cast<int64_t>(hp.acc_slots) * hp.acc_width * 4)) break;
+    try {
+      rc = dbbc::make_plan(g->host, p, hp, err, /*fit_parts=*/true);
+    } catch (const std::bad_alloc&) {
+      return fail(DBBC_E_OOM, "host allocation failed while planning");
     }
-    hp.p = p;
+    if (rc != DBBC_OK) return fail(rc, err);
     HIP_TRY(upload(d.segs, hp.segs, st));
     HIP_TRY(upload(d.seg_mid, hp.seg_mid, st));
     HIP_TRY(upload(d.small_seg_mid, hp.small_seg_mid, st));

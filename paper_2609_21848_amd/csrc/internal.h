@@ -304,6 +304,7 @@ int check_plan_params(const PlanParams& p, std::string& err);
 // The windows L, R, the dense block T per side and the accumulator width of
 // a plan of a graph with n[s] vertices per side.
 void plan_windows(const int32_t n[2], const PlanParams& p, HostPlan& plan);
-int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::string& err);
+// (fit_parts: the part budget is raised until the parts' counters fit p's room)
+int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::string& err, bool fit_parts = false);
 
 }  // namespace dbbc

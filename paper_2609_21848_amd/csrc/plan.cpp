@@ -452,7 +452,7 @@ void plan_windows(const int32_t n[2], const PlanParams& p, HostPlan& plan) {
     plan.acc_width = std::min(2 * plan.acc_width, kPVWindowPacked);
 }
 
-int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::string& err) {
+int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::string& err, bool fit_parts) {
   {
     const int rc = check_plan_params(p, err);
     if (rc != DBBC_OK) return rc;
@@ -746,60 +746,69 @@ int make_plan(const HostGraph& g, const PlanParams& p, HostPlan& plan, std::stri
   for (size_t i = 0; i < big_direct.size(); ++i) order.push_back({item_work(plan, big_direct[i]), i});
   std::sort(order.begin(), order.end(), [](auto& a, auto& b) { return a.first > b.first; });
   std::vector<Item> parts, singles;
-  for (auto& [work, i] : order) {
-    const Item& it = big_direct[i];
-    if (pv) {  // whole items, key windows of at most kPVWindow(Packed) keys
-      const HostSide& S = g.side[it.side];
-      const int32_t T = plan.T[it.side];
-      const int64_t deg_T = T < S.n ? static_cast<int64_t>(S.off[T + 1] - S.off[T]) : 0;
-      const bool packed = pv_packed(it.seg_count, (it.flags & kItemHubPairs) != 0, deg_T);
-      const int32_t win = packed ? kPVWindowPacked : kPVWindow;
-      for (int32_t lo = it.key_lo; lo < it.key_hi; lo += win) {
-        Item w = it;
-        w.key_lo = lo;
-        w.key_hi = std::min(it.key_hi, lo + win);
-        if (packed) w.flags |= kItemPacked;
-        singles.push_back(w);
+  const size_t rev_reduces = plan.reduces.size();
+  const int32_t rev_slots = plan.acc_slots;
+  for (PlanParams q = p;;) {  // (another budget splits the same items)
+    parts.clear();
+    singles.clear();
+    plan.reduces.resize(rev_reduces);
+    plan.acc_slots = rev_slots;
+    for (auto& [work, i] : order) {
+      const Item& it = big_direct[i];
+      if (pv) {  // whole items, key windows of at most kPVWindow(Packed) keys
+        const HostSide& S = g.side[it.side];
+        const int32_t T = plan.T[it.side];
+        const int64_t deg_T = T < S.n ? static_cast<int64_t>(S.off[T + 1] - S.off[T]) : 0;
+        const bool packed = pv_packed(it.seg_count, (it.flags & kItemHubPairs) != 0, deg_T);
+        const int32_t win = packed ? kPVWindowPacked : kPVWindow;
+        for (int32_t lo = it.key_lo; lo < it.key_hi; lo += win) {
+          Item w = it;
+          w.key_lo = lo;
+          w.key_hi = std::min(it.key_hi, lo + win);
+          if (packed) w.flags |= kItemPacked;
+          singles.push_back(w);
+        }
+        continue;
       }
-      continue;
-    }
-    if (work <= p.part_work && it.seg_count < 65536) {
-      singles.push_back(it);
-      continue;
-    }
-    if (plan.acc_slots > INT32_MAX - static_cast<int32_t>(std::min<uint32_t>(it.seg_count, INT32_MAX))) {
-      err = "graph too large: more than 2^31 - 1 accumulator slots";
-      return DBBC_E_TOO_LARGE;
-    }
-    const int32_t first_slot = plan.acc_slots;
-    uint32_t k = 0;
-    while (k < it.seg_count) {
-      Item part = it;
-      part.seg_begin = it.seg_begin + k;
-      int64_t pw = 0;
-      uint32_t c = 0;
-      while (k + c < it.seg_count && c < 65535) {
-        const int64_t l = plan.segs[it.seg_begin + k + c].len_g >> 1;
-        if (c > 0 && pw + l > p.part_work) break;
-        pw += l;
-        ++c;
+      if (work <= q.part_work && it.seg_count < 65536) {
+        singles.push_back(it);
+        continue;
       }
-      part.seg_count = c;
-      part.work = static_cast<uint32_t>(std::min<int64_t>(pw, 0xffffffffll));
-      part.flags = it.flags | kItemMultiPart;
-      part.acc_slot = plan.acc_slots++;
-      parts.push_back(part);
-      k += c;
+      if (plan.acc_slots > INT32_MAX - static_cast<int32_t>(std::min<uint32_t>(it.seg_count, INT32_MAX))) {
+        err = "graph too large: more than 2^31 - 1 accumulator slots";
+        return DBBC_E_TOO_LARGE;
+      }
+      const int32_t first_slot = plan.acc_slots;
+      uint32_t k = 0;
+      while (k < it.seg_count) {
+        Item part = it;
+        part.seg_begin = it.seg_begin + k;
+        int64_t pw = 0;
+        uint32_t c = 0;
+        while (k + c < it.seg_count && c < 65535) {
+          const int64_t l = plan.segs[it.seg_begin + k + c].len_g >> 1;
+          if (c > 0 && pw + l > q.part_work) break;
+          pw += l;
+          ++c;
+        }
+        part.seg_count = c;
+        part.work = static_cast<uint32_t>(std::min<int64_t>(pw, 0xffffffffll));
+        part.flags = it.flags | kItemMultiPart;
+        part.acc_slot = plan.acc_slots++;
+        parts.push_back(part);
+        k += c;
+      }
+      Reduce r{};
+      r.acc_slot = first_slot;
+      r.n_parts = plan.acc_slots - first_slot;
+      r.owner = it.owner;
+      r.key_lo = it.key_lo;
+      r.key_hi = it.key_hi;
+      r.flags = it.flags;
+      r.side = it.side;
+      plan.reduces.push_back(r);
     }
-    Reduce r{};
-    r.acc_slot = first_slot;
-    r.n_parts = plan.acc_slots - first_slot;
-    r.owner = it.owner;
-    r.key_lo = it.key_lo;
-    r.key_hi = it.key_hi;
-    r.flags = it.flags;
-    r.side = it.side;
-    plan.reduces.push_back(r);
+    if (!fit_parts || !larger_parts(q, static_cast<int64_t>(plan.acc_slots) * plan.acc_width * 4)) break;
   }
   {
     PlanSizes z{};

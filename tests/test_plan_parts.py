@@ -1,5 +1,6 @@
 """The direct items of a count plan (CPU): heaviest first, the parts of split
-pivots among the pivots that are whole."""
+pivots among the pivots that are whole; and the part budget raised, in the one
+plan, until the parts' counters fit their room."""
 
 import ctypes
 import os
@@ -37,3 +38,24 @@ def test_parts_are_ordered_with_the_others(lib, part_work):
         assert parts > 0 and 0 < before_last <= whole
     else:
         assert parts == 0 and whole > 0
+
+
+def test_parts_fit_their_room(lib):
+    g = chung_lu_graph(3000, 2000, 60000, 2.0, 1.9, 0.4, seed=5)
+    i32, i64, p = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
+    lib.plan_room.argtypes = [i32, i32, i64, p, p, p, i32, i64, p]
+
+    def plan(room):
+        out = np.zeros(4, np.int64)
+        assert lib.plan_room(g.n_u, g.n_v, g.m, g.u.ctypes.data, g.v.ctypes.data, g.sign.ctypes.data, 4096, room,
+                             out.ctypes.data) == 0
+        return out.tolist()
+    free, parts, wedges, reduces = plan(1 << 40)
+    assert parts > 100 and reduces > 0
+    seen = {parts}
+    for room in (free, free - 1, free // 5, free // 50, 1):
+        held, parts, w, reduces = plan(room)
+        assert held <= room or parts == 0  # (the reverse items' parts keep theirs)
+        assert w == wedges and (parts == 0) == (reduces == 0)
+        seen.add(parts)
+    assert len(seen) > 2 and 0 in seen
