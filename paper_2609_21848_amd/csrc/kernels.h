@@ -89,7 +89,7 @@ struct DirectArgs {
   unsigned long long* err;   // kErr* bits
   int32_t n_items;
   uint32_t long_len;  // runs at least this long are streamed by the whole wavefront
-  // count pass: what the workgroup shape is picked by
+  // count pass: what the workgroup shape and the early tickets are picked by
   int32_t max_key;    // keys lie below this
   uint64_t wedges;    // of all items
   uint64_t max_work;  // of the heaviest item

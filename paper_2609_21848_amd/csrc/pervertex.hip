@@ -14,10 +14,11 @@
 // So every item is walked twice: a tally of p and n per key as in the count
 // pass, then a credit walk that reads each wedge's final p and n and adds
 // the mid's share; the sweep credits the key vertices and, summed, the
-// item's owner.  The plan of this pass has no multi-part items, so every
-// pair's counts are complete inside one item -- except the hub pairs of a
-// dense block, whose completed counts the block's products leave in hub_xy
-// (hubpv.hip) before these kernels run.
+// item's owner.  Every pair's counts are complete inside one item -- except
+// those of heavy direct items, cut into parts whose counters meet in an
+// accumulator before the parts credit from it (k_pv_heavy_tally), and the hub
+// pairs of a dense block, whose completed counts the block's products leave in
+// hub_xy (hubpv.hip) before these kernels run.
 //
 // Mid credits are summed per run (a run has one mid) in registers, then per
 // batch in a per-wavefront LDS slot of the run's lane, and reach HBM as one

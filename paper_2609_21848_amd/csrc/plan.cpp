@@ -95,10 +95,14 @@ PlanParams default_params(const HostGraph& g, int32_t hub_slots) {
   // into the item's counters and read back).  Measured, ms per pass unsplit,
   // at the best budget and at this rule's: per-vertex 334K edges (W 8.8M) 0.44
   // / 0.27 at 2^15 / 0.27, 2M (73M) 1.77 / 1.09 at 2^17 / 1.11, 8M (458M) 12.9 /
-  // 5.5 at 2^18 / 5.5, 20M (2.2G) 18.4 / 14.8 at 2^18 / 14.8; per-edge 2M 2.33 /
-  // 1.65, 8M 18.4 / 9.5, 20M 30.9 / 26.4.  At 50M (11.4G) the launches hold
-  // enough items beside their heaviest, and parts below 2^22 only cost (44.1 ->
-  // 44.6 ms): past 2^21 the budget is the count's largest.
+  // 5.5 at 2^18 / 5.5, 12M (1.05G) 7.12 / 6.12 at 2^19 / 6.18; per-edge 2M 2.33 /
+  // 1.65, 8M 18.4 / 9.5, 12M 11.87 / 10.35 at 2^18 / 10.70, 20M (2.2G) 18.92 /
+  // 18.37 at 2^21 / 18.36.  In larger graphs the launches hold enough items
+  // beside their heaviest and the budget hardly matters: per-vertex 20M 10.19 /
+  // 10.17 / 10.20, 25M (3.6G) 12.60 / 12.57 / 13.09, 35M (6.2G) 18.49 / 18.49 /
+  // 19.12, 42M (8.1G) 23.30 / 22.91 / 22.91, per-edge 35M 43.23 / 43.07 / 43.77,
+  // 42M 54.12 / 53.94 / 53.94.  At 50M (10.6G) parts only cost: 27.72 whole,
+  // 28.85 at 2^21, 29.45 at 2^18, so past 2^21 the budget is the count's largest.
   const int64_t pv_budget =
       std::max<int64_t>(1 << 15, std::min(g.wedges_vp / std::max(1, hub_slots),
                                           (1 << 16) + g.wedges_vp / (8 * std::max(1, hub_slots))));

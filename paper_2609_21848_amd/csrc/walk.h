@@ -700,12 +700,6 @@ struct SqTotals {
   }
 };
 
-// The last flush of a launch, taken by every wavefront of a workgroup at
-// the kernel's end: each wavefront's sums go to LDS, and one thread adds them
-// to the result slots once per graph (a run of wavefronts of one graph).
-// Every wavefront of a launch adds to the same few words, and atomics to one
-// address are serialized, so per-wavefront atomics would cost a few
-// microseconds per thousand wavefronts at the end of the kernel.
 // The first rank of a side whose degree d has d * other < 2^32 (side ranks
 // are in non-increasing degree order).  Edges at rows of lower rank, or
 // whose mid in a run is of lower rank, may hold per-edge credits of 2^32 or
@@ -724,6 +718,12 @@ __device__ __forceinline__ int32_t first_narrow_rank(const uint32_t* off, int32_
   return lo;
 }
 
+// The last flush of a launch, taken by every wavefront of a workgroup at
+// the kernel's end: each wavefront's sums go to LDS, and one thread adds them
+// to the result slots once per graph (a run of wavefronts of one graph).
+// Every wavefront of a launch adds to the same few words, and atomics to one
+// address are serialized, so per-wavefront atomics would cost a few
+// microseconds per thousand wavefronts at the end of the kernel.
 struct WaveSums {
   int64_t bal, unb;
   uint32_t graph, pad;
